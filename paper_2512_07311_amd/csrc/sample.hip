@@ -42,6 +42,40 @@ struct ChainArgs {
   int* reset = nullptr;            // zeroed by the first thread of the launch, or null
 };
 
+// A operand of the shot GEMM: the row of shot m is the half of its previous W
+// it chose.  A thread stages the same rows in every K step, so the shot list,
+// the choice and the row address are read once, not in the K loop (three
+// dependent loads per element there).
+struct ChainRows {
+  static constexpr bool KFAST = true;
+  const double2* row[GT_PER];   // null: no such row
+  bool unit;                    // site 0: the row is (1)
+  int K;
+  __device__ ChainRows(const ChainArgs& a, int m0, int M) : unit(a.wprev == nullptr), K(a.dl) {
+#pragma unroll
+    for (int j = 0; j < GT_PER; ++j) {
+      const int m = m0 + (threadIdx.x + j * GT_THREADS) / GT_K;
+      row[j] = nullptr;
+      if (m < M && !unit) {
+        const int sh = a.rows ? a.rows[m] : m;
+        row[j] = a.wprev + (int64_t)sh * 2 * a.dl + (int64_t)a.sel[sh] * a.dl;
+      }
+    }
+  }
+  __device__ inline void fetch(double2 (&r)[GT_PER], int k0, int tid) const {
+    const int k = k0 + tid % GT_K;
+#pragma unroll
+    for (int j = 0; j < GT_PER; ++j) {
+      r[j] = make_double2(unit && k == 0 ? 1.0 : 0.0, 0.0);
+      if (row[j] && k < K) r[j] = row[j][k];
+    }
+  }
+  __device__ inline void commit(double2* s, const double2 (&r)[GT_PER], int tid) const {
+#pragma unroll
+    for (int j = 0; j < GT_PER; ++j) s[lds_unit<true>((tid + j * GT_THREADS) / GT_K, tid % GT_K)] = r[j];
+  }
+};
+
 __device__ inline void chain_gemm_tile(const ChainArgs& a, int tn, int tm, int s, SmemC64& sm,
                                        double (*rowsum)[GT_M]) {
   const int m0 = tm * GT_M, n0 = tn * GT_N;
@@ -49,14 +83,9 @@ __device__ inline void chain_gemm_tile(const ChainArgs& a, int tn, int tm, int s
   if (m0 >= M) return;                         // whole workgroup: nothing to do
   const int dl = a.dl, dr = a.dr;
   auto shot = [&](int m) -> int { return a.rows ? a.rows[m] : m; };
-  auto fa = [&](int m, int k) -> double2 {
-    if (a.wprev == nullptr) return (k == 0) ? make_double2(1.0, 0.0) : make_double2(0.0, 0.0);
-    const int sm_ = shot(m);
-    return a.wprev[(int64_t)sm_ * 2 * dl + (int64_t)a.sel[sm_] * dl + k];
-  };
   const double2* bs = a.site + (int64_t)s * dl * dr;
   auto fb = [&](int k, int n) -> double2 { return bs[(int64_t)k * dr + n]; };
-  LoadA<decltype(fa), true> la{fa, m0, M, dl};
+  const ChainRows la(a, m0, M);
   LoadB<decltype(fb), true> lb{fb, n0, dl, dr};
   AccC64 acc;
   acc_zero(acc);
@@ -64,47 +93,44 @@ __device__ inline void chain_gemm_tile(const ChainArgs& a, int tn, int tm, int s
 
   // store W and reduce |w|^2 per row over this tile's columns
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const int wm = (w & 1) * 32, wn = (w >> 1) * 32;
-  double rs[2][4];
-#pragma unroll
-  for (int mt = 0; mt < 2; ++mt)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) rs[mt][r] = 0.0;
-#pragma unroll
-  for (int mt = 0; mt < 2; ++mt)
-#pragma unroll
-    for (int nt = 0; nt < 2; ++nt)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        int m = m0 + wm + mt * 16 + f64_row(lane, r);
-        int n = n0 + wn + nt * 16 + (lane & 15);
-        double re = acc.re[mt][nt][r], im = acc.im[mt][nt][r];
-        if (m < M && n < dr) {
-          a.wout[(int64_t)shot(m) * 2 * dr + (int64_t)s * dr + n] = make_double2(re, im);
-          rs[mt][r] += re * re + im * im;
-        }
-      }
+  const int wm = wave_m(w), wn = wave_n(w);
 #pragma unroll
   for (int mt = 0; mt < 2; ++mt)
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      double v = rs[mt][r];
+      const int row = wm + mt * 16 + f64_row(lane, r), m = m0 + row;
+      double v = 0.0;
+      if (m < M) {
+        double2* out = a.wout + (int64_t)shot(m) * 2 * dr + (int64_t)s * dr;
+#pragma unroll
+        for (int nt = 0; nt < GT_NT; ++nt) {
+          const int n = n0 + wn + nt * 16 + (lane & 15);
+          const double re = acc.re[mt][nt][r], im = acc.im[mt][nt][r];
+          if (n < dr) {
+            out[n] = make_double2(re, im);
+            v += re * re + im * im;
+          }
+        }
+      }
       v += __shfl_xor(v, 1);
       v += __shfl_xor(v, 2);
       v += __shfl_xor(v, 4);
       v += __shfl_xor(v, 8);
-      if ((lane & 15) == 0) rowsum[w >> 1][wm + mt * 16 + f64_row(lane, r)] = v;
+      if ((lane & 15) == 0) rowsum[w >> 1][row] = v;
     }
   __syncthreads();
   if (tid < GT_M) {
-    int m = m0 + tid;
-    if (m < M) a.part[((int64_t)s * a.S + shot(m)) * a.ntiles + tn] = rowsum[0][tid] + rowsum[1][tid];
+    const int m = m0 + tid;
+    double v = rowsum[0][tid];
+#pragma unroll
+    for (int q = 1; q < GT_WN; ++q) v += rowsum[q][tid];
+    if (m < M) a.part[((int64_t)s * a.S + shot(m)) * a.ntiles + tn] = v;
   }
 }
 
 __global__ __launch_bounds__(GT_THREADS) void k_chain_gemm(ChainArgs a) {
   __shared__ SmemC64 sm;
-  __shared__ double rowsum[2][GT_M];
+  __shared__ double rowsum[GT_WN][GT_M];
   if (a.reset && blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0 && threadIdx.x == 0) *a.reset = 0;
   chain_gemm_tile(a, blockIdx.x, blockIdx.y, a.s_fixed >= 0 ? a.s_fixed : (int)blockIdx.z, sm, rowsum);
 }
@@ -118,7 +144,7 @@ struct ChainGroup {
 
 __global__ __launch_bounds__(GT_THREADS) void k_chain_gemm_grouped(const ChainGroup* groups, int ng) {
   __shared__ SmemC64 sm;
-  __shared__ double rowsum[2][GT_M];
+  __shared__ double rowsum[GT_WN][GT_M];
   const int t = blockIdx.x;
   int g = 0;
   while (g + 1 < ng && groups[g + 1].tile0 <= t) ++g;
