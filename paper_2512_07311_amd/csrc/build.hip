@@ -730,7 +730,7 @@ static SplitResult svd_split(rcs_state_s& st, BuildWork& ws, const JacobiPlan& p
                        pl.ldx, pl.len, ws.order.as<int>(), X);
     HIP_LAUNCH_OK();
   }
-  int sweeps = jacobi_run(pl, X, ws.jac.p, ws.rot.as<int>(), ws.host_rot, fro2, s, 60, ortho_only ? 1e-7 : 0.0);
+  int sweeps = jacobi_run(pl, X, ws.jac.p, ws.rot.as<int>(), ws.host_rot, fro2, s, kJacobiMaxSweeps, ortho_only ? 1e-7 : 0.0);
   st.jacobi_sweeps_max = std::max(st.jacobi_sweeps_max, sweeps);
   RCS_PROBED_LAUNCH(kKcFactor, k_colnorm, dim3(pl.cnt), dim3(256), 0, s, X, pl.ldx, pl.len, ws.sigma.as<double>());
   HIP_LAUNCH_OK();
@@ -876,7 +876,9 @@ static bool svd_split_chol(rcs_state_s& st, BuildWork& ws, const JacobiPlan& pl,
     const int64_t ne = (int64_t)py.ldx * py.cnt_pad;
     RCS_PROBED_LAUNCH(kKcFactor, k_to_c64, dim3(grid1d(ne)), dim3(256), 0, s, Y, Y32, ne);
     HIP_LAUNCH_OK();
-    sweeps = jacobi_run_f32(py, Y32, ws.jac.p, ws.rot.as<int>(), ws.host_rot, fro2, s, 60);
+    const JacobiPlan p32 = jacobi_plan(n, n, 0, true);
+    ws.jac.ensure(jacobi_work_bytes(p32));
+    sweeps = jacobi_run_f32(p32, Y32, ws.jac.p, ws.rot.as<int>(), ws.host_rot, fro2, s, kJacobiMaxSweeps);
     r = rank(Y32, true);
     if (!r.bad && r.k >= 1) {
       double sk2;
@@ -889,7 +891,7 @@ static bool svd_split_chol(rcs_state_s& st, BuildWork& ws, const JacobiPlan& pl,
       st.n_svd_f32_redone += 1;
   }
   if (!use32) {
-    sweeps = jacobi_run(py, Y, ws.jac.p, ws.rot.as<int>(), ws.host_rot, fro2, s, 60);
+    sweeps = jacobi_run(py, Y, ws.jac.p, ws.rot.as<int>(), ws.host_rot, fro2, s, kJacobiMaxSweeps);
     r = rank(Y, false);
     if (r.bad || r.k < 1) return false;
     double sk2;
@@ -1594,7 +1596,7 @@ rcs_status rcs_svd_jacobi(int32_t len, int32_t cnt, double* x_dev, double* s_dev
   double fro2 = 0.0;
   HIP_OK(hipMemcpyAsync(&fro2, ws->host_rank_dev(), sizeof(double), hipMemcpyDeviceToHost, s));
   HIP_OK(hipStreamSynchronize(s));
-  rcs::jacobi_run(pl, X, ws->jac.p, ws->rot.as<int>(), ws->host_rot, fro2, s, 60);
+  rcs::jacobi_run(pl, X, ws->jac.p, ws->rot.as<int>(), ws->host_rot, fro2, s, rcs::kJacobiMaxSweeps);
   hipLaunchKernelGGL(rcs::k_colnorm, dim3(cnt), dim3(256), 0, s, X, pl.ldx, len, ws->sigma.as<double>());
   HIP_LAUNCH_OK();
   hipLaunchKernelGGL(rcs::k_sort_rank, dim3(1), dim3(1024), 0, s, ws->sigma.as<double>(), cnt, cnt, 0.0,
@@ -1613,7 +1615,7 @@ rcs_status rcs_svd_jacobi_f32(int32_t len, int32_t cnt, const double* x_dev, dou
   RCS_REQUIRE(x_dev && s_dev && u_dev, "null device pointer");
   RCS_REQUIRE(len >= 1 && cnt >= 1 && cnt <= rcs::SORT_MAX && len <= 16384, "bad matrix shape");
   hipStream_t s = rcs::as_stream(stream);
-  rcs::JacobiPlan pl = rcs::jacobi_plan(len, cnt);
+  rcs::JacobiPlan pl = rcs::jacobi_plan(len, cnt, 0, true);
   std::unique_ptr<rcs::BuildWork, void (*)(rcs::BuildWork*)> ws(rcs::new_work(), rcs::delete_work);
   rcs::ensure_work(*ws, pl, 0);
   HIP_OK(hipMemsetAsync(ws->X.p, 0, (size_t)pl.ldx * pl.cnt_pad * sizeof(double2), s));
@@ -1643,7 +1645,7 @@ rcs_status rcs_svd_jacobi_f32(int32_t len, int32_t cnt, const double* x_dev, dou
   double fro2 = 0.0;
   HIP_OK(hipMemcpyAsync(&fro2, ws->host_rank_dev(), sizeof(double), hipMemcpyDeviceToHost, s));
   HIP_OK(hipStreamSynchronize(s));
-  rcs::jacobi_run_f32(pl, X32, ws->jac.p, ws->rot.as<int>(), ws->host_rot, fro2, s, 60);
+  rcs::jacobi_run_f32(pl, X32, ws->jac.p, ws->rot.as<int>(), ws->host_rot, fro2, s, rcs::kJacobiMaxSweeps);
   hipLaunchKernelGGL(rcs::k_colnorm_c64, dim3(cnt), dim3(256), 0, s, X32, pl.ldx, len, ws->sigma.as<double>());
   HIP_LAUNCH_OK();
   hipLaunchKernelGGL(rcs::k_sort_rank, dim3(1), dim3(1024), 0, s, ws->sigma.as<double>(), cnt, cnt, 0.0,
@@ -1714,7 +1716,7 @@ rcs_status rcs_rsvd(int32_t len, int32_t cnt, const double* x_dev, int32_t l, in
   HIP_LAUNCH_OK();
   HIP_OK(hipMemcpyAsync(fro2_host, ws->host_rank_dev(), sizeof(double), hipMemcpyDeviceToHost, s));
   HIP_OK(hipStreamSynchronize(s));
-  rcs::jacobi_run(pl, ws->X.as<double2>(), ws->jac.p, ws->rot.as<int>(), ws->host_rot, *fro2_host, s, 60);
+  rcs::jacobi_run(pl, ws->X.as<double2>(), ws->jac.p, ws->rot.as<int>(), ws->host_rot, *fro2_host, s, rcs::kJacobiMaxSweeps);
   hipLaunchKernelGGL(rcs::k_colnorm, dim3(l), dim3(256), 0, s, ws->X.as<double2>(), pl.ldx, cnt,
                      ws->sigma.as<double>());
   HIP_LAUNCH_OK();

@@ -5,6 +5,11 @@
 
 namespace rcs {
 
+// Sweep limit of every SVD.  Flat spectra take 10 to 14 sweeps; an
+// unpreconditioned matrix whose spectrum spans 12 decades takes about 60 at
+// 4096 columns, so the limit stands well clear of that.
+constexpr int kJacobiMaxSweeps = 120;
+
 struct JacobiPlan {
   int jb = 16;            // columns per block (16 or 32)
   int inner = 1;          // inner sweeps per pair meeting
@@ -17,8 +22,9 @@ struct JacobiPlan {
   int n_gchunks = 0, rows_per_gchunk = 0;   // Gram pass row chunks
 };
 
-// jb <= 0 picks the default block width for the shape.
-JacobiPlan jacobi_plan(int len, int cnt, int jb = 0);
+// jb <= 0 picks the default block width for the shape; f32: the plan of
+// jacobi_run_f32 (its Gram chunks differ).
+JacobiPlan jacobi_plan(int len, int cnt, int jb = 0, bool f32 = false);
 size_t jacobi_work_bytes(const JacobiPlan& pl);
 // Orthogonalises the columns of x in place; returns the number of sweeps
 // (the last one rotates nothing, or its largest entering cosine squared is

@@ -18,8 +18,9 @@
 //   rotate : every (pair, chunk) workgroup sums the partial Grams in fixed
 //            order, diagonalises the 32x32 Hermitian G_p in LDS by cyclic
 //            two-sided Jacobi (all workgroups of a pair compute the same
-//            unitary V_p), and applies Y_p <- Y_p V_p to its own rows on the
-//            matrix cores.
+//            rotations), and applies them to its own rows: in fp64 each
+//            rotation directly, to rows held in registers; in fp32 and for
+//            32-column blocks as the product Y_p V_p on the matrix cores.
 // A pair whose two blocks were not rotated since the pair last met is
 // skipped (it is still orthogonal), so late sweeps cost almost nothing.  A
 // sweep that rotates nothing ends the iteration, and so does a sweep whose
@@ -30,6 +31,7 @@
 #include <cstdlib>
 #include <mutex>
 #include <type_traits>
+#include <utility>
 #include <vector>
 
 #include "gemm_f64.h"
@@ -111,15 +113,26 @@ __device__ inline void load_row(const C* x, int ldx, int bi, int bj, int row, in
 
 // Partial Grams.  Waves split the chunk's rows (16-row tiles, interleaved)
 // and each accumulates the NB(NB+1)/2 upper 16x16 blocks of Y^H Y on the
-// matrix cores straight from registers; the four waves are then reduced in
-// the fixed order ((w3 + w2) + w1) + w0 through LDS.
-template <int JP, typename R>
-__global__ __launch_bounds__(256) void k_jac_gram(JacArgs<R> a) {
+// matrix cores straight from registers; the waves are then summed through LDS
+// in a fixed order (waves 4-7, if any, into 0-3, then ((w3 + w2) + w1) + w0).
+//
+// Waves per workgroup: four, each with its own 16-row tile of a 64-row chunk,
+// are the fastest launch of a small matrix (5.6 us against 7.2 with eight at
+// 512 x 512).  But every rotate workgroup of a pair reads all of the pair's
+// partials (16 KB each), and from about 768 rows that traffic costs more than
+// the launch: in fp64, eight waves on 128-row chunks make a whole round 27.7
+// us against 29.6 at 1024 x 1024 and 56.4 against 58.4 at 2048 x 2048
+// (sixteen waves: 30.8 and 59.8).  The fp32 pass keeps four waves: its
+// partials are half the size, and its singular values depend on the
+// summation order at the 1e-4 level of its drift.
+template <int JP, int NW, typename R>
+__global__ __launch_bounds__(64 * NW) void k_jac_gram(JacArgs<R> a) {
   using T = JT<R>;
   using C = typename T::C;
   using V4 = typename T::V4;
   constexpr int NB = JP / 16, NU = NB * (NB + 1) / 2;
-  __shared__ R red[NU * 8][64];
+  static_assert(NW == 4 || NW == 8, "the reduction below");
+  __shared__ R red[NW == 8 ? 4 : 1][NU * 8][64];
   const int p = blockIdx.x, chunk = blockIdx.y;
   const int bi = rr_block(p, a.round, a.nbp), bj = rr_block(a.nbp - 1 - p, a.round, a.nbp);
   if (pair_skipped(a, bi, bj)) return;
@@ -140,11 +153,11 @@ __global__ __launch_bounds__(256) void k_jac_gram(JacArgs<R> a) {
     for (int ks = 0; ks < 4; ++ks)
       load_row<JP>(a.x, a.ldx, bi, bj, rbeg + w * TR + 4 * ks + rsub, rend, cur[ks], lane);
   }
-  for (int t = w; t < ntiles; t += 4) {
-    if (t + 4 < ntiles) {
+  for (int t = w; t < ntiles; t += NW) {
+    if (t + NW < ntiles) {
 #pragma unroll
       for (int ks = 0; ks < 4; ++ks)
-        load_row<JP>(a.x, a.ldx, bi, bj, rbeg + (t + 4) * TR + 4 * ks + rsub, rend, nxt[ks], lane);
+        load_row<JP>(a.x, a.ldx, bi, bj, rbeg + (t + NW) * TR + 4 * ks + rsub, rend, nxt[ks], lane);
     }
 #pragma unroll
     for (int ks = 0; ks < 4; ++ks) {
@@ -165,6 +178,29 @@ __global__ __launch_bounds__(256) void k_jac_gram(JacArgs<R> a) {
 #pragma unroll
       for (int cb = 0; cb < NB; ++cb) cur[ks][cb] = nxt[ks][cb];
   }
+  if constexpr (NW == 8) {
+    if (w >= 4) {
+#pragma unroll
+      for (int u = 0; u < NU; ++u)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          red[w - 4][u * 8 + r][lane] = gr[u][r];
+          red[w - 4][u * 8 + 4 + r][lane] = gi[u][r];
+        }
+    }
+    __syncthreads();
+    if (w < 4) {
+#pragma unroll
+      for (int u = 0; u < NU; ++u)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          gr[u][r] += red[w][u * 8 + r][lane];
+          gi[u][r] += red[w][u * 8 + 4 + r][lane];
+        }
+    }
+    __syncthreads();
+  }
+#pragma unroll
   for (int src = 3; src >= 1; --src) {
     if (w == src) {
 #pragma unroll
@@ -173,11 +209,11 @@ __global__ __launch_bounds__(256) void k_jac_gram(JacArgs<R> a) {
         for (int r = 0; r < 4; ++r) {
           R vr = gr[u][r], vi = gi[u][r];
           if (src < 3) {
-            vr += red[u * 8 + r][lane];
-            vi += red[u * 8 + 4 + r][lane];
+            vr += red[0][u * 8 + r][lane];
+            vi += red[0][u * 8 + 4 + r][lane];
           }
-          red[u * 8 + r][lane] = vr;
-          red[u * 8 + 4 + r][lane] = vi;
+          red[0][u * 8 + r][lane] = vr;
+          red[0][u * 8 + 4 + r][lane] = vi;
         }
     }
     __syncthreads();
@@ -191,8 +227,8 @@ __global__ __launch_bounds__(256) void k_jac_gram(JacArgs<R> a) {
     for (int nb = mb; nb < NB; ++nb, ++u)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const R vr = gr[u][r] + red[u * 8 + r][lane];
-        const R vi = gi[u][r] + red[u * 8 + 4 + r][lane];
+        const R vr = gr[u][r] + red[0][u * 8 + r][lane];
+        const R vi = gi[u][r] + red[0][u * 8 + 4 + r][lane];
         const int row = mb * 16 + T::orow(lane, r), col = nb * 16 + (lane & 15);
         part[row * JP + col] = T::mk(vr, vi);
         if (mb != nb) part[col * JP + row] = T::mk(vr, -vi);
@@ -239,8 +275,8 @@ __device__ inline Rot<double> jac_rot(double gii, double gjj, double2 g, double 
   const double rh = __builtin_amdgcn_rsq(fmax(h2, 1e-300));
   const double tau = (gjj - gii) * (0.5 * rh);
   const float tf = (float)fabs(tau);
-  const float t32 = tf > 1e18f ? 0.5f * __builtin_amdgcn_rcpf(tf)
-                               : __builtin_amdgcn_rcpf(tf + __builtin_amdgcn_sqrtf(fmaf(tf, tf, 1.0f)));
+  const float root = tf + __builtin_amdgcn_sqrtf(fmaf(tf, tf, 1.0f));
+  const float t32 = __builtin_amdgcn_rcpf(tf > 1e18f ? 2.0f * tf : root);
   const double t = tau < 0.0 ? -(double)t32 : (double)t32;
   const double ex = g.x * rh, ey = g.y * rh;
   const double c = rsqrt_nr(fma(t * t, ex * ex + ey * ey, 1.0));
@@ -261,8 +297,8 @@ __device__ inline Rot<float> jac_rot(float gii, float gjj, float2 g, float tol, 
   const float rh = __builtin_amdgcn_rsqf(fmaxf(h2, JT<float>::tiny));
   const float tau = (gjj - gii) * (0.5f * rh);
   const float tf = fabsf(tau);
-  const float t32 = tf > 1e18f ? 0.5f * __builtin_amdgcn_rcpf(tf)
-                               : __builtin_amdgcn_rcpf(tf + __builtin_amdgcn_sqrtf(fmaf(tf, tf, 1.0f)));
+  const float root = tf + __builtin_amdgcn_sqrtf(fmaf(tf, tf, 1.0f));
+  const float t32 = __builtin_amdgcn_rcpf(tf > 1e18f ? 2.0f * tf : root);
   const float t = tau < 0.0f ? -t32 : t32;
   const float ex = g.x * rh, ey = g.y * rh;
   const float x = fmaf(t * t, ex * ex + ey * ey, 1.0f);
@@ -529,6 +565,333 @@ __global__ __launch_bounds__(ROT_THREADS) void k_jac_rotate(JacArgs<R> a) {
   }
 }
 
+// ------------------------------------------------- row-resident rotation
+// The fp64 rotate pass for 16-column blocks.  The two-sided solve of the
+// 32 x 32 Gram is a serial chain of rounds (16 disjoint rotations each), and
+// forming the unitary and multiplying by it costs twice the flops of
+// applying the rotations themselves, at the same fp64 rate (the vector and
+// the matrix units both reach 78.6 TFLOP/s).  So the workgroup splits:
+//   waves 0-3   run the solve, one barrier per round: thread (k, pb) holds
+//               the block of pair pa = pb + k mod 16 against pair pb, computes
+//               pair pb's rotation itself, takes pa's from the lane that has
+//               it, and writes its four entries to the other Gram buffer;
+//   waves 4...  hold one row of Y_p per lane in registers (32 columns, loaded
+//               while the partial Grams are summed) and apply each round's
+//               rotations one round behind the solve.
+// A rotation is applied as two in-place complex shears with the column scales
+// deferred (an LDU factorisation of the plane rotation, eight FMAs instead of
+// twelve):  with x = d x~,  x~_i -= conj(u) x~_j,  x~_j += w x~_i',
+//   u = t d_j / d_i,  w = c^2 t d_i / d_j,  d_i <- c d_i,  d_j <- d_j / c,
+// t the complex tangent (|t| <= 1), c = (1 + |t|^2)^(-1/2).  The scales stay
+// within 2^(+-rounds / 2) and are multiplied out before the rows are stored.
+// Rotation q sits in lane q of every 16-lane row, from where the FMA itself
+// broadcasts it (DPP row_newbcast, the one DPP form 64-bit operations have):
+// 5.6 cycles per FMA and wave, against 7.2 with separate moves (plain: 4.9).
+//
+// Bound: below about 1024 columns the chain of rounds (0.6 us each, the
+// solve's latency), at 2048 the fp64 vector rate (two row waves and one solver
+// wave per SIMD) and the read and write of the matrix (64 MB, 25 us on its
+// own).  Measured against the LDS solve with a V product on the matrix cores
+// (still the 32-column and fp32 form), per launch: 128 x 128 21.5 -> 15.5 us,
+// 1024 x 1024 23 -> 20.5 us, 2048 x 2048 43 -> 33 us inside an SVD.  Tried and
+// slower: the whole solve before any row work (41 us at 2048), a rolled row
+// loop with register rotation, the shears published by a solver wave.
+constexpr int JSOLVE = 256;   // solver threads
+
+// One round's pair q in the inner schedule: columns i < j.  full: 15 rounds
+// of the 16-column round robin inside both blocks (pairs 0-7 and 8-15), then
+// the 16 cross rounds; else the cross rounds only.
+template <bool FULL>
+__host__ __device__ constexpr int sched_rounds() { return FULL ? 31 : 16; }
+__host__ __device__ constexpr int rr16_i(int q, int r) {
+  const int u = q == 0 ? 0 : ((q - 1 + r) % 15) + 1, v = ((14 - q + r) % 15) + 1;
+  return u < v ? u : v;
+}
+__host__ __device__ constexpr int rr16_j(int q, int r) {
+  const int u = q == 0 ? 0 : ((q - 1 + r) % 15) + 1, v = ((14 - q + r) % 15) + 1;
+  return u < v ? v : u;
+}
+template <bool FULL>
+__host__ __device__ constexpr int sched_i(int q, int r) {
+  return FULL && r < 15 ? (q & 8) * 2 + rr16_i(q & 7, r) : q;
+}
+template <bool FULL>
+__host__ __device__ constexpr int sched_j(int q, int r) {
+  return FULL && r < 15 ? (q & 8) * 2 + rr16_j(q & 7, r) : 16 + ((q + (FULL ? r - 15 : r)) & 15);
+}
+
+// a_k -= conj(u_k) b_k resp. a_k += w_k b_k for four independent columns k,
+// u_k, w_k taken from lane Q + k of the 16-lane row.  Four at a time, so that
+// dependent FMAs are eight instructions apart (two apart they cost twice the
+// time with one row wave per SIMD).  The leading wait covers a u or w that
+// the compiler moved with a VALU instruction just before (a DPP source needs
+// two wait states after one).
+template <int Q>
+__device__ __forceinline__ void shear_sub(double2& a0, double2& a1, double2& a2, double2& a3, const double2& b0,
+                                          const double2& b1, const double2& b2, const double2& b3, const double2& u) {
+  asm(
+      "s_nop 1\n\t"
+      "v_fmac_f64_dpp %0, -%16, %8 row_newbcast:%18 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %2, -%16, %10 row_newbcast:%19 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %4, -%16, %12 row_newbcast:%20 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %6, -%16, %14 row_newbcast:%21 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %1, -%16, %9 row_newbcast:%18 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %3, -%16, %11 row_newbcast:%19 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %5, -%16, %13 row_newbcast:%20 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %7, -%16, %15 row_newbcast:%21 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %0, -%17, %9 row_newbcast:%18 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %2, -%17, %11 row_newbcast:%19 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %4, -%17, %13 row_newbcast:%20 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %6, -%17, %15 row_newbcast:%21 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %1, %17, %8 row_newbcast:%18 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %3, %17, %10 row_newbcast:%19 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %5, %17, %12 row_newbcast:%20 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %7, %17, %14 row_newbcast:%21 row_mask:0xf bank_mask:0xf"
+      : "+v"(a0.x), "+v"(a0.y), "+v"(a1.x), "+v"(a1.y), "+v"(a2.x), "+v"(a2.y), "+v"(a3.x), "+v"(a3.y)
+      : "v"(b0.x), "v"(b0.y), "v"(b1.x), "v"(b1.y), "v"(b2.x), "v"(b2.y), "v"(b3.x), "v"(b3.y), "v"(u.x), "v"(u.y),
+        "n"(Q), "n"(Q + 1), "n"(Q + 2), "n"(Q + 3));
+}
+template <int Q>
+__device__ __forceinline__ void shear_add(double2& a0, double2& a1, double2& a2, double2& a3, const double2& b0,
+                                          const double2& b1, const double2& b2, const double2& b3, const double2& w) {
+  asm(
+      "s_nop 1\n\t"
+      "v_fmac_f64_dpp %0, %16, %8 row_newbcast:%18 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %2, %16, %10 row_newbcast:%19 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %4, %16, %12 row_newbcast:%20 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %6, %16, %14 row_newbcast:%21 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %1, %16, %9 row_newbcast:%18 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %3, %16, %11 row_newbcast:%19 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %5, %16, %13 row_newbcast:%20 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %7, %16, %15 row_newbcast:%21 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %0, -%17, %9 row_newbcast:%18 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %2, -%17, %11 row_newbcast:%19 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %4, -%17, %13 row_newbcast:%20 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %6, -%17, %15 row_newbcast:%21 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %1, %17, %8 row_newbcast:%18 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %3, %17, %10 row_newbcast:%19 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %5, %17, %12 row_newbcast:%20 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %7, %17, %14 row_newbcast:%21 row_mask:0xf bank_mask:0xf"
+      : "+v"(a0.x), "+v"(a0.y), "+v"(a1.x), "+v"(a1.y), "+v"(a2.x), "+v"(a2.y), "+v"(a3.x), "+v"(a3.y)
+      : "v"(b0.x), "v"(b0.y), "v"(b1.x), "v"(b1.y), "v"(b2.x), "v"(b2.y), "v"(b3.x), "v"(b3.y), "v"(w.x), "v"(w.y),
+        "n"(Q), "n"(Q + 1), "n"(Q + 2), "n"(Q + 3));
+}
+
+// Round r's rotations on a row.
+template <bool FULL, int R_, int Q>
+__device__ __forceinline__ void apply_four(double2 (&y)[32], const double2& u, const double2& w) {
+  constexpr int i0 = sched_i<FULL>(Q, R_), i1 = sched_i<FULL>(Q + 1, R_), i2 = sched_i<FULL>(Q + 2, R_),
+                i3 = sched_i<FULL>(Q + 3, R_);
+  constexpr int j0 = sched_j<FULL>(Q, R_), j1 = sched_j<FULL>(Q + 1, R_), j2 = sched_j<FULL>(Q + 2, R_),
+                j3 = sched_j<FULL>(Q + 3, R_);
+  shear_sub<Q>(y[i0], y[i1], y[i2], y[i3], y[j0], y[j1], y[j2], y[j3], u);
+  shear_add<Q>(y[j0], y[j1], y[j2], y[j3], y[i0], y[i1], y[i2], y[i3], w);
+}
+template <bool FULL, int R_>
+__device__ __forceinline__ void apply_round(double2 (&y)[32], const double2& u, const double2& w) {
+  apply_four<FULL, R_, 0>(y, u, w);
+  apply_four<FULL, R_, 4>(y, u, w);
+  apply_four<FULL, R_, 8>(y, u, w);
+  apply_four<FULL, R_, 12>(y, u, w);
+}
+
+// The rotation of jac_rot in the form the row-resident pass wants: c and
+// a = c t^ with t^ = +-2 g / (|d| + sqrt(d^2 + 4 |g|^2)), d = gjj - gii (the
+// smaller-angle root), and 1 / c.  t^ may be off by the hardware estimates'
+// ~1e-8 (see jac_rot); c is refined, so c^2 (1 + |t^|^2) = 1 to rounding.
+struct RotT {
+  double c, ax, ay, ci;
+};
+__device__ inline RotT jac_rot_t(double gii, double gjj, double2 g, double tol, double neg2) {
+  const double h2 = g.x * g.x + g.y * g.y, d = gjj - gii;
+  const bool act = rot_active<double>(gii, gjj, h2, tol, neg2);
+  const double s = fmax(fma(d, d, 4.0 * h2), 1e-300);
+  const double v = fma(s, __builtin_amdgcn_rsq(s), fabs(d));
+  const double k = 2.0 * __builtin_amdgcn_rcp(v);
+  const double t = act ? (d < 0.0 ? -k : k) : 0.0;
+  const double x = fma(t * t, h2, 1.0);
+  // 1/sqrt(x), x in [1, 2]: the estimate's relative error e goes to e^3
+  const double q = __builtin_amdgcn_rsq(x);
+  const double e = fma(-x * q, q, 1.0);
+  RotT r;
+  r.c = fma(q * e, fma(0.375, e, 0.5), q);
+  r.ci = x * r.c;
+  const double ct = r.c * t;
+  r.ax = g.x * ct;
+  r.ay = g.y * ct;
+  return r;
+}
+
+struct SolveLds {
+  double2 G[2][32 * 32];
+  double2 raw[2][2][16];   // (c, 1 / c) and a of a round's 16 rotations, from the solve
+  double2 rot[2][2][16];   // their u and w, from the first row wave
+  double scale[32];
+  unsigned char ti[31][16], tj[31][16];   // the schedule
+  int any_flag, big;
+};
+
+// u and w of the round the solve has just published, lane q < 16 of the first
+// row wave for rotation q = (columns i, j), and the new column scales.
+__device__ __forceinline__ void publish_shears(SolveLds& sm, int buf, int r, int q) {
+  const int i = sm.ti[r][q], j = sm.tj[r][q];
+  const double2 cc = sm.raw[buf][0][q], av = sm.raw[buf][1][q];
+  const double di = sm.scale[i], dj = sm.scale[j];
+  const double fu = cc.y * (dj * rcp_fast(di)), fw = cc.x * (di * rcp_fast(dj));
+  sm.rot[buf][0][q] = make_double2(av.x * fu, av.y * fu);
+  sm.rot[buf][1][q] = make_double2(av.x * fw, av.y * fw);
+  sm.scale[i] = di * cc.x;
+  sm.scale[j] = dj * cc.y;
+}
+
+// Round r's shears on the lane's row.
+template <bool FULL, int R_>
+__device__ __forceinline__ void apply_published(double2 (&y)[32], const SolveLds& sm, int buf, int lane) {
+  const double2 u = sm.rot[buf][0][lane & 15], w = sm.rot[buf][1][lane & 15];
+  apply_round<FULL, R_>(y, u, w);
+}
+
+// In the phase after the solve's round r the first row wave turns
+// its rotations into shears, and every row wave applies round r - 1 (the last
+// round of the previous inner sweep, if any, for r = 0).
+template <bool FULL, int R_>
+__device__ __forceinline__ void row_phase(double2 (&y)[32], SolveLds& sm, int& buf, int lane, bool first_wave,
+                                          bool pending) {
+  constexpr int N = sched_rounds<FULL>(), P = (R_ + N - 1) % N;
+  __syncthreads();
+  if (first_wave && lane < 16) publish_shears(sm, buf, R_, lane);
+  if (R_ > 0 || pending) apply_published<FULL, P>(y, sm, buf ^ 1, lane);
+  buf ^= 1;
+}
+template <bool FULL, int... R_>
+__device__ __forceinline__ void row_phases(double2 (&y)[32], SolveLds& sm, int& buf, int lane, bool first_wave,
+                                           bool pending, std::integer_sequence<int, R_...>) {
+  (row_phase<FULL, R_>(y, sm, buf, lane, first_wave, pending), ...);
+}
+template <int ROWS, bool FULL>
+__global__ __launch_bounds__(JSOLVE + ROWS) void k_jac_rotate_rows(JacArgs<double> a) {
+  __shared__ SolveLds sm;
+  const int p = blockIdx.x, chunk = blockIdx.y;
+  const int bi = rr_block(p, a.round, a.nbp), bj = rr_block(a.nbp - 1 - p, a.round, a.nbp);
+  if (pair_skipped(a, bi, bj)) return;
+  const int tid = threadIdx.x;
+  const int rounds = sched_rounds<FULL>();
+  if (tid >= JSOLVE) {
+    const int lane = tid & 63, row = chunk * ROWS + tid - JSOLVE;
+    const bool live = row < a.len, first_wave = tid < JSOLVE + 64;
+    const int lrow = min(row, a.len - 1);   // unconditional loads: predicated ones would wait one by one
+    constexpr int N = sched_rounds<FULL>();
+    double2 y[32];
+#pragma unroll
+    for (int c = 0; c < 32; ++c)
+      y[c] = a.x[(int64_t)((c < 16 ? bi : bj) * 16 + (c & 15)) * a.ldx + lrow];
+    __syncthreads();                       // Gram summed
+    __syncthreads();                       // its pairs checked
+    if (!sm.any_flag) return;
+    int buf = 0;
+    for (int in = 0; in < a.max_inner; ++in)
+      row_phases<FULL>(y, sm, buf, lane, first_wave, in > 0, std::make_integer_sequence<int, N>{});
+    __syncthreads();
+    apply_published<FULL, N - 1>(y, sm, buf ^ 1, lane);
+    if (live) {
+#pragma unroll
+      for (int c = 0; c < 32; ++c) {
+        double2* col = a.x + (int64_t)((c < 16 ? bi : bj) * 16 + (c & 15)) * a.ldx;
+        const double d = sm.scale[c];
+        col[row] = make_double2(y[c].x * d, y[c].y * d);
+      }
+    }
+    return;
+  }
+  // partial Grams summed in chunk order, loads issued eight at a time
+  const double2* part = a.part + (int64_t)p * a.n_gchunks * 1024;
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    const int e = tid + JSOLVE * v;
+    double2 s = make_double2(0.0, 0.0);
+    for (int c0 = 0; c0 < a.n_gchunks; c0 += 8) {
+      double2 t[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+        t[u] = c0 + u < a.n_gchunks ? part[(int64_t)(c0 + u) * 1024 + e] : make_double2(0.0, 0.0);
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        s.x += t[u].x;
+        s.y += t[u].y;
+      }
+    }
+    sm.G[0][e] = s;
+  }
+  for (int e = tid; e < rounds * 16; e += JSOLVE) {
+    sm.ti[0][e] = (unsigned char)sched_i<FULL>(e & 15, e >> 4);
+    sm.tj[0][e] = (unsigned char)sched_j<FULL>(e & 15, e >> 4);
+  }
+  if (tid < 32) sm.scale[tid] = 1.0;
+  if (tid == 0) {
+    sm.any_flag = 0;
+    sm.big = 0;
+  }
+  __syncthreads();
+  // only the pairs this meeting's schedule rotates decide whether it acts
+#pragma unroll
+  for (int v = 0; v < 4; ++v) {
+    const int e = tid + JSOLVE * v, i = e >> 5, j = e & 31;
+    if (i < j && (FULL || (i < 16 && j >= 16))) {
+      const double gii = sm.G[0][33 * i].x, gjj = sm.G[0][33 * j].x;
+      const double2 g = sm.G[0][e];
+      const double h2 = g.x * g.x + g.y * g.y;
+      if (rot_active<double>(gii, gjj, h2, a.tol, a.neg2)) sm.any_flag = 1;
+      if (gii > a.neg2 && gjj > a.neg2 && h2 > a.qtol * gii * gjj) sm.big = 1;
+    }
+  }
+  __syncthreads();
+  if (chunk == 0 && tid == 0 && sm.big) *a.big_cos = 1;
+  if (!sm.any_flag) return;
+  const double tol_in = 0.5 * a.tol, neg2 = a.neg2;
+  const int pb = tid & 15, pa = (pb + (tid >> 4)) & 15, lane_a = (tid & 48) + pa;
+  int buf = 0;
+  int ib = sm.ti[0][pb], jb = sm.tj[0][pb], ia = sm.ti[0][pa], ja = sm.tj[0][pa];
+  for (int left = a.max_inner * rounds, r = 0; left > 0; --left) {
+    const double2* G = sm.G[buf];
+    double2* H = sm.G[buf ^ 1];
+    const double gii = G[33 * ib].x, gjj = G[33 * jb].x;
+    const double2 gij = G[ib * 32 + jb];
+    double2 g00 = G[ia * 32 + ib], g01 = G[ia * 32 + jb], g10 = G[ja * 32 + ib], g11 = G[ja * 32 + jb];
+    r = r + 1 == rounds ? 0 : r + 1;
+    const int ib1 = sm.ti[r][pb], jb1 = sm.tj[r][pb], ia1 = sm.ti[r][pa], ja1 = sm.tj[r][pa];
+    const RotT t = jac_rot_t(gii, gjj, gij, tol_in, neg2);
+    const RotA<double> rb{t.c, t.ax, t.ay};
+    RotA<double> ra;
+    ra.c = __shfl(rb.c, lane_a);
+    ra.ax = __shfl(rb.ax, lane_a);
+    ra.ay = __shfl(rb.ay, lane_a);
+    if (tid < 16) {   // pa == pb: the round's rotations
+      sm.raw[buf][0][pb] = make_double2(t.c, t.ci);
+      sm.raw[buf][1][pb] = make_double2(t.ax, t.ay);
+    }
+    rot_right(rb, g00, g01);
+    rot_right(rb, g10, g11);
+    rot_left(ra, g00, g10);
+    rot_left(ra, g01, g11);
+    H[ia * 32 + ib] = g00;
+    H[ia * 32 + jb] = g01;
+    H[ja * 32 + ib] = g10;
+    H[ja * 32 + jb] = g11;
+    ib = ib1;
+    jb = jb1;
+    ia = ia1;
+    ja = ja1;
+    buf ^= 1;
+    __syncthreads();
+  }
+  __syncthreads();   // the row waves' last phase
+  if (chunk == 0 && tid == 0) {
+    a.rot_cur[bi] = 1;
+    a.rot_cur[bj] = 1;
+    atomicAdd(a.rot_count, 1);
+  }
+}
+
 // rot_prev <- rot_cur (or all ones before the first sweep), rot_cur <- 0,
 // rot_count <- 0, big_cos <- 0.
 __global__ void k_jac_roll(int* rot_prev, int* rot_cur, int* rot_count, int* big_cos, int nbp, int first) {
@@ -597,7 +960,10 @@ static void tuned(int cnt, int* jb, int* inner) {
   if (i && std::atoi(i) >= 1 && std::atoi(i) <= 8) *inner = std::atoi(i);
 }
 
-JacobiPlan jacobi_plan(int len, int cnt, int jb) {
+// Waves of a Gram workgroup.
+static int gram_waves(const JacobiPlan& pl, bool f32) { return pl.jb == 16 && !f32 && pl.len > 768 ? 8 : 4; }
+
+JacobiPlan jacobi_plan(int len, int cnt, int jb, bool f32) {
   JacobiPlan pl;
   int tjb, tin;
   tuned(cnt, &tjb, &tin);
@@ -622,9 +988,11 @@ JacobiPlan jacobi_plan(int len, int cnt, int jb) {
   pl.n_chunks = std::max(1, std::min(target_chunks, max_chunks));
   pl.rows_per_chunk = (int)round_up(ceil_div(len, pl.n_chunks), TR);
   pl.n_chunks = ceil_div(len, pl.rows_per_chunk);
-  // the Gram pass is pure matrix-core streaming: twice the workgroups, so
-  // two share a compute unit and hide each other's load latency
-  pl.n_gchunks = std::max(1, std::min(2 * pl.n_chunks, max_chunks));
+  // Gram chunks: two workgroups per compute unit hide each other's loads
+  if (gram_waves(pl, f32) == 8)
+    pl.n_gchunks = std::max(1, std::min(512 / pl.n_pairs, ceil_div(len, 128)));
+  else
+    pl.n_gchunks = std::max(1, std::min(2 * pl.n_chunks, max_chunks));
   pl.rows_per_gchunk = (int)round_up(ceil_div(len, pl.n_gchunks), TR);
   pl.n_gchunks = ceil_div(len, pl.rows_per_gchunk);
   return pl;
@@ -634,6 +1002,32 @@ size_t jacobi_work_bytes(const JacobiPlan& pl) {
   const int JP = 2 * pl.jb;
   return (size_t)pl.n_pairs * pl.n_gchunks * JP * JP * sizeof(double2) + 2 * (size_t)pl.nbp * sizeof(int) +
          256;
+}
+
+// Row-resident rotate pass: the fewest rows per workgroup (64 to 512) that
+// leave at most one workgroup per compute unit.
+static int rows_per_wg(const JacobiPlan& pl) {
+  for (int rows = 64; rows < 512; rows *= 2)
+    if ((int64_t)pl.n_pairs * ceil_div(pl.len, rows) <= 256) return rows;
+  return 512;
+}
+template <int ROWS>
+static void launch_rotate_rows_n(const JacobiPlan& pl, const JacArgs<double>& a, hipStream_t stream, hipEvent_t start,
+                                 hipEvent_t stop) {
+  const dim3 grid(pl.n_pairs, ceil_div(pl.len, ROWS)), block(JSOLVE + ROWS);
+  if (a.round == 0)
+    hipExtLaunchKernelGGL((k_jac_rotate_rows<ROWS, true>), grid, block, 0, stream, start, stop, 0, a);
+  else
+    hipExtLaunchKernelGGL((k_jac_rotate_rows<ROWS, false>), grid, block, 0, stream, start, stop, 0, a);
+}
+static void launch_rotate_rows(const JacobiPlan& pl, const JacArgs<double>& a, hipStream_t stream, hipEvent_t start,
+                               hipEvent_t stop) {
+  switch (rows_per_wg(pl)) {
+    case 64: launch_rotate_rows_n<64>(pl, a, stream, start, stop); break;
+    case 128: launch_rotate_rows_n<128>(pl, a, stream, start, stop); break;
+    case 256: launch_rotate_rows_n<256>(pl, a, stream, start, stop); break;
+    default: launch_rotate_rows_n<512>(pl, a, stream, start, stop);
+  }
 }
 
 template <typename R>
@@ -650,21 +1044,25 @@ static void launch_sweep(const JacobiPlan& pl, JacArgs<R> a, hipStream_t stream,
     const double by = 16.0 * (double)pl.len * JPd * pl.n_pairs;
     {
       Probe pr(kKcJacGram, stream, fl, by);
-      if (pl.jb == 16)
-        hipExtLaunchKernelGGL((k_jac_gram<32, R>), dim3(pl.n_pairs, pl.n_gchunks), dim3(256), 0, stream, pr.start(),
-                              pr.stop(), 0, a);
+      const int waves = gram_waves(pl, std::is_same<R, float>::value);
+      const dim3 grid(pl.n_pairs, pl.n_gchunks), block(64 * waves);
+      if (pl.jb != 16)
+        hipExtLaunchKernelGGL((k_jac_gram<64, 4, R>), grid, block, 0, stream, pr.start(), pr.stop(), 0, a);
+      else if (waves == 8)
+        hipExtLaunchKernelGGL((k_jac_gram<32, 8, R>), grid, block, 0, stream, pr.start(), pr.stop(), 0, a);
       else
-        hipExtLaunchKernelGGL((k_jac_gram<64, R>), dim3(pl.n_pairs, pl.n_gchunks), dim3(256), 0, stream, pr.start(),
-                              pr.stop(), 0, a);
+        hipExtLaunchKernelGGL((k_jac_gram<32, 4, R>), grid, block, 0, stream, pr.start(), pr.stop(), 0, a);
     }
     HIP_LAUNCH_OK();
     {
       Probe pr(kKcJacRotate, stream, fl, 2.0 * by);
-      if (pl.jb == 16)
-        hipExtLaunchKernelGGL((k_jac_rotate<32, R>), dim3(pl.n_pairs, pl.n_chunks), dim3(ROT_THREADS), 0, stream,
-                              pr.start(), pr.stop(), 0, a);
-      else
+      if (pl.jb != 16)
         hipExtLaunchKernelGGL((k_jac_rotate<64, R>), dim3(pl.n_pairs, pl.n_chunks), dim3(ROT_THREADS), 0, stream,
+                              pr.start(), pr.stop(), 0, a);
+      else if constexpr (std::is_same<R, double>::value)
+        launch_rotate_rows(pl, a, stream, pr.start(), pr.stop());
+      else
+        hipExtLaunchKernelGGL((k_jac_rotate<32, R>), dim3(pl.n_pairs, pl.n_chunks), dim3(ROT_THREADS), 0, stream,
                               pr.start(), pr.stop(), 0, a);
     }
     HIP_LAUNCH_OK();
