@@ -35,8 +35,47 @@ void spectrum_features(const double* s_dev, int k, int bond, int n_sites, int cy
                        float* feat_dev, hipStream_t st);
 void mlp_forward(const float* w, const float* x, int batch, float* out, float* act, hipStream_t s);
 
-// Reduced-precision two-site products (complex64 or split-bf16 on MFMA).
-void contract_two_site_lowp(const double2* A, const double2* B, double2* T, int dl, int dm, int dr,
-                            int precision, hipStream_t s, hipEvent_t start = nullptr, hipEvent_t stop = nullptr);
+// A site tensor: element (s, a, b) at p[s * s_stride + a * ld + b].
+struct SiteView {
+  const double2* p;
+  int64_t s;
+  int ld;
+};
+struct Gate4 {
+  double2 g[16];
+};
+// Where a two-site matrix goes, column-major with leading dimension ld.
+// orient 1: M, rows (s1, a), columns (s2, c); orient 2: M^H.  x0: a second
+// copy, or null.
+struct MixOut {
+  double2* x;
+  double2* x0;
+  int ld, orient;
+};
+// Entry (a, c) of theta' from its four products.
+__device__ inline void mix_store(const double2 (&t)[4], const Gate4& G, int a, int c, int dl, int dr,
+                                 const MixOut& out) {
+#pragma unroll
+  for (int o = 0; o < 4; ++o) {
+    double re = 0.0, im = 0.0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const double2 g = G.g[o * 4 + q];
+      re += g.x * t[q].x - g.y * t[q].y;
+      im += g.x * t[q].y + g.y * t[q].x;
+    }
+    const int row = (o >> 1) * dl + a, col = (o & 1) * dr + c;
+    const int64_t idx = out.orient == 1 ? (int64_t)col * out.ld + row : (int64_t)row * out.ld + col;
+    const double2 v = make_double2(re, out.orient == 1 ? im : -im);
+    out.x[idx] = v;
+    if (out.x0) out.x0[idx] = v;
+  }
+}
+// theta' of A (dl x dm per s) and B (dm x dr per s) in the given precision.
+void contract_mix(const SiteView& A, const SiteView& B, const Gate4& G, int dl, int dm, int dr, int precision,
+                  const MixOut& out, hipStream_t s);
+// The same in complex64 or split bf16.
+void contract_mix_lowp(const SiteView& A, const SiteView& B, const Gate4& G, int dl, int dm, int dr, int precision,
+                       const MixOut& out, hipStream_t s, hipEvent_t start, hipEvent_t stop);
 
 }  // namespace rcs

@@ -96,87 +96,89 @@ __global__ void k_apply_1q(Layer1q L) {
   }
 }
 
-// T[q][a][c] = A_i^{s1'}[a][:] . A_{i+1}^{s2'}[:][c], q = 2 s1' + s2'
-__global__ __launch_bounds__(GT_THREADS) void k_two_site_f64(const double2* A, const double2* B,
-                                                            double2* T, int dl, int dm, int dr) {
-  __shared__ SmemC64 sm;
-  const int q = blockIdx.z, s1 = q >> 1, s2 = q & 1;
-  const int m0 = blockIdx.y * GT_M, n0 = blockIdx.x * GT_N;
-  const double2* a = A + (int64_t)s1 * dl * dm;
-  const double2* b = B + (int64_t)s2 * dm * dr;
-  auto fa = [&](int m, int k) -> double2 { return a[(int64_t)m * dm + k]; };
-  auto fb = [&](int k, int n) -> double2 { return b[(int64_t)k * dr + n]; };
-  LoadA<decltype(fa), true> la{fa, m0, dl, dm};
-  LoadB<decltype(fb), true> lb{fb, n0, dm, dr};
+// The two-site matrix theta'[s1][s2][a][c] = sum_q G[(s1 s2), q] T[q][a][c],
+// T[q] = A^{s1'} B^{s2'} (q = 2 s1' + s2'), in one pass: a workgroup computes
+// the four products of a 32 x 32 tile (a, c) as one 64 x 64 tile of the
+// stacked operands (rows (s1', a), columns (s2', c)), exchanges them through
+// LDS and writes the mixed result.  Written separately, the products cost a
+// 64 dl dr byte write and read: 31 us next to a 597 us product at bond 1024.
+// Strided views let the export layout be read in place.  The whole call at
+// bond 1024 takes 581 us (59 TFLOP/s), 960 us with separate products, copies
+// to the device layout and their allocations.
+constexpr int TS_T = 32;   // tile side in a and c
+
+// Tile row (or column) x = (s, i), s = x / 32, of a stacked operand:
+// element k of row (s, x0 + i) is base[s * sstride + (x0 + i) * xstride + k * kstride].
+template <bool KFAST_>
+struct StackedOp {
+  static constexpr bool KFAST = KFAST_;
+  const double2* base;
+  int64_t sstride;
+  int xstride, kstride, x0, X, K;
+  __device__ inline void fetch(double2 (&r)[GT_PER], int k0, int tid) const {
+#pragma unroll
+    for (int j = 0; j < GT_PER; ++j) {
+      const int e = tid + j * GT_THREADS;
+      const int x = KFAST ? e / GT_K : e % GT_M, k = (KFAST ? e % GT_K : e / GT_M) + k0;
+      const int i = x0 + (x & (TS_T - 1));
+      r[j] = make_double2(0.0, 0.0);
+      if (i < X && k < K) r[j] = base[(x / TS_T) * sstride + (int64_t)i * xstride + (int64_t)k * kstride];
+    }
+  }
+  __device__ inline void commit(double2* s, const double2 (&r)[GT_PER], int tid) const {
+#pragma unroll
+    for (int j = 0; j < GT_PER; ++j) {
+      const int e = tid + j * GT_THREADS;
+      s[lds_unit<KFAST>(KFAST ? e / GT_K : e % GT_M, KFAST ? e % GT_K : e / GT_M)] = r[j];
+    }
+  }
+};
+
+__global__ __launch_bounds__(GT_THREADS) void k_two_site_mix(SiteView A, SiteView B, Gate4 G, int dl, int dm, int dr,
+                                                            MixOut out) {
+  __shared__ union {
+    SmemC64 sm;
+    double2 t[4][TS_T][TS_T + 1];
+  } u;
+  const int a0 = blockIdx.y * TS_T, c0 = blockIdx.x * TS_T;
+  const StackedOp<true> la{A.p, A.s, A.ld, 1, a0, dl, dm};
+  const StackedOp<false> lb{B.p, B.s, 1, B.ld, c0, dr, dm};
   AccC64 acc;
   acc_zero(acc);
-  cgemm_mainloop(la, lb, dm, sm, acc);
-  double2* t = T + (int64_t)q * dl * dr;
+  cgemm_mainloop(la, lb, dm, u.sm, acc);
+  __syncthreads();
   acc_foreach(acc, [&](int r, int c, double re, double im) {
-    int m = m0 + r, n = n0 + c;
-    if (m < dl && n < dr) t[(int64_t)m * dr + n] = make_double2(re, im);
+    u.t[2 * (r / TS_T) + c / TS_T][r % TS_T][c % TS_T] = make_double2(re, im);
   });
+  __syncthreads();
+  for (int e = threadIdx.x; e < TS_T * TS_T; e += GT_THREADS) {
+    const int i = out.orient == 1 ? e % TS_T : e / TS_T, j = out.orient == 1 ? e / TS_T : e % TS_T;
+    if (a0 + i < dl && c0 + j < dr) {
+      const double2 t[4] = {u.t[0][i][j], u.t[1][i][j], u.t[2][i][j], u.t[3][i][j]};
+      mix_store(t, G, a0 + i, c0 + j, dl, dr, out);
+    }
+  }
 }
 
-// T = the four products A^{s1'} B^{s2'} in the requested contraction precision.
-void contract_two_site(const double2* A, const double2* B, double2* T, int dl, int dm, int dr, int precision,
-                       hipStream_t s) {
+void contract_mix(const SiteView& A, const SiteView& B, const Gate4& G, int dl, int dm, int dr, int precision,
+                  const MixOut& out, hipStream_t s) {
   Probe pr(kKcTwoSite, s, 32.0 * dl * (double)dm * dr, 16.0 * (2.0 * dl * dm + 2.0 * dm * dr + 4.0 * dl * dr));
   if (precision != RCS_PREC_C128) {
-    contract_two_site_lowp(A, B, T, dl, dm, dr, precision, s, pr.start(), pr.stop());
+    contract_mix_lowp(A, B, G, dl, dm, dr, precision, out, s, pr.start(), pr.stop());
     return;
   }
-  hipExtLaunchKernelGGL(k_two_site_f64, dim3(ceil_div(dr, GT_N), ceil_div(dl, GT_M), 4), dim3(GT_THREADS), 0, s,
-                        pr.start(), pr.stop(), 0, A, B, T, dl, dm, dr);
+  hipExtLaunchKernelGGL(k_two_site_mix, dim3(ceil_div(dr, TS_T), ceil_div(dl, TS_T)), dim3(GT_THREADS), 0, s,
+                        pr.start(), pr.stop(), 0, A, B, G, dl, dm, dr, out);
   HIP_LAUNCH_OK();
 }
 
-struct Gate4 {
-  double2 g[16];
-};
-
-// theta'[s1][s2][a][c] = sum_q G[(s1 s2), q] T[q][a][c] written to X (and X0)
-// column-major.  case 1: X = M (rows (s1,a), cols (s2,c)); case 2: X = M^H.
-__global__ void k_mix_gate(const double2* T, Gate4 G, int dl, int dr, int orient, double2* X,
-                           double2* X0, int ldx) {
-  const int64_t tot = (int64_t)dl * dr;
-  for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < tot;
-       e += (int64_t)gridDim.x * blockDim.x) {
-    int a, c;
-    if (orient == 1) {  // a fastest: column-major writes along rows (s1, a)
-      a = (int)(e % dl);
-      c = (int)(e / dl);
-    } else {            // c fastest: rows are (s2, c)
-      c = (int)(e % dr);
-      a = (int)(e / dr);
-    }
-    double2 t[4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) t[q] = T[(int64_t)q * tot + (int64_t)a * dr + c];
-#pragma unroll
-    for (int o = 0; o < 4; ++o) {
-      double re = 0.0, im = 0.0;
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        double2 g = G.g[o * 4 + q];
-        re += g.x * t[q].x - g.y * t[q].y;
-        im += g.x * t[q].y + g.y * t[q].x;
-      }
-      const int s1 = o >> 1, s2 = o & 1;
-      int64_t idx;
-      double2 v;
-      if (orient == 1) {
-        idx = (int64_t)(s2 * dr + c) * ldx + (s1 * dl + a);
-        v = make_double2(re, im);
-      } else {
-        idx = (int64_t)(s1 * dl + a) * ldx + (s2 * dr + c);
-        v = make_double2(re, -im);
-      }
-      X[idx] = v;
-      X0[idx] = v;
-    }
-  }
+static Gate4 to_gate4(const double2* g16) {
+  Gate4 G;
+  for (int e = 0; e < 16; ++e) G.g[e] = g16[e];
+  return G;
 }
+// Site tensors in the device layout [s][a][b].
+static SiteView site_view(const double2* p, int da, int db) { return SiteView{p, (int64_t)da * db, db}; }
 
 // Single-site orthogonalisation input.  right: X[b][(s,a)] = A[s][a][b];
 // left: X[a][(s,b)] = conj(A[s][a][b]).
@@ -646,21 +648,9 @@ __global__ void k_copy_basis(const double2* Q, int ldq, int len, int l, double2*
   }
 }
 
-// Export layout (a, s, b) -> device layout [s][a][b]
-__global__ void k_to_device_layout(const double2* in, int da, int db, double2* out) {
-  const int64_t tot = (int64_t)2 * da * db;
-  for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < tot;
-       e += (int64_t)gridDim.x * blockDim.x) {
-    const int b = (int)(e % db);
-    const int s = (int)((e / db) % 2);
-    const int a = (int)(e / (2 * (int64_t)db));
-    out[((int64_t)s * da + a) * db + b] = in[e];
-  }
-}
-
 // ------------------------------------------------------------ workspace
 struct BuildWork {
-  DevBuf T, X, X0, Wn, P, H, jac, sigma, sorted, order, scal, rot, tmp;
+  DevBuf X, X0, Wn, P, H, jac, sigma, sorted, order, scal, rot, tmp;
   DevBuf G, Rd, Y, order_x, cflag;   // preconditioned split
   DevBuf Y32;                         // its fp32 copy (RCS_SVD_F32)
   DevBuf Ri, Tq, qdev;                // CholeskyQR centre moves
@@ -962,7 +952,7 @@ static bool svd_split_chol(rcs_state_s& st, BuildWork& ws, const JacobiPlan& pl,
   return true;
 }
 
-void ensure_work(BuildWork& ws, const JacobiPlan& pl, int64_t t_elems) {
+void ensure_work(BuildWork& ws, const JacobiPlan& pl) {
   const size_t xbytes = (size_t)pl.ldx * pl.cnt_pad * sizeof(double2);
   ws.X.ensure(xbytes);
   ws.X0.ensure(xbytes);
@@ -975,7 +965,6 @@ void ensure_work(BuildWork& ws, const JacobiPlan& pl, int64_t t_elems) {
   ws.order.ensure((size_t)pl.cnt_pad * sizeof(int));
   ws.scal.ensure(sizeof(RankOut));
   ws.rot.ensure(2 * sizeof(int));
-  if (t_elems > 0) ws.T.ensure((size_t)t_elems * sizeof(double2));
 }
 
 // Nominal work of the factorisations (real flops, complex counted as 4x
@@ -1055,7 +1044,7 @@ static void move_center(rcs_state_s& st, BuildWork& ws, bool right) {
   const int len = right ? 2 * dl : 2 * dr;
   const int cnt = right ? dr : dl;
   JacobiPlan pl = jacobi_plan(len, cnt);
-  ensure_work(ws, pl, 0);
+  ensure_work(ws, pl);
   HIP_OK(hipMemsetAsync(ws.X.p, 0, (size_t)pl.ldx * pl.cnt_pad * sizeof(double2), s));
   HIP_OK(hipMemsetAsync(ws.X0.p, 0, (size_t)pl.ldx * pl.cnt_pad * sizeof(double2), s));
   hipLaunchKernelGGL(k_load_site, dim3(grid1d((int64_t)2 * dl * dr)), dim3(256), 0, s, st.site[c], dl, dr,
@@ -1150,7 +1139,7 @@ static void record_bond_spectrum(rcs_state_s& st, BuildWork& ws, UpdateCtx& ctx,
   ctx.bond_k[i] = kk;
 }
 
-// Randomized split of the two-site matrix (T already holds the products).
+// Randomized split of the two-site matrix.
 // Returns false when the randomized path does not apply or the judge rejects.
 static bool randomized_split(rcs_state_s& st, BuildWork& ws, UpdateCtx& ctx, int i, const double2* gate16,
                              int cap, double eps, int cycle, bool log_spectra) {
@@ -1184,18 +1173,15 @@ static bool randomized_split(rcs_state_s& st, BuildWork& ws, UpdateCtx& ctx, int
   if (l >= m) return false;   // the sketch would cover the whole space: plain split
   // predicted cap-limited cut with the fp32 full SVD available: no sketch
   if (o.svd_f32 && o.rank_mode == RCS_RANK_LEARNED && k_hat >= cap) return false;
-  // M (len x cnt, column-major) from the products
+  // M (len x cnt, column-major)
   const int ldm = (int)round_up(len, 64);
   ctx.M.ensure((size_t)ldm * round_up(cnt, 64) * sizeof(double2));
   double2* M = ctx.M.as<double2>();
-  Gate4 G;
-  for (int e = 0; e < 16; ++e) G.g[e] = gate16[e];
-  hipLaunchKernelGGL(k_mix_gate, dim3(grid1d((int64_t)dl * dr)), dim3(256), 0, s, ws.T.as<double2>(), G, dl, dr, 1,
-                     M, M, ldm);
-  HIP_LAUNCH_OK();
+  contract_mix(site_view(st.site[i], dl, dm), site_view(st.site[i + 1], dm, dr), to_gate4(gate16), dl, dm, dr,
+               o.contraction, MixOut{M, nullptr, ldm, 1}, s);
   range_finder(M, ldm, len, cnt, l, std::max(0, o.rsvd_q), o.rsvd_seed, (uint64_t)ctx.update_index, ctx.rw, s);
   JacobiPlan pl = jacobi_plan(cnt, l);
-  ensure_work(ws, pl, 0);
+  ensure_work(ws, pl);
   ws.sigma.ensure((size_t)std::max(cnt, pl.cnt_pad) * sizeof(double));
   HIP_OK(hipMemsetAsync(ws.X.p, 0, (size_t)pl.ldx * pl.cnt_pad * sizeof(double2), s));
   HIP_OK(hipMemsetAsync(ws.X0.p, 0, (size_t)pl.ldx * pl.cnt_pad * sizeof(double2), s));
@@ -1286,8 +1272,6 @@ static void two_site_update(rcs_state_s& st, BuildWork& ws, UpdateCtx& ctx, int 
   const int dl = st.dims[i], dm = st.dims[i + 1], dr = st.dims[i + 2];
   const int cap_eff = std::min(cap, st.cap[i + 1]);
   ctx.update_index += 1;
-  ws.T.ensure((size_t)4 * dl * dr * sizeof(double2));
-  contract_two_site(st.site[i], st.site[i + 1], ws.T.as<double2>(), dl, dm, dr, precision, s);
   const size_t n_log = st.rsvd_log.size();
   ctx.pred_capped = true;
   if (ctx.o && ctx.o->rank_mode != RCS_RANK_FULL_SVD &&
@@ -1310,14 +1294,11 @@ static void two_site_update(rcs_state_s& st, BuildWork& ws, UpdateCtx& ctx, int 
   const int len = orient == 1 ? 2 * dl : 2 * dr;
   const int cnt = orient == 1 ? 2 * dr : 2 * dl;
   JacobiPlan pl = jacobi_plan(len, cnt);
-  ensure_work(ws, pl, 0);
+  ensure_work(ws, pl);
   HIP_OK(hipMemsetAsync(ws.X.p, 0, (size_t)pl.ldx * pl.cnt_pad * sizeof(double2), s));
   HIP_OK(hipMemsetAsync(ws.X0.p, 0, (size_t)pl.ldx * pl.cnt_pad * sizeof(double2), s));
-  Gate4 G;
-  for (int e = 0; e < 16; ++e) G.g[e] = gate16[e];
-  hipLaunchKernelGGL(k_mix_gate, dim3(grid1d((int64_t)dl * dr)), dim3(256), 0, s, ws.T.as<double2>(), G, dl,
-                     dr, orient, ws.X.as<double2>(), ws.X0.as<double2>(), pl.ldx);
-  HIP_LAUNCH_OK();
+  contract_mix(site_view(st.site[i], dl, dm), site_view(st.site[i + 1], dm, dr), to_gate4(gate16), dl, dm, dr, precision,
+               MixOut{ws.X.as<double2>(), ws.X0.as<double2>(), pl.ldx, orient}, s);
   std::vector<double> spec;
   SplitResult r{};
   int ldw = pl.ldx, p_row = pl.cnt, side = orient;
@@ -1571,7 +1552,7 @@ rcs_status rcs_svd_jacobi(int32_t len, int32_t cnt, double* x_dev, double* s_dev
   hipStream_t s = rcs::as_stream(stream);
   rcs::JacobiPlan pl = rcs::jacobi_plan(len, cnt);
   std::unique_ptr<rcs::BuildWork, void (*)(rcs::BuildWork*)> ws(rcs::new_work(), rcs::delete_work);
-  rcs::ensure_work(*ws, pl, 0);
+  rcs::ensure_work(*ws, pl);
   HIP_OK(hipMemsetAsync(ws->X.p, 0, (size_t)pl.ldx * pl.cnt_pad * sizeof(double2), s));
   double2* X = ws->X.as<double2>();
   HIP_OK(hipMemsetAsync(ws->X0.p, 0, (size_t)pl.ldx * pl.cnt_pad * sizeof(double2), s));
@@ -1617,7 +1598,7 @@ rcs_status rcs_svd_jacobi_f32(int32_t len, int32_t cnt, const double* x_dev, dou
   hipStream_t s = rcs::as_stream(stream);
   rcs::JacobiPlan pl = rcs::jacobi_plan(len, cnt, 0, true);
   std::unique_ptr<rcs::BuildWork, void (*)(rcs::BuildWork*)> ws(rcs::new_work(), rcs::delete_work);
-  rcs::ensure_work(*ws, pl, 0);
+  rcs::ensure_work(*ws, pl);
   HIP_OK(hipMemsetAsync(ws->X.p, 0, (size_t)pl.ldx * pl.cnt_pad * sizeof(double2), s));
   HIP_OK(hipMemsetAsync(ws->X0.p, 0, (size_t)pl.ldx * pl.cnt_pad * sizeof(double2), s));
   double2* X = ws->X.as<double2>();
@@ -1665,7 +1646,7 @@ rcs_status rcs_cholqr(int32_t len, int32_t cnt, const double* x_dev, double* q_d
   hipStream_t s = rcs::as_stream(stream);
   rcs::JacobiPlan pl = rcs::jacobi_plan(len, cnt);
   std::unique_ptr<rcs::BuildWork, void (*)(rcs::BuildWork*)> ws(rcs::new_work(), rcs::delete_work);
-  rcs::ensure_work(*ws, pl, 0);
+  rcs::ensure_work(*ws, pl);
   HIP_OK(hipMemsetAsync(ws->X.p, 0, (size_t)pl.ldx * pl.cnt_pad * sizeof(double2), s));
   HIP_OK(hipMemsetAsync(ws->X0.p, 0, (size_t)pl.ldx * pl.cnt_pad * sizeof(double2), s));
   hipLaunchKernelGGL(rcs::k_copy_in, dim3(rcs::grid1d((int64_t)len * cnt)), dim3(256), 0, s,
@@ -1704,7 +1685,7 @@ rcs_status rcs_rsvd(int32_t len, int32_t cnt, const double* x_dev, int32_t l, in
   HIP_LAUNCH_OK();
   rcs::range_finder(M.as<double2>(), ldm, len, cnt, l, q, seed, step, rw, s);
   rcs::JacobiPlan pl = rcs::jacobi_plan(cnt, l);
-  rcs::ensure_work(*ws, pl, 0);
+  rcs::ensure_work(*ws, pl);
   ws->sigma.ensure((size_t)std::max(cnt, pl.cnt_pad) * sizeof(double));
   HIP_OK(hipMemsetAsync(ws->X.p, 0, (size_t)pl.ldx * pl.cnt_pad * sizeof(double2), s));
   HIP_OK(hipMemsetAsync(ws->X0.p, 0, (size_t)pl.ldx * pl.cnt_pad * sizeof(double2), s));
@@ -1757,22 +1738,12 @@ rcs_status rcs_two_site(int32_t dl, int32_t dm, int32_t dr, const double* a_dev,
   RCS_REQUIRE(dl >= 1 && dm >= 1 && dr >= 1 && dl <= 4096 && dm <= 4096 && dr <= 4096, "bad dimensions");
   RCS_REQUIRE(precision >= 0 && precision <= 2, "bad precision");
   hipStream_t s = rcs::as_stream(stream);
-  rcs::DevBuf A, B, T;
-  A.ensure((size_t)2 * dl * dm * sizeof(double2));
-  B.ensure((size_t)2 * dm * dr * sizeof(double2));
-  T.ensure((size_t)4 * dl * dr * sizeof(double2));
-  hipLaunchKernelGGL(rcs::k_to_device_layout, dim3(rcs::grid1d((int64_t)2 * dl * dm)), dim3(256), 0, s,
-                     reinterpret_cast<const double2*>(a_dev), dl, dm, A.as<double2>());
-  HIP_LAUNCH_OK();
-  hipLaunchKernelGGL(rcs::k_to_device_layout, dim3(rcs::grid1d((int64_t)2 * dm * dr)), dim3(256), 0, s,
-                     reinterpret_cast<const double2*>(b_dev), dm, dr, B.as<double2>());
-  HIP_LAUNCH_OK();
-  rcs::contract_two_site(A.as<double2>(), B.as<double2>(), T.as<double2>(), dl, dm, dr, precision, s);
   rcs::Gate4 G;
   for (int e = 0; e < 16; ++e) G.g[e] = make_double2(gate_host[2 * e], gate_host[2 * e + 1]);
-  hipLaunchKernelGGL(rcs::k_mix_gate, dim3(rcs::grid1d((int64_t)dl * dr)), dim3(256), 0, s, T.as<double2>(), G,
-                     dl, dr, 1, reinterpret_cast<double2*>(out_dev), reinterpret_cast<double2*>(out_dev), 2 * dl);
-  HIP_LAUNCH_OK();
+  // the export layout (a, s, b), read in place
+  rcs::contract_mix(rcs::SiteView{reinterpret_cast<const double2*>(a_dev), dm, 2 * dm},
+                    rcs::SiteView{reinterpret_cast<const double2*>(b_dev), dr, 2 * dr}, G, dl, dm, dr, precision,
+                    rcs::MixOut{reinterpret_cast<double2*>(out_dev), nullptr, 2 * dl, 1}, s);
   HIP_OK(hipStreamSynchronize(s));
   RCS_API_END
 }

@@ -1,4 +1,5 @@
-// Two-site contraction T^{s1 s2} = A_i^{s1} A_{i+1}^{s2} in reduced precision.
+// The two-site matrix (products A_i^{s1} A_{i+1}^{s2} mixed with the gate) in
+// reduced precision.
 //
 //  complex64 : operands rounded to fp32, v_mfma_f32_16x16x4f32, fp32 sums;
 //  split-bf16: each fp32 operand x = hi + lo with hi = bf16(x), lo =
@@ -7,8 +8,10 @@
 //              accumulation (Henry, Tang, Heinecke, ARITH 2019), complex
 //              products in the four-real-product form.
 // Site tensors stay complex128 in HBM; operands are converted while staged
-// into LDS (fp32 planes), the bf16 split happens in registers.  The result
-// is written as complex128 for the fp64 SVD.
+// into LDS, once per element.  As in the fp64 kernel a workgroup computes the
+// four products of a 32 x 32 tile (a, c) as one 64 x 64 tile of the stacked
+// operands, one product per wave, exchanges them through LDS and writes the
+// mixed complex128 result, so the products never go to memory.
 //
 // MFMA layouts (lane l): f32 16x16x4: A[l%16][l/16], B[l/16][l%16];
 // bf16 16x16x32: A[l%16][8(l/16)+j], B[8(l/16)+j][l%16], j = 0..7;
@@ -16,156 +19,230 @@
 #include <hip/hip_ext.h>
 
 #include "build.h"
-#include "gemm_f64.h"
+#include "common.h"
 
 namespace rcs {
 
-constexpr int CT_M = 64, CT_N = 64, CT_K = 32;
+constexpr int CT_T = 32;      // tile side in a and c
+constexpr int CT_K = 32;      // k-values per stage
+constexpr int CT_THREADS = 256;
 
-struct SmemF32 {
-  float ar[CT_M][CT_K + 4];  // A[m][k]
-  float ai[CT_M][CT_K + 4];
-  float br[CT_N][CT_K + 4];  // B transposed: B[k][n] at [n][k]
-  float bi[CT_N][CT_K + 4];
+// Staged operand rows x = (s, i) with k contiguous: fp32 planes (padded rows
+// of 36), or bf16 planes (re hi, re lo, im hi, im lo) of 64-byte rows whose
+// four 16-byte units are XOR-permuted by the row, so that the fragment reads
+// (16 rows at one unit) and the writes spread over the banks.
+struct StageF32 {
+  float re[2 * CT_T][CT_K + 4], im[2 * CT_T][CT_K + 4];
+};
+struct StageBf16 {
+  uint16_t v[4][2 * CT_T * CT_K];
+};
+__device__ inline int bf_off(int x, int k) { return x * CT_K + (((k >> 3) ^ ((x >> 2) & 3)) << 3) + (k & 7); }
+
+__device__ inline uint16_t bf_bits(__bf16 h) {
+  uint16_t b;
+  __builtin_memcpy(&b, &h, 2);
+  return b;
+}
+// The operand's fp32 value.  It must be rounded to fp32 before it is split:
+// under contraction the compiler would merge both roundings into one from
+// fp64 to bf16, which differs on double-rounding cases.
+__device__ inline float fp32_value(double x) {
+  float f = (float)x;
+  asm("" : "+v"(f));
+  return f;
+}
+// hi and lo parts of two neighbouring k-values, packed.
+__device__ inline void split2(float x0, float x1, uint32_t& hi, uint32_t& lo) {
+  const __bf16 h0 = (__bf16)x0, h1 = (__bf16)x1;
+  const __bf16 l0 = (__bf16)(x0 - (float)h0), l1 = (__bf16)(x1 - (float)h1);
+  hi = bf_bits(h0) | ((uint32_t)bf_bits(h1) << 16);
+  lo = bf_bits(l0) | ((uint32_t)bf_bits(l1) << 16);
+}
+__device__ inline void put2(StageF32& s, int x, int k, const double2& v0, const double2& v1) {
+  *reinterpret_cast<float2*>(&s.re[x][k]) = make_float2((float)v0.x, (float)v1.x);
+  *reinterpret_cast<float2*>(&s.im[x][k]) = make_float2((float)v0.y, (float)v1.y);
+}
+__device__ inline void put2(StageBf16& s, int x, int k, const double2& v0, const double2& v1) {
+  uint32_t hi, lo;
+  const int o = bf_off(x, k);
+  split2(fp32_value(v0.x), fp32_value(v1.x), hi, lo);
+  *reinterpret_cast<uint32_t*>(&s.v[0][o]) = hi;
+  *reinterpret_cast<uint32_t*>(&s.v[1][o]) = lo;
+  split2(fp32_value(v0.y), fp32_value(v1.y), hi, lo);
+  *reinterpret_cast<uint32_t*>(&s.v[2][o]) = hi;
+  *reinterpret_cast<uint32_t*>(&s.v[3][o]) = lo;
+}
+
+struct AccLowp {
+  float4_t re[2][2], im[2][2];
 };
 
-__device__ inline void stage_f32(SmemF32& s, const double2* a, const double2* b, int dl, int dm, int dr,
-                                 int m0, int n0, int k0, int tid) {
-  // A: 64 x 32, k contiguous in HBM (row-major dl x dm)
-  for (int e = tid; e < CT_M * CT_K; e += 256) {
-    const int k = e % CT_K, m = e / CT_K;
-    double2 v = make_double2(0.0, 0.0);
-    if (m0 + m < dl && k0 + k < dm) v = a[(int64_t)(m0 + m) * dm + k0 + k];
-    s.ar[m][k] = (float)v.x;
-    s.ai[m][k] = (float)v.y;
+// One 32-deep stage: the wave's 32 x 32 product of rows wm.. and columns wn...
+__device__ inline void mma_lowp(const StageF32& a, const StageF32& b, AccLowp& c, int wm, int wn, int lane) {
+#pragma unroll
+  for (int kk = 0; kk < CT_K; kk += 4) {
+    const int k = kk + (lane >> 4);
+    float ar[2], ai[2], br[2], bi[2];
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      ar[t] = a.re[wm + t * 16 + (lane & 15)][k];
+      ai[t] = a.im[wm + t * 16 + (lane & 15)][k];
+      br[t] = b.re[wn + t * 16 + (lane & 15)][k];
+      bi[t] = b.im[wn + t * 16 + (lane & 15)][k];
+    }
+#pragma unroll
+    for (int mt = 0; mt < 2; ++mt)
+#pragma unroll
+      for (int nt = 0; nt < 2; ++nt) {
+        c.re[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(ar[mt], br[nt], c.re[mt][nt], 0, 0, 0);
+        c.re[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(-ai[mt], bi[nt], c.re[mt][nt], 0, 0, 0);
+        c.im[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(ar[mt], bi[nt], c.im[mt][nt], 0, 0, 0);
+        c.im[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(ai[mt], br[nt], c.im[mt][nt], 0, 0, 0);
+      }
   }
-  // B: 32 x 64, n contiguous in HBM (row-major dm x dr)
-  for (int e = tid; e < CT_K * CT_N; e += 256) {
-    const int n = e % CT_N, k = e / CT_N;
-    double2 v = make_double2(0.0, 0.0);
-    if (k0 + k < dm && n0 + n < dr) v = b[(int64_t)(k0 + k) * dr + n0 + n];
-    s.br[n][k] = (float)v.x;
-    s.bi[n][k] = (float)v.y;
+}
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+__device__ inline bf16x8_t bf_frag(const StageBf16& s, int plane, int x, int lane) {
+  return *reinterpret_cast<const bf16x8_t*>(&s.v[plane][bf_off(x + (lane & 15), 8 * (lane >> 4))]);
+}
+__device__ inline bf16x8_t bf_neg(bf16x8_t v) {
+  u32x4 b;
+  __builtin_memcpy(&b, &v, 16);
+  b ^= 0x80008000u;
+  __builtin_memcpy(&v, &b, 16);
+  return v;
+}
+__device__ inline void mma_lowp(const StageBf16& a, const StageBf16& b, AccLowp& c, int wm, int wn, int lane) {
+  bf16x8_t bf[4][2];
+#pragma unroll
+  for (int p = 0; p < 4; ++p)
+#pragma unroll
+    for (int t = 0; t < 2; ++t) bf[p][t] = bf_frag(b, p, wn + t * 16, lane);
+#pragma unroll
+  for (int mt = 0; mt < 2; ++mt) {
+    const bf16x8_t arh = bf_frag(a, 0, wm + mt * 16, lane), arl = bf_frag(a, 1, wm + mt * 16, lane);
+    const bf16x8_t aih = bf_frag(a, 2, wm + mt * 16, lane), ail = bf_frag(a, 3, wm + mt * 16, lane);
+    const bf16x8_t naih = bf_neg(aih), nail = bf_neg(ail);
+    const bf16x8_t ar[6] = {arh, arh, arl, naih, naih, nail}, ai[6] = {arh, arh, arl, aih, aih, ail};
+    constexpr int pr[6] = {0, 1, 0, 2, 3, 2}, pi[6] = {2, 3, 2, 0, 1, 0};
+    // Re += Ar Br - Ai Bi, Im += Ar Bi + Ai Br, each as hi hi', hi lo', lo hi'
+#pragma unroll
+    for (int e = 0; e < 6; ++e)
+#pragma unroll
+      for (int nt = 0; nt < 2; ++nt) {
+        c.re[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ar[e], bf[pr[e]][nt], c.re[mt][nt], 0, 0, 0);
+        c.im[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ai[e], bf[pi[e]][nt], c.im[mt][nt], 0, 0, 0);
+      }
   }
 }
 
-template <int PREC>
-__global__ __launch_bounds__(256) void k_two_site_lowp(const double2* A, const double2* B, double2* T, int dl,
-                                                      int dm, int dr) {
-  __shared__ SmemF32 sm;
-  const int q = blockIdx.z, s1 = q >> 1, s2 = q & 1;
-  const int m0 = blockIdx.y * CT_M, n0 = blockIdx.x * CT_N;
-  const double2* a = A + (int64_t)s1 * dl * dm;
-  const double2* b = B + (int64_t)s2 * dm * dr;
+// Bound: the bf16 form by staging (fp64 operands read from L2/HBM, four
+// 16-bit planes written to LDS; its MFMAs take a quarter of the time), the
+// fp32 form by the fp32 matrix cores.  The next stage's operands are in
+// registers while the matrix cores work; the LDS stage is double-buffered.
+// At bonds 700, 1001, 517 the call takes 113 us in split bf16 (358 us with the
+// split made per fragment by every wave, the products written to memory and
+// mixed from there, and operands copied to the device layout first).
+template <class Stage>
+__global__ __launch_bounds__(CT_THREADS) void k_two_site_mix_lowp(SiteView A, SiteView B, Gate4 G, int dl, int dm,
+                                                                 int dr, MixOut out) {
+  __shared__ union {
+    struct {
+      Stage a, b;
+    } st[2];
+    float2 t[4][CT_T][CT_T + 1];
+  } u;
+  const int a0 = blockIdx.y * CT_T, c0 = blockIdx.x * CT_T;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const int wm = (w & 1) * 32, wn = (w >> 1) * 32;
-  float4_t cr[2][2], ci[2][2];
+  const int wm = (w & 1) * 32, wn = (w >> 1) * 32;      // wave (s1, s2)
+  // A rows: 16 lanes cover the 32 k-values of a row (two each), four passes
+  // of 16 rows; B: lanes along c, two k-values each, four passes
+  const int ak = 2 * (tid & 15), ax = tid >> 4;
+  const int bx = tid & 63, bk = 2 * (tid >> 6);
+  double2 ra[4][2], rb[4][2];
+  auto fetch = [&](int k0) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int x = ax + 16 * j, i = a0 + (x & 31);
+      const double2* row = A.p + (x >> 5) * A.s + (int64_t)i * A.ld;
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const int k = k0 + ak + h;
+        ra[j][h] = make_double2(0.0, 0.0);
+        if (i < dl && k < dm) ra[j][h] = row[k];
+      }
+    }
+    const int c = c0 + (bx & 31);
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) {
+        const int k = k0 + bk + 8 * j + h;
+        rb[j][h] = make_double2(0.0, 0.0);
+        if (c < dr && k < dm) rb[j][h] = B.p[(bx >> 5) * B.s + (int64_t)k * B.ld + c];
+      }
+  };
+  auto commit = [&](int buf) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      put2(u.st[buf].a, ax + 16 * j, ak, ra[j][0], ra[j][1]);
+      put2(u.st[buf].b, bx, bk + 8 * j, rb[j][0], rb[j][1]);
+    }
+  };
+  AccLowp acc;
 #pragma unroll
   for (int i = 0; i < 2; ++i)
 #pragma unroll
     for (int j = 0; j < 2; ++j) {
-      cr[i][j] = float4_t{0, 0, 0, 0};
-      ci[i][j] = float4_t{0, 0, 0, 0};
+      acc.re[i][j] = float4_t{0, 0, 0, 0};
+      acc.im[i][j] = float4_t{0, 0, 0, 0};
     }
+  fetch(0);
+  commit(0);
+  __syncthreads();
+  int buf = 0;
   for (int k0 = 0; k0 < dm; k0 += CT_K) {
-    stage_f32(sm, a, b, dl, dm, dr, m0, n0, k0, tid);
-    __syncthreads();
-    if (PREC == RCS_PREC_C64) {
-#pragma unroll
-      for (int kk = 0; kk < CT_K; kk += 4) {
-        const int k = kk + (lane >> 4);
-        float ar[2], ai[2], nai[2], br[2], bi[2];
-#pragma unroll
-        for (int t = 0; t < 2; ++t) {
-          ar[t] = sm.ar[wm + t * 16 + (lane & 15)][k];
-          ai[t] = sm.ai[wm + t * 16 + (lane & 15)][k];
-          nai[t] = -ai[t];
-          br[t] = sm.br[wn + t * 16 + (lane & 15)][k];
-          bi[t] = sm.bi[wn + t * 16 + (lane & 15)][k];
-        }
-#pragma unroll
-        for (int mt = 0; mt < 2; ++mt)
-#pragma unroll
-          for (int nt = 0; nt < 2; ++nt) {
-            cr[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(ar[mt], br[nt], cr[mt][nt], 0, 0, 0);
-            cr[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(nai[mt], bi[nt], cr[mt][nt], 0, 0, 0);
-            ci[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(ar[mt], bi[nt], ci[mt][nt], 0, 0, 0);
-            ci[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x4f32(ai[mt], br[nt], ci[mt][nt], 0, 0, 0);
-          }
-      }
-    } else {
-      // one 16x16x32 step covers the whole 32-wide k stage
-      const int kb = 8 * (lane >> 4);
-      bf16x8_t arh[2], arl[2], aih[2], ail[2], naih[2], nail[2];
-      bf16x8_t brh[2], brl[2], bih[2], bil[2];
-#pragma unroll
-      for (int t = 0; t < 2; ++t) {
-        const int mr = wm + t * 16 + (lane & 15), nr = wn + t * 16 + (lane & 15);
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-          float x = sm.ar[mr][kb + j];
-          __bf16 h = (__bf16)x;
-          arh[t][j] = h;
-          arl[t][j] = (__bf16)(x - (float)h);
-          x = sm.ai[mr][kb + j];
-          h = (__bf16)x;
-          aih[t][j] = h;
-          ail[t][j] = (__bf16)(x - (float)h);
-          naih[t][j] = (__bf16)(-(float)aih[t][j]);
-          nail[t][j] = (__bf16)(-(float)ail[t][j]);
-          x = sm.br[nr][kb + j];
-          h = (__bf16)x;
-          brh[t][j] = h;
-          brl[t][j] = (__bf16)(x - (float)h);
-          x = sm.bi[nr][kb + j];
-          h = (__bf16)x;
-          bih[t][j] = h;
-          bil[t][j] = (__bf16)(x - (float)h);
-        }
-      }
-#pragma unroll
-      for (int mt = 0; mt < 2; ++mt)
-#pragma unroll
-        for (int nt = 0; nt < 2; ++nt) {
-          // Re += Ar Br - Ai Bi
-          cr[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(arh[mt], brh[nt], cr[mt][nt], 0, 0, 0);
-          cr[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(arh[mt], brl[nt], cr[mt][nt], 0, 0, 0);
-          cr[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(arl[mt], brh[nt], cr[mt][nt], 0, 0, 0);
-          cr[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(naih[mt], bih[nt], cr[mt][nt], 0, 0, 0);
-          cr[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(naih[mt], bil[nt], cr[mt][nt], 0, 0, 0);
-          cr[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(nail[mt], bih[nt], cr[mt][nt], 0, 0, 0);
-          // Im += Ar Bi + Ai Br
-          ci[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(arh[mt], bih[nt], ci[mt][nt], 0, 0, 0);
-          ci[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(arh[mt], bil[nt], ci[mt][nt], 0, 0, 0);
-          ci[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(arl[mt], bih[nt], ci[mt][nt], 0, 0, 0);
-          ci[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(aih[mt], brh[nt], ci[mt][nt], 0, 0, 0);
-          ci[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(aih[mt], brl[nt], ci[mt][nt], 0, 0, 0);
-          ci[mt][nt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ail[mt], brh[nt], ci[mt][nt], 0, 0, 0);
-        }
+    const bool more = k0 + CT_K < dm;
+    if (more) fetch(k0 + CT_K);
+    mma_lowp(u.st[buf].a, u.st[buf].b, acc, wm, wn, lane);
+    buf ^= 1;
+    if (more) {
+      commit(buf);
+      __syncthreads();
     }
-    __syncthreads();
   }
-  double2* t = T + (int64_t)q * dl * dr;
+  __syncthreads();
+  const int q = 2 * (w & 1) + (w >> 1);
 #pragma unroll
   for (int mt = 0; mt < 2; ++mt)
 #pragma unroll
     for (int nt = 0; nt < 2; ++nt)
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int m = m0 + wm + mt * 16 + 4 * (lane >> 4) + r;
-        const int n = n0 + wn + nt * 16 + (lane & 15);
-        if (m < dl && n < dr) t[(int64_t)m * dr + n] = make_double2((double)cr[mt][nt][r], (double)ci[mt][nt][r]);
-      }
+      for (int r = 0; r < 4; ++r)
+        u.t[q][mt * 16 + 4 * (lane >> 4) + r][nt * 16 + (lane & 15)] =
+            make_float2(acc.re[mt][nt][r], acc.im[mt][nt][r]);
+  __syncthreads();
+  for (int e = tid; e < CT_T * CT_T; e += CT_THREADS) {
+    const int i = out.orient == 1 ? e % CT_T : e / CT_T, j = out.orient == 1 ? e / CT_T : e % CT_T;
+    if (a0 + i < dl && c0 + j < dr) {
+      double2 t[4];
+#pragma unroll
+      for (int p = 0; p < 4; ++p) t[p] = make_double2(u.t[p][i][j].x, u.t[p][i][j].y);
+      mix_store(t, G, a0 + i, c0 + j, dl, dr, out);
+    }
+  }
 }
 
-void contract_two_site_lowp(const double2* A, const double2* B, double2* T, int dl, int dm, int dr,
-                            int precision, hipStream_t s, hipEvent_t start, hipEvent_t stop) {
-  dim3 grid(ceil_div(dr, CT_N), ceil_div(dl, CT_M), 4);
+void contract_mix_lowp(const SiteView& A, const SiteView& B, const Gate4& G, int dl, int dm, int dr, int precision,
+                       const MixOut& out, hipStream_t s, hipEvent_t start, hipEvent_t stop) {
+  const dim3 grid(ceil_div(dr, CT_T), ceil_div(dl, CT_T));
   if (precision == RCS_PREC_C64)
-    hipExtLaunchKernelGGL(k_two_site_lowp<RCS_PREC_C64>, grid, dim3(256), 0, s, start, stop, 0, A, B, T, dl, dm, dr);
+    hipExtLaunchKernelGGL((k_two_site_mix_lowp<StageF32>), grid, dim3(CT_THREADS), 0, s, start, stop, 0, A, B, G, dl,
+                          dm, dr, out);
   else
-    hipExtLaunchKernelGGL(k_two_site_lowp<RCS_PREC_SPLIT_BF16>, grid, dim3(256), 0, s, start, stop, 0, A, B, T, dl,
-                          dm, dr);
+    hipExtLaunchKernelGGL((k_two_site_mix_lowp<StageBf16>), grid, dim3(CT_THREADS), 0, s, start, stop, 0, A, B, G, dl,
+                          dm, dr, out);
   HIP_LAUNCH_OK();
 }
 

@@ -54,3 +54,21 @@ def test_row_indirect_edges(env, dims, m):
     o.A = [(np.abs(a.real) + np.abs(a.imag)).astype(complex) for a in A]
     mag = o.amplitudes(bits).real
     assert np.all(np.abs(got.cpu().numpy() - ref) <= sum(2 * d + 8 for d in dims) * 2.0 ** -53 * 2 * mag)
+
+
+@pytest.mark.parametrize("precision", ["c64", "split_bf16"])
+@pytest.mark.parametrize("dl,dm,dr", [(1, 1, 1), (33, 31, 65), (32, 33, 31), (40, 129, 32)])
+def test_reduced_precision_edges(env, precision, dl, dm, dr):
+    """Against the oracle's emulation of the same operand rounding; the bar is
+    fp32 accumulation noise of dm terms of size about 2 (8 units of 2^-24
+    times the root of the term count and the sum's size)."""
+    from oracle import precision as prec
+    rcs, torch = env
+    A, B = inputs.random_complex((dl, 2, dm), 21), inputs.random_complex((dm, 2, dr), 22)
+    G = oc.fsim(np.pi / 2, np.pi / 6)
+    mm = prec.matmul_c64 if precision == "c64" else prec.matmul_split_bf16_complex
+    T = np.array([[mm(A[:, s], B[:, t]) for t in range(2)] for s in range(2)])
+    ref = np.einsum("xyst,stac->axyc", G.reshape(2, 2, 2, 2), T).transpose(1, 0, 2, 3).reshape(2 * dl, 2 * dr)
+    out = torch.zeros(2 * dr, 2 * dl, dtype=torch.complex128, device="cuda")
+    rcs.two_site(torch.from_numpy(A).cuda(), torch.from_numpy(B).cuda(), G, out, precision=precision)
+    assert np.abs(out.cpu().numpy().T - ref).max() <= 8 * 2.0 ** -24 * np.sqrt(2 * dm) * 2.0 * np.sqrt(dm)
