@@ -3,17 +3,26 @@
 // probabilities).  psi has 2^n complex128 amplitudes, index i = sum_q b_q 2^q
 // (bit q = qubit q, the bitstring convention); 34 qubits take 256 GiB.
 //
-// Each layer is applied in passes over "windows" of WIN consecutive qubit
-// bits: a workgroup stages the 2^(LOW + WIN) amplitudes whose indices vary
-// in bits [0, LOW) and [w, w + WIN) (all other bits fixed) in LDS, applies
-// every gate of the layer acting inside the window there, and writes them
-// back.  Bits [0, LOW) are always part of the tile, so each global access
-// moves 2^LOW consecutive amplitudes (256 B).  A single-qubit layer on n
-// qubits is ceil(n / WIN) passes; a two-qubit layer groups its couplers into
-// windows that contain both qubits (couplers span at most the grid width,
-// which must stay below WIN).  Every pass reads and writes psi once, so a
-// layer costs a few times 2 x 16 x 2^n bytes of HBM traffic.
+// The vector goes through in passes.  A pass picks up to 12 qubits, always
+// the 4 lowest among them (so that each global access moves 256 bytes); a
+// workgroup stages the 2^12 amplitudes whose indices vary in those bits in
+// LDS, applies every gate of the circuit that is next in line on qubits of
+// the set, across layers and cycles, and writes the amplitudes back.
+//
+// A pass costs one read and write of psi (16 x 2^n bytes each way, the bound)
+// and the gates' fp64 work, so passes are what is saved:
+//  * the single-qubit gates between two couplers of a qubit are multiplied
+//    into one 2x2 matrix and applied with the next coupler, in registers (one
+//    LDS round trip for three gates);
+//  * the qubit set of a pass is the best of the contiguous windows and of a
+//    set grown from the first gate in line, each step adding the qubits that
+//    let most gates run per qubit added.
+// 28 qubits (4 x 7), 8 cycles: 10 passes instead of the 64 that one window
+// and one layer per pass took, 34.8 ms instead of 165 (3.5 ms per pass against
+// 2.6: a pass now carries about 9 couplers with their gates; the copy rate
+// alone would be 2.0).
 #include <algorithm>
+#include <array>
 #include <vector>
 
 #include "circuit.h"
@@ -21,170 +30,352 @@
 
 namespace rcs {
 
-constexpr int DW_WIN = 8;      // window bits
-constexpr int DW_LOW = 4;      // always-staged low bits
-constexpr int DW_THREADS = 256;
-constexpr int DW_MAXOPS = 8;   // gates per pass: a window holds WIN single-qubit gates or WIN / 2 couplers
+constexpr int DW_TILE = 12;     // qubits per pass
+constexpr int DW_LOW = 4;       // always-staged low bits
+constexpr int DW_THREADS = 512;
+constexpr int DW_MAXSTEPS = 24; // per launch: the steps travel as kernel arguments (4 KB)
+constexpr int DW_SPAN = 8;      // couplers span fewer qubit numbers than this
 
-struct DenseOp {
-  int kind;      // 1: single-qubit (g[0..3]); 2: two-qubit (g[0..15], index 2 s_a + s_b)
-  int ta, tb;    // tile bits of qubit a (and b)
-  double2 g[16];
+// One step on tile bits ta, tb: ua and ub (2x2, row-major) on their qubits,
+// then the fSim.  kind 0: all three; 1: ua and ub; 2: ua only.
+struct DenseStep {
+  double2 ua[4], ub[4];
+  int kind, ta, tb;
 };
 
 struct DensePass {
-  int w, win, low;   // window base bit, window width, staged low bits
-  int nops;
-  DenseOp ops[DW_MAXOPS];
+  int tbits, low;              // tile bits, of which the lowest `low` are qubits 0..low-1
+  int bit[DW_TILE];            // qubit of each tile bit, ascending
+  int nsteps, init;            // init: psi is |0...0> (not read)
+  double2 f00, f11, f12, f21, f22, f33;   // the fSim's nonzero entries
+  DenseStep st[DW_MAXSTEPS];
 };
+static_assert(sizeof(DensePass) + 64 <= 4096, "kernel argument space");
 
 __global__ void k_dense_init(double2* psi, int64_t len) {
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < len; i += (int64_t)gridDim.x * blockDim.x)
     psi[i] = make_double2(i == 0 ? 1.0 : 0.0, 0.0);
 }
 
+__device__ inline double2 cmul(double2 a, double2 b) {
+  return make_double2(fma(a.x, b.x, -a.y * b.y), fma(a.x, b.y, a.y * b.x));
+}
 __device__ inline double2 cfma(double2 a, double2 b, double2 c) {   // c + a b
   return make_double2(fma(a.x, b.x, fma(-a.y, b.y, c.x)), fma(a.x, b.y, fma(a.y, b.x, c.y)));
 }
+__device__ inline void apply2(const double2 (&u)[4], double2& x0, double2& x1) {
+  const double2 y0 = cfma(u[1], x1, cmul(u[0], x0)), y1 = cfma(u[3], x1, cmul(u[2], x0));
+  x0 = y0;
+  x1 = y1;
+}
+
+// LDS position of tile index t: bits 4 and 5 are folded into the low four, so
+// that 16 consecutive work items stay conflict-free when a gate on one of the
+// low bits (or on two neighbouring ones) makes them skip it.
+__device__ inline int dw_pos(int t) { return t ^ (((t >> 4) & 1) * 15) ^ (((t >> 5) & 1) * 5); }
+// t with a zero bit inserted at position b.
+__device__ inline int dw_insert0(int t, int b) { return ((t >> b) << (b + 1)) | (t & ((1 << b) - 1)); }
 
 // One workgroup per combination of the bits outside the tile.
-__global__ __launch_bounds__(DW_THREADS) void k_dense_pass(double2* psi, int n, DensePass P) {
+__global__ __launch_bounds__(DW_THREADS) void k_dense_pass(double2* psi, DensePass P) {
   extern __shared__ double2 tile[];
-  const int tb = P.low + P.win;              // tile bits
-  const int tsz = 1 << tb;
-  const int mid_bits = P.w - P.low;          // bits [low, w) outside the tile
-  const int64_t g = blockIdx.x;
-  const int64_t mid = g & ((int64_t(1) << mid_bits) - 1);
-  const int64_t hi = g >> mid_bits;
-  const int64_t base = (mid << P.low) | (hi << (P.w + P.win));
-  auto gidx = [&](int t) -> int64_t {
-    const int64_t lo = t & ((1 << P.low) - 1);
-    const int64_t wv = t >> P.low;
-    return base | lo | (wv << P.w);
-  };
-  for (int t = threadIdx.x; t < tsz; t += DW_THREADS) tile[t] = psi[gidx(t)];
+  __shared__ int64_t hi[1 << (DW_TILE - DW_LOW)];
+  const int tsz = 1 << P.tbits, lowmask = (1 << P.low) - 1;
+  int64_t base = blockIdx.x;
+  for (int k = 0; k < P.tbits; ++k) base = ((base >> P.bit[k]) << (P.bit[k] + 1)) | (base & ((int64_t(1) << P.bit[k]) - 1));
+  for (int v = threadIdx.x; v < (tsz >> P.low); v += DW_THREADS) {
+    int64_t h = 0;
+    for (int k = P.low; k < P.tbits; ++k) h |= (int64_t)((v >> (k - P.low)) & 1) << P.bit[k];
+    hi[v] = h;
+  }
   __syncthreads();
-  for (int o = 0; o < P.nops; ++o) {
-    const DenseOp& op = P.ops[o];
-    if (op.kind == 1) {
-      const int b = op.ta, m = 1 << b;
+  constexpr int PER = (1 << DW_TILE) / DW_THREADS;
+  double2 r[PER];
+#pragma unroll
+  for (int j = 0; j < PER; ++j) {
+    const int t = threadIdx.x + j * DW_THREADS;
+    r[j] = make_double2(0.0, 0.0);
+    if (t < tsz) {
+      const int64_t i = base + (t & lowmask) + hi[t >> P.low];
+      if (P.init)
+        r[j].x = i == 0 ? 1.0 : 0.0;
+      else
+        r[j] = psi[i];
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < PER; ++j) {
+    const int t = threadIdx.x + j * DW_THREADS;
+    if (t < tsz) tile[dw_pos(t)] = r[j];
+  }
+  __syncthreads();
+  for (int o = 0; o < P.nsteps; ++o) {
+    const DenseStep& S = P.st[o];
+    if (S.kind == 2) {
       for (int p = threadIdx.x; p < (tsz >> 1); p += DW_THREADS) {
-        const int t0 = ((p >> b) << (b + 1)) | (p & (m - 1));
-        const int t1 = t0 | m;
-        const double2 x0 = tile[t0], x1 = tile[t1];
-        double2 y0 = make_double2(0.0, 0.0), y1 = make_double2(0.0, 0.0);
-        y0 = cfma(op.g[0], x0, y0);
-        y0 = cfma(op.g[1], x1, y0);
-        y1 = cfma(op.g[2], x0, y1);
-        y1 = cfma(op.g[3], x1, y1);
-        tile[t0] = y0;
-        tile[t1] = y1;
+        const int t0 = dw_pos(dw_insert0(p, S.ta)), t1 = dw_pos(dw_insert0(p, S.ta) | (1 << S.ta));
+        double2 x0 = tile[t0], x1 = tile[t1];
+        apply2(S.ua, x0, x1);
+        tile[t0] = x0;
+        tile[t1] = x1;
       }
     } else {
-      const int ba = op.ta, bb = op.tb;
-      const int lo = min(ba, bb), hb = max(ba, bb);
+      const int lo = min(S.ta, S.tb), hb = max(S.ta, S.tb);
       for (int p = threadIdx.x; p < (tsz >> 2); p += DW_THREADS) {
-        // insert zero bits at lo and hb
-        int t = ((p >> lo) << (lo + 1)) | (p & ((1 << lo) - 1));
-        t = ((t >> hb) << (hb + 1)) | (t & ((1 << hb) - 1));
-        int idx[4];
-        double2 x[4];
-#pragma unroll
-        for (int s = 0; s < 4; ++s) {      // s = 2 s_a + s_b
-          idx[s] = t | (((s >> 1) & 1) << ba) | ((s & 1) << bb);
-          x[s] = tile[idx[s]];
+        const int t = dw_insert0(dw_insert0(p, lo), hb);
+        const int t00 = dw_pos(t), t01 = dw_pos(t | (1 << S.tb)), t10 = dw_pos(t | (1 << S.ta)),
+                  t11 = dw_pos(t | (1 << S.ta) | (1 << S.tb));
+        double2 x00 = tile[t00], x01 = tile[t01], x10 = tile[t10], x11 = tile[t11];
+        apply2(S.ua, x00, x10);
+        apply2(S.ua, x01, x11);
+        apply2(S.ub, x00, x01);
+        apply2(S.ub, x10, x11);
+        if (S.kind == 0) {
+          const double2 y01 = cfma(P.f12, x10, cmul(P.f11, x01)), y10 = cfma(P.f22, x10, cmul(P.f21, x01));
+          x00 = cmul(P.f00, x00);
+          x01 = y01;
+          x10 = y10;
+          x11 = cmul(P.f33, x11);
         }
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          double2 y = make_double2(0.0, 0.0);
-#pragma unroll
-          for (int s = 0; s < 4; ++s) y = cfma(op.g[r * 4 + s], x[s], y);
-          tile[idx[r]] = y;
-        }
+        tile[t00] = x00;
+        tile[t01] = x01;
+        tile[t10] = x10;
+        tile[t11] = x11;
       }
     }
     __syncthreads();
   }
-  for (int t = threadIdx.x; t < tsz; t += DW_THREADS) psi[gidx(t)] = tile[t];
+#pragma unroll
+  for (int j = 0; j < PER; ++j) {
+    const int t = threadIdx.x + j * DW_THREADS;
+    if (t < tsz) psi[base + (t & lowmask) + hi[t >> P.low]] = tile[dw_pos(t)];
+  }
 }
 
-static void launch_pass(double2* psi, int n, DensePass& P, hipStream_t s) {
-  if (P.nops == 0) return;
-  const int tb = P.low + P.win;
-  const int64_t groups = int64_t(1) << (n - tb);
-  RCS_REQUIRE(groups <= (int64_t(1) << 31) - 1, "state vector too large for the grid");
-  hipLaunchKernelGGL(k_dense_pass, dim3((unsigned)groups), dim3(DW_THREADS), (size_t(1) << tb) * sizeof(double2), s,
-                     psi, n, P);
-  HIP_LAUNCH_OK();
+namespace {
+
+using Mat2 = std::array<cplx, 4>;
+Mat2 mul(const Mat2& a, const Mat2& b) {
+  return Mat2{a[0] * b[0] + a[1] * b[2], a[0] * b[1] + a[1] * b[3], a[2] * b[0] + a[3] * b[2],
+              a[2] * b[1] + a[3] * b[3]};
+}
+const Mat2 kIdentity{cplx(1.0), cplx(0.0), cplx(0.0), cplx(1.0)};
+
+// A coupler with the single-qubit gates since the previous coupler of each of
+// its qubits.
+struct Block {
+  int a, b;
+  Mat2 ua, ub;
+};
+
+// The circuit as blocks per qubit, in order, and what is left to run.
+struct Planner {
+  int n;
+  std::vector<Block> blocks;
+  std::vector<std::vector<int>> line;   // blocks of each qubit
+  std::vector<Mat2> last;               // gates after a qubit's last block
+  std::vector<char> last_left;
+  std::vector<int> next;                // position in line
+
+  // Runs what a set of qubits allows from the positions nx, at most
+  // DW_MAXSTEPS steps.  Returns a score (two per block, one per last gate);
+  // `ran` (nullable) receives the blocks in order.
+  int run(uint64_t set, std::vector<int>& nx, std::vector<int>* ran) const {
+    int steps = 0;
+    bool again = true;
+    while (again && steps < DW_MAXSTEPS) {
+      again = false;
+      for (uint64_t m = set; m && steps < DW_MAXSTEPS; m &= m - 1) {
+        const int q = __builtin_ctzll(m);
+        while (nx[q] < (int)line[q].size() && steps < DW_MAXSTEPS) {
+          const int i = line[q][nx[q]];
+          const int o = blocks[i].a == q ? blocks[i].b : blocks[i].a;
+          if (!((set >> o) & 1) || line[o][nx[o]] != i) break;
+          ++nx[q];
+          ++nx[o];
+          ++steps;
+          again = true;
+          if (ran) ran->push_back(i);
+        }
+      }
+    }
+    int score = 2 * steps, lasts = 0;
+    for (uint64_t m = set; m; m &= m - 1) {
+      const int q = __builtin_ctzll(m);
+      lasts += last_left[q] && nx[q] == (int)line[q].size();
+    }
+    return score + std::min(lasts, 2 * (DW_MAXSTEPS - steps));
+  }
+
+  // Set grown from a seed: adds, as long as qubits fit, the one or two that
+  // raise the score most per qubit.
+  uint64_t grow(uint64_t set, int room) const {
+    std::vector<int> nx, ny;
+    while (room > 0) {
+      nx = next;
+      const int s0 = run(set, nx, nullptr);
+      uint64_t best = 0;
+      double gain = 0.0;
+      auto offer = [&](uint64_t add) {
+        const int k = __builtin_popcountll(add);
+        if (k == 0 || k > room) return;
+        ny = next;
+        const double g = (double)(run(set | add, ny, nullptr) - s0) / k;
+        if (g > gain) {
+          gain = g;
+          best = add;
+        }
+      };
+      for (int q = 0; q < n; ++q) {
+        if (nx[q] < (int)line[q].size()) {
+          const Block& b = blocks[line[q][nx[q]]];
+          if (q == b.a || !((set >> b.a) & 1)) offer(((uint64_t(1) << b.a) | (uint64_t(1) << b.b)) & ~set);
+        } else if (last_left[q] && !((set >> q) & 1)) {
+          offer(uint64_t(1) << q);
+        }
+      }
+      if (!best) break;
+      set |= best;
+      room -= __builtin_popcountll(best);
+    }
+    return set;
+  }
+
+  bool done() const {
+    for (int q = 0; q < n; ++q)
+      if (next[q] < (int)line[q].size() || last_left[q]) return false;
+    return true;
+  }
+};
+
+void to_dev(const Mat2& m, double2 (&d)[4]) {
+  for (int e = 0; e < 4; ++e) d[e] = make_double2(m[e].real(), m[e].imag());
 }
 
-// Window [w, w + win) and the staged low bits [0, low) for n qubits.
-static DensePass make_pass(int n, int w) {
-  DensePass P{};
-  P.win = std::min(DW_WIN, n);
-  P.w = std::min(w, n - P.win);
-  P.low = std::min(DW_LOW, P.w);
-  P.nops = 0;
-  return P;
-}
-
-static void add_1q(DensePass& P, int q, const std::array<cplx, 4>& u) {
-  RCS_REQUIRE(P.nops < DW_MAXOPS, "too many gates in one dense pass");
-  DenseOp& op = P.ops[P.nops++];
-  op.kind = 1;
-  op.ta = P.low + (q - P.w);
-  op.tb = 0;
-  for (int e = 0; e < 4; ++e) op.g[e] = make_double2(u[e].real(), u[e].imag());
-}
-
-static void add_2q(DensePass& P, int qa, int qb, const std::array<cplx, 16>& G) {
-  RCS_REQUIRE(P.nops < DW_MAXOPS, "too many gates in one dense pass");
-  DenseOp& op = P.ops[P.nops++];
-  op.kind = 2;
-  op.ta = P.low + (qa - P.w);
-  op.tb = P.low + (qb - P.w);
-  for (int e = 0; e < 16; ++e) op.g[e] = make_double2(G[e].real(), G[e].imag());
-}
+}  // namespace
 
 void dense_simulate(const rcs_circuit_s& c, double2* psi, hipStream_t s) {
   const int n = c.n;
-  const int64_t len = int64_t(1) << n;
-  hipLaunchKernelGGL(k_dense_init, dim3((unsigned)std::min<int64_t>((len + 255) / 256, 1 << 20)), dim3(256), 0, s,
-                     psi, len);
-  HIP_LAUNCH_OK();
+  for (int t = 0; t < c.n_cycles; ++t)
+    for (auto& e : c.layers_2q[t])
+      RCS_REQUIRE(std::abs(e.first - e.second) < std::min(DW_SPAN, n), "coupler wider than the dense window");
+  Planner pl;
+  pl.n = n;
+  pl.line.resize(n);
+  pl.next.assign(n, 0);
+  pl.last.assign(n, kIdentity);
+  pl.last_left.assign(n, 0);
   auto layer_1q = [&](const std::vector<int>& g) {
-    for (int w0 = 0; w0 < n; w0 += DW_WIN) {
-      DensePass P = make_pass(n, w0);
-      for (int q = std::max(w0, P.w); q < std::min(n, w0 + DW_WIN); ++q) add_1q(P, q, one_qubit_gate(g[q]));
-      // qubits the clamped window covers but an earlier pass already did
-      // are not repeated (the loop starts at w0)
-      launch_pass(psi, n, P, s);
+    for (int q = 0; q < n; ++q) {
+      pl.last[q] = mul(one_qubit_gate(g[q]), pl.last[q]);
+      pl.last_left[q] = 1;
     }
   };
-  const size_t n1 = c.layers_1q.size();
   for (int t = 0; t < c.n_cycles; ++t) {
     layer_1q(c.layers_1q[t]);
-    std::vector<std::pair<int, int>> cp;
-    for (auto& e : c.layers_2q[t]) cp.emplace_back(std::min(e.first, e.second), std::max(e.first, e.second));
-    std::sort(cp.begin(), cp.end());
-    size_t i = 0;
-    std::vector<char> done(cp.size(), 0);
-    while (i < cp.size()) {
-      if (done[i]) {
-        ++i;
-        continue;
+    for (auto& e : c.layers_2q[t]) {
+      const int a = std::min(e.first, e.second), b = std::max(e.first, e.second);
+      for (int q : {a, b}) pl.line[q].push_back((int)pl.blocks.size());
+      pl.blocks.push_back(Block{a, b, pl.last[a], pl.last[b]});
+      for (int q : {a, b}) {
+        pl.last[q] = kIdentity;
+        pl.last_left[q] = 0;
       }
-      RCS_REQUIRE(cp[i].second - cp[i].first < std::min(DW_WIN, n), "coupler wider than the dense window");
-      DensePass P = make_pass(n, cp[i].first);
-      for (size_t j = i; j < cp.size(); ++j)
-        if (!done[j] && cp[j].first >= P.w && cp[j].second < P.w + P.win && P.nops < DW_MAXOPS) {
-          add_2q(P, cp[j].first, cp[j].second, c.fsim);
-          done[j] = 1;
-        }
-      launch_pass(psi, n, P, s);
     }
   }
-  if (c.final_layer && n1 > (size_t)c.n_cycles) layer_1q(c.layers_1q[c.n_cycles]);
+  if (c.final_layer && c.layers_1q.size() > (size_t)c.n_cycles) layer_1q(c.layers_1q[c.n_cycles]);
+
+  const int low = std::min(DW_LOW, n), tbits = std::min(DW_TILE, n);
+  const uint64_t lowset = (uint64_t(1) << low) - 1;
+  DensePass P{};
+  auto entry = [&](int e) { return make_double2(c.fsim[e].real(), c.fsim[e].imag()); };
+  P.f00 = entry(0);
+  P.f11 = entry(5);
+  P.f12 = entry(6);
+  P.f21 = entry(9);
+  P.f22 = entry(10);
+  P.f33 = entry(15);
+  P.init = 1;
+  if (pl.done()) {   // no gate at all
+    const int64_t len = int64_t(1) << n;
+    hipLaunchKernelGGL(k_dense_init, dim3((unsigned)std::min<int64_t>((len + 255) / 256, 1 << 20)), dim3(256), 0, s,
+                       psi, len);
+    HIP_LAUNCH_OK();
+    return;
+  }
+  const int64_t groups = int64_t(1) << (n - tbits);
+  RCS_REQUIRE(groups <= (int64_t(1) << 31) - 1, "state vector too large for the grid");
+  std::vector<int> nx, ran;
+  while (!pl.done()) {
+    // the qubit set
+    uint64_t set = (uint64_t(1) << n) - 1;
+    if (n > tbits) {
+      int best = -1;
+      auto offer = [&](uint64_t cand) {
+        nx = pl.next;
+        const int sc = pl.run(cand, nx, nullptr);
+        if (sc > best) {
+          best = sc;
+          set = cand;
+        }
+      };
+      uint64_t seed = 0;
+      for (int i = 0; i < (int)pl.blocks.size() && !seed; ++i) {
+        const Block& b = pl.blocks[i];
+        if (pl.next[b.a] < (int)pl.line[b.a].size() && pl.line[b.a][pl.next[b.a]] == i)
+          seed = (uint64_t(1) << b.a) | (uint64_t(1) << b.b);
+      }
+      offer(pl.grow(lowset | seed, tbits - __builtin_popcountll(lowset | seed)));
+      for (int w = low; w + (tbits - low) <= n; ++w) offer(lowset | (((uint64_t(1) << (tbits - low)) - 1) << w));
+      // exactly tbits qubits: fill up with the lowest ones left
+      for (int q = 0; q < n && __builtin_popcountll(set) < tbits; ++q) set |= uint64_t(1) << q;
+    }
+    P.tbits = tbits;
+    P.low = low;
+    int pos[64], k = 0;
+    for (uint64_t m = set; m; m &= m - 1) {
+      const int q = __builtin_ctzll(m);
+      pos[q] = k;
+      P.bit[k++] = q;
+    }
+    // its steps
+    ran.clear();
+    pl.run(set, pl.next, &ran);
+    P.nsteps = 0;
+    for (int i : ran) {
+      DenseStep& S = P.st[P.nsteps++];
+      S.kind = 0;
+      S.ta = pos[pl.blocks[i].a];
+      S.tb = pos[pl.blocks[i].b];
+      to_dev(pl.blocks[i].ua, S.ua);
+      to_dev(pl.blocks[i].ub, S.ub);
+    }
+    int held = -1;   // a last gate waiting for a partner
+    for (uint64_t m = set; m; m &= m - 1) {
+      const int q = __builtin_ctzll(m);
+      if (!pl.last_left[q] || pl.next[q] < (int)pl.line[q].size()) continue;
+      if (held >= 0) {
+        DenseStep& S = P.st[P.nsteps - 1];
+        S.kind = 1;
+        S.tb = pos[q];
+        to_dev(pl.last[q], S.ub);
+        held = -1;
+      } else {
+        if (P.nsteps == DW_MAXSTEPS) break;
+        DenseStep& S = P.st[P.nsteps++];
+        S.kind = 2;
+        S.ta = pos[q];
+        S.tb = 0;
+        to_dev(pl.last[q], S.ua);
+        held = q;
+      }
+      pl.last_left[q] = 0;
+    }
+    hipLaunchKernelGGL(k_dense_pass, dim3((unsigned)groups), dim3(DW_THREADS), (size_t(1) << tbits) * sizeof(double2), s,
+                       psi, P);
+    HIP_LAUNCH_OK();
+    P.init = 0;
+  }
 }
 
 // out[i] = psi[bits[i]] (mode 0: amplitude, complex) or |psi[bits[i]]|^2
