@@ -377,8 +377,8 @@ rcs_status rcs_svd_jacobi_f32(int32_t len, int32_t cnt, const double* x_dev, dou
 
 /* Thin QR of a complex len x cnt matrix (cnt <= len, 64 <= cnt <= 4096),
  * column-major in x_dev, as the build's centre moves compute it
- * (CholeskyQR: R from the Cholesky factor of X^H X, Q = X R^{-1}, then three
- * Newton-Schulz steps Q <- Q (3I - Q^H Q)/2): q_dev (len x cnt,
+ * (CholeskyQR: R from the Cholesky factor of X^H X, Q = X R^{-1}, then one to
+ * three Newton-Schulz steps Q <- Q (3I - Q^H Q)/2, by the measured defect): q_dev (len x cnt,
  * column-major) has orthonormal columns spanning range(X), r_dev (cnt x cnt,
  * column-major) = Q^H X, upper triangular up to the Newton-Schulz
  * correction (about u cond(X)^2 relative), and X = Q R.  x_dev is not

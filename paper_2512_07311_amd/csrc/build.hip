@@ -992,8 +992,9 @@ static bool cholqr_moves_enabled() {
 // Q^H Q) / 2.  Q1's orthogonality defect is about u cond(X)^2; the first
 // step measures it and the move is left to the Jacobi path (false) when it
 // exceeds 1e-4 (cond(X) above about 1e6) or the Cholesky breaks down
-// (X rank deficient).  From 1e-4 two more steps reach rounding level
-// (e -> 3e^2/4 each).  On success ws.wn_final holds Q (ld pl.ldx).
+// (X rank deficient).  The measured defect decides how many steps reach
+// rounding level (e -> 3e^2/4 each): one for the conditioning of ordinary
+// sites, up to three.  On success ws.wn_final holds Q (ld pl.ldx).
 static bool move_cholqr(rcs_state_s& st, BuildWork& ws, const JacobiPlan& pl) {
   hipStream_t s = st.stream;
   const int len = pl.len, n = pl.cnt;
@@ -1011,7 +1012,8 @@ static bool move_cholqr(rcs_state_s& st, BuildWork& ws, const JacobiPlan& pl) {
          ws.Tq.as<double2>(), Wn, pl.ldx, ws.cflag.as<int>(), s);
   double2* src = Wn;
   double2* dst = X;
-  for (int it = 0; it < 3; ++it) {
+  int steps = 3;
+  for (int it = 0; it < steps; ++it) {
     RCS_PROBED_LAUNCH(kKcFactor, k_ns_gram, dim3(ceil_div(n, GT_N), ceil_div(n, GT_M)), dim3(GT_THREADS), 0, s, src, pl.ldx,
                        len, n, ws.H.as<double2>());
     HIP_LAUNCH_OK();
@@ -1023,6 +1025,8 @@ static bool move_cholqr(rcs_state_s& st, BuildWork& ws, const JacobiPlan& pl) {
       HIP_OK(hipStreamSynchronize(s));
       dev = ws.host_rank->w;      // max |H - I| = max |I - Q^H Q| / 2
       if (*ws.host_rot != 0 || !(dev <= 0.5e-4)) return false;
+      const double e = 2.0 * dev * n;   // bounds ||I - Q^H Q||_2; a step takes it to 3 e^2 / 4
+      steps = e <= 1e-8 ? 1 : e <= 1e-4 ? 2 : 3;
     }
     RCS_PROBED_LAUNCH(kKcFactor, k_ns_apply, dim3(ceil_div(n, GT_N), ceil_div(len, GT_M)), dim3(GT_THREADS), 0, s, src,
                        pl.ldx, len, n, ws.H.as<double2>(), dst);

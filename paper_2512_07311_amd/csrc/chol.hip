@@ -18,8 +18,8 @@
 //   panel kernel:  every workgroup factors the 64 x 64 diagonal block of G
 //                  in LDS (redundantly); workgroup 0 stores R_jj in a
 //                  separate array (the others are still reading G_jj), the
-//                  others invert R_jj in place and solve their 64-column tile
-//                  of the block row, R_jt = R_jj^{-H} G_jt;
+//                  others solve their 64-column tile of the block row,
+//                  R_jt = R_jj^{-H} G_jt;
 //   update kernel: G_tu -= R_jt^H R_ju for the upper tiles of the trailing
 //                  matrix, on the matrix cores.
 // G is stored column-major with ld = round_up(n, 64); the padding carries an
@@ -31,7 +31,6 @@
 namespace rcs {
 
 constexpr int CB = 64;          // Cholesky block
-constexpr int CHOL_THREADS = 256;
 
 // G (ld ldg, column-major) = X^H X over the upper tiles (blockIdx.y <=
 // blockIdx.x); entries outside n x n are the identity's.
@@ -66,113 +65,210 @@ __device__ inline double2 cmul_hc(double2 a, double2 b) {
   return make_double2(a.x * b.x + a.y * b.y, a.x * b.y - a.y * b.x);
 }
 
-// Panel jb, 256 threads per workgroup: thread (q, c) = (t / 64, t % 64)
-// works on column c of the 64 x 64 blocks in LDS and on the rows (or sum
-// terms) congruent to q mod 4, so the four waves share each step's work:
-//  * every workgroup factors the diagonal block G_jj = R^H R (right-looking:
-//    at step k row k of R is formed once in a separate buffer, then each
-//    thread updates its rows of its column's trailing part); a pivot that is
-//    not positive and finite sets *flag;
-//  * workgroup 0 stores R_jj (column-major in Rd) and, when Ri is given, the
-//    diagonal block of R^{-1} (back substitution on every column at once);
-//  * workgroup t >= 1 solves its tile of the block row, R_jt = R^{-H} G_jt,
-//    by forward substitution on every column at once.
-// The substitutions sum their terms in four interleaved partial sums,
-// combined in a fixed order.
-constexpr int PANEL_THREADS = 256;
+// Panel jb: every workgroup factors the 64 x 64 diagonal block G_jj = R^H R in
+// LDS, in four 16-wide steps; workgroup t >= 1 carries its 64-column tile of
+// the block row along (R_jt = R^{-H} G_jt), workgroup 0 stores R_jj
+// (column-major in Rd) and, when Ri is given, the diagonal block of R^{-1}.
+// A step:
+//   factor  one wave factors the 16 x 16 diagonal block in registers (four
+//           rows of a column per lane, rows handed around by shuffles: no
+//           barrier in the 16-step chain), R^{-H} with it;
+//   solve   the other blocks of the block row, times the inverse, and
+//   update  the rows below, both as 16 x 16 matrix-core products, one block
+//           per wave.
+// A pivot that is not positive and finite sets *flag.
+//
+// Bound: the chain of 64 pivots (sqrt, division and a shuffle each).  Two
+// barriers per pivot and per substitution row, with every thread's terms read
+// from LDS, took 112 us per panel; this form takes 39 us.
+constexpr int PANEL_THREADS = 512;
+constexpr int PW = 16;                     // inner block
+constexpr int PLD = CB + 1;
+
+struct PanelLds {
+  double2 T[CB][PLD];                      // diagonal block, then R_jj
+  double2 A[CB][PLD];                      // tile of the block row (workgroup 0: R_jj^{-1})
+  double2 W[CB / PW][PW][PW + 1];          // R^{-H} of R_jj's 16 x 16 diagonal blocks
+};
 
 // B[r][cc] = G[row0 + r][col0 + cc] (G column-major, ld ldg) for a 64 x 64
-// block: each thread loads four columns' entries of one row, sixteen loads
-// in flight before their LDS stores.
-__device__ inline void load_block64(const double2* G, int ldg, int row0, int col0, double2 (*B)[CB + 1]) {
+// block, a thread's eight loads in flight before its LDS stores.
+__device__ inline void load_block64(const double2* G, int ldg, int row0, int col0, double2 (*B)[PLD]) {
+  constexpr int PER = CB * CB / PANEL_THREADS;
   const int r = threadIdx.x & (CB - 1), q = threadIdx.x >> 6;
-  double2 v[16];
+  double2 v[PER];
 #pragma unroll
-  for (int u = 0; u < 16; ++u) v[u] = G[(int64_t)(col0 + q + 4 * u) * ldg + row0 + r];
+  for (int u = 0; u < PER; ++u) v[u] = G[(int64_t)(col0 + q + (PANEL_THREADS / CB) * u) * ldg + row0 + r];
 #pragma unroll
-  for (int u = 0; u < 16; ++u) B[r][q + 4 * u] = v[u];
+  for (int u = 0; u < PER; ++u) B[r][q + (PANEL_THREADS / CB) * u] = v[u];
+}
+
+__device__ inline double2 shfl2(double2 v, int lane) { return make_double2(__shfl(v.x, lane), __shfl(v.y, lane)); }
+
+// One wave: R^H R = T[k0.., k0..] (16 x 16, upper triangle used), R into T and
+// R^{-H} (zero above the diagonal) into W.  The elimination runs on [G | I]:
+// the row operations that turn G into R turn I into R^{-H}.
+__device__ inline void factor16(double2 (*T)[PLD], int k0, double2 (*W)[PW + 1], int lane, int* flag) {
+  const int c = lane & 15, g = lane >> 4;
+  double2 a[4], b[4];
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    a[j] = T[k0 + 4 * g + j][k0 + c];
+    b[j] = make_double2(4 * g + j == c ? 1.0 : 0.0, 0.0);
+  }
+#pragma unroll
+  for (int k = 0; k < PW; ++k) {
+    const int own = (k >> 2) * 16;          // lanes holding row k
+    double d = __shfl(a[k & 3].x, own + k);
+    const bool bad = !(d > 0.0) || !(d < 1e300);
+    if (bad) {
+      d = 1.0;
+      if (lane == 0) atomicExch(flag, 1);
+    }
+    const double inv = rsqrt_fast(d);
+    double2 xc = shfl2(a[k & 3], own + c), bc = shfl2(b[k & 3], own + c);
+    xc = make_double2(xc.x * inv, xc.y * inv);
+    bc = make_double2(bc.x * inv, bc.y * inv);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int row = 4 * g + j;
+      double2 xr = shfl2(a[k & 3], own + row);
+      xr = make_double2(xr.x * inv, xr.y * inv);
+      if (row > k) {
+        const double2 p = cmul_hc(xr, xc), q = cmul_hc(xr, bc);
+        a[j] = make_double2(a[j].x - p.x, a[j].y - p.y);
+        b[j] = make_double2(b[j].x - q.x, b[j].y - q.y);
+      }
+    }
+    if (g == (k >> 2)) {
+      a[k & 3] = c == k ? make_double2(d * inv, 0.0) : xc;
+      b[k & 3] = bc;
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < 4; ++j) {
+    const int row = 4 * g + j;
+    if (c >= row) T[k0 + row][k0 + c] = a[j];
+    W[row][c] = c <= row ? b[j] : make_double2(0.0, 0.0);
+  }
+}
+
+// One wave: acc (16 x 16) = A^H B (HERM) or A B of 16 x 16 LDS blocks.
+struct Acc16 {
+  double4_t re, im;
+};
+template <bool HERM, int LDA, int LDB>
+__device__ inline Acc16 mul16(const double2 (*A)[LDA], int ar, int ac, const double2 (*B)[LDB], int br, int bc,
+                              int lane) {
+  Acc16 c{double4_t{0, 0, 0, 0}, double4_t{0, 0, 0, 0}};
+  const int m = lane & 15, kl = lane >> 4;
+#pragma unroll
+  for (int kk = 0; kk < PW; kk += 4) {
+    const int k = kk + kl;
+    double2 x = HERM ? A[ar + k][ac + m] : A[ar + m][ac + k];
+    if (HERM) x.y = -x.y;
+    const double2 y = B[br + k][bc + m];
+    c.re = __builtin_amdgcn_mfma_f64_16x16x4f64(x.x, y.x, c.re, 0, 0, 0);
+    c.im = __builtin_amdgcn_mfma_f64_16x16x4f64(x.x, y.y, c.im, 0, 0, 0);
+    c.re = __builtin_amdgcn_mfma_f64_16x16x4f64(-x.y, y.y, c.re, 0, 0, 0);
+    c.im = __builtin_amdgcn_mfma_f64_16x16x4f64(x.y, y.x, c.im, 0, 0, 0);
+  }
+  return c;
 }
 
 __global__ __launch_bounds__(PANEL_THREADS) void k_chol_panel(double2* G, int ldg, int jb, int* flag, double2* Rd,
                                                               double2* Ri) {
-  __shared__ double2 T[CB][CB + 1];
-  __shared__ double2 A[CB][CB + 1];
-  __shared__ double2 rowk[CB];
-  __shared__ double2 part[4][CB];
-  const int c = threadIdx.x & (CB - 1), q = threadIdx.x >> 6;
-  const int j0 = jb * CB;
-  load_block64(G, ldg, j0, j0, T);
+  __shared__ PanelLds sm;
+  constexpr int NB = CB / PW, NWAVE = PANEL_THREADS / 64;
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6, c = threadIdx.x & (CB - 1), q = threadIdx.x >> 6;
+  const int j0 = jb * CB, t0 = j0 + blockIdx.x * CB;
+  const bool tile = blockIdx.x > 0;
+  load_block64(G, ldg, j0, j0, sm.T);
+  if (tile) load_block64(G, ldg, j0, t0, sm.A);
   __syncthreads();
-  for (int k = 0; k < CB; ++k) {
-    double d = T[k][k].x;
-    const bool bad = !(d > 0.0) || !(d < 1e300);
-    if (bad) d = 1.0;
-    if (bad && threadIdx.x == 0) atomicExch(flag, 1);
-    const double r = sqrt(d), inv = 1.0 / r;
-    if (q == 0 && c >= k) rowk[c] = c == k ? make_double2(r, 0.0) : make_double2(T[k][c].x * inv, T[k][c].y * inv);
+  for (int kb = 0; kb < NB; ++kb) {
+    const int k0 = kb * PW;
+    if (w == 0) factor16(sm.T, k0, sm.W[kb], lane, flag);
     __syncthreads();
-    if (q == 0 && c >= k) T[k][c] = rowk[c];
-    if (c > k) {
-      const double2 rc = rowk[c];
-      for (int rr = k + 1 + q; rr <= c; rr += 4) {
-        const double2 p = cmul_hc(rowk[rr], rc);
-        T[rr][c] = make_double2(T[rr][c].x - p.x, T[rr][c].y - p.y);
+    // block row kb: T's blocks right of the diagonal, the tile's four
+    const int nt = NB - 1 - kb, solves = nt + (tile ? NB : 0);
+    for (int e = w; e < solves; e += NWAVE) {
+      double2(*M)[PLD] = e < nt ? sm.T : sm.A;
+      const int col = e < nt ? (kb + 1 + e) * PW : (e - nt) * PW;
+      const Acc16 x = mul16<false>(sm.W[kb], 0, 0, M, k0, col, lane);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) M[k0 + f64_row(lane, r)][col + (lane & 15)] = make_double2(x.re[r], x.im[r]);
+    }
+    __syncthreads();
+    // rows below: upper blocks of T, all four columns of the tile
+    const int ut = nt * (nt + 1) / 2, updates = ut + (tile ? nt * NB : 0);
+    for (int e = w; e < updates; e += NWAVE) {
+      int ti, col;
+      double2(*M)[PLD] = sm.T;
+      if (e < ut) {
+        int p = e;
+        ti = 0;
+        while (p >= nt - ti) {
+          p -= nt - ti;
+          ++ti;
+        }
+        col = (kb + 1 + ti + p) * PW;
+      } else {
+        ti = (e - ut) / NB;
+        col = ((e - ut) % NB) * PW;
+        M = sm.A;
+      }
+      const int row = (kb + 1 + ti) * PW;
+      const Acc16 x = mul16<true>(sm.T, k0, row, M, k0, col, lane);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        double2& v = M[row + f64_row(lane, r)][col + (lane & 15)];
+        v = make_double2(v.x - x.re[r], v.y - x.im[r]);
       }
     }
     __syncthreads();
   }
-  if (blockIdx.x == 0) {
-    double2* rd = Rd + (int64_t)jb * CB * CB;
-    for (int cc = q; cc < CB; cc += 4) rd[cc * CB + c] = c <= cc ? T[c][cc] : make_double2(0.0, 0.0);
-    if (Ri) {
-      // column c of R^{-1}: x_c = 1 / R_cc; x_i = -(sum_{m=i+1}^{c} R_im x_m) / R_ii, i < c
-      if (q == 0) A[c][c] = make_double2(1.0 / T[c][c].x, 0.0);
-      __syncthreads();
-      for (int i = CB - 2; i >= 0; --i) {
-        double2 s2 = make_double2(0.0, 0.0);
-        if (c > i)
-          for (int m = i + 1 + q; m <= c; m += 4) {
-            const double2 p = cmul_c(T[i][m], A[m][c]);
-            s2.x += p.x;
-            s2.y += p.y;
-          }
-        part[q][c] = s2;
-        __syncthreads();
-        if (q == 0 && c > i) {
-          const double2 t0 = part[0][c], t1 = part[1][c], t2 = part[2][c], t3 = part[3][c];
-          const double sx = (t0.x + t1.x) + (t2.x + t3.x), sy = (t0.y + t1.y) + (t2.y + t3.y);
-          const double qq = -1.0 / T[i][i].x;
-          A[i][c] = make_double2(qq * sx, qq * sy);
-        }
-        __syncthreads();
-      }
-      for (int cc = q; cc < CB; cc += 4)
-        Ri[(int64_t)(j0 + cc) * ldg + j0 + c] = c <= cc ? A[c][cc] : make_double2(0.0, 0.0);
-    }
+  if (tile) {
+    for (int cc = q; cc < CB; cc += NWAVE) G[(int64_t)(t0 + cc) * ldg + j0 + c] = sm.A[c][cc];
     return;
   }
-  const int t0 = j0 + blockIdx.x * CB;    // first column of this tile
-  load_block64(G, ldg, j0, t0, A);
+  double2* rd = Rd + (int64_t)jb * CB * CB;
+  for (int cc = q; cc < CB; cc += NWAVE) rd[cc * CB + c] = c <= cc ? sm.T[c][cc] : make_double2(0.0, 0.0);
+  if (!Ri) return;
+  // R_jj^{-1} from its 16 x 16 diagonal blocks: the block diagonals above the
+  // main one in turn, X_ij = -R_ii^{-1} sum_{i < l <= j} R_il X_lj
+  for (int e = threadIdx.x; e < CB * CB; e += PANEL_THREADS) {
+    const int i = e / CB, j = e % CB;
+    const double2 v = sm.W[i / PW][j % PW][i % PW];
+    sm.A[i][j] = i / PW == j / PW ? make_double2(v.x, -v.y) : make_double2(0.0, 0.0);
+  }
   __syncthreads();
-  // R^H X = A, column c: X_i = (A_i - sum_{m<i} conj(R_mi) X_m) / R_ii
-  for (int i = 0; i < CB; ++i) {
-    double2 s2 = make_double2(0.0, 0.0);
-    for (int m = q; m < i; m += 4) {
-      const double2 p = cmul_hc(T[m][i], A[m][c]);
-      s2.x += p.x;
-      s2.y += p.y;
+  for (int dgn = 1; dgn < NB; ++dgn) {
+    const int i = w, j = w + dgn;
+    const bool mine = j < NB;
+    if (mine) {
+      double4_t re{0, 0, 0, 0}, im{0, 0, 0, 0};
+      for (int l = i + 1; l <= j; ++l) {
+        const Acc16 x = mul16<false>(sm.T, i * PW, l * PW, sm.A, l * PW, j * PW, lane);
+        re += x.re;
+        im += x.im;
+      }
+#pragma unroll
+      for (int r = 0; r < 4; ++r) sm.A[i * PW + f64_row(lane, r)][j * PW + (lane & 15)] = make_double2(re[r], im[r]);
     }
-    part[q][c] = s2;
     __syncthreads();
-    if (q == 0) {
-      const double2 t0p = part[0][c], t1 = part[1][c], t2 = part[2][c], t3 = part[3][c];
-      const double sx = (t0p.x + t1.x) + (t2.x + t3.x), sy = (t0p.y + t1.y) + (t2.y + t3.y);
-      const double qq = 1.0 / T[i][i].x;
-      A[i][c] = make_double2(qq * (A[i][c].x - sx), qq * (A[i][c].y - sy));
+    Acc16 y;
+    if (mine) y = mul16<true>(sm.W[i], 0, 0, sm.A, i * PW, j * PW, lane);
+    __syncthreads();
+    if (mine) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        sm.A[i * PW + f64_row(lane, r)][j * PW + (lane & 15)] = make_double2(-y.re[r], -y.im[r]);
     }
     __syncthreads();
   }
-  for (int cc = q; cc < CB; cc += 4) G[(int64_t)(t0 + cc) * ldg + j0 + c] = A[c][cc];
+  for (int cc = q; cc < CB; cc += NWAVE)
+    Ri[(int64_t)(j0 + cc) * ldg + j0 + c] = sm.A[c][cc];
 }
 
 // Trailing update after panel jb: tile (ti, tj), jb < ti <= tj < nb:
