@@ -33,7 +33,7 @@ void build_one(rcs_state_s& st, const rcs_circuit_s& c, int chi, double eps, con
 // Learned-rank network pieces (fp32).
 void spectrum_features(const double* s_dev, int k, int bond, int n_sites, int cycle, int n_cycles,
                        float* feat_dev, hipStream_t st);
-void mlp_forward(const float* w, const float* x, int batch, float* out, float* act, hipStream_t s);
+void mlp_forward(const float* w, const float* x, int batch, float* out, hipStream_t s);
 
 // A site tensor: element (s, a, b) at p[s * s_stride + a * ld + b].
 struct SiteView {

@@ -1162,7 +1162,7 @@ static bool randomized_split(rcs_state_s& st, BuildWork& ws, UpdateCtx& ctx, int
   if (o.rank_mode == RCS_RANK_LEARNED) {
     spectrum_features(ctx.bond_spec.as<double>() + (size_t)i * ctx.chi_cap, ctx.bond_k[i], i, st.n, cycle,
                       ctx.n_cycles, ctx.feat.as<float>(), s);
-    mlp_forward(ctx.w_mlp.as<float>(), ctx.feat.as<float>(), 1, ctx.yhat.as<float>(), nullptr, s);
+    mlp_forward(ctx.w_mlp.as<float>(), ctx.feat.as<float>(), 1, ctx.yhat.as<float>(), s);
     HIP_OK(hipMemcpyAsync(rec.y, ctx.yhat.p, sizeof(rec.y), hipMemcpyDeviceToHost, s));
     HIP_OK(hipMemcpyAsync(rec.feat, ctx.feat.p, sizeof(rec.feat), hipMemcpyDeviceToHost, s));
     HIP_OK(hipStreamSynchronize(s));

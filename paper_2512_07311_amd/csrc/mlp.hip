@@ -3,8 +3,8 @@
 // Network: Linear(66,128) - ReLU - Linear(128,128) - ReLU - Linear(128,32),
 // packed weights W1[128][66], b1[128], W2[128][128], b2[128], W3[32][128],
 // b3[32].  Loss: mean over batch and outputs of (out - y)^2.  Every
-// reduction has a fixed order (one thread per output element, sequential over
-// the batch or the fan-in), so forward, backward and Adam are deterministic.
+// reduction has a fixed order, so forward, backward and Adam are
+// deterministic.
 //
 // Features (66): 64-bin histogram of log10(s^2 / sum s^2) of a bond's kept
 // singular values (0.25-decade bins over [-16, 0), clamped at both ends,
@@ -88,120 +88,195 @@ void spectrum_targets(const double* s_dev, int m, float* y_dev, hipStream_t st) 
   HIP_LAUNCH_OK();
 }
 
-// ---------------------------------------------------------------- forward
-// Per sample: one block of 128 threads; activations stay in LDS.  When
-// `act` is non-null the pre-activations z1, z2 and activations h1, h2 are
-// stored for the backward pass ([batch][4][128]).
-__global__ __launch_bounds__(128) void k_mlp_fwd(const float* w, const float* x, int batch, float* out,
-                                                 float* act) {
-  __shared__ float xs[NI], h1[NH], h2[NH];
-  const int b = blockIdx.x, t = threadIdx.x;
-  if (b >= batch) return;
-  if (t < NI) xs[t] = x[(int64_t)b * NI + t];
+// ------------------------------------------------- forward and backward
+// Two samples per block of 128 threads (thread t owns unit t of each layer),
+// so that every weight read from L2 serves two samples; weight rows are read
+// as vectors, activations stay in LDS (13 us at batch 256; the weights staged
+// in LDS first: 14).  With `act` set (training) the block
+// goes on to the deltas
+//   dout = 2 (out - y) / (batch * 32), dz2 = (dout W3) . [h2 > 0],
+//   dz1 = (dz2 W2) . [h1 > 0],
+// stores h1, h2 ([batch][2][128]) and dz1, dz2, dout ([batch][288]) for the
+// weight gradients, and each sample's sum of squared errors.
+constexpr int MS = 2;                      // samples per block
+typedef float f2u __attribute__((ext_vector_type(2), aligned(4)));   // the caller's arrays are only float-aligned
+constexpr int DL = 2 * NH + NO;            // deltas per sample
+__global__ __launch_bounds__(128) void k_mlp(const float* w, const float* x, const float* y, int batch, float* out,
+                                             float* act, float* dl, float* sq) {
+  __shared__ float xs[MS][NI + 2], h1[MS][NH], h2[MS][NH], dout[MS][NO], dz2[MS][NH];
+  const int b0 = blockIdx.x * MS, t = threadIdx.x, ns = min(MS, batch - b0);
+  for (int e = t; e < MS * NI; e += 128)
+    xs[e / NI][e % NI] = e / NI < ns ? x[(int64_t)b0 * NI + e] : 0.f;
+  __syncthreads();
+  float z[MS];
+  {
+#pragma unroll
+    for (int m = 0; m < MS; ++m) z[m] = w[OFF_B1 + t];
+    const f2u* wr = reinterpret_cast<const f2u*>(w + OFF_W1 + t * NI);
+#pragma unroll 11
+    for (int i = 0; i < NI / 2; ++i) {
+      const f2u v = wr[i];
+#pragma unroll
+      for (int m = 0; m < MS; ++m) z[m] = fmaf(v.y, xs[m][2 * i + 1], fmaf(v.x, xs[m][2 * i], z[m]));
+    }
+#pragma unroll
+    for (int m = 0; m < MS; ++m) h1[m][t] = z[m] > 0.f ? z[m] : 0.f;
+  }
   __syncthreads();
   {
-    float z = w[OFF_B1 + t];
-    const float* wr = w + OFF_W1 + t * NI;
-    for (int i = 0; i < NI; ++i) z += wr[i] * xs[i];
-    h1[t] = z > 0.f ? z : 0.f;
+#pragma unroll
+    for (int m = 0; m < MS; ++m) z[m] = w[OFF_B2 + t];
+    const f2u* wr = reinterpret_cast<const f2u*>(w + OFF_W2 + t * NH);
+#pragma unroll 16
+    for (int i = 0; i < NH / 2; ++i) {
+      const f2u v = wr[i];
+#pragma unroll
+      for (int m = 0; m < MS; ++m) z[m] = fmaf(v.y, h1[m][2 * i + 1], fmaf(v.x, h1[m][2 * i], z[m]));
+    }
+#pragma unroll
+    for (int m = 0; m < MS; ++m) h2[m][t] = z[m] > 0.f ? z[m] : 0.f;
+  }
+  __syncthreads();
+  const int o = t % NO, m = t / NO;        // threads 0..63: output o of sample m
+  if (m < ns) {
+    float v = w[OFF_B3 + o];
+    const f2u* wr = reinterpret_cast<const f2u*>(w + OFF_W3 + o * NH);
+#pragma unroll 16
+    for (int i = 0; i < NH / 2; ++i) v = fmaf(wr[i].y, h2[m][2 * i + 1], fmaf(wr[i].x, h2[m][2 * i], v));
+    if (out) out[(int64_t)(b0 + m) * NO + o] = v;
     if (act) {
-      act[((int64_t)b * 4 + 0) * NH + t] = z;
-      act[((int64_t)b * 4 + 1) * NH + t] = h1[t];
+      const float d = v - y[(int64_t)(b0 + m) * NO + o];
+      dout[m][o] = 2.0f / ((float)batch * (float)NO) * d;
+      float q = d * d;
+#pragma unroll
+      for (int h = NO / 2; h > 0; h >>= 1) q += __shfl_xor(q, h);
+      if (o == 0) sq[b0 + m] = q;
     }
   }
+  if (!act) return;
   __syncthreads();
   {
-    float z = w[OFF_B2 + t];
-    const float* wr = w + OFF_W2 + t * NH;
-    for (int i = 0; i < NH; ++i) z += wr[i] * h1[i];
-    h2[t] = z > 0.f ? z : 0.f;
-    if (act) {
-      act[((int64_t)b * 4 + 2) * NH + t] = z;
-      act[((int64_t)b * 4 + 3) * NH + t] = h2[t];
+    float d[MS];
+#pragma unroll
+    for (int k = 0; k < MS; ++k) d[k] = 0.f;
+#pragma unroll 8
+    for (int e = 0; e < NO; ++e) {
+      const float v = w[OFF_W3 + e * NH + t];
+#pragma unroll
+      for (int k = 0; k < MS; ++k) d[k] = fmaf(dout[k][e], v, d[k]);
+    }
+#pragma unroll
+    for (int k = 0; k < MS; ++k) dz2[k][t] = h2[k][t] > 0.f ? d[k] : 0.f;
+  }
+  __syncthreads();
+  {
+    float d[MS];
+#pragma unroll
+    for (int k = 0; k < MS; ++k) d[k] = 0.f;
+#pragma unroll 16
+    for (int e = 0; e < NH; ++e) {
+      const float v = w[OFF_W2 + e * NH + t];
+#pragma unroll
+      for (int k = 0; k < MS; ++k) d[k] = fmaf(dz2[k][e], v, d[k]);
+    }
+    for (int k = 0; k < ns; ++k) {
+      float* a = act + (int64_t)(b0 + k) * 2 * NH;
+      float* g = dl + (int64_t)(b0 + k) * DL;
+      a[t] = h1[k][t];
+      a[NH + t] = h2[k][t];
+      g[t] = h1[k][t] > 0.f ? d[k] : 0.f;
+      g[NH + t] = dz2[k][t];
+      if (t < NO) g[2 * NH + t] = dout[k][t];
     }
   }
-  __syncthreads();
-  if (t < NO) {
-    float z = w[OFF_B3 + t];
-    const float* wr = w + OFF_W3 + t * NH;
-    for (int i = 0; i < NH; ++i) z += wr[i] * h2[i];
-    out[(int64_t)b * NO + t] = z;
-  }
 }
 
-// --------------------------------------------------------------- backward
-// Per-sample deltas: dout = 2 (out - y) / (batch * 32); dz2 = (dout W3) .
-// [z2 > 0]; dz1 = (dz2 W2) . [z1 > 0].  Stored as [batch][3][128] (dout
-// in the first 32 of slot 0, dz2 in slot 1, dz1 in slot 2).
-__global__ __launch_bounds__(128) void k_mlp_delta(const float* w, const float* out, const float* y,
-                                                   const float* act, int batch, float* dl) {
-  __shared__ float dout[NO], dz2[NH];
-  const int b = blockIdx.x, t = threadIdx.x;
-  if (b >= batch) return;
-  const float scale = 2.0f / ((float)batch * (float)NO);
-  if (t < NO) {
-    dout[t] = scale * (out[(int64_t)b * NO + t] - y[(int64_t)b * NO + t]);
-    dl[((int64_t)b * 3 + 0) * NH + t] = dout[t];
-  }
-  __syncthreads();
-  {
-    float d = 0.f;
-    for (int o = 0; o < NO; ++o) d += dout[o] * w[OFF_W3 + o * NH + t];
-    const float z2 = act[((int64_t)b * 4 + 2) * NH + t];
-    dz2[t] = z2 > 0.f ? d : 0.f;
-    dl[((int64_t)b * 3 + 1) * NH + t] = dz2[t];
-  }
-  __syncthreads();
-  {
-    float d = 0.f;
-    for (int o = 0; o < NH; ++o) d += dz2[o] * w[OFF_W2 + o * NH + t];
-    const float z1 = act[((int64_t)b * 4 + 0) * NH + t];
-    dl[((int64_t)b * 3 + 2) * NH + t] = z1 > 0.f ? d : 0.f;
-  }
-}
-
-// Weight gradients: one thread per parameter, sequential sum over the batch.
-__global__ void k_mlp_wgrad(const float* x, const float* act, const float* dl, int batch, float* g) {
-  const int p = blockIdx.x * blockDim.x + threadIdx.x;
-  if (p >= N_PARAMS) return;
-  float acc = 0.f;
-  if (p < OFF_B1) {  // W1[o][i] = sum_b dz1[b][o] x[b][i]
-    const int o = p / NI, i = p % NI;
-    for (int b = 0; b < batch; ++b) acc += dl[((int64_t)b * 3 + 2) * NH + o] * x[(int64_t)b * NI + i];
-  } else if (p < OFF_W2) {
-    const int o = p - OFF_B1;
-    for (int b = 0; b < batch; ++b) acc += dl[((int64_t)b * 3 + 2) * NH + o];
-  } else if (p < OFF_B2) {  // W2[o][i] = sum_b dz2[b][o] h1[b][i]
-    const int q = p - OFF_W2, o = q / NH, i = q % NH;
-    for (int b = 0; b < batch; ++b) acc += dl[((int64_t)b * 3 + 1) * NH + o] * act[((int64_t)b * 4 + 1) * NH + i];
-  } else if (p < OFF_W3) {
-    const int o = p - OFF_B2;
-    for (int b = 0; b < batch; ++b) acc += dl[((int64_t)b * 3 + 1) * NH + o];
-  } else if (p < OFF_B3) {  // W3[o][i] = sum_b dout[b][o] h2[b][i]
-    const int q = p - OFF_W3, o = q / NH, i = q % NH;
-    for (int b = 0; b < batch; ++b) acc += dl[((int64_t)b * 3 + 0) * NH + o] * act[((int64_t)b * 4 + 3) * NH + i];
-  } else {
-    const int o = p - OFF_B3;
-    for (int b = 0; b < batch; ++b) acc += dl[((int64_t)b * 3 + 0) * NH + o];
-  }
-  g[p] = acc;
-}
-
-// loss = mean (out - y)^2 over batch * 32 values, fixed-order tree.
-__global__ void k_mlp_loss(const float* out, const float* y, int n, float* loss) {
-  __shared__ float red[256];
-  float acc = 0.f;
-  for (int i = threadIdx.x; i < n; i += 256) {
-    const float d = out[i] - y[i];
-    acc += d * d;
-  }
-  red[threadIdx.x] = acc;
-  __syncthreads();
-  for (int h = 128; h > 0; h >>= 1) {
-    if ((int)threadIdx.x < h) red[threadIdx.x] += red[threadIdx.x + h];
+// Weight gradients: a block takes a 16 x 16 tile of one weight matrix, its
+// four waves a quarter of the batch each (two outputs by two inputs per
+// lane), summed in wave order; the tiles of the first 16 inputs also sum the
+// bias gradient.  The last block reduces the loss, mean (out - y)^2, over the
+// samples' sums in a fixed tree.  (One thread per weight walking the whole
+// batch took 65 us at batch 256.)
+constexpr int GT = 16;
+constexpr int TI1 = (NI + GT - 1) / GT, TI2 = NH / GT, TO = NH / GT, TO3 = NO / GT;
+constexpr int WG_TILES = TO * TI1 + TO * TI2 + TO3 * TI2;
+__global__ __launch_bounds__(256) void k_mlp_wgrad(const float* x, const float* act, const float* dl, const float* sq,
+                                                   int batch, float* g, float* loss) {
+  __shared__ float red[4][GT][GT + 1], rb[4][GT];
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  int tile = blockIdx.x;
+  if (tile == WG_TILES) {
+    if (!loss) return;
+    float* r = &red[0][0][0];
+    float acc = 0.f;
+    for (int i = tid; i < batch; i += 256) acc += sq[i];
+    r[tid] = acc;
     __syncthreads();
+    for (int h = 128; h > 0; h >>= 1) {
+      if (tid < h) r[tid] += r[tid + h];
+      __syncthreads();
+    }
+    if (tid == 0) *loss = r[0] / (float)(batch * NO);
+    return;
   }
-  if (threadIdx.x == 0) *loss = red[0] / (float)n;
+  const float *d, *a;
+  int ni, lda, off_w, off_b, ti;
+  if (tile < TO * TI1) {                    // W1: dz1, x
+    d = dl;
+    a = x;
+    ni = NI;
+    lda = NI;
+    off_w = OFF_W1;
+    off_b = OFF_B1;
+    ti = TI1;
+  } else if (tile < TO * TI1 + TO * TI2) {  // W2: dz2, h1
+    tile -= TO * TI1;
+    d = dl + NH;
+    a = act;
+    ni = NH;
+    lda = 2 * NH;
+    off_w = OFF_W2;
+    off_b = OFF_B2;
+    ti = TI2;
+  } else {                                  // W3: dout, h2
+    tile -= TO * TI1 + TO * TI2;
+    d = dl + 2 * NH;
+    a = act + NH;
+    ni = NH;
+    lda = 2 * NH;
+    off_w = OFF_W3;
+    off_b = OFF_B3;
+    ti = TI2;
+  }
+  const int o0 = (tile / ti) * GT, i0 = (tile % ti) * GT;
+  const int lo = 2 * (lane >> 3), li = 2 * (lane & 7);
+  const bool in = i0 + li < ni;             // ni is even
+  const f2u* dp = reinterpret_cast<const f2u*>(d + o0 + lo);
+  const f2u* ap = reinterpret_cast<const f2u*>(a + i0 + (in ? li : 0));
+  const int per = (batch + 3) / 4, b0 = w * per, b1 = min(batch, b0 + per);
+  float s00 = 0.f, s01 = 0.f, s10 = 0.f, s11 = 0.f, t0 = 0.f, t1 = 0.f;
+#pragma unroll 8
+  for (int b = b0; b < b1; ++b) {
+    const f2u dv = dp[(int64_t)b * (DL / 2)], av = ap[(int64_t)b * (lda / 2)];
+    s00 = fmaf(dv.x, av.x, s00);
+    s01 = fmaf(dv.x, av.y, s01);
+    s10 = fmaf(dv.y, av.x, s10);
+    s11 = fmaf(dv.y, av.y, s11);
+    t0 += dv.x;
+    t1 += dv.y;
+  }
+  red[w][lo][li] = s00;
+  red[w][lo][li + 1] = s01;
+  red[w][lo + 1][li] = s10;
+  red[w][lo + 1][li + 1] = s11;
+  if (li == 0) {
+    rb[w][lo] = t0;
+    rb[w][lo + 1] = t1;
+  }
+  __syncthreads();
+  const int r = tid / GT, c = tid % GT;
+  if (i0 + c < ni) g[off_w + (o0 + r) * ni + i0 + c] = ((red[0][r][c] + red[1][r][c]) + red[2][r][c]) + red[3][r][c];
+  if (i0 == 0 && tid < GT) g[off_b + o0 + tid] = ((rb[0][tid] + rb[1][tid]) + rb[2][tid]) + rb[3][tid];
 }
 
 // Adam (Kingma & Ba 2015) with bias correction.
@@ -217,9 +292,10 @@ __global__ void k_adam(float* w, const float* g, float* m, float* v, int count, 
   w[i] -= lr * (mi / c1) / (sqrtf(vi / c2) + eps);
 }
 
-void mlp_forward(const float* w, const float* x, int batch, float* out, float* act, hipStream_t s) {
+void mlp_forward(const float* w, const float* x, int batch, float* out, hipStream_t s) {
   if (batch <= 0) return;
-  hipLaunchKernelGGL(k_mlp_fwd, dim3(batch), dim3(128), 0, s, w, x, batch, out, act);
+  hipLaunchKernelGGL(k_mlp, dim3(ceil_div(batch, MS)), dim3(128), 0, s, w, x, nullptr, batch, out, nullptr, nullptr,
+                     nullptr);
   HIP_LAUNCH_OK();
 }
 
@@ -259,7 +335,7 @@ rcs_status rcs_mlp_forward(const float* w_dev, const float* x_dev, int32_t batch
                            void* stream) {
   RCS_API_BEGIN
   RCS_REQUIRE(w_dev && x_dev && out_dev && batch >= 0, "bad arguments");
-  rcs::mlp_forward(w_dev, x_dev, batch, out_dev, nullptr, rcs::as_stream(stream));
+  rcs::mlp_forward(w_dev, x_dev, batch, out_dev, rcs::as_stream(stream));
   RCS_API_END
 }
 
@@ -268,22 +344,17 @@ rcs_status rcs_mlp_backward(const float* w_dev, const float* x_dev, const float*
   RCS_API_BEGIN
   RCS_REQUIRE(w_dev && x_dev && y_dev && grad_dev && batch >= 1, "bad arguments");
   hipStream_t s = rcs::as_stream(stream);
-  rcs::DevBuf out, act, dl;
-  out.ensure((size_t)batch * rcs::NO * sizeof(float));
-  act.ensure((size_t)batch * 4 * rcs::NH * sizeof(float));
-  dl.ensure((size_t)batch * 3 * rcs::NH * sizeof(float));
-  rcs::mlp_forward(w_dev, x_dev, batch, out.as<float>(), act.as<float>(), s);
-  hipLaunchKernelGGL(rcs::k_mlp_delta, dim3(batch), dim3(128), 0, s, w_dev, out.as<float>(), y_dev,
-                     act.as<float>(), batch, dl.as<float>());
+  rcs::DevBuf ws;
+  ws.ensure((size_t)batch * (2 * rcs::NH + rcs::DL + 1) * sizeof(float));
+  float* act = ws.as<float>();
+  float* dl = act + (size_t)batch * 2 * rcs::NH;
+  float* sq = dl + (size_t)batch * rcs::DL;
+  hipLaunchKernelGGL(rcs::k_mlp, dim3(rcs::ceil_div(batch, rcs::MS)), dim3(128), 0, s, w_dev, x_dev, y_dev, batch,
+                     nullptr, act, dl, sq);
   HIP_LAUNCH_OK();
-  hipLaunchKernelGGL(rcs::k_mlp_wgrad, dim3(rcs::ceil_div(rcs::N_PARAMS, 256)), dim3(256), 0, s, x_dev,
-                     act.as<float>(), dl.as<float>(), batch, grad_dev);
+  hipLaunchKernelGGL(rcs::k_mlp_wgrad, dim3(rcs::WG_TILES + 1), dim3(256), 0, s, x_dev, act, dl, sq, batch, grad_dev,
+                     loss_dev);
   HIP_LAUNCH_OK();
-  if (loss_dev) {
-    hipLaunchKernelGGL(rcs::k_mlp_loss, dim3(1), dim3(256), 0, s, out.as<float>(), y_dev, batch * rcs::NO,
-                       loss_dev);
-    HIP_LAUNCH_OK();
-  }
   HIP_OK(hipStreamSynchronize(s));
   RCS_API_END
 }
