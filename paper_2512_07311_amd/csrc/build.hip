@@ -1055,7 +1055,7 @@ static void move_center(rcs_state_s& st, BuildWork& ws, bool right) {
                      right ? 1 : 0, ws.X.as<double2>(), ws.X0.as<double2>(), pl.ldx);
   HIP_LAUNCH_OK();
   int k;
-  if (cholqr_moves_enabled() && cnt >= 64 && cnt <= len && move_cholqr(st, ws, pl)) {
+  if (cholqr_moves_enabled() && cnt >= 2 && cnt <= len && move_cholqr(st, ws, pl)) {
     k = cnt;
     st.n_moves_cholqr += 1;
     RCS_PROBED_LAUNCH(kKcFactor, k_project, dim3(ceil_div(cnt, GT_N), ceil_div(k, GT_M)), dim3(GT_THREADS), 0, s,
