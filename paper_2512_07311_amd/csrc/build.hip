@@ -30,6 +30,7 @@
 #include "circuit.h"
 #include "gemm_f64.h"
 #include "jacobi.h"
+#include "split_small.h"
 #include "prof.h"
 #include "rsvd.h"
 #include "state.h"
@@ -273,13 +274,6 @@ __global__ void k_sum_sq(const double* v, int n, double* out) {
 //  w = sum s^2; s^2 <= 1e-24 w counts as zero; tail(k) = sum_{r>=k} s_r^2
 //  from the smallest upward; k_eps = min{k>=1 : tail(k) <= eps w};
 //  k = min(k_eps, cap); eps_step = tail(k)/w; nrm = sqrt(sum_{r<k} s_r^2).
-struct RankOut {
-  int k;
-  int nnz;
-  double eps_step, w, nrm;
-  int bad;
-};
-
 constexpr int SORT_MAX = 4096;
 
 __global__ __launch_bounds__(1024) void k_sort_rank(const double* sigma, int cnt, int cap,
@@ -765,6 +759,45 @@ static SplitResult svd_split(rcs_state_s& st, BuildWork& ws, const JacobiPlan& p
   return out;
 }
 
+// svd_split of a small matrix in one launch; X is read from ws.X0 only.
+static SplitResult svd_split_small(rcs_state_s& st, BuildWork& ws, const JacobiPlan& pl, int cap, double eps,
+                                   bool renorm, std::vector<double>* spectrum_out, bool ortho_only) {
+  hipStream_t s = st.stream;
+  const JacobiTol t = jacobi_tol(pl.len, ortho_only ? 1e-7 : 0.0);
+  SplitSmallArgs a{};
+  a.x = ws.X0.as<double2>();
+  a.ldx = pl.ldx;
+  a.len = pl.len;
+  a.cnt = pl.cnt;
+  a.cap = cap;
+  a.eps = eps;
+  a.tol = t.tol;
+  a.qtol = t.qtol;
+  a.delta2 = t.delta2;
+  a.max_sweeps = kJacobiMaxSweeps;
+  a.ns_steps = ortho_only ? 2 : 1;
+  a.sort = sort_columns_first();
+  a.renorm = renorm;
+  a.wn = ws.Wn.as<double2>();
+  a.p = ws.P.as<double2>();
+  a.sorted = ws.sorted.as<double>();
+  a.out = ws.scal.as<RankOut>();
+  split_small(a, s);
+  HIP_OK(hipMemcpyAsync(ws.host_rank, ws.scal.p, sizeof(RankOut), hipMemcpyDeviceToHost, s));
+  HIP_OK(hipStreamSynchronize(s));
+  const RankOut r = *ws.host_rank;
+  if (r.sweeps < 0) fail(RCS_ERR_NUMERIC, "one-sided Jacobi SVD did not converge");
+  st.jacobi_sweeps_max = std::max(st.jacobi_sweeps_max, r.sweeps);
+  if (r.bad) fail(RCS_ERR_NUMERIC, "non-finite singular values");
+  if (spectrum_out) {
+    spectrum_out->resize(pl.cnt);
+    HIP_OK(hipMemcpyAsync(spectrum_out->data(), ws.sorted.p, pl.cnt * sizeof(double), hipMemcpyDeviceToHost, s));
+    HIP_OK(hipStreamSynchronize(s));
+  }
+  ws.wn_final = ws.Wn.as<double2>();
+  return SplitResult{r.k, r.nnz, r.sweeps, r.eps_step, r.w, r.nrm};
+}
+
 static bool svd_precondition_enabled() {
   static const bool v = [] {
     const char* e = std::getenv("RCS_SVD_PRECOND");
@@ -1061,6 +1094,8 @@ static void move_center(rcs_state_s& st, BuildWork& ws, bool right) {
     RCS_PROBED_LAUNCH(kKcFactor, k_project, dim3(ceil_div(cnt, GT_N), ceil_div(k, GT_M)), dim3(GT_THREADS), 0, s,
                        ws.wn_final, ws.X0.as<double2>(), pl.ldx, len, k, cnt, 1.0, ws.P.as<double2>());
     HIP_LAUNCH_OK();
+  } else if (split_small_fits(len, cnt)) {
+    k = svd_split_small(st, ws, pl, right ? st.cap[c + 1] : st.cap[c], 0.0, false, nullptr, true).k;
   } else {
     // the CholeskyQR attempt (if any) left X untouched only where it ran
     // out of steps: reload it
@@ -1299,10 +1334,15 @@ static void two_site_update(rcs_state_s& st, BuildWork& ws, UpdateCtx& ctx, int 
   const int cnt = orient == 1 ? 2 * dr : 2 * dl;
   JacobiPlan pl = jacobi_plan(len, cnt);
   ensure_work(ws, pl);
-  HIP_OK(hipMemsetAsync(ws.X.p, 0, (size_t)pl.ldx * pl.cnt_pad * sizeof(double2), s));
-  HIP_OK(hipMemsetAsync(ws.X0.p, 0, (size_t)pl.ldx * pl.cnt_pad * sizeof(double2), s));
+  // the one-launch split reads its input with bounds and works in LDS: no
+  // padding to clear, no second copy
+  const bool small = split_small_fits(len, cnt);
+  if (!small) {
+    HIP_OK(hipMemsetAsync(ws.X.p, 0, (size_t)pl.ldx * pl.cnt_pad * sizeof(double2), s));
+    HIP_OK(hipMemsetAsync(ws.X0.p, 0, (size_t)pl.ldx * pl.cnt_pad * sizeof(double2), s));
+  }
   contract_mix(site_view(st.site[i], dl, dm), site_view(st.site[i + 1], dm, dr), to_gate4(gate16), dl, dm, dr, precision,
-               MixOut{ws.X.as<double2>(), ws.X0.as<double2>(), pl.ldx, orient}, s);
+               MixOut{ws.X0.as<double2>(), small ? nullptr : ws.X.as<double2>(), pl.ldx, orient}, s);
   std::vector<double> spec;
   SplitResult r{};
   int ldw = pl.ldx, p_row = pl.cnt, side = orient;
@@ -1310,7 +1350,9 @@ static void two_site_update(rcs_state_s& st, BuildWork& ws, UpdateCtx& ctx, int 
   // result would be redone in fp64)
   const bool try32 =
       ctx.o && ctx.o->svd_f32 && (ctx.o->rank_mode != RCS_RANK_LEARNED || ctx.pred_capped);
-  if (precond && svd_split_chol(st, ws, pl, cap_eff, eps, true, log_spectra ? &spec : nullptr, r, &ldw, try32)) {
+  if (small) {
+    r = svd_split_small(st, ws, pl, cap_eff, eps, true, log_spectra ? &spec : nullptr, false);
+  } else if (precond && svd_split_chol(st, ws, pl, cap_eff, eps, true, log_spectra ? &spec : nullptr, r, &ldw, try32)) {
     // orthonormal factor on X's column side: the other orientation's layout
     side = 3 - orient;
     p_row = len;

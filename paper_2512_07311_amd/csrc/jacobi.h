@@ -22,6 +22,15 @@ struct JacobiPlan {
   int n_gchunks = 0, rows_per_gchunk = 0;   // Gram pass row chunks
 };
 
+// Tolerances of the fp64 iteration on len rows: relative orthogonality (tol >
+// 0 replaces the default), the squared cosine below which the next sweep
+// would rotate nothing (0: rule off), and the squared column norm, relative
+// to ||X||_F^2, that counts as zero.
+struct JacobiTol {
+  double tol, qtol, delta2;
+};
+JacobiTol jacobi_tol(int len, double tol = 0.0);
+
 // jb <= 0 picks the default block width for the shape; f32: the plan of
 // jacobi_run_f32 (its Gram chunks differ).
 JacobiPlan jacobi_plan(int len, int cnt, int jb = 0, bool f32 = false);

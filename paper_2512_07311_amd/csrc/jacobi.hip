@@ -36,38 +36,12 @@
 
 #include "gemm_f64.h"
 #include "jacobi.h"
+#include "jacobi_dev.h"
 #include "prof.h"
 
 namespace rcs {
 
 constexpr int TR = 16;        // rows per wave tile (four 4-row MFMA k steps)
-
-// Per-precision pieces: the complex type, the 16x16x4 matrix-core product
-// and the row of accumulator element r in a lane (the fp64 instruction
-// interleaves rows, the fp32 one gives each 16-lane group four consecutive
-// rows).
-template <typename R>
-struct JT;
-template <>
-struct JT<double> {
-  using C = double2;
-  using V4 = double4_t;
-  static constexpr double u = 1.11e-16;
-  static constexpr double tiny = 1e-300;
-  __device__ static V4 mma(double a, double b, V4 c) { return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0); }
-  __device__ static int orow(int lane, int r) { return (lane >> 4) + 4 * r; }
-  __host__ __device__ static C mk(double x, double y) { return make_double2(x, y); }
-};
-template <>
-struct JT<float> {
-  using C = float2;
-  using V4 = float4_t;
-  static constexpr double u = 5.97e-8;
-  static constexpr float tiny = 1e-36f;
-  __device__ static V4 mma(float a, float b, V4 c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
-  __device__ static int orow(int lane, int r) { return 4 * (lane >> 4) + r; }
-  __host__ __device__ static C mk(float x, float y) { return make_float2(x, y); }
-};
 
 __device__ inline int rr_block(int slot, int round, int nbp) {
   return slot == 0 ? 0 : ((slot - 1 + round) % (nbp - 1)) + 1;
@@ -233,107 +207,6 @@ __global__ __launch_bounds__(64 * NW) void k_jac_gram(JacArgs<R> a) {
         part[row * JP + col] = T::mk(vr, vi);
         if (mb != nb) part[col * JP + row] = T::mk(vr, -vi);
       }
-}
-
-// 1/sqrt(x) for normal positive x: hardware estimate plus two Newton steps
-// (each doubles the correct bits; the estimate carries about 23), i.e.
-// within a couple of ulps.
-__device__ inline double rsqrt_nr(double x) {
-  double r = __builtin_amdgcn_rsq(x);
-  const double h = 0.5 * x;
-  double e = fma(-h * r, r, 0.5);
-  r = fma(r, e, r);
-  e = fma(-h * r, r, 0.5);
-  return fma(r, e, r);
-}
-
-// Plane rotation J = [[c, s e], [-s conj(e), c]] (rows: old columns i < j,
-// columns: new) that (nearly) zeroes G_ij of the Hermitian 2x2 [[gii, g],
-// [conj g, gjj]] in J^H G J; the identity when the pair is already
-// orthogonal to tol or either column is negligible.
-//
-// Only unitarity has to hold to fp64 accuracy: the angle may be a few
-// 1e-8 off (it leaves an off-diagonal of that relative size, which the
-// next sweep's fresh Gram sees and removes, so convergence stays
-// quadratic).  Hence e = g * rsq(|g|^2) with the raw hardware estimate
-// (exact phase, modulus within ~2^-23 of one), tan(theta) in fp32 from
-// tau = (gjj - gii) / (2|g|) (the smaller-angle root, |t| <= 1), and
-// c = 1/sqrt(1 + t^2 |e|^2) refined in fp64, s = t c, which makes
-// c^2 + s^2 |e|^2 = 1 to rounding.  Branch-free: inactive pairs select the
-// identity.
-template <typename R>
-struct Rot {
-  R c, s, ex, ey;
-};
-template <typename R>
-__device__ inline bool rot_active(R gii, R gjj, R h2, R tol, R neg2) {
-  return gii > neg2 && gjj > neg2 && h2 > JT<R>::tiny && h2 > tol * tol * gii * gjj;
-}
-__device__ inline Rot<double> jac_rot(double gii, double gjj, double2 g, double tol, double neg2) {
-  const double h2 = g.x * g.x + g.y * g.y;
-  const bool act = rot_active<double>(gii, gjj, h2, tol, neg2);
-  const double rh = __builtin_amdgcn_rsq(fmax(h2, 1e-300));
-  const double tau = (gjj - gii) * (0.5 * rh);
-  const float tf = (float)fabs(tau);
-  const float root = tf + __builtin_amdgcn_sqrtf(fmaf(tf, tf, 1.0f));
-  const float t32 = __builtin_amdgcn_rcpf(tf > 1e18f ? 2.0f * tf : root);
-  const double t = tau < 0.0 ? -(double)t32 : (double)t32;
-  const double ex = g.x * rh, ey = g.y * rh;
-  const double c = rsqrt_nr(fma(t * t, ex * ex + ey * ey, 1.0));
-  Rot<double> r;
-  r.c = act ? c : 1.0;
-  r.s = act ? t * c : 0.0;
-  r.ex = act ? ex : 1.0;
-  r.ey = act ? ey : 0.0;
-  return r;
-}
-
-// fp32: the same rotation with every step in fp32; c takes one Newton step
-// on the hardware 1/sqrt estimate, so c^2 (1 + t^2 |e|^2) = 1 to fp32
-// rounding.
-__device__ inline Rot<float> jac_rot(float gii, float gjj, float2 g, float tol, float neg2) {
-  const float h2 = g.x * g.x + g.y * g.y;
-  const bool act = rot_active<float>(gii, gjj, h2, tol, neg2);
-  const float rh = __builtin_amdgcn_rsqf(fmaxf(h2, JT<float>::tiny));
-  const float tau = (gjj - gii) * (0.5f * rh);
-  const float tf = fabsf(tau);
-  const float root = tf + __builtin_amdgcn_sqrtf(fmaf(tf, tf, 1.0f));
-  const float t32 = __builtin_amdgcn_rcpf(tf > 1e18f ? 2.0f * tf : root);
-  const float t = tau < 0.0f ? -t32 : t32;
-  const float ex = g.x * rh, ey = g.y * rh;
-  const float x = fmaf(t * t, ex * ex + ey * ey, 1.0f);
-  float c = __builtin_amdgcn_rsqf(x);
-  c = fmaf(c, fmaf(-0.5f * x * c, c, 0.5f), c);
-  Rot<float> r;
-  r.c = act ? c : 1.0f;
-  r.s = act ? t * c : 0.0f;
-  r.ex = act ? ex : 1.0f;
-  r.ey = act ? ey : 0.0f;
-  return r;
-}
-
-// With a = s e (precomputed once per rotation: RotA = {c, Re a, Im a}):
-// right action (X J):  x_i' = c x_i - conj(a) x_j,  x_j' = a x_i + c x_j;
-// left action (J^H X): x_i' = c x_i - a x_j,        x_j' = conj(a) x_i + c x_j.
-template <typename R>
-struct RotA {
-  R c, ax, ay;
-};
-template <typename R>
-__device__ inline RotA<R> rot_a(const Rot<R>& r) { return RotA<R>{r.c, r.s * r.ex, r.s * r.ey}; }
-template <typename R, typename C>
-__device__ inline void rot_right(const RotA<R>& r, C& xi, C& xj) {
-  const R ax = r.ax, ay = r.ay;
-  const C ni(fma(r.c, xi.x, -fma(ax, xj.x, ay * xj.y)), fma(r.c, xi.y, fma(ay, xj.x, -ax * xj.y)));
-  xj = C(fma(r.c, xj.x, fma(ax, xi.x, -ay * xi.y)), fma(r.c, xj.y, fma(ax, xi.y, ay * xi.x)));
-  xi = ni;
-}
-template <typename R, typename C>
-__device__ inline void rot_left(const RotA<R>& r, C& xi, C& xj) {
-  const R ax = r.ax, ay = r.ay;
-  const C ni(fma(r.c, xi.x, -fma(ax, xj.x, -ay * xj.y)), fma(r.c, xi.y, -fma(ax, xj.y, ay * xj.x)));
-  xj = C(fma(r.c, xj.x, fma(ax, xi.x, ay * xi.y)), fma(r.c, xj.y, fma(ax, xi.y, -ay * xi.x)));
-  xi = ni;
 }
 
 // Members (i < j) of pair q in round-robin round `round` of JP columns, and
@@ -565,222 +438,19 @@ __global__ __launch_bounds__(ROT_THREADS) void k_jac_rotate(JacArgs<R> a) {
   }
 }
 
-// ------------------------------------------------- row-resident rotation
-// The fp64 rotate pass for 16-column blocks.  The two-sided solve of the
-// 32 x 32 Gram is a serial chain of rounds (16 disjoint rotations each), and
-// forming the unitary and multiplying by it costs twice the flops of
-// applying the rotations themselves, at the same fp64 rate (the vector and
-// the matrix units both reach 78.6 TFLOP/s).  So the workgroup splits:
-//   waves 0-3   run the solve, one barrier per round: thread (k, pb) holds
-//               the block of pair pa = pb + k mod 16 against pair pb, computes
-//               pair pb's rotation itself, takes pa's from the lane that has
-//               it, and writes its four entries to the other Gram buffer;
-//   waves 4...  hold one row of Y_p per lane in registers (32 columns, loaded
-//               while the partial Grams are summed) and apply each round's
-//               rotations one round behind the solve.
-// A rotation is applied as two in-place complex shears with the column scales
-// deferred (an LDU factorisation of the plane rotation, eight FMAs instead of
-// twelve):  with x = d x~,  x~_i -= conj(u) x~_j,  x~_j += w x~_i',
-//   u = t d_j / d_i,  w = c^2 t d_i / d_j,  d_i <- c d_i,  d_j <- d_j / c,
-// t the complex tangent (|t| <= 1), c = (1 + |t|^2)^(-1/2).  The scales stay
-// within 2^(+-rounds / 2) and are multiplied out before the rows are stored.
-// Rotation q sits in lane q of every 16-lane row, from where the FMA itself
-// broadcasts it (DPP row_newbcast, the one DPP form 64-bit operations have):
-// 5.6 cycles per FMA and wave, against 7.2 with separate moves (plain: 4.9).
-//
-// Bound: below about 1024 columns the chain of rounds (0.6 us each, the
-// solve's latency), at 2048 the fp64 vector rate (two row waves and one solver
-// wave per SIMD) and the read and write of the matrix (64 MB, 25 us on its
-// own).  Measured against the LDS solve with a V product on the matrix cores
-// (still the 32-column and fp32 form), per launch: 128 x 128 21.5 -> 15.5 us,
-// 1024 x 1024 23 -> 20.5 us, 2048 x 2048 43 -> 33 us inside an SVD.  Tried and
-// slower: the whole solve before any row work (41 us at 2048), a rolled row
-// loop with register rotation, the shears published by a solver wave.
-constexpr int JSOLVE = 256;   // solver threads
-
-// One round's pair q in the inner schedule: columns i < j.  full: 15 rounds
-// of the 16-column round robin inside both blocks (pairs 0-7 and 8-15), then
-// the 16 cross rounds; else the cross rounds only.
-template <bool FULL>
-__host__ __device__ constexpr int sched_rounds() { return FULL ? 31 : 16; }
-__host__ __device__ constexpr int rr16_i(int q, int r) {
-  const int u = q == 0 ? 0 : ((q - 1 + r) % 15) + 1, v = ((14 - q + r) % 15) + 1;
-  return u < v ? u : v;
-}
-__host__ __device__ constexpr int rr16_j(int q, int r) {
-  const int u = q == 0 ? 0 : ((q - 1 + r) % 15) + 1, v = ((14 - q + r) % 15) + 1;
-  return u < v ? v : u;
-}
-template <bool FULL>
-__host__ __device__ constexpr int sched_i(int q, int r) {
-  return FULL && r < 15 ? (q & 8) * 2 + rr16_i(q & 7, r) : q;
-}
-template <bool FULL>
-__host__ __device__ constexpr int sched_j(int q, int r) {
-  return FULL && r < 15 ? (q & 8) * 2 + rr16_j(q & 7, r) : 16 + ((q + (FULL ? r - 15 : r)) & 15);
-}
-
-// a_k -= conj(u_k) b_k resp. a_k += w_k b_k for four independent columns k,
-// u_k, w_k taken from lane Q + k of the 16-lane row.  Four at a time, so that
-// dependent FMAs are eight instructions apart (two apart they cost twice the
-// time with one row wave per SIMD).  The leading wait covers a u or w that
-// the compiler moved with a VALU instruction just before (a DPP source needs
-// two wait states after one).
-template <int Q>
-__device__ __forceinline__ void shear_sub(double2& a0, double2& a1, double2& a2, double2& a3, const double2& b0,
-                                          const double2& b1, const double2& b2, const double2& b3, const double2& u) {
-  asm(
-      "s_nop 1\n\t"
-      "v_fmac_f64_dpp %0, -%16, %8 row_newbcast:%18 row_mask:0xf bank_mask:0xf\n\t"
-      "v_fmac_f64_dpp %2, -%16, %10 row_newbcast:%19 row_mask:0xf bank_mask:0xf\n\t"
-      "v_fmac_f64_dpp %4, -%16, %12 row_newbcast:%20 row_mask:0xf bank_mask:0xf\n\t"
-      "v_fmac_f64_dpp %6, -%16, %14 row_newbcast:%21 row_mask:0xf bank_mask:0xf\n\t"
-      "v_fmac_f64_dpp %1, -%16, %9 row_newbcast:%18 row_mask:0xf bank_mask:0xf\n\t"
-      "v_fmac_f64_dpp %3, -%16, %11 row_newbcast:%19 row_mask:0xf bank_mask:0xf\n\t"
-      "v_fmac_f64_dpp %5, -%16, %13 row_newbcast:%20 row_mask:0xf bank_mask:0xf\n\t"
-      "v_fmac_f64_dpp %7, -%16, %15 row_newbcast:%21 row_mask:0xf bank_mask:0xf\n\t"
-      "v_fmac_f64_dpp %0, -%17, %9 row_newbcast:%18 row_mask:0xf bank_mask:0xf\n\t"
-      "v_fmac_f64_dpp %2, -%17, %11 row_newbcast:%19 row_mask:0xf bank_mask:0xf\n\t"
-      "v_fmac_f64_dpp %4, -%17, %13 row_newbcast:%20 row_mask:0xf bank_mask:0xf\n\t"
-      "v_fmac_f64_dpp %6, -%17, %15 row_newbcast:%21 row_mask:0xf bank_mask:0xf\n\t"
-      "v_fmac_f64_dpp %1, %17, %8 row_newbcast:%18 row_mask:0xf bank_mask:0xf\n\t"
-      "v_fmac_f64_dpp %3, %17, %10 row_newbcast:%19 row_mask:0xf bank_mask:0xf\n\t"
-      "v_fmac_f64_dpp %5, %17, %12 row_newbcast:%20 row_mask:0xf bank_mask:0xf\n\t"
-      "v_fmac_f64_dpp %7, %17, %14 row_newbcast:%21 row_mask:0xf bank_mask:0xf"
-      : "+v"(a0.x), "+v"(a0.y), "+v"(a1.x), "+v"(a1.y), "+v"(a2.x), "+v"(a2.y), "+v"(a3.x), "+v"(a3.y)
-      : "v"(b0.x), "v"(b0.y), "v"(b1.x), "v"(b1.y), "v"(b2.x), "v"(b2.y), "v"(b3.x), "v"(b3.y), "v"(u.x), "v"(u.y),
-        "n"(Q), "n"(Q + 1), "n"(Q + 2), "n"(Q + 3));
-}
-template <int Q>
-__device__ __forceinline__ void shear_add(double2& a0, double2& a1, double2& a2, double2& a3, const double2& b0,
-                                          const double2& b1, const double2& b2, const double2& b3, const double2& w) {
-  asm(
-      "s_nop 1\n\t"
-      "v_fmac_f64_dpp %0, %16, %8 row_newbcast:%18 row_mask:0xf bank_mask:0xf\n\t"
-      "v_fmac_f64_dpp %2, %16, %10 row_newbcast:%19 row_mask:0xf bank_mask:0xf\n\t"
-      "v_fmac_f64_dpp %4, %16, %12 row_newbcast:%20 row_mask:0xf bank_mask:0xf\n\t"
-      "v_fmac_f64_dpp %6, %16, %14 row_newbcast:%21 row_mask:0xf bank_mask:0xf\n\t"
-      "v_fmac_f64_dpp %1, %16, %9 row_newbcast:%18 row_mask:0xf bank_mask:0xf\n\t"
-      "v_fmac_f64_dpp %3, %16, %11 row_newbcast:%19 row_mask:0xf bank_mask:0xf\n\t"
-      "v_fmac_f64_dpp %5, %16, %13 row_newbcast:%20 row_mask:0xf bank_mask:0xf\n\t"
-      "v_fmac_f64_dpp %7, %16, %15 row_newbcast:%21 row_mask:0xf bank_mask:0xf\n\t"
-      "v_fmac_f64_dpp %0, -%17, %9 row_newbcast:%18 row_mask:0xf bank_mask:0xf\n\t"
-      "v_fmac_f64_dpp %2, -%17, %11 row_newbcast:%19 row_mask:0xf bank_mask:0xf\n\t"
-      "v_fmac_f64_dpp %4, -%17, %13 row_newbcast:%20 row_mask:0xf bank_mask:0xf\n\t"
-      "v_fmac_f64_dpp %6, -%17, %15 row_newbcast:%21 row_mask:0xf bank_mask:0xf\n\t"
-      "v_fmac_f64_dpp %1, %17, %8 row_newbcast:%18 row_mask:0xf bank_mask:0xf\n\t"
-      "v_fmac_f64_dpp %3, %17, %10 row_newbcast:%19 row_mask:0xf bank_mask:0xf\n\t"
-      "v_fmac_f64_dpp %5, %17, %12 row_newbcast:%20 row_mask:0xf bank_mask:0xf\n\t"
-      "v_fmac_f64_dpp %7, %17, %14 row_newbcast:%21 row_mask:0xf bank_mask:0xf"
-      : "+v"(a0.x), "+v"(a0.y), "+v"(a1.x), "+v"(a1.y), "+v"(a2.x), "+v"(a2.y), "+v"(a3.x), "+v"(a3.y)
-      : "v"(b0.x), "v"(b0.y), "v"(b1.x), "v"(b1.y), "v"(b2.x), "v"(b2.y), "v"(b3.x), "v"(b3.y), "v"(w.x), "v"(w.y),
-        "n"(Q), "n"(Q + 1), "n"(Q + 2), "n"(Q + 3));
-}
-
-// Round r's rotations on a row.
-template <bool FULL, int R_, int Q>
-__device__ __forceinline__ void apply_four(double2 (&y)[32], const double2& u, const double2& w) {
-  constexpr int i0 = sched_i<FULL>(Q, R_), i1 = sched_i<FULL>(Q + 1, R_), i2 = sched_i<FULL>(Q + 2, R_),
-                i3 = sched_i<FULL>(Q + 3, R_);
-  constexpr int j0 = sched_j<FULL>(Q, R_), j1 = sched_j<FULL>(Q + 1, R_), j2 = sched_j<FULL>(Q + 2, R_),
-                j3 = sched_j<FULL>(Q + 3, R_);
-  shear_sub<Q>(y[i0], y[i1], y[i2], y[i3], y[j0], y[j1], y[j2], y[j3], u);
-  shear_add<Q>(y[j0], y[j1], y[j2], y[j3], y[i0], y[i1], y[i2], y[i3], w);
-}
-template <bool FULL, int R_>
-__device__ __forceinline__ void apply_round(double2 (&y)[32], const double2& u, const double2& w) {
-  apply_four<FULL, R_, 0>(y, u, w);
-  apply_four<FULL, R_, 4>(y, u, w);
-  apply_four<FULL, R_, 8>(y, u, w);
-  apply_four<FULL, R_, 12>(y, u, w);
-}
-
-// The rotation of jac_rot in the form the row-resident pass wants: c and
-// a = c t^ with t^ = +-2 g / (|d| + sqrt(d^2 + 4 |g|^2)), d = gjj - gii (the
-// smaller-angle root), and 1 / c.  t^ may be off by the hardware estimates'
-// ~1e-8 (see jac_rot); c is refined, so c^2 (1 + |t^|^2) = 1 to rounding.
-struct RotT {
-  double c, ax, ay, ci;
-};
-__device__ inline RotT jac_rot_t(double gii, double gjj, double2 g, double tol, double neg2) {
-  const double h2 = g.x * g.x + g.y * g.y, d = gjj - gii;
-  const bool act = rot_active<double>(gii, gjj, h2, tol, neg2);
-  const double s = fmax(fma(d, d, 4.0 * h2), 1e-300);
-  const double v = fma(s, __builtin_amdgcn_rsq(s), fabs(d));
-  const double k = 2.0 * __builtin_amdgcn_rcp(v);
-  const double t = act ? (d < 0.0 ? -k : k) : 0.0;
-  const double x = fma(t * t, h2, 1.0);
-  // 1/sqrt(x), x in [1, 2]: the estimate's relative error e goes to e^3
-  const double q = __builtin_amdgcn_rsq(x);
-  const double e = fma(-x * q, q, 1.0);
-  RotT r;
-  r.c = fma(q * e, fma(0.375, e, 0.5), q);
-  r.ci = x * r.c;
-  const double ct = r.c * t;
-  r.ax = g.x * ct;
-  r.ay = g.y * ct;
-  return r;
-}
-
-struct SolveLds {
-  double2 G[2][32 * 32];
-  double2 raw[2][2][16];   // (c, 1 / c) and a of a round's 16 rotations, from the solve
-  double2 rot[2][2][16];   // their u and w, from the first row wave
-  double scale[32];
-  unsigned char ti[31][16], tj[31][16];   // the schedule
-  int any_flag, big;
-};
-
-// u and w of the round the solve has just published, lane q < 16 of the first
-// row wave for rotation q = (columns i, j), and the new column scales.
-__device__ __forceinline__ void publish_shears(SolveLds& sm, int buf, int r, int q) {
-  const int i = sm.ti[r][q], j = sm.tj[r][q];
-  const double2 cc = sm.raw[buf][0][q], av = sm.raw[buf][1][q];
-  const double di = sm.scale[i], dj = sm.scale[j];
-  const double fu = cc.y * (dj * rcp_fast(di)), fw = cc.x * (di * rcp_fast(dj));
-  sm.rot[buf][0][q] = make_double2(av.x * fu, av.y * fu);
-  sm.rot[buf][1][q] = make_double2(av.x * fw, av.y * fw);
-  sm.scale[i] = di * cc.x;
-  sm.scale[j] = dj * cc.y;
-}
-
-// Round r's shears on the lane's row.
-template <bool FULL, int R_>
-__device__ __forceinline__ void apply_published(double2 (&y)[32], const SolveLds& sm, int buf, int lane) {
-  const double2 u = sm.rot[buf][0][lane & 15], w = sm.rot[buf][1][lane & 15];
-  apply_round<FULL, R_>(y, u, w);
-}
-
-// In the phase after the solve's round r the first row wave turns
-// its rotations into shears, and every row wave applies round r - 1 (the last
-// round of the previous inner sweep, if any, for r = 0).
-template <bool FULL, int R_>
-__device__ __forceinline__ void row_phase(double2 (&y)[32], SolveLds& sm, int& buf, int lane, bool first_wave,
-                                          bool pending) {
-  constexpr int N = sched_rounds<FULL>(), P = (R_ + N - 1) % N;
-  __syncthreads();
-  if (first_wave && lane < 16) publish_shears(sm, buf, R_, lane);
-  if (R_ > 0 || pending) apply_published<FULL, P>(y, sm, buf ^ 1, lane);
-  buf ^= 1;
-}
-template <bool FULL, int... R_>
-__device__ __forceinline__ void row_phases(double2 (&y)[32], SolveLds& sm, int& buf, int lane, bool first_wave,
-                                           bool pending, std::integer_sequence<int, R_...>) {
-  (row_phase<FULL, R_>(y, sm, buf, lane, first_wave, pending), ...);
-}
-template <int ROWS, bool FULL>
+// Rotate pass with rows in registers (see jacobi_dev.h): waves 0-3 sum the
+// partial Grams and solve, the others hold ROWS rows of Y_p.
+template <int ROWS, class S>
 __global__ __launch_bounds__(JSOLVE + ROWS) void k_jac_rotate_rows(JacArgs<double> a) {
   __shared__ SolveLds sm;
   const int p = blockIdx.x, chunk = blockIdx.y;
   const int bi = rr_block(p, a.round, a.nbp), bj = rr_block(a.nbp - 1 - p, a.round, a.nbp);
   if (pair_skipped(a, bi, bj)) return;
   const int tid = threadIdx.x;
-  const int rounds = sched_rounds<FULL>();
   if (tid >= JSOLVE) {
     const int lane = tid & 63, row = chunk * ROWS + tid - JSOLVE;
-    const bool live = row < a.len, first_wave = tid < JSOLVE + 64;
+    const bool live = row < a.len;
     const int lrow = min(row, a.len - 1);   // unconditional loads: predicated ones would wait one by one
-    constexpr int N = sched_rounds<FULL>();
     double2 y[32];
 #pragma unroll
     for (int c = 0; c < 32; ++c)
@@ -788,11 +458,7 @@ __global__ __launch_bounds__(JSOLVE + ROWS) void k_jac_rotate_rows(JacArgs<doubl
     __syncthreads();                       // Gram summed
     __syncthreads();                       // its pairs checked
     if (!sm.any_flag) return;
-    int buf = 0;
-    for (int in = 0; in < a.max_inner; ++in)
-      row_phases<FULL>(y, sm, buf, lane, first_wave, in > 0, std::make_integer_sequence<int, N>{});
-    __syncthreads();
-    apply_published<FULL, N - 1>(y, sm, buf ^ 1, lane);
+    row_sweeps<S>(y, sm, lane, tid < JSOLVE + 64, a.max_inner);
     if (live) {
 #pragma unroll
       for (int c = 0; c < 32; ++c) {
@@ -822,10 +488,7 @@ __global__ __launch_bounds__(JSOLVE + ROWS) void k_jac_rotate_rows(JacArgs<doubl
     }
     sm.G[0][e] = s;
   }
-  for (int e = tid; e < rounds * 16; e += JSOLVE) {
-    sm.ti[0][e] = (unsigned char)sched_i<FULL>(e & 15, e >> 4);
-    sm.tj[0][e] = (unsigned char)sched_j<FULL>(e & 15, e >> 4);
-  }
+  fill_schedule<S>(sm, tid, JSOLVE);
   if (tid < 32) sm.scale[tid] = 1.0;
   if (tid == 0) {
     sm.any_flag = 0;
@@ -836,7 +499,7 @@ __global__ __launch_bounds__(JSOLVE + ROWS) void k_jac_rotate_rows(JacArgs<doubl
 #pragma unroll
   for (int v = 0; v < 4; ++v) {
     const int e = tid + JSOLVE * v, i = e >> 5, j = e & 31;
-    if (i < j && (FULL || (i < 16 && j >= 16))) {
+    if (i < j && (S::rounds == SchedFull::rounds || (i < 16 && j >= 16))) {
       const double gii = sm.G[0][33 * i].x, gjj = sm.G[0][33 * j].x;
       const double2 g = sm.G[0][e];
       const double h2 = g.x * g.x + g.y * g.y;
@@ -847,44 +510,7 @@ __global__ __launch_bounds__(JSOLVE + ROWS) void k_jac_rotate_rows(JacArgs<doubl
   __syncthreads();
   if (chunk == 0 && tid == 0 && sm.big) *a.big_cos = 1;
   if (!sm.any_flag) return;
-  const double tol_in = 0.5 * a.tol, neg2 = a.neg2;
-  const int pb = tid & 15, pa = (pb + (tid >> 4)) & 15, lane_a = (tid & 48) + pa;
-  int buf = 0;
-  int ib = sm.ti[0][pb], jb = sm.tj[0][pb], ia = sm.ti[0][pa], ja = sm.tj[0][pa];
-  for (int left = a.max_inner * rounds, r = 0; left > 0; --left) {
-    const double2* G = sm.G[buf];
-    double2* H = sm.G[buf ^ 1];
-    const double gii = G[33 * ib].x, gjj = G[33 * jb].x;
-    const double2 gij = G[ib * 32 + jb];
-    double2 g00 = G[ia * 32 + ib], g01 = G[ia * 32 + jb], g10 = G[ja * 32 + ib], g11 = G[ja * 32 + jb];
-    r = r + 1 == rounds ? 0 : r + 1;
-    const int ib1 = sm.ti[r][pb], jb1 = sm.tj[r][pb], ia1 = sm.ti[r][pa], ja1 = sm.tj[r][pa];
-    const RotT t = jac_rot_t(gii, gjj, gij, tol_in, neg2);
-    const RotA<double> rb{t.c, t.ax, t.ay};
-    RotA<double> ra;
-    ra.c = __shfl(rb.c, lane_a);
-    ra.ax = __shfl(rb.ax, lane_a);
-    ra.ay = __shfl(rb.ay, lane_a);
-    if (tid < 16) {   // pa == pb: the round's rotations
-      sm.raw[buf][0][pb] = make_double2(t.c, t.ci);
-      sm.raw[buf][1][pb] = make_double2(t.ax, t.ay);
-    }
-    rot_right(rb, g00, g01);
-    rot_right(rb, g10, g11);
-    rot_left(ra, g00, g10);
-    rot_left(ra, g01, g11);
-    H[ia * 32 + ib] = g00;
-    H[ia * 32 + jb] = g01;
-    H[ja * 32 + ib] = g10;
-    H[ja * 32 + jb] = g11;
-    ib = ib1;
-    jb = jb1;
-    ia = ia1;
-    ja = ja1;
-    buf ^= 1;
-    __syncthreads();
-  }
-  __syncthreads();   // the row waves' last phase
+  solve_sweeps<S>(sm, 0, tid, 0.5 * a.tol, a.neg2, a.max_inner);
   if (chunk == 0 && tid == 0) {
     a.rot_cur[bi] = 1;
     a.rot_cur[bj] = 1;
@@ -1016,9 +642,9 @@ static void launch_rotate_rows_n(const JacobiPlan& pl, const JacArgs<double>& a,
                                  hipEvent_t stop) {
   const dim3 grid(pl.n_pairs, ceil_div(pl.len, ROWS)), block(JSOLVE + ROWS);
   if (a.round == 0)
-    hipExtLaunchKernelGGL((k_jac_rotate_rows<ROWS, true>), grid, block, 0, stream, start, stop, 0, a);
+    hipExtLaunchKernelGGL((k_jac_rotate_rows<ROWS, SchedFull>), grid, block, 0, stream, start, stop, 0, a);
   else
-    hipExtLaunchKernelGGL((k_jac_rotate_rows<ROWS, false>), grid, block, 0, stream, start, stop, 0, a);
+    hipExtLaunchKernelGGL((k_jac_rotate_rows<ROWS, SchedCross>), grid, block, 0, stream, start, stop, 0, a);
 }
 static void launch_rotate_rows(const JacobiPlan& pl, const JacArgs<double>& a, hipStream_t stream, hipEvent_t start,
                                hipEvent_t stop) {
@@ -1076,7 +702,7 @@ static void launch_sweep(const JacobiPlan& pl, JacArgs<R> a, hipStream_t stream,
 // 53-qubit chi 1024 build this skips 1,016 of 1,278 such verification
 // sweeps, and in none of the skipped cases did the sweep rotate anything
 // when run.
-static double qstop_factor() {
+static double jacobi_qstop() {
   static const double v = [] {
     const char* e = std::getenv("RCS_JACOBI_QSTOP");
     const double f = e ? std::atof(e) : 100.0;
@@ -1084,6 +710,20 @@ static double qstop_factor() {
   }();
   return v;
 }
+
+static JacobiTol jacobi_tol_u(double u, int len, double tol) {
+  JacobiTol t;
+  t.tol = tol > 0.0 ? tol : 16.0 * u * std::sqrt((double)std::max(len, 16));
+  // columns shorter than delta ||X||_F (delta = 8 u sqrt(len)) are numerically
+  // zero: below the absolute accuracy of any SVD in this precision, and they
+  // must not be required to be mutually orthogonal (a wide matrix has more
+  // columns than its rank)
+  const double delta = 8.0 * u * std::sqrt((double)len);
+  t.delta2 = delta * delta;
+  t.qtol = jacobi_qstop() > 0.0 ? t.tol / jacobi_qstop() : 0.0;
+  return t;
+}
+JacobiTol jacobi_tol(int len, double tol) { return jacobi_tol_u(JT<double>::u, len, tol); }
 
 static bool use_graphs() {
   static const bool v = [] {
@@ -1153,15 +793,10 @@ static int jacobi_run_t(const JacobiPlan& pl, typename JT<R>::C* x, void* work, 
   a.rot_cur = a.rot_prev + pl.nbp;
   a.rot_count = rot_count_dev;
   a.big_cos = rot_count_dev + 1;
-  const double u = JT<R>::u;
-  a.tol = (R)(tol > 0.0 ? tol : 16.0 * u * std::sqrt((double)std::max(pl.len, 16)));
-  // columns shorter than delta ||X||_F (delta = 8 u sqrt(len)) are numerically
-  // zero: below the absolute accuracy of any SVD in this precision, and they
-  // must not be required to be mutually orthogonal (a wide matrix has more
-  // columns than its rank)
-  const double delta = 8.0 * u * std::sqrt((double)pl.len);
-  a.neg2 = (R)(delta * delta * std::max(fro2, 1e-300));
-  a.qtol = (R)(qstop_factor() > 0.0 ? (double)a.tol / qstop_factor() : 0.0);
+  const JacobiTol t = jacobi_tol_u(JT<R>::u, pl.len, tol);
+  a.tol = (R)t.tol;
+  a.neg2 = (R)(t.delta2 * std::max(fro2, 1e-300));
+  a.qtol = (R)(jacobi_qstop() > 0.0 ? (double)a.tol / jacobi_qstop() : 0.0);
   a.max_inner = pl.inner;
   bool graphs = false;
   if constexpr (std::is_same<R, double>::value) graphs = use_graphs() && pl.nbp > 4;
@@ -1183,7 +818,7 @@ static int jacobi_run_t(const JacobiPlan& pl, typename JT<R>::C* x, void* work, 
     if (*rot_count_host == 0) return sweep;
     // quadratic convergence: after a sweep whose meetings all entered with
     // squared cosines below tol / f, the next one starts below ~tol^2 / f^2
-    if (qstop_factor() > 0.0 && !big) return sweep;
+    if (jacobi_qstop() > 0.0 && !big) return sweep;
   }
   fail(RCS_ERR_NUMERIC, "one-sided Jacobi SVD did not converge");
 }
