@@ -439,7 +439,7 @@ __global__ __launch_bounds__(ROT_THREADS) void k_jac_rotate(JacArgs<R> a) {
 }
 
 // Rotate pass with rows in registers (see jacobi_dev.h): waves 0-3 sum the
-// partial Grams and solve, the others hold ROWS rows of Y_p.
+// partial Grams, solve and publish, the others hold ROWS rows of Y_p.
 template <int ROWS, class S>
 __global__ __launch_bounds__(JSOLVE + ROWS) void k_jac_rotate_rows(JacArgs<double> a) {
   __shared__ SolveLds sm;
@@ -458,7 +458,7 @@ __global__ __launch_bounds__(JSOLVE + ROWS) void k_jac_rotate_rows(JacArgs<doubl
     __syncthreads();                       // Gram summed
     __syncthreads();                       // its pairs checked
     if (!sm.any_flag) return;
-    row_sweeps<S>(y, sm, lane, tid < JSOLVE + 64, a.max_inner);
+    row_sweeps<S>(y, sm, lane, a.max_inner);
     if (live) {
 #pragma unroll
       for (int c = 0; c < 32; ++c) {
@@ -486,22 +486,24 @@ __global__ __launch_bounds__(JSOLVE + ROWS) void k_jac_rotate_rows(JacArgs<doubl
         s.y += t[u].y;
       }
     }
-    sm.G[0][e] = s;
+    sm.G[e] = s;
   }
   fill_schedule<S>(sm, tid, JSOLVE);
+  const Moves<S> moves = block_moves<S>(tid);
   if (tid < 32) sm.scale[tid] = 1.0;
   if (tid == 0) {
     sm.any_flag = 0;
     sm.big = 0;
   }
   __syncthreads();
+  load_blocks<S>(sm, tid);
   // only the pairs this meeting's schedule rotates decide whether it acts
 #pragma unroll
   for (int v = 0; v < 4; ++v) {
     const int e = tid + JSOLVE * v, i = e >> 5, j = e & 31;
     if (i < j && (S::rounds == SchedFull::rounds || (i < 16 && j >= 16))) {
-      const double gii = sm.G[0][33 * i].x, gjj = sm.G[0][33 * j].x;
-      const double2 g = sm.G[0][e];
+      const double gii = sm.G[33 * i].x, gjj = sm.G[33 * j].x;
+      const double2 g = sm.G[e];
       const double h2 = g.x * g.x + g.y * g.y;
       if (rot_active<double>(gii, gjj, h2, a.tol, a.neg2)) sm.any_flag = 1;
       if (gii > a.neg2 && gjj > a.neg2 && h2 > a.qtol * gii * gjj) sm.big = 1;
@@ -510,7 +512,7 @@ __global__ __launch_bounds__(JSOLVE + ROWS) void k_jac_rotate_rows(JacArgs<doubl
   __syncthreads();
   if (chunk == 0 && tid == 0 && sm.big) *a.big_cos = 1;
   if (!sm.any_flag) return;
-  solve_sweeps<S>(sm, 0, tid, 0.5 * a.tol, a.neg2, a.max_inner);
+  solve_sweeps<S>(sm, moves, tid, 0.5 * a.tol, a.neg2, a.max_inner);
   if (chunk == 0 && tid == 0) {
     a.rot_cur[bi] = 1;
     a.rot_cur[bj] = 1;

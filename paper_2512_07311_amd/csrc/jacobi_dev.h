@@ -69,7 +69,7 @@ struct Rot {
 };
 template <typename R>
 __device__ inline bool rot_active(R gii, R gjj, R h2, R tol, R neg2) {
-  return gii > neg2 && gjj > neg2 && h2 > JT<R>::tiny && h2 > tol * tol * gii * gjj;
+  return (gii > neg2) & (gjj > neg2) & (h2 > JT<R>::tiny) & (h2 > tol * tol * gii * gjj);
 }
 __device__ inline Rot<double> jac_rot(double gii, double gjj, double2 g, double tol, double neg2) {
   const double h2 = g.x * g.x + g.y * g.y;
@@ -144,10 +144,13 @@ __device__ inline void rot_left(const RotA<R>& r, C& xi, C& xj) {
 // forming the unitary and multiplying by it costs twice the flops of
 // applying the rotations themselves, at the same fp64 rate (the vector and
 // the matrix units both reach 78.6 TFLOP/s).  So the workgroup splits:
-//   waves 0-3   run the solve, one barrier per round: thread (k, pb) holds
-//               the block of pair pa = pb + k mod 16 against pair pb, computes
-//               pair pb's rotation itself, takes pa's from the lane that has
-//               it, and writes its four entries to the other Gram buffer;
+//   waves 0-2   run the solve, one barrier per round: thread (k, b) holds the
+//               block of pair a = b + k mod 16 against pair b, computes pair
+//               b's rotation itself, takes pair a's from the lane that has
+//               it, and moves its four entries to where the next round needs
+//               them;
+//   wave 3      computes the same 16 rotations, one a lane, and publishes
+//               them in the form the row waves want;
 //   waves 4...  hold one row of Y_p per lane in registers (32 columns, loaded
 //               while the partial Grams are summed) and apply each round's
 //               rotations one round behind the solve.
@@ -161,41 +164,68 @@ __device__ inline void rot_left(const RotA<R>& r, C& xi, C& xj) {
 // broadcasts it (DPP row_newbcast, the one DPP form 64-bit operations have):
 // 5.6 cycles per FMA and wave, against 7.2 with separate moves (plain: 4.9).
 //
-// Bound: below about 1024 columns the chain of rounds (0.6 us each, the
-// solve's latency), at 2048 the fp64 vector rate (two row waves and one solver
+// Bound: below about 1024 columns the chain of rounds (0.48 us each: reads
+// 200 cycles, rotation 210, exchange 140, 4 x 12 fp64 operations 300, writes
+// and barrier 300), at 2048 the fp64 vector rate (two row waves and one solver
 // wave per SIMD) and the read and write of the matrix (64 MB, 25 us on its
-// own).  Measured against the LDS solve with a V product on the matrix cores
-// (still the 32-column and fp32 form), per launch: 128 x 128 21.5 -> 15.5 us,
-// 1024 x 1024 23 -> 20.5 us, 2048 x 2048 43 -> 33 us inside an SVD.  Tried and
-// slower: the whole solve before any row work (41 us at 2048), a rolled row
-// loop with register rotation, the shears published by a solver wave.
-constexpr int JSOLVE = 256;   // solver threads
+// own).  Measured, per launch at 64 x 64 / 512 x 512: the LDS solve with a V
+// product on the matrix cores (still the 32-column and fp32 form) 21.5 / 22
+// us, this scheme 12.1 / 13.7 us; 2048 x 2048 43 -> 32 us inside an SVD.  Its
+// first form, a full Gram of 256 blocks in four waves, places computed each
+// round and the shears from a row wave, took 15.2 / 16.7 us: index arithmetic
+// between barriers cost 310 cycles a round.  Tried and slower: the whole
+// solve before any row work (41 us at 2048), a rolled row loop with register
+// rotation.
+constexpr int JSOLVE = 256;   // threads of waves 0-3
 
-// Inner schedules: pair q of round r is columns i(q, r) < j(q, r).
+// Inner schedules: pair q of round r is columns i(q, r) and j(q, r).
 //   SchedRR<N>  : round robin over N columns, N/2 pairs, N - 1 rounds;
 //   SchedCross  : two 16-column blocks against each other, 16 rounds;
 //   SchedFull   : the round robin inside both blocks at once, then the cross
 //                 rounds: every pair of the 32 columns once.
+// Slot s of a round is pair s's first column, slot pairs + s its second one.
+// Between rounds the columns move by a fixed permutation of the slots, next(),
+// per segment of rounds; after the last segment they are back where they began.
 template <int N>
 struct SchedRR {
-  static constexpr int cols = N, pairs = N / 2, rounds = N - 1;
-  __host__ __device__ static constexpr int u(int q, int r) { return q == 0 ? 0 : ((q - 1 + r) % (N - 1)) + 1; }
-  __host__ __device__ static constexpr int v(int q, int r) { return ((N - 2 - q + r) % (N - 1)) + 1; }
-  __host__ __device__ static constexpr int i(int q, int r) { return u(q, r) < v(q, r) ? u(q, r) : v(q, r); }
-  __host__ __device__ static constexpr int j(int q, int r) { return u(q, r) < v(q, r) ? v(q, r) : u(q, r); }
+  static constexpr int cols = N, pairs = N / 2, rounds = N - 1, segments = 1;
+  __host__ __device__ static constexpr int i(int q, int r) { return q == 0 ? 0 : ((q - 1 + r) % (N - 1)) + 1; }
+  __host__ __device__ static constexpr int j(int q, int r) { return ((N - 2 - q + r) % (N - 1)) + 1; }
+  __host__ __device__ static constexpr int segment(int) { return rounds; }
+  // column 0 stays; column ((x + r) mod (N - 1)) + 1 is at place x of a ring
+  __host__ __device__ static constexpr int ring(int s) { return s < pairs ? s - 1 : N - 2 - (s - pairs); }
+  __host__ __device__ static constexpr int unring(int x) { return x <= pairs - 2 ? x + 1 : pairs + N - 2 - x; }
+  __host__ __device__ static constexpr int next(int s, int) {
+    return s == 0 ? 0 : unring(ring(s) == 0 ? N - 2 : ring(s) - 1);
+  }
 };
 struct SchedCross {
-  static constexpr int cols = 32, pairs = 16, rounds = 16;
+  static constexpr int cols = 32, pairs = 16, rounds = 16, segments = 1;
   __host__ __device__ static constexpr int i(int q, int) { return q; }
   __host__ __device__ static constexpr int j(int q, int r) { return 16 + ((q + r) & 15); }
+  __host__ __device__ static constexpr int segment(int) { return rounds; }
+  __host__ __device__ static constexpr int next(int s, int) { return s < 16 ? s : 16 + ((s - 1) & 15); }
 };
 struct SchedFull {
-  static constexpr int cols = 32, pairs = 16, rounds = 31;
-  __host__ __device__ static constexpr int i(int q, int r) {
-    return r < 15 ? (q & 8) * 2 + SchedRR<16>::i(q & 7, r) : q;
-  }
+  using RR = SchedRR<16>;
+  static constexpr int cols = 32, pairs = 16, rounds = 31, segments = 4;
+  __host__ __device__ static constexpr int i(int q, int r) { return r < 15 ? (q & 8) * 2 + RR::i(q & 7, r) : q; }
   __host__ __device__ static constexpr int j(int q, int r) {
-    return r < 15 ? (q & 8) * 2 + SchedRR<16>::j(q & 7, r) : SchedCross::j(q, r - 15);
+    return r < 15 ? (q & 8) * 2 + RR::j(q & 7, r) : SchedCross::j(q, r - 15);
+  }
+  // 14 steps of the round robins, one from their end to the cross rounds, 15
+  // steps of these, one back
+  __host__ __device__ static constexpr int segment(int g) { return g == 0 ? 14 : g == 2 ? 15 : 1; }
+  __host__ __device__ static constexpr int next(int s, int g) {
+    if (g < 2) {
+      const int half = s & 8, t = RR::next((s & 7) | (s & 16) >> 1, 0);   // slot within the block's round robin
+      if (g == 0) return half | (t & 7) | (t & 8) << 1;
+      return half * 2 + (t < 8 ? RR::i(t, 0) : RR::j(t - 8, 0));           // cross slots are the columns
+    }
+    const int c = SchedCross::next(s, 0);
+    if (g == 2) return c;
+    const int t = (c & 15) == 0 ? 0 : RR::unring((c & 15) - 1);
+    return (c & 16) >> 1 | (t & 7) | (t & 8) << 1;
   }
 };
 
@@ -275,53 +305,43 @@ __device__ __forceinline__ void apply_round(double2 (&y)[S::cols], const double2
 }
 
 // The rotation of jac_rot in the form the row-resident pass wants: c and
-// a = c t^ with t^ = +-2 g / (|d| + sqrt(d^2 + 4 |g|^2)), d = gjj - gii (the
-// smaller-angle root), and 1 / c.  t^ may be off by the hardware estimates'
-// ~1e-8 (see jac_rot); c is refined, so c^2 (1 + |t^|^2) = 1 to rounding.
+// a = c t with t = +-g / (|d| + sqrt(d^2 + |g|^2)), d = (gjj - gii) / 2 (the
+// smaller-angle root), and 1 / c.  t may be off by the hardware estimates'
+// ~1e-8 (see jac_rot); c is refined, so c^2 (1 + |t|^2) = 1 to rounding.
+// The dependent chain is what a round waits
+// for: the guard against 0 sits in |g|^2's first product, an inactive pair's
+// infinity in the addend of the denominator, the sign on g, and the test is
+// one comparison (a conjunction of four goes through the scalar unit).
 struct RotT {
   double c, ax, ay, ci;
 };
 __device__ inline RotT jac_rot_t(double gii, double gjj, double2 g, double tol, double neg2) {
-  const double h2 = g.x * g.x + g.y * g.y, d = gjj - gii;
-  const bool act = rot_active<double>(gii, gjj, h2, tol, neg2);
-  const double s = fmax(fma(d, d, 4.0 * h2), 1e-300);
-  const double v = fma(s, __builtin_amdgcn_rsq(s), fabs(d));
-  const double k = 2.0 * __builtin_amdgcn_rcp(v);
-  const double t = act ? (d < 0.0 ? -k : k) : 0.0;
-  const double x = fma(t * t, h2, 1.0);
+  const double h2 = fma(g.x, g.x, fma(g.y, g.y, 1e-300)), d = 0.5 * (gjj - gii);
+  const double lim = (gii < gjj ? gii : gjj) > neg2 ? tol * tol * (gii * gjj) : __builtin_inf();
+  const double m = h2 > fmax(lim, JT<double>::tiny) ? fabs(d) : __builtin_inf();
+  const double s = fma(d, d, h2);
+  const double k = __builtin_amdgcn_rcp(fma(s, __builtin_amdgcn_rsq(s), m));
+  const double x = fma(k * k, h2, 1.0);
   // 1/sqrt(x), x in [1, 2]: the estimate's relative error e goes to e^3
   const double q = __builtin_amdgcn_rsq(x);
   const double e = fma(-x * q, q, 1.0);
   RotT r;
   r.c = fma(q * e, fma(0.375, e, 0.5), q);
   r.ci = x * r.c;
-  const double ct = r.c * t;
-  r.ax = g.x * ct;
-  r.ay = g.y * ct;
+  const double ct = r.c * k;
+  r.ax = (d < 0.0 ? -g.x : g.x) * ct;
+  r.ay = (d < 0.0 ? -g.y : g.y) * ct;
   return r;
 }
 
 struct SolveLds {
-  double2 G[2][32 * 32];
-  double2 raw[2][2][16];   // (c, 1 / c) and a of a round's 16 rotations, from the solve
-  double2 rot[2][2][16];   // their u and w, from the first row wave
+  double2 G[32 * 32];      // the Gram, all of it
+  double2 B[2][4][192];    // the solve's copy: entry (side a, side b) of a thread's pair block
+  double2 rot[2][2][16];   // u and w of a round's rotations, from the publishing wave
   double scale[32];
-  unsigned char ti[31][16], tj[31][16];   // the schedule
+  unsigned short pair[31][16];   // the schedule: i | j << 8
   int any_flag, big;
 };
-
-// u and w of the round the solve has just published, lane q < 16 of the first
-// row wave for rotation q = (columns i, j), and the new column scales.
-__device__ __forceinline__ void publish_shears(SolveLds& sm, int buf, int r, int q) {
-  const int i = sm.ti[r][q], j = sm.tj[r][q];
-  const double2 cc = sm.raw[buf][0][q], av = sm.raw[buf][1][q];
-  const double di = sm.scale[i], dj = sm.scale[j];
-  const double fu = cc.y * (dj * rcp_fast(di)), fw = cc.x * (di * rcp_fast(dj));
-  sm.rot[buf][0][q] = make_double2(av.x * fu, av.y * fu);
-  sm.rot[buf][1][q] = make_double2(av.x * fw, av.y * fw);
-  sm.scale[i] = di * cc.x;
-  sm.scale[j] = dj * cc.y;
-}
 
 // Round r's shears on the lane's row.
 template <class S, int R_>
@@ -330,31 +350,28 @@ __device__ __forceinline__ void apply_published(double2 (&y)[S::cols], const Sol
   apply_round<S, R_>(y, u, w);
 }
 
-// In the phase after the solve's round r the first row wave turns its
-// rotations into shears, and every row wave applies round r - 1 (the last
+// While the solve is at round r, every row wave applies round r - 1 (the last
 // round of the previous inner sweep, if any, for r = 0).
 template <class S, int R_>
-__device__ __forceinline__ void row_phase(double2 (&y)[S::cols], SolveLds& sm, int& buf, int lane, bool first_wave,
+__device__ __forceinline__ void row_phase(double2 (&y)[S::cols], const SolveLds& sm, int& buf, int lane,
                                           bool pending) {
   constexpr int P = (R_ + S::rounds - 1) % S::rounds;
-  __syncthreads();
-  if (first_wave && lane < S::pairs) publish_shears(sm, buf, R_, lane);
   if (R_ > 0 || pending) apply_published<S, P>(y, sm, buf ^ 1, lane);
+  __syncthreads();
   buf ^= 1;
 }
 template <class S, int... R_>
-__device__ __forceinline__ void row_phases(double2 (&y)[S::cols], SolveLds& sm, int& buf, int lane, bool first_wave,
-                                           bool pending, std::integer_sequence<int, R_...>) {
-  (row_phase<S, R_>(y, sm, buf, lane, first_wave, pending), ...);
+__device__ __forceinline__ void row_phases(double2 (&y)[S::cols], const SolveLds& sm, int& buf, int lane, bool pending,
+                                           std::integer_sequence<int, R_...>) {
+  (row_phase<S, R_>(y, sm, buf, lane, pending), ...);
 }
-// The row waves' side of `inner` sweeps (inner * rounds + 1 barriers); the
-// rows are left with their column scales in sm.scale.
+// The row waves' side of `inner` sweeps (inner * rounds barriers); the rows
+// are left with their column scales in sm.scale.
 template <class S>
-__device__ __forceinline__ void row_sweeps(double2 (&y)[S::cols], SolveLds& sm, int lane, bool first_wave, int inner) {
+__device__ __forceinline__ void row_sweeps(double2 (&y)[S::cols], const SolveLds& sm, int lane, int inner) {
   int buf = 0;
   for (int in = 0; in < inner; ++in)
-    row_phases<S>(y, sm, buf, lane, first_wave, in > 0, std::make_integer_sequence<int, S::rounds>{});
-  __syncthreads();
+    row_phases<S>(y, sm, buf, lane, in > 0, std::make_integer_sequence<int, S::rounds>{});
   apply_published<S, S::rounds - 1>(y, sm, buf ^ 1, lane);
 }
 
@@ -363,59 +380,147 @@ template <class S>
 __device__ inline void fill_schedule(SolveLds& sm, int tid, int nthreads) {
   for (int e = tid; e < S::rounds * 16; e += nthreads) {
     const int q = e & 15, r = e >> 4;
-    if (q < S::pairs) {
-      sm.ti[r][q] = (unsigned char)S::i(q, r);
-      sm.tj[r][q] = (unsigned char)S::j(q, r);
-    }
+    if (q < S::pairs) sm.pair[r][q] = (unsigned short)(S::i(q, r) | S::j(q, r) << 8);
   }
 }
 
-// The solver waves' side (the first JSOLVE threads): `inner` sweeps of
-// two-sided rotations on the Gram in sm.G[gbuf], publishing each round's.
+// The solve.  Thread (k, b) = tid = k P + b, k <= P / 2, has the 2 x 2 block of
+// pair a = b + k mod P against pair b: the Gram is Hermitian, so each block
+// of two pairs is kept once, at its thread's own place.  As the columns move
+// between rounds by a fixed permutation of the slots, so do the entries
+// between the threads' places: a thread reads its block from one place and
+// writes its entries to four others in every round, with no index arithmetic
+// between barriers (which cost more there than the rotation itself).
 template <class S>
-__device__ inline void solve_sweeps(SolveLds& sm, int gbuf, int tid, double tol_in, double neg2, int inner) {
+struct Blocks {
+  static constexpr int P = S::pairs, n = P * P / 2 + P / 2, waves = (P * P / 2 + P + 63) / 64;
+};
+// Place of entry (slot sa, slot sb), a byte offset into B[.], with the sign
+// bit set where the place holds its conjugate.
+template <class S>
+__device__ inline unsigned block_entry(int sa, int sb) {
   constexpr int P = S::pairs;
-  const bool works = tid < P * P;
-  const int pb = tid & (P - 1), pa = (pb + tid / P) & (P - 1), lane_a = (tid & 63 & ~(P - 1)) + pa;
-  int buf = 0;
-  int ib = sm.ti[0][pb], jb = sm.tj[0][pb], ia = sm.ti[0][pa], ja = sm.tj[0][pa];
-  for (int left = inner * S::rounds, r = 0; left > 0; --left) {
-    r = r + 1 == S::rounds ? 0 : r + 1;
-    if (works) {
-      const double2* G = sm.G[gbuf];
-      double2* H = sm.G[gbuf ^ 1];
-      const double gii = G[33 * ib].x, gjj = G[33 * jb].x;
-      const double2 gij = G[ib * 32 + jb];
-      double2 g00 = G[ia * 32 + ib], g01 = G[ia * 32 + jb], g10 = G[ja * 32 + ib], g11 = G[ja * 32 + jb];
-      const int ib1 = sm.ti[r][pb], jb1 = sm.tj[r][pb], ia1 = sm.ti[r][pa], ja1 = sm.tj[r][pa];
-      const RotT t = jac_rot_t(gii, gjj, gij, tol_in, neg2);
-      const RotA<double> rb{t.c, t.ax, t.ay};
-      RotA<double> ra;
-      ra.c = __shfl(rb.c, lane_a);
-      ra.ax = __shfl(rb.ax, lane_a);
-      ra.ay = __shfl(rb.ay, lane_a);
-      if (tid < P) {   // pa == pb: the round's rotations
-        sm.raw[buf][0][pb] = make_double2(t.c, t.ci);
-        sm.raw[buf][1][pb] = make_double2(t.ax, t.ay);
-      }
-      rot_right(rb, g00, g01);
-      rot_right(rb, g10, g11);
-      rot_left(ra, g00, g10);
-      rot_left(ra, g01, g11);
-      H[ia * 32 + ib] = g00;
-      H[ia * 32 + jb] = g01;
-      H[ja * 32 + ib] = g10;
-      H[ja * 32 + jb] = g11;
-      ib = ib1;
-      jb = jb1;
-      ia = ia1;
-      ja = ja1;
-    }
-    buf ^= 1;
-    gbuf ^= 1;
-    __syncthreads();
+  const int qa = sa & (P - 1), qb = sb & (P - 1), ha = sa / P, hb = sb / P;
+  const int k = (qa - qb) & (P - 1);
+  const bool swap = k > P / 2 || (k == P / 2 && qb >= P / 2) || (k == 0 && ha > hb);
+  const int at = swap ? ((P - k) & (P - 1)) * P + qa : k * P + qb;
+  const int type = swap ? 2 * hb + ha : 2 * ha + hb;
+  return (unsigned)((type * 192 + at) * (int)sizeof(double2)) | (swap ? 0x80000000u : 0u);
+}
+// Thread tid's block from the Gram (all solver threads; a barrier follows).
+template <class S>
+__device__ inline void load_blocks(SolveLds& sm, int tid) {
+  constexpr int P = S::pairs;
+  if (tid >= Blocks<S>::waves * 64) return;
+  const int qb = tid & (P - 1), qa = (qb + tid / P) & (P - 1);
+#pragma unroll
+  for (int t = 0; t < 4; ++t) {
+    const int row = t >= 2 ? S::j(qa, 0) : S::i(qa, 0), col = t & 1 ? S::j(qb, 0) : S::i(qb, 0);
+    sm.B[0][t][tid] = sm.G[row * 32 + col];
   }
-  __syncthreads();   // the row waves' last phase
+}
+__device__ __forceinline__ void block_write(SolveLds& sm, int buf, unsigned e, double2 v) {
+  v.y = __hiloint2double(__double2hiint(v.y) ^ (int)(e & 0x80000000u), __double2loint(v.y));
+  *reinterpret_cast<double2*>(reinterpret_cast<char*>(&sm.B[0][0][0]) +
+                              (buf * (int)sizeof(sm.B[0]) + (int)(e & 0x7fffu))) = v;
+}
+
+// Where thread tid's entries go, by segment.  The last wave's spare lanes work
+// on places of their own.
+template <class S>
+struct Moves {
+  unsigned e[S::segments][4];
+};
+template <class S>
+__device__ inline Moves<S> block_moves(int tid) {
+  constexpr int P = S::pairs;
+  const int qb = tid & (P - 1), qa = (qb + tid / P) & (P - 1);
+  Moves<S> m;
+#pragma unroll
+  for (int g = 0; g < S::segments; ++g) {
+    const int ia = S::next(qa, g), ja = S::next(qa + P, g), ib = S::next(qb, g), jb = S::next(qb + P, g);
+    const int to[4][2] = {{ia, ib}, {ia, jb}, {ja, ib}, {ja, jb}};
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+      m.e[g][t] = tid < Blocks<S>::n ? block_entry<S>(to[t][0], to[t][1])
+                                     : (unsigned)((t * 192 + min(tid, 191)) * (int)sizeof(double2));
+  }
+  return m;
+}
+
+// The publishing wave's side: it takes the same rotations from the blocks as
+// the solve does, one a lane, and turns them into shears with the column
+// scales, which the solve's chain does not wait for.
+template <class S>
+__device__ inline void publish_sweeps(SolveLds& sm, int lane, double tol_in, double neg2, int inner) {
+  constexpr int P = S::pairs;
+  const int q = lane & (P - 1);
+  int buf = 0;
+  for (int left = inner * S::rounds, r = 0; left > 0; --left) {
+    const double gii = sm.B[buf][0][q].x, gjj = sm.B[buf][3][q].x;
+    const double2 gij = sm.B[buf][1][q];
+    const int pair = sm.pair[r][q], i = pair & 31, j = pair >> 8;
+    const double di = sm.scale[i], dj = sm.scale[j];
+    const double qi = dj * rcp_fast(di), qj = di * rcp_fast(dj);
+    const RotT t = jac_rot_t(gii, gjj, gij, tol_in, neg2);
+    if (lane < P) {
+      const double fu = t.ci * qi, fw = t.c * qj;
+      sm.rot[buf][0][q] = make_double2(t.ax * fu, t.ay * fu);
+      sm.rot[buf][1][q] = make_double2(t.ax * fw, t.ay * fw);
+      sm.scale[i] = di * t.c;
+      sm.scale[j] = dj * t.ci;
+    }
+    __syncthreads();
+    buf ^= 1;
+    r = r + 1 == S::rounds ? 0 : r + 1;
+  }
+}
+
+// The first JSOLVE threads' side: `inner` sweeps of two-sided rotations on
+// the blocks in B[0] by waves 0-2, publishing by wave 3.
+template <class S>
+__device__ inline void solve_sweeps(SolveLds& sm, const Moves<S>& mv, int tid, double tol_in, double neg2,
+                                    int inner) {
+  constexpr int P = S::pairs;
+  const int lane = tid & 63;
+  if (tid >= JSOLVE - 64) {
+    publish_sweeps<S>(sm, lane, tol_in, neg2, inner);
+    return;
+  }
+  if (tid >= Blocks<S>::waves * 64) {   // whole waves with no block
+    for (int left = inner * S::rounds; left > 0; --left) __syncthreads();
+    return;
+  }
+  const int qb = tid & (P - 1), qa = (qb + tid / P) & (P - 1), lane_a = (lane & ~(P - 1)) + qa;
+  int buf = 0;
+  for (int in = 0; in < inner; ++in) {
+#pragma unroll
+    for (int g = 0; g < S::segments; ++g) {
+      for (int left = S::segment(g); left > 0; --left) {
+        const double gii = sm.B[buf][0][qb].x, gjj = sm.B[buf][3][qb].x;   // thread (0, b)'s block
+        const double2 gij = sm.B[buf][1][qb];
+        double2 g00 = sm.B[buf][0][tid], g01 = sm.B[buf][1][tid], g10 = sm.B[buf][2][tid], g11 = sm.B[buf][3][tid];
+        __builtin_amdgcn_sched_barrier(0);   // all reads on their way before the rotation's chain
+        const RotT t = jac_rot_t(gii, gjj, gij, tol_in, neg2);
+        const RotA<double> rb{t.c, t.ax, t.ay};
+        RotA<double> ra;
+        ra.c = __shfl(rb.c, lane_a);
+        ra.ax = __shfl(rb.ax, lane_a);
+        ra.ay = __shfl(rb.ay, lane_a);
+        if (tid < P) g10 = make_double2(gij.x, -gij.y);   // not kept
+        rot_right(rb, g00, g01);
+        rot_right(rb, g10, g11);
+        rot_left(ra, g00, g10);
+        rot_left(ra, g01, g11);
+        buf ^= 1;
+        block_write(sm, buf, mv.e[g][2], g10);
+        block_write(sm, buf, mv.e[g][0], g00);
+        block_write(sm, buf, mv.e[g][1], g01);   // k = 0: to g10's place
+        block_write(sm, buf, mv.e[g][3], g11);
+        __syncthreads();
+      }
+    }
+  }
 }
 
 }  // namespace rcs

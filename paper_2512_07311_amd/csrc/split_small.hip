@@ -6,13 +6,13 @@
 // host per sweep cost far more than its arithmetic.  Here rows 0-127 sit in
 // the registers of waves 4 and 5 throughout (one row per lane), the Gram is
 // taken from an LDS copy of them on the matrix cores (3.4 us at 128 x 32),
-// and waves 0-3 solve it; jacobi_dev.h has the scheme.  One sweep is a round
-// robin over all 8, 16 or 32 columns, so the Gram is fresh once a sweep, as
-// in the general path with one column block.
-// Bound: the chain of rounds (0.7 us each, 31 a sweep at 32 columns).
+// and waves 0-3 solve it and publish; jacobi_dev.h has the scheme.  One sweep
+// is a round robin over all 8, 16 or 32 columns, so the Gram is fresh once a
+// sweep, as in the general path with one column block.
+// Bound: the chain of rounds (0.48 us each, 31 a sweep at 32 columns).
 // Measured, kernel time at 8 / 16 / 32 columns in an exact 12-qubit build:
-// 20 / 67 / 220 us, where the general split's 35 or so launches and its wait
-// per sweep took about 380 us; the whole build 48.0 -> 25.7 ms.
+// 19 / 58 / 180 us, where the general split's 35 or so launches and its wait
+// per sweep took about 380 us; the whole build 48.0 -> 23.7 ms.
 //
 // Range: what one workgroup's registers hold, 128 rows of 32 columns.  That
 // covers every split with a neighbouring bond of at most 16; a 64-column
@@ -48,7 +48,7 @@ struct SmallLds {
 
 // G = Y^H Y over the first len rows (those from len on are zero), by all waves.
 template <int N>
-__device__ inline void small_gram(SmallLds<N>& sm, int gbuf, int len, int tid) {
+__device__ inline void small_gram(SmallLds<N>& sm, int len, int tid) {
   using D = SmallDims<N>;
   using T = JT<double>;
   const int lane = tid & 63, w = tid >> 6;
@@ -73,7 +73,7 @@ __device__ inline void small_gram(SmallLds<N>& sm, int gbuf, int len, int tid) {
     }
   }
   __syncthreads();
-  double2* G = sm.sv.G[gbuf];
+  double2* G = sm.sv.G;
   for (int e = tid; e < D::tiles * 256; e += SS_THREADS) {
     const int u = e >> 8, r = (e >> 6) & 3, l = e & 63;
     double re = 0.0, im = 0.0;
@@ -89,7 +89,7 @@ __device__ inline void small_gram(SmallLds<N>& sm, int gbuf, int len, int tid) {
   __syncthreads();
 }
 
-// Y <- Y H, H (cols x cols) in G[0]; a wave's 16-row tiles depend only on
+// Y <- Y H, H (cols x cols) in G; a wave's 16-row tiles depend only on
 // their own rows, so the product is in place.
 template <int N>
 __device__ inline void small_apply(SmallLds<N>& sm, int len, int tid) {
@@ -97,7 +97,7 @@ __device__ inline void small_apply(SmallLds<N>& sm, int len, int tid) {
   using T = JT<double>;
   const int lane = tid & 63, w = tid >> 6, c = lane & 15;
   if (w < 4) {
-    const double2* H = sm.sv.G[0];
+    const double2* H = sm.sv.G;
     for (int rt = w; rt * 16 < len; rt += 4) {
       double4_t re[D::nb], im[D::nb];
 #pragma unroll
@@ -216,6 +216,7 @@ __global__ __launch_bounds__(SS_THREADS) void k_split_small(SplitSmallArgs a) {
   __shared__ SmallLds<N> sm;
   const int tid = threadIdx.x, lane = tid & 63, row = tid - JSOLVE;
   const bool row_wave = tid >= JSOLVE;
+  const Moves<S> moves = block_moves<S>(tid);
   double2 y[N];
   if (row_wave) {
     const int lrow = min(row, a.len - 1);
@@ -235,13 +236,13 @@ __global__ __launch_bounds__(SS_THREADS) void k_split_small(SplitSmallArgs a) {
     if (tid == 0) sm.sv.any_flag = sm.sv.big = sm.bad = 0;
   }
   __syncthreads();
-  small_gram(sm, 0, a.len, tid);
+  small_gram(sm, a.len, tid);
   // columns by norm
   double fro2 = 0.0;
 #pragma unroll
-  for (int c = 0; c < N; ++c) fro2 += sm.sv.G[0][33 * c].x;
+  for (int c = 0; c < N; ++c) fro2 += sm.sv.G[33 * c].x;
   const double neg2 = a.delta2 * fmax(fro2, 1e-300);
-  if (tid < 32) sm.key[tid] = sm.sv.G[0][33 * tid].x;
+  if (tid < 32) sm.key[tid] = sm.sv.G[33 * tid].x;
   __syncthreads();
   if (a.sort) rank_keys(sm.key, a.cnt, sm.order, tid);
   __syncthreads();
@@ -250,20 +251,27 @@ __global__ __launch_bounds__(SS_THREADS) void k_split_small(SplitSmallArgs a) {
     for (int c = 0; c < N; ++c) y[c] = sm.Y[sm.order[c] * SS_LD + row];
 #pragma unroll
     for (int c = 0; c < N; ++c) sm.Y[c * SS_LD + row] = y[c];
-  } else {
-    for (int e = tid; e < 32 * N; e += JSOLVE) {
-      const int i = e >> 5, j = e & 31;
-      if (j < N) sm.sv.G[1][e] = sm.sv.G[0][sm.order[i] * 32 + sm.order[j]];
-    }
+  }
+  constexpr int GP = (32 * N + SS_THREADS - 1) / SS_THREADS;
+  double2 g[GP];
+#pragma unroll
+  for (int v = 0; v < GP; ++v) {
+    const int e = tid + SS_THREADS * v, i = (e >> 5) & (N - 1), j = e & 31;
+    g[v] = sm.sv.G[sm.order[i] * 32 + sm.order[j]];
   }
   __syncthreads();
-  int cur = 1, sweeps = 0;
+#pragma unroll
+  for (int v = 0; v < GP; ++v)
+    if (tid + SS_THREADS * v < 32 * N) sm.sv.G[tid + SS_THREADS * v] = g[v];
+  __syncthreads();
+  int sweeps = 0;
   for (;;) {
+    if (!row_wave) load_blocks<S>(sm.sv, tid);
     for (int e = tid; e < 32 * N; e += SS_THREADS) {
       const int i = e >> 5, j = e & 31;
       if (i < j && j < N) {
-        const double gii = sm.sv.G[cur][33 * i].x, gjj = sm.sv.G[cur][33 * j].x;
-        const double2 g = sm.sv.G[cur][e];
+        const double gii = sm.sv.G[33 * i].x, gjj = sm.sv.G[33 * j].x;
+        const double2 g = sm.sv.G[e];
         const double h2 = g.x * g.x + g.y * g.y;
         if (rot_active<double>(gii, gjj, h2, a.tol, neg2)) sm.sv.any_flag = 1;
         if (gii > neg2 && gjj > neg2 && h2 > a.qtol * gii * gjj) sm.sv.big = 1;
@@ -274,7 +282,7 @@ __global__ __launch_bounds__(SS_THREADS) void k_split_small(SplitSmallArgs a) {
     ++sweeps;
     if (!any) break;
     if (row_wave) {
-      row_sweeps<S>(y, sm.sv, lane, tid < JSOLVE + 64, 1);
+      row_sweeps<S>(y, sm.sv, lane, 1);
 #pragma unroll
       for (int c = 0; c < N; ++c) {
         const double d = sm.sv.scale[c];
@@ -282,13 +290,12 @@ __global__ __launch_bounds__(SS_THREADS) void k_split_small(SplitSmallArgs a) {
         sm.Y[c * SS_LD + row] = y[c];
       }
     } else {
-      solve_sweeps<S>(sm.sv, cur, tid, 0.5 * a.tol, neg2, 1);
+      solve_sweeps<S>(sm.sv, moves, tid, 0.5 * a.tol, neg2, 1);
     }
     __syncthreads();
     if (tid < 32) sm.sv.scale[tid] = 1.0;
     if (tid == 0) sm.sv.any_flag = sm.sv.big = 0;
-    cur = 0;
-    small_gram(sm, 0, a.len, tid);
+    small_gram(sm, a.len, tid);
     if (a.qtol > 0.0 && !big) break;
     if (sweeps == a.max_sweeps) {
       sweeps = -1;
@@ -297,7 +304,7 @@ __global__ __launch_bounds__(SS_THREADS) void k_split_small(SplitSmallArgs a) {
   }
   // singular values and rank
   if (tid < 32) {
-    const double s = sqrt(sm.sv.G[cur][33 * (tid < N ? tid : 0)].x);
+    const double s = sqrt(sm.sv.G[33 * (tid < N ? tid : 0)].x);
     sm.key[tid] = s;
     sm.order[tid] = tid;
     if (tid < a.cnt && (!(s == s) || s > 1e300)) sm.bad = 1;
@@ -332,8 +339,8 @@ __global__ __launch_bounds__(SS_THREADS) void k_split_small(SplitSmallArgs a) {
   }
   __syncthreads();
   for (int it = 0; it < a.ns_steps; ++it) {
-    small_gram(sm, 0, a.len, tid);
-    double2* H = sm.sv.G[0];
+    small_gram(sm, a.len, tid);
+    double2* H = sm.sv.G;
     for (int e = tid; e < 32 * D::cols; e += SS_THREADS) {
       const int i = e >> 5, j = e & 31;
       if (j < D::cols) H[e] = make_double2((i == j ? 1.5 : 0.0) - 0.5 * H[e].x, -0.5 * H[e].y);
