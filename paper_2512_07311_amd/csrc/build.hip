@@ -1059,7 +1059,7 @@ static bool move_cholqr(rcs_state_s& st, BuildWork& ws, const JacobiPlan& pl) {
       dev = ws.host_rank->w;      // max |H - I| = max |I - Q^H Q| / 2
       if (*ws.host_rot != 0 || !(dev <= 0.5e-4)) return false;
       const double e = 2.0 * dev * n;   // bounds ||I - Q^H Q||_2; a step takes it to 3 e^2 / 4
-      steps = e <= 1e-8 ? 1 : e <= 1e-4 ? 2 : 3;
+      steps = ns_steps_for(e);
     }
     RCS_PROBED_LAUNCH(kKcFactor, k_ns_apply, dim3(ceil_div(n, GT_N), ceil_div(len, GT_M)), dim3(GT_THREADS), 0, s, src,
                        pl.ldx, len, n, ws.H.as<double2>(), dst);
@@ -1068,6 +1068,19 @@ static bool move_cholqr(rcs_state_s& st, BuildWork& ws, const JacobiPlan& pl) {
   }
   ws.wn_final = src;
   return true;
+}
+
+// The same in one launch for a small site, P included.
+static bool move_cholqr_small(rcs_state_s& st, BuildWork& ws, const JacobiPlan& pl) {
+  hipStream_t s = st.stream;
+  ws.cflag.ensure(sizeof(int));
+  qr_small(QrSmallArgs{ws.X0.as<double2>(), pl.ldx, pl.len, pl.cnt, 1e-4, ws.Wn.as<double2>(), ws.P.as<double2>(),
+                       ws.cflag.as<int>()},
+           s);
+  HIP_OK(hipMemcpyAsync(ws.host_rot, ws.cflag.p, sizeof(int), hipMemcpyDeviceToHost, s));
+  HIP_OK(hipStreamSynchronize(s));
+  ws.wn_final = ws.Wn.as<double2>();
+  return *ws.host_rot != 0;
 }
 
 // Move the orthogonality centre one step: X = Q P with Q orthonormal
@@ -1082,19 +1095,27 @@ static void move_center(rcs_state_s& st, BuildWork& ws, bool right) {
   const int cnt = right ? dr : dl;
   JacobiPlan pl = jacobi_plan(len, cnt);
   ensure_work(ws, pl);
-  HIP_OK(hipMemsetAsync(ws.X.p, 0, (size_t)pl.ldx * pl.cnt_pad * sizeof(double2), s));
-  HIP_OK(hipMemsetAsync(ws.X0.p, 0, (size_t)pl.ldx * pl.cnt_pad * sizeof(double2), s));
+  // the one-launch forms read their input with bounds: no padding to clear
+  const bool small = split_small_fits(len, cnt);
+  if (!small) {
+    HIP_OK(hipMemsetAsync(ws.X.p, 0, (size_t)pl.ldx * pl.cnt_pad * sizeof(double2), s));
+    HIP_OK(hipMemsetAsync(ws.X0.p, 0, (size_t)pl.ldx * pl.cnt_pad * sizeof(double2), s));
+  }
   hipLaunchKernelGGL(k_load_site, dim3(grid1d((int64_t)2 * dl * dr)), dim3(256), 0, s, st.site[c], dl, dr,
                      right ? 1 : 0, ws.X.as<double2>(), ws.X0.as<double2>(), pl.ldx);
   HIP_LAUNCH_OK();
+  const bool try_chol = cholqr_moves_enabled() && cnt >= 2 && cnt <= len;
   int k;
-  if (cholqr_moves_enabled() && cnt >= 2 && cnt <= len && move_cholqr(st, ws, pl)) {
+  if (small && try_chol && move_cholqr_small(st, ws, pl)) {
+    k = cnt;
+    st.n_moves_cholqr += 1;
+  } else if (!small && try_chol && move_cholqr(st, ws, pl)) {
     k = cnt;
     st.n_moves_cholqr += 1;
     RCS_PROBED_LAUNCH(kKcFactor, k_project, dim3(ceil_div(cnt, GT_N), ceil_div(k, GT_M)), dim3(GT_THREADS), 0, s,
                        ws.wn_final, ws.X0.as<double2>(), pl.ldx, len, k, cnt, 1.0, ws.P.as<double2>());
     HIP_LAUNCH_OK();
-  } else if (split_small_fits(len, cnt)) {
+  } else if (small) {
     k = svd_split_small(st, ws, pl, right ? st.cap[c + 1] : st.cap[c], 0.0, false, nullptr, true).k;
   } else {
     // the CholeskyQR attempt (if any) left X untouched only where it ran

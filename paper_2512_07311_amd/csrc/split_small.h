@@ -33,4 +33,20 @@ struct SplitSmallArgs {
 };
 void split_small(const SplitSmallArgs& a, hipStream_t s);
 
+// X = Q P of a small matrix, cnt <= len, by CholeskyQR with one to three
+// Newton-Schulz steps; *ok = 0, and nothing else written, when a pivot is not
+// positive or Q_1's orthogonality defect exceeds defect_max.
+struct QrSmallArgs {
+  const double2* x;   // len x cnt, column-major, leading dimension ldx
+  int ldx, len, cnt;
+  double defect_max;
+  double2* wn;        // out: Q, ld ldx
+  double2* p;         // out: cnt x cnt, row-major
+  int* ok;
+};
+void qr_small(const QrSmallArgs& a, hipStream_t s);
+// Newton-Schulz steps that take an orthogonality defect bounded by e to
+// rounding (e -> 3 e^2 / 4 each).
+__host__ __device__ inline int ns_steps_for(double e) { return e <= 1e-8 ? 1 : e <= 1e-4 ? 2 : 3; }
+
 }  // namespace rcs

@@ -125,9 +125,20 @@ __device__ inline void small_apply(SmallLds<N>& sm, int len, int tid) {
   __syncthreads();
 }
 
-// P (k x cnt) = scale Y^H X, X from memory; one wave per 16 x 16 tile.
+// G <- (3 I - G) / 2
 template <int N>
-__device__ inline void small_project(const SmallLds<N>& sm, const SplitSmallArgs& a, int k, double scale, int tid) {
+__device__ inline void small_ns(SmallLds<N>& sm, int tid) {
+  double2* H = sm.sv.G;
+  for (int e = tid; e < 32 * SmallDims<N>::cols; e += SS_THREADS) {
+    const int i = e >> 5, j = e & 31;
+    if (j < SmallDims<N>::cols) H[e] = make_double2((i == j ? 1.5 : 0.0) - 0.5 * H[e].x, -0.5 * H[e].y);
+  }
+  __syncthreads();
+}
+
+// P (k x cnt) = scale Y^H X, X from memory; one wave per 16 x 16 tile.
+template <int N, class Args>
+__device__ inline void small_project(const SmallLds<N>& sm, const Args& a, int k, double scale, int tid) {
   using D = SmallDims<N>;
   using T = JT<double>;
   const int lane = tid & 63, w = tid >> 6;
@@ -340,12 +351,7 @@ __global__ __launch_bounds__(SS_THREADS) void k_split_small(SplitSmallArgs a) {
   __syncthreads();
   for (int it = 0; it < a.ns_steps; ++it) {
     small_gram(sm, a.len, tid);
-    double2* H = sm.sv.G;
-    for (int e = tid; e < 32 * D::cols; e += SS_THREADS) {
-      const int i = e >> 5, j = e & 31;
-      if (j < D::cols) H[e] = make_double2((i == j ? 1.5 : 0.0) - 0.5 * H[e].x, -0.5 * H[e].y);
-    }
-    __syncthreads();
+    small_ns(sm, tid);
     small_apply(sm, a.len, tid);
   }
   if (row_wave) {
@@ -353,6 +359,110 @@ __global__ __launch_bounds__(SS_THREADS) void k_split_small(SplitSmallArgs a) {
       for (int j = 0; j < k; ++j) a.wn[(int64_t)j * a.ldx + row] = sm.Y[j * SS_LD + row];
   } else {
     small_project(sm, a, k, a.renorm ? 1.0 / sm.rk.nrm : 1.0, tid);
+  }
+}
+
+// CholeskyQR of a small matrix in one launch, for centre moves: the general
+// path's Gram, Cholesky panel (a 64-column one, 39 us), inverse, products,
+// clears and copies are about sixteen launches.
+// Elimination on [G | I] by the whole workgroup, one barrier a pivot: the row
+// operations that turn G into R turn I into R^{-H}, both up to a row scale.
+// Bound: the chain of pivots and the launch itself.  Measured: the exact
+// 12-qubit build, with 96 moves, 23.7 -> 17.7 ms.
+template <int N>
+__global__ __launch_bounds__(SS_THREADS) void k_qr_small(QrSmallArgs a) {
+  using D = SmallDims<N>;
+  __shared__ SmallLds<N> sm;
+  const int tid = threadIdx.x, row = tid - JSOLVE;
+  const bool row_wave = tid >= JSOLVE;
+  double2* G = sm.sv.G;
+  double2* B = &sm.sv.B[0][0][0];   // N x N, ld 32
+  static_assert(sizeof(sm.sv.B) >= 32 * 32 * sizeof(double2), "B in place of the solve's blocks");
+  unsigned long long* dev = reinterpret_cast<unsigned long long*>(&sm.key[0]);
+  if (row_wave) {
+    const int lrow = min(row, a.len - 1);
+#pragma unroll
+    for (int c = 0; c < D::cols; ++c) {
+      const double2 v = a.x[(int64_t)min(c, a.cnt - 1) * a.ldx + lrow];
+      sm.Y[c * SS_LD + row] = c < a.cnt && row < a.len ? v : make_double2(0.0, 0.0);
+    }
+  } else {
+    for (int e = tid; e < 32 * N; e += JSOLVE) B[e] = make_double2((e >> 5) == (e & 31) ? 1.0 : 0.0, 0.0);
+    if (tid == 0) *dev = 0;
+  }
+  __syncthreads();
+  small_gram(sm, a.len, tid);
+  bool ok = true;
+  for (int k = 0; k < a.cnt; ++k) {
+    const double d = G[33 * k].x;           // the same value in every thread: nobody writes row k any more
+    if (!(d > 0.0) || !(d < 1e300)) {
+      ok = false;
+      break;
+    }
+    const double inv = 1.0 / d;
+    for (int e = tid; e < (a.cnt - 1 - k) * 2 * N; e += SS_THREADS) {
+      const int i = k + 1 + e / (2 * N), c = e & (2 * N - 1);
+      double2* M = c < N ? G : B;
+      const int j = c & (N - 1);
+      const double2 f = G[k * 32 + i], r = M[k * 32 + j];
+      double2& v = M[i * 32 + j];
+      if (c >= N || j > k) {   // v -= conj(f) r / d
+        const double fx = f.x * inv, fy = f.y * inv;
+        v = make_double2(v.x - (fx * r.x + fy * r.y), v.y - (fx * r.y - fy * r.x));
+      }
+    }
+    __syncthreads();
+  }
+  if (ok) {
+    // R^{-1}[j][k] = conj(R^{-H}[k][j]), row k of R^{-H} = B's over sqrt(d_k)
+    constexpr int GP = (32 * D::cols + SS_THREADS - 1) / SS_THREADS;
+    double2 g[GP];
+#pragma unroll
+    for (int v = 0; v < GP; ++v) {
+      const int e = tid + SS_THREADS * v, j = e >> 5, k = e & 31;
+      const bool in = j < a.cnt && k < a.cnt;
+      const double s = in ? 1.0 / sqrt(G[33 * k].x) : 0.0;
+      const double2 b = in ? B[k * 32 + j] : make_double2(0.0, 0.0);
+      g[v] = make_double2(b.x * s, -b.y * s);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int v = 0; v < GP; ++v)
+      if (tid + SS_THREADS * v < 32 * D::cols) G[tid + SS_THREADS * v] = g[v];
+    __syncthreads();
+    small_apply(sm, a.len, tid);
+    int steps = 3;
+    for (int it = 0; it < steps && ok; ++it) {
+      small_gram(sm, a.len, tid);
+      if (it == 0) {
+        double m = 0.0;
+        for (int e = tid; e < 32 * a.cnt; e += SS_THREADS) {
+          const int i = e >> 5, j = e & 31;
+          if (j < a.cnt) {
+            const double2 h = G[e];
+            m = fmax(m, fmax(fabs(h.x - (i == j ? 1.0 : 0.0)), fabs(h.y)));
+            if (!(h.x == h.x) || !(h.y == h.y)) m = 1e300;
+          }
+        }
+        atomicMax(dev, (unsigned long long)__double_as_longlong(m));
+        __syncthreads();
+        const double defect = __longlong_as_double((long long)*dev);   // max |I - Q^H Q|
+        ok = defect <= a.defect_max;
+        steps = ns_steps_for(defect * a.cnt);
+      }
+      if (ok) {
+        small_ns(sm, tid);
+        small_apply(sm, a.len, tid);
+      }
+    }
+  }
+  if (tid == 0) *a.ok = ok ? 1 : 0;
+  if (!ok) return;
+  if (row_wave) {
+    if (row < a.len)
+      for (int j = 0; j < a.cnt; ++j) a.wn[(int64_t)j * a.ldx + row] = sm.Y[j * SS_LD + row];
+  } else {
+    small_project(sm, a, a.cnt, 1.0, tid);
   }
 }
 
@@ -368,6 +478,19 @@ void split_small(const SplitSmallArgs& a, hipStream_t s) {
     RCS_PROBED_LAUNCH(kKcFactor, k_split_small<16>, grid, block, 0, s, a);
   else
     RCS_PROBED_LAUNCH(kKcFactor, k_split_small<32>, grid, block, 0, s, a);
+  HIP_LAUNCH_OK();
+}
+
+void qr_small(const QrSmallArgs& a, hipStream_t s) {
+  RCS_REQUIRE(a.cnt >= 1 && a.cnt <= a.len && split_small_fits(a.len, a.cnt) && a.ldx >= a.len,
+              "matrix too large for the small QR");
+  const dim3 grid(1), block(SS_THREADS);
+  if (a.cnt <= 8)
+    RCS_PROBED_LAUNCH(kKcFactor, k_qr_small<8>, grid, block, 0, s, a);
+  else if (a.cnt <= 16)
+    RCS_PROBED_LAUNCH(kKcFactor, k_qr_small<16>, grid, block, 0, s, a);
+  else
+    RCS_PROBED_LAUNCH(kKcFactor, k_qr_small<32>, grid, block, 0, s, a);
   HIP_LAUNCH_OK();
 }
 

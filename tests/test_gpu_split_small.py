@@ -1,4 +1,4 @@
-"""The one-launch split at the edges of its 8, 16 and 32 column forms and of
+"""The one-launch split and centre move at the edges of its 8, 16 and 32 column forms and of
 its range, through builds whose bond cap sets the split's columns to twice
 itself."""
 import numpy as np
@@ -6,7 +6,7 @@ import pytest
 
 from oracle import circuit as oc, mps
 from tests import inputs
-from tests.gpu_util import truncated_tolerance, get_rcs, to_complex, normwise_rel
+from tests.gpu_util import truncated_tolerance, get_rcs, to_complex, normwise_rel, oracle_state_from
 
 pytestmark = pytest.mark.gpu
 
@@ -35,6 +35,7 @@ def test_small_split_build(env, rows, cols, cyc, chi, eps):
     amps = torch.zeros(len(b), 2, dtype=torch.float64, device="cuda")
     g.amplitudes(bits, amps)
     assert normwise_rel(to_complex(amps), om.amplitudes(b)) < truncated_tolerance(om)
+    assert oracle_state_from(g.to_host()).canonical_residual() < 1e-12
     for rec in g.spectra():
         v = np.asarray(rec["values"])
         assert len(v) == rec["m"] and np.all(np.diff(v) <= 0.0) and np.all(np.isfinite(v))
