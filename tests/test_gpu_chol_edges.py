@@ -42,3 +42,17 @@ def test_breakdown_is_reported(env):
     with pytest.raises(rcs.RcsError) as ei:
         rcs.cholqr(x, q, r)
     assert ei.value.status == 5
+
+
+@pytest.mark.parametrize("cond", [1e1, 1e4, 1e5])
+def test_q_in_place_of_x(env, cond):
+    """x is read while q is written: one buffer for both gives the same bytes."""
+    rcs, torch = env
+    M = inputs.planted_matrix(200, 127, np.geomspace(1.0, 1.0 / cond, 127), seed=9)
+    x = torch.from_numpy(np.ascontiguousarray(M.T)).cuda()
+    q = torch.zeros(127, 200, dtype=torch.complex128, device="cuda")
+    r = torch.zeros(127, 127, dtype=torch.complex128, device="cuda")
+    r2 = torch.zeros_like(r)
+    rcs.cholqr(x, q, r)
+    rcs.cholqr(x, x, r2)
+    assert torch.equal(q, x) and torch.equal(r, r2)
