@@ -224,6 +224,74 @@ __device__ inline int rr_pair_of(int c, int round) {
   return min(slot, JP - 1 - slot);
 }
 
+constexpr int ROT_THREADS = 512;
+
+// Y_p <- Y_p V_p for this chunk's rows on the matrix cores (all ROT_THREADS).
+template <int JP, typename R, int LDV>
+__device__ inline void rotate_rows_by(const JacArgs<R>& a, const typename JT<R>::C (*V)[LDV], int bi, int bj,
+                                      int chunk) {
+  using T = JT<R>;
+  using C = typename T::C;
+  using V4 = typename T::V4;
+  constexpr int NB = JP / 16;
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  // waves take 16-row tiles; A operand straight from global
+  // (16 consecutive rows of one column per 16 lanes), B = V from LDS.
+  const int rbeg = chunk * a.rows_per_chunk;
+  const int rend = min(a.len, rbeg + a.rows_per_chunk);
+  const int ntiles = (rend - rbeg + TR - 1) / TR;
+  constexpr int KS = JP / 4, NW = ROT_THREADS / 64;
+  C cur[KS], nxt[KS];
+  const int m = lane & 15, ksub = lane >> 4;
+  auto load_tile_regs = [&](int tt, C (&v)[KS]) {
+    const int row = rbeg + tt * TR + m;
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      const int col = pair_col<JP>(4 * ks + ksub, bi, bj);
+      v[ks] = row < rend ? a.x[(int64_t)col * a.ldx + row] : C(0, 0);
+    }
+  };
+  if (w < ntiles) load_tile_regs(w, cur);
+  for (int tt = w; tt < ntiles; tt += NW) {
+    if (tt + NW < ntiles) load_tile_regs(tt + NW, nxt);
+    V4 cr[NB], ci[NB];
+#pragma unroll
+    for (int nt = 0; nt < NB; ++nt) {
+      cr[nt] = V4{0, 0, 0, 0};
+      ci[nt] = V4{0, 0, 0, 0};
+    }
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) {
+      const C y = cur[ks];
+      const int k = 4 * ks + ksub;
+#pragma unroll
+      for (int nt = 0; nt < NB; ++nt) {
+        const C v = V[k][nt * 16 + m];
+        cr[nt] = T::mma(y.x, v.x, cr[nt]);
+        cr[nt] = T::mma(-y.y, v.y, cr[nt]);
+        ci[nt] = T::mma(y.x, v.y, ci[nt]);
+        ci[nt] = T::mma(y.y, v.x, ci[nt]);
+      }
+    }
+    const int row0 = rbeg + tt * TR;
+#pragma unroll
+    for (int nt = 0; nt < NB; ++nt)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int row = row0 + T::orow(lane, r);
+        const int col = nt * 16 + m;
+        if (row < rend) a.x[(int64_t)pair_col<JP>(col, bi, bj) * a.ldx + row] = T::mk(cr[nt][r], ci[nt][r]);
+      }
+#pragma unroll
+    for (int ks = 0; ks < KS; ++ks) cur[ks] = nxt[ks];
+  }
+  if (chunk == 0 && tid == 0) {
+    a.rot_cur[bi] = 1;
+    a.rot_cur[bj] = 1;
+    atomicAdd(a.rot_count, 1);
+  }
+}
+
 // Sum partial Grams (fixed order), diagonalise the JP x JP Hermitian G_p by
 // cyclic two-sided Jacobi in LDS (every workgroup of a pair computes the
 // same unitary V_p), and rotate this chunk's rows, Y_p <- Y_p V_p, on the
@@ -235,8 +303,8 @@ __device__ inline int rr_pair_of(int c, int round) {
 // V[rows of a, pair b] <- V J_b (one of each per SIMD, so their latencies
 // overlap), all in place: each entry belongs to one job per round.  The
 // diagonal and the next round's pair entries are handed on through small
-// double-buffered arrays.
-constexpr int ROT_THREADS = 512;
+// double-buffered arrays.  Used by 64-column pairs and, in fp32, by a sweep's
+// first round; k_jac_rotate_cross has the other fp32 rounds.
 template <int JP, typename R>
 __global__ __launch_bounds__(ROT_THREADS) void k_jac_rotate(JacArgs<R> a) {
   using T = JT<R>;
@@ -381,61 +449,140 @@ __global__ __launch_bounds__(ROT_THREADS) void k_jac_rotate(JacArgs<R> a) {
     round = nround;
     __syncthreads();
   }
-  // Y_p <- Y_p V_p: waves take 16-row tiles; A operand straight from global
-  // (16 consecutive rows of one column per 16 lanes), B = V from LDS.
-  const int rbeg = chunk * a.rows_per_chunk;
-  const int rend = min(a.len, rbeg + a.rows_per_chunk);
-  const int ntiles = (rend - rbeg + TR - 1) / TR;
-  constexpr int KS = JP / 4, NW = ROT_THREADS / 64;
-  C cur[KS], nxt[KS];
-  const int m = lane & 15, ksub = lane >> 4;
-  auto load_tile_regs = [&](int tt, C (&v)[KS]) {
-    const int row = rbeg + tt * TR + m;
+  rotate_rows_by<JP>(a, V, bi, bj, chunk);
+}
+
+// The fp32 rotate pass of the cross rounds (all but a sweep's first): the same
+// operations on the same values as k_jac_rotate, in the same order, so the
+// same bits, without its index tables and with one barrier a round.
+// Column q of block bi stays in pair q, and column q of block bj is in pair
+// q - r in round r.  Thread (a, b) of waves 0-3 holds the 2 x 2 block of pairs
+// a and b and computes pair b's rotation itself (pair a's by a shuffle): of
+// its entries (i, i) stays, (i, j) moves one lane down within its 16 lanes,
+// and only (j, i), (j, j) and the next rotations' inputs go through LDS.
+// Thread (row, b) of waves 4-7 holds V's entries of two rows, which need no LDS
+// at all, one round behind.
+// Bound: the chain of rounds (0.45 us each) and the launch's loads and stores
+// around it (10 us).  1024 x 1024: 21.5 -> 17.8 us a launch.  Tried and no
+// faster: the chunk's rows loaded ahead of the solve.
+__device__ inline float2 lane_down(float2 v) {   // lane l + 1 of the 16-lane row
+  const int x = __builtin_amdgcn_update_dpp(0, __float_as_int(v.x), 0x12f, 0xf, 0xf, false);
+  const int y = __builtin_amdgcn_update_dpp(0, __float_as_int(v.y), 0x12f, 0xf, 0xf, false);
+  return make_float2(__int_as_float(x), __int_as_float(y));
+}
+__global__ __launch_bounds__(ROT_THREADS) void k_jac_rotate_cross(JacArgs<float> a) {
+  constexpr int JP = 32, NP = 16;
+  __shared__ float2 G[JP][JP + 1];   // the Gram, later V
+  __shared__ float2 mji[2][NP][NP], mjj[2][NP][NP];
+  __shared__ float dii[2][NP], djj[2][NP];
+  __shared__ float2 dij[2][NP];
+  __shared__ RotA<float> rp[2][NP];
+  __shared__ int any_flag, big_lds;
+  const int p = blockIdx.x, chunk = blockIdx.y;
+  const int bi = rr_block(p, a.round, a.nbp), bj = rr_block(a.nbp - 1 - p, a.round, a.nbp);
+  if (pair_skipped(a, bi, bj)) return;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const float2* part = a.part + (int64_t)p * a.n_gchunks * JP * JP;
+  for (int e = tid; e < JP * JP; e += ROT_THREADS) {
+    float2 s(0, 0);
+    for (int c0 = 0; c0 < a.n_gchunks; c0 += 8) {
+      float2 t[8];
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-      const int col = pair_col<JP>(4 * ks + ksub, bi, bj);
-      v[ks] = row < rend ? a.x[(int64_t)col * a.ldx + row] : C(0, 0);
-    }
-  };
-  if (w < ntiles) load_tile_regs(w, cur);
-  for (int tt = w; tt < ntiles; tt += NW) {
-    if (tt + NW < ntiles) load_tile_regs(tt + NW, nxt);
-    V4 cr[NB], ci[NB];
+      for (int u = 0; u < 8; ++u)
+        t[u] = c0 + u < a.n_gchunks ? part[(int64_t)(c0 + u) * JP * JP + e] : float2(0, 0);
 #pragma unroll
-    for (int nt = 0; nt < NB; ++nt) {
-      cr[nt] = V4{0, 0, 0, 0};
-      ci[nt] = V4{0, 0, 0, 0};
-    }
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-      const C y = cur[ks];
-      const int k = 4 * ks + ksub;
-#pragma unroll
-      for (int nt = 0; nt < NB; ++nt) {
-        const C v = V[k][nt * 16 + m];
-        cr[nt] = T::mma(y.x, v.x, cr[nt]);
-        cr[nt] = T::mma(-y.y, v.y, cr[nt]);
-        ci[nt] = T::mma(y.x, v.y, ci[nt]);
-        ci[nt] = T::mma(y.y, v.x, ci[nt]);
+      for (int u = 0; u < 8; ++u) {
+        s.x += t[u].x;
+        s.y += t[u].y;
       }
     }
-    const int row0 = rbeg + tt * TR;
-#pragma unroll
-    for (int nt = 0; nt < NB; ++nt)
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int row = row0 + T::orow(lane, r);
-        const int col = nt * 16 + m;
-        if (row < rend) a.x[(int64_t)pair_col<JP>(col, bi, bj) * a.ldx + row] = T::mk(cr[nt][r], ci[nt][r]);
+    G[e / JP][e % JP] = s;
+  }
+  if (tid == 0) {
+    any_flag = 0;
+    big_lds = 0;
+  }
+  __syncthreads();
+  for (int e = tid; e < JP * JP; e += ROT_THREADS) {
+    const int i = e / JP, j = e % JP;
+    if (i < NP && j >= NP) {
+      const float gii = G[i][i].x, gjj = G[j][j].x, h2 = G[i][j].x * G[i][j].x + G[i][j].y * G[i][j].y;
+      if (rot_active<float>(gii, gjj, h2, a.tol, a.neg2)) any_flag = 1;
+      if (gii > a.neg2 && gjj > a.neg2 && h2 > a.qtol * gii * gjj) big_lds = 1;
+    }
+  }
+  if (tid < NP) {
+    dii[0][tid] = G[tid][tid].x;
+    djj[0][tid] = G[NP + tid][NP + tid].x;
+    dij[0][tid] = G[tid][NP + tid];
+  }
+  const bool g_waves = tid < 256;
+  const int t = tid & 255, pa = t >> 4, pb = t & 15, lane_a = (lane & 48) + pa;
+  const int up_a = (pa - 1) & 15, up_b = (pb - 1) & 15;
+  // waves 0-3: entries (i, i), (i, j), (j, i), (j, j) of the block; waves 4-7:
+  // V's columns i and j of pair b in rows pa and 16 + pa
+  float2 x00, x01, x10, x11;
+  if (g_waves) {
+    x00 = G[pa][pb];
+    x01 = G[pa][NP + pb];
+    x10 = G[NP + pa][pb];
+    x11 = G[NP + pa][NP + pb];
+  } else {
+    x00 = x11 = make_float2(pa == pb ? 1.0f : 0.0f, 0.0f);
+    x01 = x10 = make_float2(0.0f, 0.0f);
+  }
+  __syncthreads();
+  if (chunk == 0 && tid == 0 && big_lds) *a.big_cos = 1;
+  if (!any_flag) return;
+  const float tol_in = 0.5f * a.tol, neg2 = a.neg2;
+  const int rounds = a.max_inner * NP;
+  for (int it = 0; it < rounds; ++it) {
+    const int buf = it & 1;
+    if (g_waves) {
+      if (it > 0) {
+        x10 = mji[buf][pa][pb];
+        x11 = mjj[buf][pa][pb];
       }
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) cur[ks] = nxt[ks];
+      const RotA<float> rb = rot_a(jac_rot(dii[buf][pb], djj[buf][pb], dij[buf][pb], tol_in, neg2));
+      RotA<float> ra;
+      ra.c = __shfl(rb.c, lane_a);
+      ra.ax = __shfl(rb.ax, lane_a);
+      ra.ay = __shfl(rb.ay, lane_a);
+      if (pa == 0) rp[buf][pb] = rb;
+      rot_right(rb, x00, x01);
+      rot_right(rb, x10, x11);
+      rot_left(ra, x00, x10);
+      rot_left(ra, x01, x11);
+      mji[buf ^ 1][up_a][pb] = x10;
+      mjj[buf ^ 1][up_a][up_b] = x11;
+      if (pa == pb) {
+        dii[buf ^ 1][pa] = x00.x;
+        djj[buf ^ 1][up_a] = x11.x;
+      }
+      if (up_b == pa) dij[buf ^ 1][pa] = x01;
+      x01 = lane_down(x01);
+    } else if (it > 0) {
+      const RotA<float> rb = rp[buf ^ 1][pb];
+      rot_right(rb, x00, x01);
+      rot_right(rb, x10, x11);
+      x01 = lane_down(x01);
+      x11 = lane_down(x11);
+    }
+    __syncthreads();
   }
-  if (chunk == 0 && tid == 0) {
-    a.rot_cur[bi] = 1;
-    a.rot_cur[bj] = 1;
-    atomicAdd(a.rot_count, 1);
+  if (!g_waves) {
+    const RotA<float> rb = rp[(rounds - 1) & 1][pb];
+    rot_right(rb, x00, x01);
+    rot_right(rb, x10, x11);
+    x01 = lane_down(x01);
+    x11 = lane_down(x11);
+    G[pa][pb] = x00;
+    G[pa][NP + pb] = x01;
+    G[NP + pa][pb] = x10;
+    G[NP + pa][NP + pb] = x11;
   }
+  __syncthreads();
+  rotate_rows_by<JP>(a, G, bi, bj, chunk);
 }
 
 // Rotate pass with rows in registers (see jacobi_dev.h): waves 0-3 sum the
@@ -689,8 +836,11 @@ static void launch_sweep(const JacobiPlan& pl, JacArgs<R> a, hipStream_t stream,
                               pr.start(), pr.stop(), 0, a);
       else if constexpr (std::is_same<R, double>::value)
         launch_rotate_rows(pl, a, stream, pr.start(), pr.stop());
-      else
+      else if (r == 0)
         hipExtLaunchKernelGGL((k_jac_rotate<32, R>), dim3(pl.n_pairs, pl.n_chunks), dim3(ROT_THREADS), 0, stream,
+                              pr.start(), pr.stop(), 0, a);
+      else
+        hipExtLaunchKernelGGL(k_jac_rotate_cross, dim3(pl.n_pairs, pl.n_chunks), dim3(ROT_THREADS), 0, stream,
                               pr.start(), pr.stop(), 0, a);
     }
     HIP_LAUNCH_OK();
