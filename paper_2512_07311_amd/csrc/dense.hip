@@ -13,14 +13,18 @@
 // and the gates' fp64 work, so passes are what is saved:
 //  * the single-qubit gates between two couplers of a qubit are multiplied
 //    into one 2x2 matrix and applied with the next coupler, in registers (one
-//    LDS round trip for three gates);
+//    LDS round trip for three gates); the matrix is a real rotation between
+//    phases, and the phases are multiplied into the couplers on either side,
+//    which leaves 52 instead of 88 fp64 operations per four amplitudes;
 //  * the qubit set of a pass is the best of the contiguous windows and of a
 //    set grown from the first gate in line, each step adding the qubits that
 //    let most gates run per qubit added.
 // 28 qubits (4 x 7), 8 cycles: 10 passes instead of the 64 that one window
-// and one layer per pass took, 34.8 ms instead of 165 (3.5 ms per pass against
+// and one layer per pass took, 27.9 ms instead of 165 (2.7 ms per pass against
 // 2.6: a pass now carries about 9 couplers with their gates; the copy rate
-// alone would be 2.0).
+// alone would be 2.0).  With general 2x2 matrices and places worked out for
+// every amplitude: 34.8 ms.  Error against extended precision 2.6e-15 (gate by
+// gate: 1.6e-15).
 #include <algorithm>
 #include <array>
 #include <vector>
@@ -36,10 +40,14 @@ constexpr int DW_THREADS = 512;
 constexpr int DW_MAXSTEPS = 24; // per launch: the steps travel as kernel arguments (4 KB)
 constexpr int DW_SPAN = 8;      // couplers span fewer qubit numbers than this
 
-// One step on tile bits ta, tb: ua and ub (2x2, row-major) on their qubits,
-// then the fSim.  kind 0: all three; 1: ua and ub; 2: ua only.
+// One step on tile bits ta, tb.
+//  kCoupler, kCouplerUnit: real rotations [[c, -s], [s, c]] with m[0] = (ca, sa)
+//    and m[1] = (cb, sb) on the two qubits, then the coupler with the phases
+//    around it: m[2..7] = its entries 00, 11, 12, 21, 22, 33 (Unit: 00 is 1);
+//  kGates2: 2x2 matrices m[0..3] and m[4..7]; kGate1: m[0..3] on ta only.
+enum { kCoupler, kCouplerUnit, kGates2, kGate1 };
 struct DenseStep {
-  double2 ua[4], ub[4];
+  double2 m[8];
   int kind, ta, tb;
 };
 
@@ -47,7 +55,6 @@ struct DensePass {
   int tbits, low;              // tile bits, of which the lowest `low` are qubits 0..low-1
   int bit[DW_TILE];            // qubit of each tile bit, ascending
   int nsteps, init;            // init: psi is |0...0> (not read)
-  double2 f00, f11, f12, f21, f22, f33;   // the fSim's nonzero entries
   DenseStep st[DW_MAXSTEPS];
 };
 static_assert(sizeof(DensePass) + 64 <= 4096, "kernel argument space");
@@ -63,10 +70,15 @@ __device__ inline double2 cmul(double2 a, double2 b) {
 __device__ inline double2 cfma(double2 a, double2 b, double2 c) {   // c + a b
   return make_double2(fma(a.x, b.x, fma(-a.y, b.y, c.x)), fma(a.x, b.y, fma(a.y, b.x, c.y)));
 }
-__device__ inline void apply2(const double2 (&u)[4], double2& x0, double2& x1) {
+__device__ inline void apply2(const double2* u, double2& x0, double2& x1) {
   const double2 y0 = cfma(u[1], x1, cmul(u[0], x0)), y1 = cfma(u[3], x1, cmul(u[2], x0));
   x0 = y0;
   x1 = y1;
+}
+__device__ inline void rotate2(double2 cs, double2& x0, double2& x1) {
+  const double2 y0 = make_double2(fma(cs.x, x0.x, -cs.y * x1.x), fma(cs.x, x0.y, -cs.y * x1.y));
+  x1 = make_double2(fma(cs.x, x1.x, cs.y * x0.x), fma(cs.x, x1.y, cs.y * x0.y));
+  x0 = y0;
 }
 
 // LDS position of tile index t: bits 4 and 5 are folded into the low four, so
@@ -90,52 +102,61 @@ __global__ __launch_bounds__(DW_THREADS) void k_dense_pass(double2* psi, DensePa
   }
   __syncthreads();
   constexpr int PER = (1 << DW_TILE) / DW_THREADS;
+  // a full tile takes the loops without the bound: a predicated load waits for
+  // the one before it
+  const bool full = P.tbits == DW_TILE && !P.init;
   double2 r[PER];
+  if (full) {
 #pragma unroll
-  for (int j = 0; j < PER; ++j) {
-    const int t = threadIdx.x + j * DW_THREADS;
-    r[j] = make_double2(0.0, 0.0);
-    if (t < tsz) {
-      const int64_t i = base + (t & lowmask) + hi[t >> P.low];
-      if (P.init)
-        r[j].x = i == 0 ? 1.0 : 0.0;
-      else
-        r[j] = psi[i];
+    for (int j = 0; j < PER; ++j) {
+      const int t = threadIdx.x + j * DW_THREADS;
+      r[j] = psi[base + (t & lowmask) + hi[t >> P.low]];
     }
-  }
 #pragma unroll
-  for (int j = 0; j < PER; ++j) {
-    const int t = threadIdx.x + j * DW_THREADS;
-    if (t < tsz) tile[dw_pos(t)] = r[j];
+    for (int j = 0; j < PER; ++j) tile[dw_pos(threadIdx.x + j * DW_THREADS)] = r[j];
+  } else {
+    for (int t = threadIdx.x; t < tsz; t += DW_THREADS) {
+      const int64_t i = base + (t & lowmask) + hi[t >> P.low];
+      tile[dw_pos(t)] = P.init ? make_double2(i == 0 ? 1.0 : 0.0, 0.0) : psi[i];
+    }
   }
   __syncthreads();
   for (int o = 0; o < P.nsteps; ++o) {
     const DenseStep& S = P.st[o];
-    if (S.kind == 2) {
+    if (S.kind == kGate1) {
       for (int p = threadIdx.x; p < (tsz >> 1); p += DW_THREADS) {
         const int t0 = dw_pos(dw_insert0(p, S.ta)), t1 = dw_pos(dw_insert0(p, S.ta) | (1 << S.ta));
         double2 x0 = tile[t0], x1 = tile[t1];
-        apply2(S.ua, x0, x1);
+        apply2(S.m, x0, x1);
         tile[t0] = x0;
         tile[t1] = x1;
       }
     } else {
+      // dw_insert0 and dw_pos are linear over the bits of the index, so the
+      // places of a thread's later items and of an item's other three
+      // amplitudes are its first place XOR a number that is the same for all
       const int lo = min(S.ta, S.tb), hb = max(S.ta, S.tb);
-      for (int p = threadIdx.x; p < (tsz >> 2); p += DW_THREADS) {
-        const int t = dw_insert0(dw_insert0(p, lo), hb);
-        const int t00 = dw_pos(t), t01 = dw_pos(t | (1 << S.tb)), t10 = dw_pos(t | (1 << S.ta)),
-                  t11 = dw_pos(t | (1 << S.ta) | (1 << S.tb));
+      const int pa = dw_pos(1 << S.ta), pb = dw_pos(1 << S.tb);
+      const int p0 = dw_pos(dw_insert0(dw_insert0(threadIdx.x, lo), hb));
+      for (int p = 0; p + (int)threadIdx.x < (tsz >> 2); p += DW_THREADS) {
+        const int t00 = p0 ^ dw_pos(dw_insert0(dw_insert0(p, lo), hb)), t01 = t00 ^ pb, t10 = t00 ^ pa,
+                  t11 = t01 ^ pa;
         double2 x00 = tile[t00], x01 = tile[t01], x10 = tile[t10], x11 = tile[t11];
-        apply2(S.ua, x00, x10);
-        apply2(S.ua, x01, x11);
-        apply2(S.ub, x00, x01);
-        apply2(S.ub, x10, x11);
-        if (S.kind == 0) {
-          const double2 y01 = cfma(P.f12, x10, cmul(P.f11, x01)), y10 = cfma(P.f22, x10, cmul(P.f21, x01));
-          x00 = cmul(P.f00, x00);
+        if (S.kind == kGates2) {
+          apply2(S.m, x00, x10);
+          apply2(S.m, x01, x11);
+          apply2(S.m + 4, x00, x01);
+          apply2(S.m + 4, x10, x11);
+        } else {
+          rotate2(S.m[0], x00, x10);
+          rotate2(S.m[0], x01, x11);
+          rotate2(S.m[1], x00, x01);
+          rotate2(S.m[1], x10, x11);
+          const double2 y01 = cfma(S.m[4], x10, cmul(S.m[3], x01)), y10 = cfma(S.m[6], x10, cmul(S.m[5], x01));
+          if (S.kind == kCoupler) x00 = cmul(S.m[2], x00);
           x01 = y01;
           x10 = y10;
-          x11 = cmul(P.f33, x11);
+          x11 = cmul(S.m[7], x11);
         }
         tile[t00] = x00;
         tile[t01] = x01;
@@ -145,7 +166,6 @@ __global__ __launch_bounds__(DW_THREADS) void k_dense_pass(double2* psi, DensePa
     }
     __syncthreads();
   }
-#pragma unroll
   for (int j = 0; j < PER; ++j) {
     const int t = threadIdx.x + j * DW_THREADS;
     if (t < tsz) psi[base + (t & lowmask) + hi[t >> P.low]] = tile[dw_pos(t)];
@@ -154,19 +174,49 @@ __global__ __launch_bounds__(DW_THREADS) void k_dense_pass(double2* psi, DensePa
 
 namespace {
 
-using Mat2 = std::array<cplx, 4>;
+// Gates are few and repeat, so a rounding error in one would add up over the
+// circuit instead of averaging out: the matrices are prepared in extended
+// precision.
+using xcplx = std::complex<long double>;
+using Mat2 = std::array<xcplx, 4>;
 Mat2 mul(const Mat2& a, const Mat2& b) {
   return Mat2{a[0] * b[0] + a[1] * b[2], a[0] * b[1] + a[1] * b[3], a[2] * b[0] + a[3] * b[2],
               a[2] * b[1] + a[3] * b[3]};
 }
-const Mat2 kIdentity{cplx(1.0), cplx(0.0), cplx(0.0), cplx(1.0)};
+const Mat2 kIdentity{xcplx(1.0L), xcplx(0.0L), xcplx(0.0L), xcplx(1.0L)};
+Mat2 gate_matrix(int g) {
+  const auto u = one_qubit_gate(g);
+  return Mat2{xcplx(u[0]), xcplx(u[1]), xcplx(u[2]), xcplx(u[3])};
+}
 
 // A coupler with the single-qubit gates since the previous coupler of each of
-// its qubits.
+// its qubits, as real rotations (cos, sin) and the entries 00, 11, 12, 21, 22,
+// 33 of the coupler with phases.
 struct Block {
   int a, b;
-  Mat2 ua, ub;
+  double ca, sa, cb, sb;
+  xcplx f[6];
 };
+
+// A unitary u = common diag(1, d1) [[c, -s], [s, c]] diag(1, d2); common also
+// holds what c and s lost in rounding.
+struct Euler {
+  xcplx common, d1, d2;
+  double c, s;
+};
+Euler euler(const Mat2& u) {
+  auto unit = [](const xcplx& z) { return std::abs(z) > 0.0L ? z / std::abs(z) : xcplx(1.0L); };
+  const long double c = std::abs(u[0]), s = std::abs(u[2]);
+  const xcplx p0 = unit(u[0]), p1 = unit(u[2]);
+  Euler e;
+  e.c = (double)c;
+  e.s = (double)s;
+  e.d1 = p1 / p0;
+  // the larger of cos and sin gives the second phase: u11 = p1 c d2, u01 = -p0 s d2
+  e.d2 = c >= s ? unit(u[3]) / p1 : -unit(u[1]) / p0;
+  e.common = p0 * (std::hypot(c, s) / std::hypot((long double)e.c, (long double)e.s));
+  return e;
+}
 
 // The circuit as blocks per qubit, in order, and what is left to run.
 struct Planner {
@@ -248,8 +298,11 @@ struct Planner {
   }
 };
 
-void to_dev(const Mat2& m, double2 (&d)[4]) {
-  for (int e = 0; e < 4; ++e) d[e] = make_double2(m[e].real(), m[e].imag());
+// Rows and columns (2 a + b) of a coupler's entries.
+constexpr int kCouplerRow[6] = {0, 1, 1, 2, 2, 3}, kCouplerCol[6] = {0, 1, 2, 1, 2, 3};
+
+void to_dev(const Mat2& m, double2* d) {
+  for (int e = 0; e < 4; ++e) d[e] = make_double2((double)m[e].real(), (double)m[e].imag());
 }
 
 }  // namespace
@@ -267,34 +320,47 @@ void dense_simulate(const rcs_circuit_s& c, double2* psi, hipStream_t s) {
   pl.last_left.assign(n, 0);
   auto layer_1q = [&](const std::vector<int>& g) {
     for (int q = 0; q < n; ++q) {
-      pl.last[q] = mul(one_qubit_gate(g[q]), pl.last[q]);
+      pl.last[q] = mul(gate_matrix(g[q]), pl.last[q]);
       pl.last_left[q] = 1;
     }
   };
+  xcplx common(1.0L);
   for (int t = 0; t < c.n_cycles; ++t) {
     layer_1q(c.layers_1q[t]);
     for (auto& e : c.layers_2q[t]) {
       const int a = std::min(e.first, e.second), b = std::max(e.first, e.second);
-      for (int q : {a, b}) pl.line[q].push_back((int)pl.blocks.size());
-      pl.blocks.push_back(Block{a, b, pl.last[a], pl.last[b]});
+      // The rotations' inner phases go to the coupler, their outer ones to the
+      // qubit's previous coupler (a phase of one qubit commutes with all that
+      // acts on others; on |0> it is nothing), their common one to the first.
+      const Euler ea = euler(pl.last[a]), eb = euler(pl.last[b]);
+      Block B{a, b, ea.c, ea.s, eb.c, eb.s, {}};
+      for (int e = 0; e < 6; ++e) {
+        const int row = kCouplerRow[e], col = kCouplerCol[e];
+        B.f[e] = xcplx(c.fsim[4 * row + col]) * (col & 2 ? ea.d1 : xcplx(1.0L)) * (col & 1 ? eb.d1 : xcplx(1.0L));
+      }
+      common *= ea.common * eb.common;
+      for (int q : {a, b}) {
+        if (!pl.line[q].empty()) {
+          Block& prev = pl.blocks[pl.line[q].back()];
+          for (int e = 0; e < 6; ++e)
+            if (kCouplerRow[e] & (q == prev.a ? 2 : 1)) prev.f[e] *= q == a ? ea.d2 : eb.d2;
+        }
+        pl.line[q].push_back((int)pl.blocks.size());
+      }
+      pl.blocks.push_back(B);
       for (int q : {a, b}) {
         pl.last[q] = kIdentity;
         pl.last_left[q] = 0;
       }
     }
   }
+  if (!pl.blocks.empty())
+    for (xcplx& f : pl.blocks[0].f) f *= common;
   if (c.final_layer && c.layers_1q.size() > (size_t)c.n_cycles) layer_1q(c.layers_1q[c.n_cycles]);
 
   const int low = std::min(DW_LOW, n), tbits = std::min(DW_TILE, n);
   const uint64_t lowset = (uint64_t(1) << low) - 1;
   DensePass P{};
-  auto entry = [&](int e) { return make_double2(c.fsim[e].real(), c.fsim[e].imag()); };
-  P.f00 = entry(0);
-  P.f11 = entry(5);
-  P.f12 = entry(6);
-  P.f21 = entry(9);
-  P.f22 = entry(10);
-  P.f33 = entry(15);
   P.init = 1;
   if (pl.done()) {   // no gate at all
     const int64_t len = int64_t(1) << n;
@@ -344,11 +410,13 @@ void dense_simulate(const rcs_circuit_s& c, double2* psi, hipStream_t s) {
     P.nsteps = 0;
     for (int i : ran) {
       DenseStep& S = P.st[P.nsteps++];
-      S.kind = 0;
-      S.ta = pos[pl.blocks[i].a];
-      S.tb = pos[pl.blocks[i].b];
-      to_dev(pl.blocks[i].ua, S.ua);
-      to_dev(pl.blocks[i].ub, S.ub);
+      const Block& B = pl.blocks[i];
+      S.kind = B.f[0] == xcplx(1.0L) ? kCouplerUnit : kCoupler;
+      S.ta = pos[B.a];
+      S.tb = pos[B.b];
+      S.m[0] = make_double2(B.ca, B.sa);
+      S.m[1] = make_double2(B.cb, B.sb);
+      for (int e = 0; e < 6; ++e) S.m[2 + e] = make_double2((double)B.f[e].real(), (double)B.f[e].imag());
     }
     int held = -1;   // a last gate waiting for a partner
     for (uint64_t m = set; m; m &= m - 1) {
@@ -356,17 +424,17 @@ void dense_simulate(const rcs_circuit_s& c, double2* psi, hipStream_t s) {
       if (!pl.last_left[q] || pl.next[q] < (int)pl.line[q].size()) continue;
       if (held >= 0) {
         DenseStep& S = P.st[P.nsteps - 1];
-        S.kind = 1;
+        S.kind = kGates2;
         S.tb = pos[q];
-        to_dev(pl.last[q], S.ub);
+        to_dev(pl.last[q], S.m + 4);
         held = -1;
       } else {
         if (P.nsteps == DW_MAXSTEPS) break;
         DenseStep& S = P.st[P.nsteps++];
-        S.kind = 2;
+        S.kind = kGate1;
         S.ta = pos[q];
         S.tb = 0;
-        to_dev(pl.last[q], S.ua);
+        to_dev(pl.last[q], S.m);
         held = q;
       }
       pl.last_left[q] = 0;
