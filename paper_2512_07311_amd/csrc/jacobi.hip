@@ -52,7 +52,7 @@ struct JacArgs {
   typename JT<R>::C* x;
   int ldx, len, nbp, round, rows_per_chunk, n_chunks;   // rotate chunks
   int rows_per_gchunk, n_gchunks;                      // Gram chunks
-  typename JT<R>::C* part;   // [pair][chunk][JP][JP]
+  typename JT<R>::C* part;   // [pair][chunk][JP][JP], cross rounds of the row-resident pass: [pair][chunk][16][16]
   int* rot_prev;      // [nbp] block rotated during the previous sweep
   int* rot_cur;       // [nbp] block rotated during this sweep
   int* rot_count;
@@ -61,6 +61,7 @@ struct JacArgs {
   R tol;              // relative orthogonality tolerance
   R neg2;             // squared column norm below which a column counts as zero
   int max_inner;      // inner two-sided sweeps per pair meeting
+  typename JT<R>::C* bg;     // row-resident pass: [2][block][16][16], the blocks' own Grams
 };
 
 template <typename R>
@@ -99,13 +100,17 @@ __device__ inline void load_row(const C* x, int ldx, int bi, int bj, int row, in
 // (sixteen waves: 30.8 and 59.8).  The fp32 pass keeps four waves: its
 // partials are half the size, and its singular values depend on the
 // summation order at the 1e-4 level of its drift.
-template <int JP, int NW, typename R>
+//
+// CROSS: only the product of the two blocks with each other; the rotate pass
+// has their own Grams from the blocks' previous meeting.
+template <int JP, int NW, typename R, bool CROSS = false>
 __global__ __launch_bounds__(64 * NW) void k_jac_gram(JacArgs<R> a) {
   using T = JT<R>;
   using C = typename T::C;
   using V4 = typename T::V4;
-  constexpr int NB = JP / 16, NU = NB * (NB + 1) / 2;
+  constexpr int NB = JP / 16, NU = CROSS ? 1 : NB * (NB + 1) / 2;
   static_assert(NW == 4 || NW == 8, "the reduction below");
+  static_assert(!CROSS || JP == 32, "two 16-column blocks");
   __shared__ R red[NW == 8 ? 4 : 1][NU * 8][64];
   const int p = blockIdx.x, chunk = blockIdx.y;
   const int bi = rr_block(p, a.round, a.nbp), bj = rr_block(a.nbp - 1 - p, a.round, a.nbp);
@@ -135,17 +140,21 @@ __global__ __launch_bounds__(64 * NW) void k_jac_gram(JacArgs<R> a) {
     }
 #pragma unroll
     for (int ks = 0; ks < 4; ++ks) {
-      int u = 0;
+      auto product = [&](int u, const C& ym, const C& yn) {
+        gr[u] = T::mma(ym.x, yn.x, gr[u]);
+        gr[u] = T::mma(ym.y, yn.y, gr[u]);
+        gi[u] = T::mma(ym.x, yn.y, gi[u]);
+        gi[u] = T::mma(-ym.y, yn.x, gi[u]);
+      };
+      if constexpr (CROSS) {
+        product(0, cur[ks][0], cur[ks][1]);
+      } else {
+        int u = 0;
 #pragma unroll
-      for (int mb = 0; mb < NB; ++mb)
+        for (int mb = 0; mb < NB; ++mb)
 #pragma unroll
-        for (int nb = mb; nb < NB; ++nb, ++u) {
-          const C ym = cur[ks][mb], yn = cur[ks][nb];
-          gr[u] = T::mma(ym.x, yn.x, gr[u]);
-          gr[u] = T::mma(ym.y, yn.y, gr[u]);
-          gi[u] = T::mma(ym.x, yn.y, gi[u]);
-          gi[u] = T::mma(-ym.y, yn.x, gi[u]);
-        }
+          for (int nb = mb; nb < NB; ++nb, ++u) product(u, cur[ks][mb], cur[ks][nb]);
+      }
     }
 #pragma unroll
     for (int ks = 0; ks < 4; ++ks)
@@ -193,6 +202,13 @@ __global__ __launch_bounds__(64 * NW) void k_jac_gram(JacArgs<R> a) {
     __syncthreads();
   }
   if (w != 0) return;
+  if constexpr (CROSS) {
+    C* part = a.part + ((int64_t)p * a.n_gchunks + chunk) * 256;
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+      part[T::orow(lane, r) * 16 + (lane & 15)] = T::mk(gr[0][r] + red[0][r][lane], gi[0][r] + red[0][4 + r][lane]);
+    return;
+  }
   C* part = a.part + ((int64_t)p * a.n_gchunks + chunk) * JP * JP;
   int u = 0;
 #pragma unroll
@@ -587,13 +603,34 @@ __global__ __launch_bounds__(ROT_THREADS) void k_jac_rotate_cross(JacArgs<float>
 
 // Rotate pass with rows in registers (see jacobi_dev.h): waves 0-3 sum the
 // partial Grams, solve and publish, the others hold ROWS rows of Y_p.
+//
+// A sweep's first round takes the pair's whole Gram from the Gram pass.  The
+// cross rounds take only the product of the two blocks from it: the blocks'
+// own Grams are what the solve of each block's previous meeting left (two
+// buffers by the round's parity, since a pair's first workgroup writes the new
+// ones while others may still read; every block meets once a round, and the
+// last round of a sweep, of which there is an odd number, writes the buffer
+// that a skipped pair of the next first round leaves in place).  They drift
+// by rounding only and are taken afresh every sweep.  At 2048 x 2048 the Gram
+// pass of a cross round takes 13.5 instead of 22.8 us and the rotate pass, with
+// a quarter of the partials to read, 29 instead of 32.
 template <int ROWS, class S>
 __global__ __launch_bounds__(JSOLVE + ROWS) void k_jac_rotate_rows(JacArgs<double> a) {
   __shared__ SolveLds sm;
+  constexpr bool kFull = S::rounds == SchedFull::rounds;
   const int p = blockIdx.x, chunk = blockIdx.y;
   const int bi = rr_block(p, a.round, a.nbp), bj = rr_block(a.nbp - 1 - p, a.round, a.nbp);
-  if (pair_skipped(a, bi, bj)) return;
   const int tid = threadIdx.x;
+  const bool skipped = pair_skipped(a, bi, bj);
+  const double2* bg_in = a.bg + (int64_t)(a.round & 1) * a.nbp * 256;
+  double2* bg_out = a.bg + (int64_t)((a.round & 1) ^ 1) * a.nbp * 256;
+  if (skipped) {
+    if (!kFull && chunk == 0 && tid < 256) {
+      bg_out[bi * 256 + tid] = bg_in[bi * 256 + tid];
+      bg_out[bj * 256 + tid] = bg_in[bj * 256 + tid];
+    }
+    return;
+  }
   if (tid >= JSOLVE) {
     const int lane = tid & 63, row = chunk * ROWS + tid - JSOLVE;
     const bool live = row < a.len;
@@ -617,23 +654,34 @@ __global__ __launch_bounds__(JSOLVE + ROWS) void k_jac_rotate_rows(JacArgs<doubl
     return;
   }
   // partial Grams summed in chunk order, loads issued eight at a time
-  const double2* part = a.part + (int64_t)p * a.n_gchunks * 1024;
-#pragma unroll
-  for (int v = 0; v < 4; ++v) {
-    const int e = tid + JSOLVE * v;
+  constexpr int E = kFull ? 1024 : 256;
+  const double2* part = a.part + (int64_t)p * a.n_gchunks * E;
+  auto sum_part = [&](int e) {
     double2 s = make_double2(0.0, 0.0);
     for (int c0 = 0; c0 < a.n_gchunks; c0 += 8) {
       double2 t[8];
 #pragma unroll
       for (int u = 0; u < 8; ++u)
-        t[u] = c0 + u < a.n_gchunks ? part[(int64_t)(c0 + u) * 1024 + e] : make_double2(0.0, 0.0);
+        t[u] = c0 + u < a.n_gchunks ? part[(int64_t)(c0 + u) * E + e] : make_double2(0.0, 0.0);
 #pragma unroll
       for (int u = 0; u < 8; ++u) {
         s.x += t[u].x;
         s.y += t[u].y;
       }
     }
-    sm.G[e] = s;
+    return s;
+  };
+  if constexpr (kFull) {
+#pragma unroll
+    for (int v = 0; v < 4; ++v) sm.G[tid + JSOLVE * v] = sum_part(tid + JSOLVE * v);
+  } else {
+    const int m = tid >> 4, n = tid & 15;
+    const double2 gi = bg_in[bi * 256 + tid], gj = bg_in[bj * 256 + tid];
+    const double2 s = sum_part(tid);
+    sm.G[m * 32 + n] = gi;
+    sm.G[(16 + m) * 32 + 16 + n] = gj;
+    sm.G[m * 32 + 16 + n] = s;
+    sm.G[(16 + n) * 32 + m] = make_double2(s.x, -s.y);
   }
   fill_schedule<S>(sm, tid, JSOLVE);
   const Moves<S> moves = block_moves<S>(tid);
@@ -648,7 +696,7 @@ __global__ __launch_bounds__(JSOLVE + ROWS) void k_jac_rotate_rows(JacArgs<doubl
 #pragma unroll
   for (int v = 0; v < 4; ++v) {
     const int e = tid + JSOLVE * v, i = e >> 5, j = e & 31;
-    if (i < j && (S::rounds == SchedFull::rounds || (i < 16 && j >= 16))) {
+    if (i < j && (kFull || (i < 16 && j >= 16))) {
       const double gii = sm.G[33 * i].x, gjj = sm.G[33 * j].x;
       const double2 g = sm.G[e];
       const double h2 = g.x * g.x + g.y * g.y;
@@ -658,12 +706,34 @@ __global__ __launch_bounds__(JSOLVE + ROWS) void k_jac_rotate_rows(JacArgs<doubl
   }
   __syncthreads();
   if (chunk == 0 && tid == 0 && sm.big) *a.big_cos = 1;
-  if (!sm.any_flag) return;
+  if (!sm.any_flag) {
+    if (chunk == 0) {
+      const int m = tid >> 4, n = tid & 15;
+      bg_out[bi * 256 + tid] = sm.G[m * 32 + n];
+      bg_out[bj * 256 + tid] = sm.G[(16 + m) * 32 + 16 + n];
+    }
+    return;
+  }
   solve_sweeps<S>(sm, moves, tid, 0.5 * a.tol, a.neg2, a.max_inner);
-  if (chunk == 0 && tid == 0) {
-    a.rot_cur[bi] = 1;
-    a.rot_cur[bj] = 1;
-    atomicAdd(a.rot_count, 1);
+  if (chunk == 0) {
+    // the blocks' Grams: the solve's copy is back in the order of round 0
+    if (tid < Blocks<S>::n) {
+      const int qb = tid & 15, qa = (qb + tid / 16) & 15, buf = (a.max_inner * S::rounds) & 1;
+#pragma unroll
+      for (int t = 0; t < 4; ++t) {
+        const int r = t >= 2 ? S::j(qa, 0) : S::i(qa, 0), c = t & 1 ? S::j(qb, 0) : S::i(qb, 0);
+        if ((r ^ c) & 16 || (t == 2 && tid < 16)) continue;   // between the blocks, or not kept
+        const double2 g = sm.B[buf][t][tid];
+        double2* out = bg_out + (r < 16 ? bi : bj) * 256;
+        out[(r & 15) * 16 + (c & 15)] = g;
+        if (r != c) out[(c & 15) * 16 + (r & 15)] = make_double2(g.x, -g.y);
+      }
+    }
+    if (tid == 0) {
+      a.rot_cur[bi] = 1;
+      a.rot_cur[bj] = 1;
+      atomicAdd(a.rot_count, 1);
+    }
   }
 }
 
@@ -775,8 +845,8 @@ JacobiPlan jacobi_plan(int len, int cnt, int jb, bool f32) {
 
 size_t jacobi_work_bytes(const JacobiPlan& pl) {
   const int JP = 2 * pl.jb;
-  return (size_t)pl.n_pairs * pl.n_gchunks * JP * JP * sizeof(double2) + 2 * (size_t)pl.nbp * sizeof(int) +
-         256;
+  return ((size_t)pl.n_pairs * pl.n_gchunks * JP * JP + 2 * (size_t)pl.nbp * 256) * sizeof(double2) +
+         2 * (size_t)pl.nbp * sizeof(int) + 256;
 }
 
 // Row-resident rotate pass: the fewest rows per workgroup (64 to 512) that
@@ -821,12 +891,23 @@ static void launch_sweep(const JacobiPlan& pl, JacArgs<R> a, hipStream_t stream,
       Probe pr(kKcJacGram, stream, fl, by);
       const int waves = gram_waves(pl, std::is_same<R, float>::value);
       const dim3 grid(pl.n_pairs, pl.n_gchunks), block(64 * waves);
-      if (pl.jb != 16)
-        hipExtLaunchKernelGGL((k_jac_gram<64, 4, R>), grid, block, 0, stream, pr.start(), pr.stop(), 0, a);
-      else if (waves == 8)
-        hipExtLaunchKernelGGL((k_jac_gram<32, 8, R>), grid, block, 0, stream, pr.start(), pr.stop(), 0, a);
-      else
-        hipExtLaunchKernelGGL((k_jac_gram<32, 4, R>), grid, block, 0, stream, pr.start(), pr.stop(), 0, a);
+      auto launch = [&](auto kernel) { hipExtLaunchKernelGGL(kernel, grid, block, 0, stream, pr.start(), pr.stop(), 0, a); };
+      bool cross = false;   // the row-resident pass takes only the cross products after a sweep's first round
+      if constexpr (std::is_same<R, double>::value) {
+        cross = pl.jb == 16 && r > 0;
+        if (cross && waves == 8)
+          launch(k_jac_gram<32, 8, R, true>);
+        else if (cross)
+          launch(k_jac_gram<32, 4, R, true>);
+      }
+      if (!cross) {
+        if (pl.jb != 16)
+          launch(k_jac_gram<64, 4, R>);
+        else if (waves == 8)
+          launch(k_jac_gram<32, 8, R>);
+        else
+          launch(k_jac_gram<32, 4, R>);
+      }
     }
     HIP_LAUNCH_OK();
     {
@@ -941,6 +1022,8 @@ static int jacobi_run_t(const JacobiPlan& pl, typename JT<R>::C* x, void* work, 
   char* w = reinterpret_cast<char*>(work);
   a.part = reinterpret_cast<C*>(w);
   w += (size_t)pl.n_pairs * pl.n_gchunks * (2 * pl.jb) * (2 * pl.jb) * sizeof(C);
+  a.bg = reinterpret_cast<C*>(w);
+  w += 2 * (size_t)pl.nbp * 256 * sizeof(C);
   a.rot_prev = reinterpret_cast<int*>(w);
   a.rot_cur = a.rot_prev + pl.nbp;
   a.rot_count = rot_count_dev;
