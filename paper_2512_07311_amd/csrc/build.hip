@@ -399,27 +399,6 @@ __global__ void k_gather_normalize_c64(const float2* X, int ldx, const int* orde
 // Newton-Schulz orthonormalisation of the kept columns (the Jacobi stops at
 // an absolute floor, so columns of small singular values are orthonormal
 // only to ~floor / (s_i s_j)):  Wn <- Wn (3 I - Wn^H Wn) / 2.
-// H (k x k, row-major) = (3 I - Wn^H Wn) / 2
-__global__ __launch_bounds__(GT_THREADS) void k_ns_gram(const double2* Wn, int ldx, int len, int k,
-                                                       double2* H) {
-  __shared__ SmemC64 sm;
-  const int m0 = blockIdx.y * GT_M, n0 = blockIdx.x * GT_N;
-  auto fa = [&](int m, int kk) -> double2 {
-    double2 v = Wn[(int64_t)m * ldx + kk];
-    return make_double2(v.x, -v.y);
-  };
-  auto fb = [&](int kk, int n) -> double2 { return Wn[(int64_t)n * ldx + kk]; };
-  LoadA<decltype(fa), true> la{fa, m0, k, len};
-  LoadB<decltype(fb), false> lb{fb, n0, len, k};
-  AccC64 acc;
-  acc_zero(acc);
-  cgemm_mainloop(la, lb, len, sm, acc);
-  acc_foreach(acc, [&](int r, int c, double re, double im) {
-    int m = m0 + r, n = n0 + c;
-    if (m < k && n < k) H[(int64_t)m * k + n] = make_double2(((m == n) ? 1.5 : 0.0) - 0.5 * re, -0.5 * im);
-  });
-}
-
 // Out (len x k, column-major, ld ldx) = Wn H
 __global__ __launch_bounds__(GT_THREADS) void k_ns_apply(const double2* Wn, int ldx, int len, int k,
                                                         const double2* H, double2* Out) {
@@ -435,28 +414,6 @@ __global__ __launch_bounds__(GT_THREADS) void k_ns_apply(const double2* Wn, int 
   acc_foreach(acc, [&](int r, int c, double re, double im) {
     int m = m0 + r, n = n0 + c;
     if (m < len && n < k) Out[(int64_t)n * ldx + m] = make_double2(re, im);
-  });
-}
-
-// P (k x cnt, element (m, n) at m pm + n pn) = scale * Wn^H X0
-__global__ __launch_bounds__(GT_THREADS) void k_project(const double2* Wn, const double2* X0, int ldx,
-                                                       int ldx0, int len, int k, int cnt, double scale, double2* P,
-                                                       int64_t pm, int64_t pn) {
-  __shared__ SmemC64 sm;
-  const int m0 = blockIdx.y * GT_M, n0 = blockIdx.x * GT_N;
-  auto fa = [&](int m, int kk) -> double2 {
-    double2 v = Wn[(int64_t)m * ldx + kk];
-    return make_double2(v.x, -v.y);
-  };
-  auto fb = [&](int kk, int n) -> double2 { return X0[(int64_t)n * ldx0 + kk]; };
-  LoadA<decltype(fa), true> la{fa, m0, k, len};
-  LoadB<decltype(fb), false> lb{fb, n0, len, cnt};
-  AccC64 acc;
-  acc_zero(acc);
-  cgemm_mainloop(la, lb, len, sm, acc);
-  acc_foreach(acc, [&](int r, int c, double re, double im) {
-    int m = m0 + r, n = n0 + c;
-    if (m < k && n < cnt) P[m * pm + n * pn] = make_double2(re * scale, im * scale);
   });
 }
 
@@ -634,6 +591,11 @@ struct BuildWork {
   DevBuf G, Rd, Y, order_x, cflag;   // preconditioned split
   DevBuf Y32;                         // its fp32 copy (RCS_SVD_F32)
   DevBuf qr;                          // CholeskyQR centre moves
+  DevBuf part;                        // partial tiles of split products
+  double2* ahb_part(int M, int N, int K, bool upper) {
+    part.ensure(ahb_part_bytes(M, N, K, upper));
+    return part.as<double2>();
+  }
   std::vector<double> host_sorted;
   double2* wn_final = nullptr;   // orthonormal kept columns after svd_split
   void* host_rank_dev() {
@@ -731,9 +693,7 @@ static SplitResult svd_split(rcs_state_s& st, BuildWork& ws, const JacobiPlan& p
   double2* src = ws.Wn.as<double2>();
   double2* dst = X;
   for (int it = 0; it < (ortho_only ? 2 : 1); ++it) {
-    RCS_PROBED_LAUNCH(kKcFactor, k_ns_gram, dim3(ceil_div(out.k, GT_N), ceil_div(out.k, GT_M)), dim3(GT_THREADS), 0, s, src,
-                       pl.ldx, pl.len, out.k, ws.H.as<double2>());
-    HIP_LAUNCH_OK();
+    ns_gram(src, pl.ldx, pl.len, out.k, ws.H.as<double2>(), ws.ahb_part(out.k, out.k, pl.len, true), s);
     RCS_PROBED_LAUNCH(kKcFactor, k_ns_apply, dim3(ceil_div(out.k, GT_N), ceil_div(pl.len, GT_M)), dim3(GT_THREADS), 0, s,
                        src, pl.ldx, pl.len, out.k, ws.H.as<double2>(), dst);
     HIP_LAUNCH_OK();
@@ -741,10 +701,8 @@ static SplitResult svd_split(rcs_state_s& st, BuildWork& ws, const JacobiPlan& p
   }
   ws.wn_final = src;
   const double scale = renorm ? 1.0 / out.nrm : 1.0;
-  RCS_PROBED_LAUNCH(kKcFactor, k_project, dim3(ceil_div(pl.cnt, GT_N), ceil_div(out.k, GT_M)), dim3(GT_THREADS), 0, s,
-                     ws.wn_final, ws.X0.as<double2>(), pl.ldx, pl.ldx, pl.len, out.k, pl.cnt, scale,
-                     ws.P.as<double2>(), (int64_t)pl.cnt, (int64_t)1);
-  HIP_LAUNCH_OK();
+  project(ws.wn_final, pl.ldx, ws.X0.as<double2>(), pl.ldx, pl.len, out.k, pl.cnt, scale, ws.P.as<double2>(),
+          pl.cnt, 1, ws.ahb_part(out.k, pl.cnt, pl.len, false), s);
   return out;
 }
 
@@ -846,7 +804,7 @@ static bool svd_split_chol(rcs_state_s& st, BuildWork& ws, const JacobiPlan& pl,
   ws.cflag.ensure(sizeof(int));
   HIP_OK(hipMemsetAsync(ws.cflag.p, 0, sizeof(int), s));
   chol_precondition(X, pl.ldx, len, n, ws.G.as<double2>(), ldg, ws.Rd.as<double2>(), ws.Y.as<double2>(), py.ldx,
-                    py.cnt_pad, ws.cflag.as<int>(), s);
+                    py.cnt_pad, ws.cflag.as<int>(), ws.ahb_part(n, n, len, true), s);
   HIP_OK(hipMemcpyAsync(&ws.host_rank->w, ws.host_rank_dev(), sizeof(double), hipMemcpyDeviceToHost, s));
   HIP_OK(hipMemcpyAsync(ws.host_rot, ws.cflag.p, sizeof(int), hipMemcpyDeviceToHost, s));
   HIP_OK(hipStreamSynchronize(s));
@@ -933,9 +891,7 @@ static bool svd_split_chol(rcs_state_s& st, BuildWork& ws, const JacobiPlan& pl,
   double2* src = Wn;
   double2* dst = Y;
   for (int it = 0; it < (use32 ? 2 : 0); ++it) {
-    RCS_PROBED_LAUNCH(kKcFactor, k_ns_gram, dim3(ceil_div(k, GT_N), ceil_div(k, GT_M)), dim3(GT_THREADS), 0, s, src,
-                       py.ldx, n, k, ws.H.as<double2>());
-    HIP_LAUNCH_OK();
+    ns_gram(src, py.ldx, n, k, ws.H.as<double2>(), ws.ahb_part(k, k, n, true), s);
     RCS_PROBED_LAUNCH(kKcFactor, k_ns_apply, dim3(ceil_div(k, GT_N), ceil_div(n, GT_M)), dim3(GT_THREADS), 0, s, src,
                        py.ldx, n, k, ws.H.as<double2>(), dst);
     HIP_LAUNCH_OK();
@@ -1016,6 +972,7 @@ struct QrWork {
   double* status;   // the largest entry of |H - I|, then the Cholesky's flag
   int ldg;
   static int pad(int n) { return (int)round_up(n, 64); }
+  static size_t factor_bytes(int n) { return 2 * (size_t)pad(n) * pad(n) * sizeof(double2); }   // G and Ri
   static size_t bytes(int n) {
     const size_t ldg = pad(n);
     return (3 * ldg * ldg + ldg * 64) * sizeof(double2) + 2 * sizeof(double);
@@ -1037,17 +994,17 @@ struct QrWork {
 // how many steps reach rounding level (e -> 3e^2/4 each): one for the
 // conditioning of ordinary sites, up to three.  Q1 goes to qa, further
 // iterates to qb and qa in turn (ld ldq); returns the one that holds Q.
-// host: two pinned or pageable doubles.
+// part: the partial tiles of split products, or null if they fit qa (for the
+// Gram, before Q1) and G and Ri (after).  host: two pinned or pageable doubles.
 static double2* cholqr_refined(const double2* X, int ldx, int len, int n, const QrWork& w, double2* qa, double2* qb,
-                               int ldq, double* host, hipStream_t s) {
+                               int ldq, double2* part, double* host, hipStream_t s) {
   HIP_OK(hipMemsetAsync(w.status, 0, 2 * sizeof(double), s));
-  cholqr(X, ldx, len, n, w.G, w.ldg, w.Rd, w.Ri, w.T, qa, ldq, reinterpret_cast<int*>(w.status + 1), s);
+  cholqr(X, ldx, len, n, w.G, w.ldg, w.Rd, w.Ri, w.T, qa, ldq, reinterpret_cast<int*>(w.status + 1),
+         part ? part : qa, s);
   double2* H = w.T;   // free after R^{-1}
   int steps = 3;
   for (int it = 0; it < steps; ++it) {
-    RCS_PROBED_LAUNCH(kKcFactor, k_ns_gram, dim3(ceil_div(n, GT_N), ceil_div(n, GT_M)), dim3(GT_THREADS), 0, s, qa, ldq,
-                       len, n, H);
-    HIP_LAUNCH_OK();
+    ns_gram(qa, ldq, len, n, H, part ? part : w.G, s);
     if (it == 0) {
       max_dev_identity(H, n, w.status, s);
       HIP_OK(hipMemcpyAsync(host, w.status, 2 * sizeof(double), hipMemcpyDeviceToHost, s));
@@ -1070,7 +1027,8 @@ static double2* cholqr_refined(const double2* X, int ldx, int len, int n, const 
 static bool move_cholqr(rcs_state_s& st, BuildWork& ws, const JacobiPlan& pl) {
   ws.qr.ensure(QrWork::bytes(pl.cnt));
   double2* q = cholqr_refined(ws.X0.as<double2>(), pl.ldx, pl.len, pl.cnt, QrWork(ws.qr.p, pl.cnt),
-                              ws.Wn.as<double2>(), ws.X.as<double2>(), pl.ldx, ws.host_status, st.stream);
+                              ws.Wn.as<double2>(), ws.X.as<double2>(), pl.ldx,
+                              ws.ahb_part(pl.cnt, pl.cnt, pl.len, true), ws.host_status, st.stream);
   if (q) ws.wn_final = q;
   return q != nullptr;
 }
@@ -1117,10 +1075,8 @@ static void move_center(rcs_state_s& st, BuildWork& ws, bool right) {
   } else if (!small && try_chol && move_cholqr(st, ws, pl)) {
     k = cnt;
     st.n_moves_cholqr += 1;
-    RCS_PROBED_LAUNCH(kKcFactor, k_project, dim3(ceil_div(cnt, GT_N), ceil_div(k, GT_M)), dim3(GT_THREADS), 0, s,
-                       ws.wn_final, ws.X0.as<double2>(), pl.ldx, pl.ldx, len, k, cnt, 1.0, ws.P.as<double2>(),
-                       (int64_t)cnt, (int64_t)1);
-    HIP_LAUNCH_OK();
+    project(ws.wn_final, pl.ldx, ws.X0.as<double2>(), pl.ldx, len, k, cnt, 1.0, ws.P.as<double2>(), cnt, 1,
+            ws.ahb_part(k, cnt, len, false), s);
   } else if (small) {
     k = svd_split_small(st, ws, pl, right ? st.cap[c + 1] : st.cap[c], 0.0, false, nullptr, true).k;
   } else {
@@ -1717,34 +1673,37 @@ rcs_status rcs_cholqr(int32_t len, int32_t cnt, const double* x_dev, double* q_d
   RCS_REQUIRE(x_dev && q_dev && r_dev, "null device pointer");
   RCS_REQUIRE(cnt >= 64 && cnt <= len && cnt <= rcs::SORT_MAX && len <= 16384, "bad matrix shape");
   hipStream_t s = rcs::as_stream(stream);
-  // Works from x and into q directly: one allocation (Q1 and the triangular
-  // matrices) instead of an SVD's workspace with padded copies: 4.8 -> 3.1 ms
-  // at 2048 x 1024.  An output that overlaps x gets a copy of x.
+  // Works from x and into q directly: only Q1 and the triangular matrices
+  // are allocated instead of an SVD's workspace with padded copies: 4.8 -> 3.1 ms
+  // at 2048 x 1024 (2.8 with split products).  An output that overlaps x gets a copy of x.
   const size_t xbytes = (size_t)len * cnt * sizeof(double2), rbytes = (size_t)cnt * cnt * sizeof(double2);
   auto overlaps = [&](const void* out, size_t n) {
     const uintptr_t x = reinterpret_cast<uintptr_t>(x_dev), o = reinterpret_cast<uintptr_t>(out);
     return o < x + xbytes && x < o + n;
   };
   const bool copy = overlaps(q_dev, xbytes) || overlaps(r_dev, rbytes);
+  // One allocation: beyond 64 MB in all, each costs about 300 us.  The partial
+  // tiles go where nothing is needed meanwhile, if they fit there.
+  const size_t qrbytes = rcs::QrWork::bytes(cnt), nelem = (size_t)len * cnt;
+  const size_t pbytes = std::max(rcs::ahb_part_bytes(cnt, cnt, len, true), rcs::ahb_part_bytes(cnt, cnt, len, false));
+  const bool share = pbytes <= std::min(xbytes, rcs::QrWork::factor_bytes(cnt));
   rcs::DevBuf buf;
-  buf.ensure(xbytes * (copy ? 2 : 1) + rcs::QrWork::bytes(cnt));
+  buf.ensure(xbytes * (copy ? 2 : 1) + qrbytes + (share ? 0 : pbytes));
   double2* q1 = buf.as<double2>();
-  const rcs::QrWork work(q1 + (size_t)len * cnt * (copy ? 2 : 1), cnt);
+  const rcs::QrWork work(q1 + nelem * (copy ? 2 : 1), cnt);
+  double2* part = share ? nullptr : q1 + nelem * (copy ? 2 : 1) + qrbytes / sizeof(double2);
   const double2* x = reinterpret_cast<const double2*>(x_dev);
   double2* q = reinterpret_cast<double2*>(q_dev);
   if (copy) {
-    HIP_OK(hipMemcpyAsync(q1 + (size_t)len * cnt, x, xbytes, hipMemcpyDeviceToDevice, s));
-    x = q1 + (size_t)len * cnt;
+    HIP_OK(hipMemcpyAsync(q1 + nelem, x, xbytes, hipMemcpyDeviceToDevice, s));
+    x = q1 + nelem;
   }
   double status[2];
-  const double2* got = rcs::cholqr_refined(x, len, len, cnt, work, q1, q, len, status, s);
+  const double2* got = rcs::cholqr_refined(x, len, len, cnt, work, q1, q, len, part, status, s);
   if (!got) rcs::fail(RCS_ERR_NUMERIC, "CholeskyQR: matrix rank deficient or too ill-conditioned");
   if (got != q) HIP_OK(hipMemcpyAsync(q, got, xbytes, hipMemcpyDeviceToDevice, s));
   // R = Q^H X, column-major
-  hipLaunchKernelGGL(rcs::k_project, dim3(rcs::ceil_div(cnt, rcs::GT_N), rcs::ceil_div(cnt, rcs::GT_M)),
-                     dim3(rcs::GT_THREADS), 0, s, q, x, len, len, len, cnt, cnt, 1.0,
-                     reinterpret_cast<double2*>(r_dev), (int64_t)1, (int64_t)cnt);
-  HIP_LAUNCH_OK();
+  rcs::project(q, len, x, len, len, cnt, cnt, 1.0, reinterpret_cast<double2*>(r_dev), 1, cnt, part ? part : work.G, s);
   HIP_OK(hipStreamSynchronize(s));
   RCS_API_END
 }

@@ -13,14 +13,23 @@ namespace rcs {
 // zero-padded.  *flag_dev is set to 1 (never cleared here) when a pivot is
 // not positive, i.e. X is numerically rank deficient.
 void chol_precondition(const double2* X, int ldx, int len, int n, double2* G, int ldg, double2* Rd, double2* Y,
-                       int ldy, int ycols, int* flag_dev, hipStream_t s);
+                       int ldy, int ycols, int* flag_dev, double2* part, hipStream_t s);
 // CholeskyQR: R from the Cholesky factor of X^H X (X: len x n, ld ldx),
 // R^{-1} in Ri (ldg x ldg, upper, by recursive doubling of its 64 x 64
 // diagonal blocks; T is ldg x ldg scratch), Q = X R^{-1} (ld ldq).  Q is
 // orthonormal up to about u cond(X)^2; *flag_dev is set on a non-positive
 // pivot.
 void cholqr(const double2* X, int ldx, int len, int n, double2* G, int ldg, double2* Rd, double2* Ri, double2* T,
-            double2* Q, int ldq, int* flag_dev, hipStream_t s);
+            double2* Q, int ldq, int* flag_dev, double2* part, hipStream_t s);
+// Bytes of `part`, the partial tiles of a product A^H B (K x M, K x N; upper:
+// only the upper triangle of tiles) split over K; `part` of the calls above is
+// for (n, n, len, true), and may be null where this is 0.
+size_t ahb_part_bytes(int M, int N, int K, bool upper);
+// H (k x k, row-major) = (3 I - Q^H Q) / 2, Q: len x k (ld ldq).
+void ns_gram(const double2* Q, int ldq, int len, int k, double2* H, double2* part, hipStream_t s);
+// P (k x cnt, element (m, n) at m pm + n pn) = scale Q^H X.
+void project(const double2* Q, int ldq, const double2* X, int ldx, int len, int k, int cnt, double scale, double2* P,
+             int64_t pm, int64_t pn, double2* part, hipStream_t s);
 // *dev = max entry of |H - I|, H k x k row-major (one workgroup).
 void max_dev_identity(const double2* H, int k, double* dev, hipStream_t s);
 // P (k x len, row-major) = scale (X U)^H; X len x n (ld ldx), U n x k (ld ldu).

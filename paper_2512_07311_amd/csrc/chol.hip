@@ -32,29 +32,143 @@ namespace rcs {
 
 constexpr int CB = 64;          // Cholesky block
 
-// G (ld ldg, column-major) = X^H X over the upper tiles (blockIdx.y <=
-// blockIdx.x); entries outside n x n are the identity's.
-__global__ __launch_bounds__(GT_THREADS) void k_gram_upper(const double2* X, int ldx, int len, int n,
-                                                          double2* G, int ldg) {
-  if (blockIdx.y > blockIdx.x) return;
+// Products C = A^H B over long columns (A: K x M, B: K x N, column-major).
+// Up to about a thousand columns there are too few 64 x 64 tiles to fill the
+// chip (136 on and above the diagonal at 1024 columns, 36 at 512, for 256
+// compute units), so a tile's K range is split, units write partial tiles, and
+// a second launch sums each tile's in order; one unit per tile stores its
+// result itself.  Upper: only tiles on and above the diagonal (M = N).
+// Bound: the fp64 matrix cores.  Measured: Gram of 2048 x 1024 in 3 ranges 221
+// us instead of 330 (whole tiles, both triangles 336); the 20-qubit build at
+// bond 512, whose Grams have 36 tiles and fewer, 234 -> 221 ms.
+constexpr int AHB_MIN_K = 128;     // rows of a unit, at least
+constexpr int AHB_UNITS = 576;     // units of a split product, at most (64 KB of partials each)
+
+// Tile t of a product: row-major over all tiles, or over the upper triangle.
+__device__ inline void ahb_tile(int t, int nbn, int upper, int& tm, int& tn) {
+  if (!upper) {
+    tm = t / nbn;
+    tn = t % nbn;
+    return;
+  }
+  tm = 0;
+  while (t >= nbn - tm) {
+    t -= nbn - tm;
+    ++tm;
+  }
+  tn = tm + t;
+}
+template <class Store>
+__global__ __launch_bounds__(GT_THREADS) void k_ahb(const double2* A, int lda, const double2* B, int ldb, int K, int M,
+                                                   int N, int nbn, int upper, int kper, double2* part, Store store) {
   __shared__ SmemC64 sm;
-  const int m0 = blockIdx.y * GT_M, n0 = blockIdx.x * GT_N;
-  auto fa = [&](int m, int kk) -> double2 {
-    const double2 v = X[(int64_t)m * ldx + kk];
+  int tm, tn;
+  ahb_tile(blockIdx.x, nbn, upper, tm, tn);
+  const int m0 = tm * GT_M, n0 = tn * GT_N, k0 = blockIdx.y * kper, kn = min(kper, K - k0);
+  auto fa = [&](int m, int k) -> double2 {
+    const double2 v = A[(int64_t)m * lda + k0 + k];
     return make_double2(v.x, -v.y);
   };
-  auto fb = [&](int kk, int c) -> double2 { return X[(int64_t)c * ldx + kk]; };
-  LoadA<decltype(fa), true> la{fa, m0, n, len};
-  LoadB<decltype(fb), false> lb{fb, n0, len, n};
+  auto fb = [&](int k, int n) -> double2 { return B[(int64_t)n * ldb + k0 + k]; };
+  LoadA<decltype(fa), true> la{fa, m0, M, kn};
+  LoadB<decltype(fb), false> lb{fb, n0, kn, N};
   AccC64 acc;
   acc_zero(acc);
-  cgemm_mainloop(la, lb, len, sm, acc);
-  acc_foreach(acc, [&](int r, int c, double re, double im) {
-    const int m = m0 + r, col = n0 + c;
-    double2 v = make_double2(re, im);
-    if (m >= n || col >= n) v = make_double2(m == col ? 1.0 : 0.0, 0.0);
-    G[(int64_t)col * ldg + m] = v;
-  });
+  cgemm_mainloop(la, lb, kn, sm, acc);
+  if (gridDim.y == 1) {
+    acc_foreach(acc, [&](int r, int c, double re, double im) { store(m0 + r, n0 + c, make_double2(re, im)); });
+    return;
+  }
+  double2* out = part + ((int64_t)blockIdx.y * gridDim.x + blockIdx.x) * (GT_M * GT_N);
+  acc_foreach(acc, [&](int r, int c, double re, double im) { out[r * GT_N + c] = make_double2(re, im); });
+}
+template <class Store>
+__global__ void k_ahb_sum(const double2* part, int splits, int nbn, int upper, Store store) {
+  int tm, tn;
+  ahb_tile(blockIdx.x, nbn, upper, tm, tn);
+  const int e = blockIdx.y * blockDim.x + threadIdx.x;
+  const double2* p = part + (int64_t)blockIdx.x * (GT_M * GT_N) + e;
+  double2 s = p[0];
+  for (int q = 1; q < splits; ++q) {
+    const double2 v = p[(int64_t)q * gridDim.x * (GT_M * GT_N)];
+    s.x += v.x;
+    s.y += v.y;
+  }
+  store(tm * GT_M + e / GT_N, tn * GT_N + e % GT_N, s);
+}
+
+namespace {
+struct StoreGram {   // G (column-major), the identity beyond n
+  double2* G;
+  int ldg, n;
+  __device__ void operator()(int m, int c, double2 v) const {
+    if (m >= n || c >= n) v = make_double2(m == c ? 1.0 : 0.0, 0.0);
+    G[(int64_t)c * ldg + m] = v;
+  }
+};
+struct StoreNs {     // H = (3 I - C) / 2 (row-major), both triangles
+  double2* H;
+  int k;
+  __device__ void operator()(int m, int c, double2 v) const {
+    if (m >= k || c >= k) return;
+    const double2 h = make_double2((m == c ? 1.5 : 0.0) - 0.5 * v.x, -0.5 * v.y);
+    H[(int64_t)m * k + c] = h;
+    if (m / GT_M != c / GT_N) H[(int64_t)c * k + m] = make_double2(h.x, -h.y);
+  }
+};
+struct StoreP {      // scale C at m pm + c pn
+  double2* P;
+  int M, N;
+  int64_t pm, pn;
+  double scale;
+  __device__ void operator()(int m, int c, double2 v) const {
+    if (m < M && c < N) P[m * pm + c * pn] = make_double2(v.x * scale, v.y * scale);
+  }
+};
+
+int ahb_tiles(int M, int N, bool upper) {
+  const int nbm = ceil_div(M, GT_M), nbn = ceil_div(N, GT_N);
+  return upper ? nbn * (nbn + 1) / 2 : nbm * nbn;
+}
+// The number of K ranges that leaves the fewest rounds of the chip, a little
+// charged for each range's partials.
+int ahb_splits(int tiles, int K) {
+  int best = 1;
+  double cost = 1e30;
+  for (int s = 1; s == 1 || (s <= 16 && s * AHB_MIN_K <= K && s * tiles <= AHB_UNITS); ++s) {
+    const double c = (double)ceil_div(tiles * s, 256) / s + 0.02 * s;
+    if (c < cost) {
+      cost = c;
+      best = s;
+    }
+  }
+  return best;
+}
+template <class Store>
+void ahb(const double2* A, int lda, const double2* B, int ldb, int K, int M, int N, bool upper, double2* part,
+         const Store& store, hipStream_t s) {
+  const int nbn = ceil_div(N, GT_N), tiles = ahb_tiles(M, N, upper);
+  const int kper = (int)round_up(ceil_div(K, ahb_splits(tiles, K)), GT_K), splits = ceil_div(K, kper);
+  RCS_PROBED_LAUNCH(kKcFactor, k_ahb<Store>, dim3(tiles, splits), dim3(GT_THREADS), 0, s, A, lda, B, ldb, K, M, N, nbn,
+                    upper ? 1 : 0, kper, part, store);
+  HIP_LAUNCH_OK();
+  if (splits == 1) return;
+  RCS_PROBED_LAUNCH(kKcFactor, k_ahb_sum<Store>, dim3(tiles, GT_M * GT_N / 256), dim3(256), 0, s, part, splits, nbn,
+                    upper ? 1 : 0, store);
+  HIP_LAUNCH_OK();
+}
+}  // namespace
+
+size_t ahb_part_bytes(int M, int N, int K, bool upper) {
+  const int tiles = ahb_tiles(M, N, upper), splits = ahb_splits(tiles, K);
+  return splits > 1 ? (size_t)tiles * splits * GT_M * GT_N * sizeof(double2) : 0;
+}
+void ns_gram(const double2* Q, int ldq, int len, int k, double2* H, double2* part, hipStream_t s) {
+  ahb(Q, ldq, Q, ldq, len, k, k, true, part, StoreNs{H, k}, s);
+}
+void project(const double2* Q, int ldq, const double2* X, int ldx, int len, int k, int cnt, double scale, double2* P,
+             int64_t pm, int64_t pn, double2* part, hipStream_t s) {
+  ahb(Q, ldq, X, ldx, len, k, cnt, false, part, StoreP{P, k, cnt, pm, pn, scale}, s);
 }
 
 __device__ inline double2 cmul_c(double2 a, double2 b) {
@@ -322,11 +436,10 @@ __global__ void k_chol_to_y(const double2* G, int ldg, const double2* Rd, int n,
 // Gram and blocked Cholesky (R's off-diagonal blocks in G, diagonal blocks
 // in Rd, diagonal blocks of R^{-1} in Ri when Ri is not null).
 static void gram_cholesky(const double2* X, int ldx, int len, int n, double2* G, int ldg, double2* Rd, double2* Ri,
-                          int* flag_dev, hipStream_t s) {
+                          int* flag_dev, double2* part, hipStream_t s) {
   RCS_REQUIRE(ldg % CB == 0 && ldg >= n, "Gram leading dimension must be a multiple of 64");
   const int nb = ldg / CB;
-  RCS_PROBED_LAUNCH(kKcFactor, k_gram_upper, dim3(nb, nb), dim3(GT_THREADS), 0, s, X, ldx, len, n, G, ldg);
-  HIP_LAUNCH_OK();
+  ahb(X, ldx, X, ldx, len, n, n, true, part, StoreGram{G, ldg, n}, s);
   for (int jb = 0; jb < nb; ++jb) {
     RCS_PROBED_LAUNCH(kKcFactor, k_chol_panel, dim3(nb - jb), dim3(PANEL_THREADS), 0, s, G, ldg, jb, flag_dev, Rd, Ri);
     HIP_LAUNCH_OK();
@@ -339,8 +452,8 @@ static void gram_cholesky(const double2* X, int ldx, int len, int n, double2* G,
 }
 
 void chol_precondition(const double2* X, int ldx, int len, int n, double2* G, int ldg, double2* Rd, double2* Y,
-                       int ldy, int ycols, int* flag_dev, hipStream_t s) {
-  gram_cholesky(X, ldx, len, n, G, ldg, Rd, nullptr, flag_dev, s);
+                       int ldy, int ycols, int* flag_dev, double2* part, hipStream_t s) {
+  gram_cholesky(X, ldx, len, n, G, ldg, Rd, nullptr, flag_dev, part, s);
   const int64_t tot = (int64_t)ldy * ycols;
   RCS_PROBED_LAUNCH(kKcFactor, k_chol_to_y, dim3((unsigned)std::min<int64_t>((tot + 255) / 256, 65535)), dim3(256), 0, s, G,
                      ldg, Rd, n, Y, ldy, ycols);
@@ -349,23 +462,31 @@ void chol_precondition(const double2* X, int ldx, int len, int n, double2* G, in
 
 // Batched column-major complex GEMM on sub-blocks: for batch z,
 // D_z = alpha A_z B_z with A_z = A + z sa (M x K, ld lda), B_z = B + z sb
-// (K x N, ld ldb), D_z = D + z sd (M x N, ld ldd), overwritten.
+// (K x N, ld ldb), D_z = D + z sd (M x N, ld ldd), overwritten.  kUpperA /
+// kUpperB: that operand is upper triangular, and the K range it leaves zero in
+// a tile is not gone through (half of the work).
+enum { kGeneral, kUpperA, kUpperB };
 __global__ __launch_bounds__(GT_THREADS) void k_cgemm_cm(const double2* A, int lda, int64_t sa, const double2* B,
                                                         int ldb, int64_t sb, double2* D, int ldd, int64_t sd, int M,
-                                                        int N, int K, double alpha) {
+                                                        int N, int K, double alpha, int upper) {
   __shared__ SmemC64 sm;
   const int64_t z = blockIdx.z;
   const double2* a = A + z * sa;
   const double2* b = B + z * sb;
   double2* d = D + z * sd;
-  const int m0 = blockIdx.y * GT_M, n0 = blockIdx.x * GT_N;
-  auto fa = [&](int m, int k) -> double2 { return a[(int64_t)k * lda + m]; };
-  auto fb = [&](int k, int n) -> double2 { return b[(int64_t)n * ldb + k]; };
-  LoadA<decltype(fa), false> la{fa, m0, M, K};
-  LoadB<decltype(fb), false> lb{fb, n0, K, N};
+  // a triangular B's columns from the longest in the launch's first half and
+  // from the shortest in its second, so that a compute unit with one tile of
+  // each has about the average work
+  const bool flip = upper == kUpperB && 2 * blockIdx.y < gridDim.y;
+  const int m0 = blockIdx.y * GT_M, n0 = (flip ? (int)(gridDim.x - 1 - blockIdx.x) : (int)blockIdx.x) * GT_N;
+  const int k0 = upper == kUpperA ? m0 : 0, kn = (upper == kUpperB ? min(K, n0 + GT_N) : K) - k0;
+  auto fa = [&](int m, int k) -> double2 { return a[(int64_t)(k0 + k) * lda + m]; };
+  auto fb = [&](int k, int n) -> double2 { return b[(int64_t)n * ldb + k0 + k]; };
+  LoadA<decltype(fa), false> la{fa, m0, M, kn};
+  LoadB<decltype(fb), false> lb{fb, n0, kn, N};
   AccC64 acc;
   acc_zero(acc);
-  cgemm_mainloop(la, lb, K, sm, acc);
+  cgemm_mainloop(la, lb, kn, sm, acc);
   acc_foreach(acc, [&](int r, int c, double re, double im) {
     const int m = m0 + r, n = n0 + c;
     if (m < M && n < N) d[(int64_t)n * ldd + m] = make_double2(alpha * re, alpha * im);
@@ -373,10 +494,10 @@ __global__ __launch_bounds__(GT_THREADS) void k_cgemm_cm(const double2* A, int l
 }
 
 static void cgemm_cm(const double2* A, int lda, int64_t sa, const double2* B, int ldb, int64_t sb, double2* D,
-                     int ldd, int64_t sd, int M, int N, int K, double alpha, int batch, hipStream_t s) {
+                     int ldd, int64_t sd, int M, int N, int K, double alpha, int batch, int upper, hipStream_t s) {
   if (batch <= 0 || M <= 0 || N <= 0) return;
   RCS_PROBED_LAUNCH(kKcFactor, k_cgemm_cm, dim3(ceil_div(N, GT_N), ceil_div(M, GT_M), batch), dim3(GT_THREADS), 0, s, A, lda,
-                     sa, B, ldb, sb, D, ldd, sd, M, N, K, alpha);
+                     sa, B, ldb, sb, D, ldd, sd, M, N, K, alpha, upper);
   HIP_LAUNCH_OK();
 }
 
@@ -391,25 +512,25 @@ static void triangular_inverse(const double2* G, int ldg, double2* Ri, double2* 
     const int64_t stride = (int64_t)2 * h * ldg + 2 * h;
     // T_AC = R_AC R^{-1}_CC, then Ri_AC = -R^{-1}_AA T_AC
     cgemm_cm(G + (int64_t)h * ldg, ldg, stride, Ri + (int64_t)h * ldg + h, ldg, stride, T + (int64_t)h * ldg, ldg,
-             stride, h, h, h, 1.0, full, s);
+             stride, h, h, h, 1.0, full, kUpperB, s);
     cgemm_cm(Ri, ldg, stride, T + (int64_t)h * ldg, ldg, stride, Ri + (int64_t)h * ldg, ldg, stride, h, h, h, -1.0,
-             full, s);
+             full, kUpperA, s);
     const int hc = ldg - tail0 - h;
     if (hc > 0) {
       const int64_t a0 = (int64_t)tail0 * ldg + tail0, c0 = (int64_t)(tail0 + h) * ldg + (tail0 + h);
       const int64_t ac = (int64_t)(tail0 + h) * ldg + tail0;
-      cgemm_cm(G + ac, ldg, 0, Ri + c0, ldg, 0, T + ac, ldg, 0, h, hc, hc, 1.0, 1, s);
-      cgemm_cm(Ri + a0, ldg, 0, T + ac, ldg, 0, Ri + ac, ldg, 0, h, hc, h, -1.0, 1, s);
+      cgemm_cm(G + ac, ldg, 0, Ri + c0, ldg, 0, T + ac, ldg, 0, h, hc, hc, 1.0, 1, kUpperB, s);
+      cgemm_cm(Ri + a0, ldg, 0, T + ac, ldg, 0, Ri + ac, ldg, 0, h, hc, h, -1.0, 1, kUpperA, s);
     }
   }
 }
 
 void cholqr(const double2* X, int ldx, int len, int n, double2* G, int ldg, double2* Rd, double2* Ri, double2* T,
-            double2* Q, int ldq, int* flag_dev, hipStream_t s) {
+            double2* Q, int ldq, int* flag_dev, double2* part, hipStream_t s) {
   HIP_OK(hipMemsetAsync(Ri, 0, (size_t)ldg * ldg * sizeof(double2), s));
-  gram_cholesky(X, ldx, len, n, G, ldg, Rd, Ri, flag_dev, s);
+  gram_cholesky(X, ldx, len, n, G, ldg, Rd, Ri, flag_dev, part, s);
   triangular_inverse(G, ldg, Ri, T, s);
-  cgemm_cm(X, ldx, 0, Ri, ldg, 0, Q, ldq, 0, len, n, n, 1.0, 1, s);
+  cgemm_cm(X, ldx, 0, Ri, ldg, 0, Q, ldq, 0, len, n, n, 1.0, 1, kUpperB, s);
 }
 
 // *dev = max over entries of |H - I| (H k x k, row-major); *dev must be 0

@@ -56,3 +56,18 @@ def test_q_in_place_of_x(env, cond):
     rcs.cholqr(x, q, r)
     rcs.cholqr(x, x, r2)
     assert torch.equal(q, x) and torch.equal(r, r2)
+
+
+@pytest.mark.parametrize("ln,cnt", [(256, 64), (517, 65), (1030, 130), (2050, 64)])
+def test_qr_split_products(env, ln, cnt):
+    """K ranges of the split products that end within a 16-row stage, and the
+    most ranges; the bars of test_qr_edges."""
+    rcs, torch = env
+    M = inputs.planted_matrix(ln, cnt, np.geomspace(1.0, 1e-3, cnt), seed=ln)
+    x = torch.from_numpy(np.ascontiguousarray(M.T)).cuda()
+    q = torch.zeros(cnt, ln, dtype=torch.complex128, device="cuda")
+    r = torch.zeros(cnt, cnt, dtype=torch.complex128, device="cuda")
+    rcs.cholqr(x, q, r)
+    Q, R = q.cpu().numpy().T, r.cpu().numpy().T
+    assert np.abs(Q.conj().T @ Q - np.eye(cnt)).max() < 1e-13
+    assert np.linalg.norm(M - Q @ R) <= 1e-14 * np.linalg.norm(M) * np.sqrt(cnt)
