@@ -85,10 +85,11 @@ def source_hash(kernel):
 
 # kernels of the fp64 factorisation stage (Jacobi passes and the probed
 # factorisation class) and the sources that hold them
-STAGE_KERNELS = ("k_jac_gram", "k_jac_rotate", "k_cgemm_cm", "k_chol_panel", "k_chol_to_y", "k_chol_update",
-                 "k_colnorm", "k_gather_normalize", "k_gram_upper", "k_max_dev_identity", "k_ns_apply", "k_ns_gram",
-                 "k_permute_cols", "k_project", "k_project_rows", "k_sort_rank", "k_sum_sq", "k_unpermute_rows")
-STAGE_SOURCES = ("jacobi.hip", "chol.hip", "build.hip")
+STAGE_KERNELS = ("k_jac_gram", "k_jac_rotate", "k_jac_rotate_rows", "k_jac_rotate_cross", "k_split_small",
+                 "k_qr_small", "k_ahb", "k_ahb_sum", "k_cgemm_cm", "k_chol_panel", "k_chol_to_y", "k_chol_update",
+                 "k_colnorm", "k_gather_normalize", "k_max_dev_identity", "k_ns_apply", "k_permute_cols",
+                 "k_project_rows", "k_sort_rank", "k_sum_sq", "k_unpermute_rows")
+STAGE_SOURCES = ("jacobi.hip", "jacobi_dev.h", "split_small.hip", "chol.hip", "build.hip")
 
 
 def stage_hash():

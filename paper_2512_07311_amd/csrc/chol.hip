@@ -24,6 +24,8 @@
 //                  matrix, on the matrix cores.
 // G is stored column-major with ld = round_up(n, 64); the padding carries an
 // identity diagonal so that the padded matrix factors as blockdiag(R, I).
+#include <utility>
+
 #include "chol.h"
 #include "gemm_f64.h"
 #include "prof.h"
@@ -184,9 +186,8 @@ __device__ inline double2 cmul_hc(double2 a, double2 b) {
 // the block row along (R_jt = R^{-H} G_jt), workgroup 0 stores R_jj
 // (column-major in Rd) and, when Ri is given, the diagonal block of R^{-1}.
 // A step:
-//   factor  one wave factors the 16 x 16 diagonal block in registers (four
-//           rows of a column per lane, rows handed around by shuffles: no
-//           barrier in the 16-step chain), R^{-H} with it;
+//   factor  one wave factors the 16 x 16 diagonal block in registers (a column
+//           per lane: no barrier in the 16-step chain), R^{-H} with it;
 //   solve   the other blocks of the block row, times the inverse, and
 //   update  the rows below, both as 16 x 16 matrix-core products, one block
 //           per wave.
@@ -194,7 +195,8 @@ __device__ inline double2 cmul_hc(double2 a, double2 b) {
 //
 // Bound: the chain of 64 pivots (sqrt, division and a shuffle each).  Two
 // barriers per pivot and per substitution row, with every thread's terms read
-// from LDS, took 112 us per panel; this form takes 39 us.
+// from LDS, took 112 us per panel; this form with four rows of a column per
+// lane, handed around by shuffles, 39 us, and with whole columns 32 us.
 constexpr int PANEL_THREADS = 512;
 constexpr int PW = 16;                     // inner block
 constexpr int PLD = CB + 1;
@@ -219,51 +221,60 @@ __device__ inline void load_block64(const double2* G, int ldg, int row0, int col
 
 __device__ inline double2 shfl2(double2 v, int lane) { return make_double2(__shfl(v.x, lane), __shfl(v.y, lane)); }
 
+// a -= conj(t_I) s, t_I from lane I of the 16-lane row.
+template <int I>
+__device__ __forceinline__ void eliminate(double2& a, const double2& t, const double2& s) {
+  asm("s_nop 1\n\t"
+      "v_fmac_f64_dpp %0, -%2, %4 row_newbcast:%6 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %1, -%2, %5 row_newbcast:%6 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %0, -%3, %5 row_newbcast:%6 row_mask:0xf bank_mask:0xf\n\t"
+      "v_fmac_f64_dpp %1, %3, %4 row_newbcast:%6 row_mask:0xf bank_mask:0xf"
+      : "+v"(a.x), "+v"(a.y)
+      : "v"(t.x), "v"(t.y), "v"(s.x), "v"(s.y), "n"(I));
+}
+template <int K, int... J>
+__device__ __forceinline__ void pivot_row(double2 (&a)[PW], int c, bool& bad, std::integer_sequence<int, J...>) {
+  const double2 t = shfl2(a[K], c);   // row K of G in every 16-lane row
+  double d = __shfl(t.x, K);
+  if (!(d > 0.0) || !(d < 1e300)) {
+    d = 1.0;
+    bad = true;
+  }
+  const double inv = rsqrt_fast(d);
+  const double2 r = make_double2(a[K].x * inv, a[K].y * inv), s = make_double2(r.x * inv, r.y * inv);
+  (eliminate<K + 1 + J>(a[K + 1 + J], t, s), ...);
+  a[K] = r;
+}
+template <int... K>
+__device__ __forceinline__ void pivot_rows(double2 (&a)[PW], int c, bool& bad, std::integer_sequence<int, K...>) {
+  (pivot_row<K>(a, c, bad, std::make_integer_sequence<int, PW - 1 - K>{}), ...);
+}
+
 // One wave: R^H R = T[k0.., k0..] (16 x 16, upper triangle used), R into T and
 // R^{-H} (zero above the diagonal) into W.  The elimination runs on [G | I]:
-// the row operations that turn G into R turn I into R^{-H}.
+// the row operations that turn G into R turn I into R^{-H}.  A lane holds one
+// of the 32 columns (the wave's upper half repeats the lower one), and a
+// pivot's multipliers are broadcast by the FMAs that use them.
 __device__ inline void factor16(double2 (*T)[PLD], int k0, double2 (*W)[PW + 1], int lane, int* flag) {
-  const int c = lane & 15, g = lane >> 4;
-  double2 a[4], b[4];
+  const int c = lane & 15;
+  const bool left = (lane & 16) == 0;   // a column of G, else of I
+  double2 a[PW];
 #pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    a[j] = T[k0 + 4 * g + j][k0 + c];
-    b[j] = make_double2(4 * g + j == c ? 1.0 : 0.0, 0.0);
+  for (int i = 0; i < PW; ++i) {
+    const double2 g = T[k0 + i][k0 + c];
+    a[i] = left ? g : make_double2(i == c ? 1.0 : 0.0, 0.0);
   }
+  bool bad = false;
+  pivot_rows(a, c, bad, std::make_integer_sequence<int, PW>{});
+  if (bad && lane == 0) atomicExch(flag, 1);
+  if (lane >= 32) return;
 #pragma unroll
-  for (int k = 0; k < PW; ++k) {
-    const int own = (k >> 2) * 16;          // lanes holding row k
-    double d = __shfl(a[k & 3].x, own + k);
-    const bool bad = !(d > 0.0) || !(d < 1e300);
-    if (bad) {
-      d = 1.0;
-      if (lane == 0) atomicExch(flag, 1);
+  for (int i = 0; i < PW; ++i) {
+    if (left) {
+      if (c >= i) T[k0 + i][k0 + c] = c == i ? make_double2(a[i].x, 0.0) : a[i];
+    } else {
+      W[i][c] = c <= i ? a[i] : make_double2(0.0, 0.0);
     }
-    const double inv = rsqrt_fast(d);
-    double2 xc = shfl2(a[k & 3], own + c), bc = shfl2(b[k & 3], own + c);
-    xc = make_double2(xc.x * inv, xc.y * inv);
-    bc = make_double2(bc.x * inv, bc.y * inv);
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int row = 4 * g + j;
-      double2 xr = shfl2(a[k & 3], own + row);
-      xr = make_double2(xr.x * inv, xr.y * inv);
-      if (row > k) {
-        const double2 p = cmul_hc(xr, xc), q = cmul_hc(xr, bc);
-        a[j] = make_double2(a[j].x - p.x, a[j].y - p.y);
-        b[j] = make_double2(b[j].x - q.x, b[j].y - q.y);
-      }
-    }
-    if (g == (k >> 2)) {
-      a[k & 3] = c == k ? make_double2(d * inv, 0.0) : xc;
-      b[k & 3] = bc;
-    }
-  }
-#pragma unroll
-  for (int j = 0; j < 4; ++j) {
-    const int row = 4 * g + j;
-    if (c >= row) T[k0 + row][k0 + c] = a[j];
-    W[row][c] = c <= row ? b[j] : make_double2(0.0, 0.0);
   }
 }
 
