@@ -707,8 +707,14 @@ static SplitResult svd_split(rcs_state_s& st, BuildWork& ws, const JacobiPlan& p
 }
 
 // svd_split of a small matrix in one launch; X is read from ws.X0 only.
+// dst: the sites the factors go to, or null for ws.wn_final and ws.P.
+struct SmallSites {
+  double2 *ai, *aj;
+  int dl, dr, side;
+};
 static SplitResult svd_split_small(rcs_state_s& st, BuildWork& ws, const JacobiPlan& pl, int cap, double eps,
-                                   bool renorm, std::vector<double>* spectrum_out, bool ortho_only) {
+                                   bool renorm, std::vector<double>* spectrum_out, bool ortho_only,
+                                   const SmallSites* dst) {
   hipStream_t s = st.stream;
   const JacobiTol t = jacobi_tol(pl.len, ortho_only ? 1e-7 : 0.0);
   SplitSmallArgs a{};
@@ -728,9 +734,15 @@ static SplitResult svd_split_small(rcs_state_s& st, BuildWork& ws, const JacobiP
   a.wn = ws.Wn.as<double2>();
   a.p = ws.P.as<double2>();
   a.sorted = ws.sorted.as<double>();
-  a.out = ws.scal.as<RankOut>();
+  if (dst) {
+    a.ai = dst->ai;
+    a.aj = dst->aj;
+    a.dl = dst->dl;
+    a.dr = dst->dr;
+    a.side = dst->side;
+  }
+  a.out = ws.host_rank;   // pinned: the kernel writes it there itself
   split_small(a, s);
-  HIP_OK(hipMemcpyAsync(ws.host_rank, ws.scal.p, sizeof(RankOut), hipMemcpyDeviceToHost, s));
   HIP_OK(hipStreamSynchronize(s));
   const RankOut r = *ws.host_rank;
   if (r.sweeps < 0) fail(RCS_ERR_NUMERIC, "one-sided Jacobi SVD did not converge");
@@ -1033,16 +1045,12 @@ static bool move_cholqr(rcs_state_s& st, BuildWork& ws, const JacobiPlan& pl) {
   return q != nullptr;
 }
 
-// The same in one launch for a small site, P included.
-static bool move_cholqr_small(rcs_state_s& st, BuildWork& ws, const JacobiPlan& pl) {
-  hipStream_t s = st.stream;
-  ws.cflag.ensure(sizeof(int));
-  qr_small(QrSmallArgs{ws.X0.as<double2>(), pl.ldx, pl.len, pl.cnt, 1e-4, ws.Wn.as<double2>(), ws.P.as<double2>(),
-                       ws.cflag.as<int>()},
-           s);
-  HIP_OK(hipMemcpyAsync(ws.host_rot, ws.cflag.p, sizeof(int), hipMemcpyDeviceToHost, s));
-  HIP_OK(hipStreamSynchronize(s));
-  ws.wn_final = ws.Wn.as<double2>();
+// The same in one launch for a small site: Q in its place, P in ws.P.
+static bool move_cholqr_small(rcs_state_s& st, BuildWork& ws, double2* site, int dl, int dr, bool right) {
+  const int len = right ? 2 * dl : 2 * dr, cnt = right ? dr : dl;
+  const MatView x = right ? MatView{site, 0, dr, 1, len, 0} : MatView{site, (int64_t)dl * dr, 1, dr, dr, 1};
+  qr_small(QrSmallArgs{x, len, cnt, 1e-4, ws.P.as<double2>(), ws.host_rot}, st.stream);
+  HIP_OK(hipStreamSynchronize(st.stream));
   return *ws.host_rot != 0;
 }
 
@@ -1058,18 +1066,20 @@ static void move_center(rcs_state_s& st, BuildWork& ws, bool right) {
   const int cnt = right ? dr : dl;
   JacobiPlan pl = jacobi_plan(len, cnt);
   ensure_work(ws, pl);
-  // the one-launch forms read their input with bounds: no padding to clear
-  const bool small = split_small_fits(len, cnt);
-  if (!small) {
-    HIP_OK(hipMemsetAsync(ws.X.p, 0, (size_t)pl.ldx * pl.cnt_pad * sizeof(double2), s));
-    HIP_OK(hipMemsetAsync(ws.X0.p, 0, (size_t)pl.ldx * pl.cnt_pad * sizeof(double2), s));
+  const bool small = split_small_fits(len, cnt), try_chol = cholqr_moves_enabled() && cnt >= 2 && cnt <= len;
+  const bool in_place = small && try_chol && move_cholqr_small(st, ws, st.site[c], dl, dr, right);
+  if (!in_place) {
+    // the one-launch split reads its input with bounds: no padding to clear
+    if (!small) {
+      HIP_OK(hipMemsetAsync(ws.X.p, 0, (size_t)pl.ldx * pl.cnt_pad * sizeof(double2), s));
+      HIP_OK(hipMemsetAsync(ws.X0.p, 0, (size_t)pl.ldx * pl.cnt_pad * sizeof(double2), s));
+    }
+    hipLaunchKernelGGL(k_load_site, dim3(grid1d((int64_t)2 * dl * dr)), dim3(256), 0, s, st.site[c], dl, dr,
+                       right ? 1 : 0, ws.X.as<double2>(), ws.X0.as<double2>(), pl.ldx);
+    HIP_LAUNCH_OK();
   }
-  hipLaunchKernelGGL(k_load_site, dim3(grid1d((int64_t)2 * dl * dr)), dim3(256), 0, s, st.site[c], dl, dr,
-                     right ? 1 : 0, ws.X.as<double2>(), ws.X0.as<double2>(), pl.ldx);
-  HIP_LAUNCH_OK();
-  const bool try_chol = cholqr_moves_enabled() && cnt >= 2 && cnt <= len;
   int k;
-  if (small && try_chol && move_cholqr_small(st, ws, pl)) {
+  if (in_place) {
     k = cnt;
     st.n_moves_cholqr += 1;
   } else if (!small && try_chol && move_cholqr(st, ws, pl)) {
@@ -1078,7 +1088,7 @@ static void move_center(rcs_state_s& st, BuildWork& ws, bool right) {
     project(ws.wn_final, pl.ldx, ws.X0.as<double2>(), pl.ldx, len, k, cnt, 1.0, ws.P.as<double2>(), cnt, 1,
             ws.ahb_part(k, cnt, len, false), s);
   } else if (small) {
-    k = svd_split_small(st, ws, pl, right ? st.cap[c + 1] : st.cap[c], 0.0, false, nullptr, true).k;
+    k = svd_split_small(st, ws, pl, right ? st.cap[c + 1] : st.cap[c], 0.0, false, nullptr, true, nullptr).k;
   } else {
     // the CholeskyQR attempt (if any) left X untouched only where it ran
     // out of steps: reload it
@@ -1088,9 +1098,11 @@ static void move_center(rcs_state_s& st, BuildWork& ws, bool right) {
   }
   st.n_moves += 1;
   st.nominal_qr_flops += nominal_qr_flops(len, cnt);
-  hipLaunchKernelGGL(k_write_ortho, dim3(grid1d((int64_t)2 * k * std::max(dl, dr))), dim3(256), 0, s,
-                     ws.wn_final, pl.ldx, k, dl, dr, right ? 1 : 0, st.site[c]);
-  HIP_LAUNCH_OK();
+  if (!in_place) {
+    hipLaunchKernelGGL(k_write_ortho, dim3(grid1d((int64_t)2 * k * std::max(dl, dr))), dim3(256), 0, s,
+                       ws.wn_final, pl.ldx, k, dl, dr, right ? 1 : 0, st.site[c]);
+    HIP_LAUNCH_OK();
+  }
   if (right) {
     const int d2 = st.dims[c + 2];
     hipLaunchKernelGGL(k_absorb, dim3(ceil_div(d2, GT_N), ceil_div(k, GT_M), 2), dim3(GT_THREADS), 0, s,
@@ -1334,7 +1346,8 @@ static void two_site_update(rcs_state_s& st, BuildWork& ws, UpdateCtx& ctx, int 
   const bool try32 =
       ctx.o && ctx.o->svd_f32 && (ctx.o->rank_mode != RCS_RANK_LEARNED || ctx.pred_capped);
   if (small) {
-    r = svd_split_small(st, ws, pl, cap_eff, eps, true, log_spectra ? &spec : nullptr, false);
+    const SmallSites dst{st.site[i], st.site[i + 1], dl, dr, orient};
+    r = svd_split_small(st, ws, pl, cap_eff, eps, true, log_spectra ? &spec : nullptr, false, &dst);
   } else if (precond && svd_split_chol(st, ws, pl, cap_eff, eps, true, log_spectra ? &spec : nullptr, r, &ldw, try32)) {
     // orthonormal factor on X's column side: the other orientation's layout
     side = 3 - orient;
@@ -1353,10 +1366,12 @@ static void two_site_update(rcs_state_s& st, BuildWork& ws, UpdateCtx& ctx, int 
   st.nominal_svd_flops += nominal_svd_flops(len, cnt);
   record_bond_spectrum(st, ws, ctx, i, k);
   if (ctx.o) ctx.prev_eps[i] = r.eps_step;
-  hipLaunchKernelGGL(k_write_split, dim3(grid1d((int64_t)2 * k * (dl + dr))), dim3(256), 0, s,
-                     ws.wn_final, ldw, ws.P.as<double2>(), p_row, k, dl, dr, side,
-                     st.site[i], st.site[i + 1]);
-  HIP_LAUNCH_OK();
+  if (!small) {
+    hipLaunchKernelGGL(k_write_split, dim3(grid1d((int64_t)2 * k * (dl + dr))), dim3(256), 0, s,
+                       ws.wn_final, ldw, ws.P.as<double2>(), p_row, k, dl, dr, side,
+                       st.site[i], st.site[i + 1]);
+    HIP_LAUNCH_OK();
+  }
   st.updates.push_back(UpdateRecord{i, cycle, dl, dm, dr, k, randomized_tried ? 2 : 0});
   st.dims[i + 1] = k;
   st.center = side == 1 ? i + 1 : i;

@@ -17,6 +17,19 @@ struct RankOut {
 constexpr int kSplitSmallRows = 128, kSplitSmallCols = 32;
 inline bool split_small_fits(int len, int cnt) { return len <= kSplitSmallRows && cnt <= kSplitSmallCols; }
 
+// Where a small kernel's matrix lives: element (r, c) at
+// p[(r / h) hs + (r % h) rs + c cs], conjugated if conj.  Covers both
+// orientations of a site tensor [s][a][b] and plain columns.
+struct MatView {
+  double2* p;
+  int64_t hs, rs, cs;
+  int h, conj;
+  __device__ inline double2* at(int r, int c) const {
+    const int top = r >= h ? 1 : 0;   // at most two halves
+    return p + top * hs + (int64_t)(r - top * h) * rs + c * cs;
+  }
+};
+
 struct SplitSmallArgs {
   const double2* x;   // len x cnt, column-major, leading dimension ldx
   int ldx, len, cnt, cap;
@@ -26,10 +39,15 @@ struct SplitSmallArgs {
   int max_sweeps;
   int ns_steps;       // Newton-Schulz steps on the kept columns
   int sort, renorm;
-  double2* wn;        // out: k orthonormal columns, ld ldx
-  double2* p;         // out: k x cnt, row-major: wn^H x (/ nrm with renorm)
-  double* sorted;     // out: cnt singular values, descending
-  RankOut* out;
+  // Out, in this order of preference: the two factors straight into the sites
+  // (ai, aj: tensors [s][dl][k] and [s][k][dr]; side 1: the rows of x are
+  // ai's, side 2: conjugated, aj's), or, without sites, k orthonormal columns
+  // wn (ld ldx) and p = wn^H x (k x cnt, row-major), over nrm with renorm.
+  double2 *ai, *aj;
+  int dl, dr, side;
+  double2 *wn, *p;
+  double* sorted;     // cnt singular values, descending
+  RankOut* out;       // device or pinned host memory
 };
 void split_small(const SplitSmallArgs& a, hipStream_t s);
 
@@ -37,12 +55,11 @@ void split_small(const SplitSmallArgs& a, hipStream_t s);
 // Newton-Schulz steps; *ok = 0, and nothing else written, when a pivot is not
 // positive or Q_1's orthogonality defect exceeds defect_max.
 struct QrSmallArgs {
-  const double2* x;   // len x cnt, column-major, leading dimension ldx
-  int ldx, len, cnt;
+  MatView x;          // len x cnt; replaced by Q
+  int len, cnt;
   double defect_max;
-  double2* wn;        // out: Q, ld ldx
   double2* p;         // out: cnt x cnt, row-major
-  int* ok;
+  int* ok;            // device or pinned host memory
 };
 void qr_small(const QrSmallArgs& a, hipStream_t s);
 // Newton-Schulz steps that take an orthogonality defect bounded by e to

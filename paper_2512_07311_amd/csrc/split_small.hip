@@ -12,7 +12,9 @@
 // Bound: the chain of rounds (0.48 us each, 31 a sweep at 32 columns).
 // Measured, kernel time at 8 / 16 / 32 columns in an exact 12-qubit build:
 // 19 / 58 / 180 us, where the general split's 35 or so launches and its wait
-// per sweep took about 380 us; the whole build 48.0 -> 23.7 ms.
+// per sweep took about 380 us; the whole build 48.0 -> 23.7 ms.  The factors
+// go straight into the site tensors and the rank into pinned host memory,
+// which saves two launches an update and three a move (17.4 -> 16.4 ms).
 //
 // Range: what one workgroup's registers hold, 128 rows of 32 columns.  That
 // covers every split with a neighbouring bond of at most 16; a 64-column
@@ -136,23 +138,25 @@ __device__ inline void small_ns(SmallLds<N>& sm, int tid) {
   __syncthreads();
 }
 
-// P (k x cnt) = scale Y^H X, X from memory; one wave per 16 x 16 tile.
-template <int N, class Args>
-__device__ inline void small_project(const SmallLds<N>& sm, const Args& a, int k, double scale, int tid) {
+// P (k x cnt) = scale Y^H X, X from memory (load(row, column)); one wave per
+// 16 x 16 tile, elements passed to store(m, c, v).
+template <int N, class Load, class Store>
+__device__ inline void small_project(const SmallLds<N>& sm, int len, int cnt, int k, double scale, int tid,
+                                     const Load& load, const Store& store) {
   using D = SmallDims<N>;
   using T = JT<double>;
   const int lane = tid & 63, w = tid >> 6;
   if (w >= D::nb * D::nb) return;
   const int m0 = (w / D::nb) * 16, n0 = (w % D::nb) * 16;
-  if (m0 >= k || n0 >= a.cnt) return;
+  if (m0 >= k || n0 >= cnt) return;
   const int c = n0 + (lane & 15), rsub = lane >> 4;
-  const double2* x = a.x + (int64_t)min(c, a.cnt - 1) * a.ldx;   // columns from cnt on are not stored
+  const int lc = min(c, cnt - 1);   // columns from cnt on are not stored
   const double2* y = sm.Y + (m0 + (lane & 15)) * SS_LD;
   double4_t re{0, 0, 0, 0}, im{0, 0, 0, 0};
-  for (int r0 = 0; r0 < a.len; r0 += 32) {
+  for (int r0 = 0; r0 < len; r0 += 32) {
     double2 b[8];
 #pragma unroll
-    for (int q = 0; q < 8; ++q) b[q] = x[min(r0 + 4 * q + rsub, a.len - 1)];   // Y is zero from len on
+    for (int q = 0; q < 8; ++q) b[q] = load(min(r0 + 4 * q + rsub, len - 1), lc);   // Y is zero from len on
 #pragma unroll
     for (int q = 0; q < 8; ++q) {
       const double2 v = y[r0 + 4 * q + rsub];
@@ -165,7 +169,7 @@ __device__ inline void small_project(const SmallLds<N>& sm, const Args& a, int k
 #pragma unroll
   for (int r = 0; r < 4; ++r) {
     const int m = m0 + T::orow(lane, r);
-    if (m < k && c < a.cnt) a.p[(int64_t)m * a.cnt + c] = make_double2(re[r] * scale, im[r] * scale);
+    if (m < k && c < cnt) store(m, c, make_double2(re[r] * scale, im[r] * scale));
   }
 }
 
@@ -354,11 +358,41 @@ __global__ __launch_bounds__(SS_THREADS) void k_split_small(SplitSmallArgs a) {
     small_ns(sm, tid);
     small_apply(sm, a.len, tid);
   }
+  const auto load = [&](int r, int c) { return a.x[(int64_t)c * a.ldx + r]; };
+  const double scale = a.renorm ? 1.0 / sm.rk.nrm : 1.0;
+  if (!a.ai) {
+    if (row_wave) {
+      if (row < a.len)
+        for (int j = 0; j < k; ++j) a.wn[(int64_t)j * a.ldx + row] = sm.Y[j * SS_LD + row];
+    } else {
+      small_project(sm, a.len, a.cnt, k, scale, tid, load,
+                    [&](int m, int c, double2 v) { a.p[(int64_t)m * a.cnt + c] = v; });
+    }
+    return;
+  }
+  // row (s, a) of ai's side and column j, row (s, c) of aj's side and j
+  auto left = [&](int r, int j, double2 v) { a.ai[(int64_t)r * k + j] = v; };
+  auto right = [&](int r, int j, double2 v) {
+    const int s = r >= a.dr ? 1 : 0;
+    a.aj[((int64_t)s * k + j) * a.dr + r - s * a.dr] = v;
+  };
+  auto conj = [](double2 v) { return make_double2(v.x, -v.y); };
   if (row_wave) {
     if (row < a.len)
-      for (int j = 0; j < k; ++j) a.wn[(int64_t)j * a.ldx + row] = sm.Y[j * SS_LD + row];
+      for (int j = 0; j < k; ++j) {
+        const double2 v = sm.Y[j * SS_LD + row];
+        if (a.side == 1)
+          left(row, j, v);
+        else
+          right(row, j, conj(v));
+      }
   } else {
-    small_project(sm, a, k, a.renorm ? 1.0 / sm.rk.nrm : 1.0, tid);
+    small_project(sm, a.len, a.cnt, k, scale, tid, load, [&](int m, int c, double2 v) {
+      if (a.side == 1)
+        right(c, m, v);
+      else
+        left(c, m, conj(v));
+    });
   }
 }
 
@@ -379,11 +413,16 @@ __global__ __launch_bounds__(SS_THREADS) void k_qr_small(QrSmallArgs a) {
   double2* B = &sm.sv.B[0][0][0];   // N x N, ld 32
   static_assert(sizeof(sm.sv.B) >= 32 * 32 * sizeof(double2), "B in place of the solve's blocks");
   unsigned long long* dev = reinterpret_cast<unsigned long long*>(&sm.key[0]);
+  const double sgn = a.x.conj ? -1.0 : 1.0;
+  const auto load = [&](int r, int c) {
+    const double2 v = *a.x.at(r, c);
+    return make_double2(v.x, sgn * v.y);
+  };
   if (row_wave) {
     const int lrow = min(row, a.len - 1);
 #pragma unroll
     for (int c = 0; c < D::cols; ++c) {
-      const double2 v = a.x[(int64_t)min(c, a.cnt - 1) * a.ldx + lrow];
+      const double2 v = load(lrow, min(c, a.cnt - 1));
       sm.Y[c * SS_LD + row] = c < a.cnt && row < a.len ? v : make_double2(0.0, 0.0);
     }
   } else {
@@ -458,12 +497,15 @@ __global__ __launch_bounds__(SS_THREADS) void k_qr_small(QrSmallArgs a) {
   }
   if (tid == 0) *a.ok = ok ? 1 : 0;
   if (!ok) return;
-  if (row_wave) {
-    if (row < a.len)
-      for (int j = 0; j < a.cnt; ++j) a.wn[(int64_t)j * a.ldx + row] = sm.Y[j * SS_LD + row];
-  } else {
-    small_project(sm, a, a.cnt, 1.0, tid);
-  }
+  if (!row_wave)
+    small_project(sm, a.len, a.cnt, a.cnt, 1.0, tid, load,
+                  [&](int m, int c, double2 v) { a.p[(int64_t)m * a.cnt + c] = v; });
+  __syncthreads();   // x is read; Q takes its place
+  if (row_wave && row < a.len)
+    for (int j = 0; j < a.cnt; ++j) {
+      const double2 v = sm.Y[j * SS_LD + row];
+      *a.x.at(row, j) = make_double2(v.x, sgn * v.y);
+    }
 }
 
 }  // namespace
@@ -482,7 +524,7 @@ void split_small(const SplitSmallArgs& a, hipStream_t s) {
 }
 
 void qr_small(const QrSmallArgs& a, hipStream_t s) {
-  RCS_REQUIRE(a.cnt >= 1 && a.cnt <= a.len && split_small_fits(a.len, a.cnt) && a.ldx >= a.len,
+  RCS_REQUIRE(a.cnt >= 1 && a.cnt <= a.len && split_small_fits(a.len, a.cnt) && a.len <= 2 * a.x.h,
               "matrix too large for the small QR");
   const dim3 grid(1), block(SS_THREADS);
   if (a.cnt <= 8)
