@@ -99,7 +99,6 @@ __global__ void k_ahb_sum(const double2* part, int splits, int nbn, int upper, S
   store(tm * GT_M + e / GT_N, tn * GT_N + e % GT_N, s);
 }
 
-namespace {
 struct StoreGram {   // G (column-major), the identity beyond n
   double2* G;
   int ldg, n;
@@ -128,13 +127,13 @@ struct StoreP {      // scale C at m pm + c pn
   }
 };
 
-int ahb_tiles(int M, int N, bool upper) {
+static int ahb_tiles(int M, int N, bool upper) {
   const int nbm = ceil_div(M, GT_M), nbn = ceil_div(N, GT_N);
   return upper ? nbn * (nbn + 1) / 2 : nbm * nbn;
 }
 // The number of K ranges that leaves the fewest rounds of the chip, a little
 // charged for each range's partials.
-int ahb_splits(int tiles, int K) {
+static int ahb_splits(int tiles, int K) {
   int best = 1;
   double cost = 1e30;
   for (int s = 1; s == 1 || (s <= 16 && s * AHB_MIN_K <= K && s * tiles <= AHB_UNITS); ++s) {
@@ -147,7 +146,7 @@ int ahb_splits(int tiles, int K) {
   return best;
 }
 template <class Store>
-void ahb(const double2* A, int lda, const double2* B, int ldb, int K, int M, int N, bool upper, double2* part,
+static void ahb(const double2* A, int lda, const double2* B, int ldb, int K, int M, int N, bool upper, double2* part,
          const Store& store, hipStream_t s) {
   const int nbn = ceil_div(N, GT_N), tiles = ahb_tiles(M, N, upper);
   const int kper = (int)round_up(ceil_div(K, ahb_splits(tiles, K)), GT_K), splits = ceil_div(K, kper);
@@ -159,7 +158,6 @@ void ahb(const double2* A, int lda, const double2* B, int ldb, int K, int M, int
                     upper ? 1 : 0, store);
   HIP_LAUNCH_OK();
 }
-}  // namespace
 
 size_t ahb_part_bytes(int M, int N, int K, bool upper) {
   const int tiles = ahb_tiles(M, N, upper), splits = ahb_splits(tiles, K);

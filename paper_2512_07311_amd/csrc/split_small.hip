@@ -24,7 +24,6 @@
 #include "split_small.h"
 
 namespace rcs {
-namespace {
 
 constexpr int SS_THREADS = JSOLVE + kSplitSmallRows;
 constexpr int SS_LD = kSplitSmallRows + 1;   // odd: 16 columns x 4 rows of an MFMA operand spread over the banks
@@ -507,8 +506,6 @@ __global__ __launch_bounds__(SS_THREADS) void k_qr_small(QrSmallArgs a) {
       *a.x.at(row, j) = make_double2(v.x, sgn * v.y);
     }
 }
-
-}  // namespace
 
 void split_small(const SplitSmallArgs& a, hipStream_t s) {
   RCS_REQUIRE(a.len >= 1 && a.cnt >= 1 && split_small_fits(a.len, a.cnt) && a.ldx >= a.len && a.cap >= 1,
