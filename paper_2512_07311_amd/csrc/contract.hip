@@ -137,13 +137,27 @@ __device__ inline void mma_lowp(const StageBf16& a, const StageBf16& b, AccLowp&
   }
 }
 
-// Bound: the bf16 form by staging (fp64 operands read from L2/HBM, four
-// 16-bit planes written to LDS; its MFMAs take a quarter of the time), the
-// fp32 form by the fp32 matrix cores.  The next stage's operands are in
-// registers while the matrix cores work; the LDS stage is double-buffered.
-// At bonds 700, 1001, 517 the call takes 113 us in split bf16 (358 us with the
+// Tile of this workgroup.  Consecutive workgroups go to the eight dies in
+// turn, each with an L2 of its own, so die d takes the d-th eighth of an
+// order that walks strips of six tile columns row by row: its tiles form a
+// patch that shares operand rows and columns.
+__device__ inline void xcd_tile(int& tx, int& ty) {
+  const int gx = gridDim.x, gy = gridDim.y, n = gx * gy, id = blockIdx.y * gx + blockIdx.x;
+  const int d = id & 7, q = n / 8, r = n % 8, t = d * q + min(d, r) + (id >> 3);
+  constexpr int W = 6;
+  const int whole = gx / W * W * gy, w = t < whole ? W : gx % W, u = t < whole ? t % (W * gy) : t - whole;
+  tx = (t < whole ? t / (W * gy) * W : gx / W * W) + u % w;
+  ty = u / w;
+}
+
+// Bound: the bf16 form by LDS and conversion (fp64 operands split into four
+// 16-bit planes per tile; the MFMAs take a sixth of the time), the fp32 form by
+// the fp32 matrix cores.  Loads are two stages ahead, the LDS stage is
+// double-buffered.  At bonds 700, 1001, 517 the call takes 99 us in split bf16;
+// 113 with predicated loads one stage ahead, tiles in launch order and B
+// written by 64 columns at a time (four-way bank conflicts); 344 with the
 // split made per fragment by every wave, the products written to memory and
-// mixed from there, and operands copied to the device layout first).
+// mixed from there, and operands copied to the device layout first.
 template <class Stage>
 __global__ __launch_bounds__(CT_THREADS) void k_two_site_mix_lowp(SiteView A, SiteView B, Gate4 G, int dl, int dm,
                                                                  int dr, MixOut out) {
@@ -153,41 +167,56 @@ __global__ __launch_bounds__(CT_THREADS) void k_two_site_mix_lowp(SiteView A, Si
     } st[2];
     float2 t[4][CT_T][CT_T + 1];
   } u;
-  const int a0 = blockIdx.y * CT_T, c0 = blockIdx.x * CT_T;
+  int tx, ty;
+  xcd_tile(tx, ty);
+  const int a0 = ty * CT_T, c0 = tx * CT_T;
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
   const int wm = (w & 1) * 32, wn = (w >> 1) * 32;      // wave (s1, s2)
-  // A rows: 16 lanes cover the 32 k-values of a row (two each), four passes
-  // of 16 rows; B: lanes along c, two k-values each, four passes
+  // A: 16 lanes cover the 32 k-values of a row (two each), four passes of 16
+  // rows; B: 16 lanes along c, two k-values each, four passes of 16 columns (a
+  // wave's LDS writes then cover 16 columns x 4 pairs, which is all banks)
   const int ak = 2 * (tid & 15), ax = tid >> 4;
-  const int bx = tid & 63, bk = 2 * (tid >> 6);
-  double2 ra[4][2], rb[4][2];
-  auto fetch = [&](int k0) {
+  const int bx = tid & 15, bk = 2 * (tid >> 4);
+  double2 pa[2][4][2], pb[2][4][2];   // stages s + 1 and s + 2
+  // Loads without a predicate (a predicated one waits for the last): rows and
+  // columns past the end repeat the last one and their products are not
+  // stored, k-values past the end are cleared.
+  const double2* arow[4];
 #pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const int x = ax + 16 * j, i = a0 + (x & 31);
-      const double2* row = A.p + (x >> 5) * A.s + (int64_t)i * A.ld;
+  for (int j = 0; j < 4; ++j) {
+    const int x = ax + 16 * j;
+    arow[j] = A.p + (x >> 5) * A.s + (int64_t)min(a0 + (x & 31), dl - 1) * A.ld;
+  }
+  const double2* bcol[4];
 #pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const int k = k0 + ak + h;
-        ra[j][h] = make_double2(0.0, 0.0);
-        if (i < dl && k < dm) ra[j][h] = row[k];
-      }
-    }
-    const int c = c0 + (bx & 31);
+  for (int j = 0; j < 4; ++j) {
+    const int x = bx + 16 * j;
+    bcol[j] = B.p + (x >> 5) * B.s + min(c0 + (x & 31), dr - 1);
+  }
+  auto fetch = [&](double2 (&ra)[4][2], double2 (&rb)[4][2], int k0) {
 #pragma unroll
     for (int j = 0; j < 4; ++j)
 #pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const int k = k0 + bk + 8 * j + h;
-        rb[j][h] = make_double2(0.0, 0.0);
-        if (c < dr && k < dm) rb[j][h] = B.p[(bx >> 5) * B.s + (int64_t)k * B.ld + c];
-      }
+      for (int h = 0; h < 2; ++h) ra[j][h] = arow[j][min(k0 + ak + h, dm - 1)];
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int h = 0; h < 2; ++h) rb[j][h] = bcol[j][(int64_t)min(k0 + bk + h, dm - 1) * B.ld];
+    if (k0 + CT_K > dm) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+          if (k0 + ak + h >= dm) ra[j][h] = make_double2(0.0, 0.0);
+          if (k0 + bk + h >= dm) rb[j][h] = make_double2(0.0, 0.0);
+        }
+    }
   };
-  auto commit = [&](int buf) {
+  auto commit = [&](const double2 (&ra)[4][2], const double2 (&rb)[4][2], int buf) {
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
       put2(u.st[buf].a, ax + 16 * j, ak, ra[j][0], ra[j][1]);
-      put2(u.st[buf].b, bx, bk + 8 * j, rb[j][0], rb[j][1]);
+      put2(u.st[buf].b, bx + 16 * j, bk, rb[j][0], rb[j][1]);
     }
   };
   AccLowp acc;
@@ -198,18 +227,21 @@ __global__ __launch_bounds__(CT_THREADS) void k_two_site_mix_lowp(SiteView A, Si
       acc.re[i][j] = float4_t{0, 0, 0, 0};
       acc.im[i][j] = float4_t{0, 0, 0, 0};
     }
-  fetch(0);
-  commit(0);
+  fetch(pa[0], pb[0], 0);
+  if (CT_K < dm) fetch(pa[1], pb[1], CT_K);
+  commit(pa[0], pb[0], 0);
   __syncthreads();
-  int buf = 0;
-  for (int k0 = 0; k0 < dm; k0 += CT_K) {
-    const bool more = k0 + CT_K < dm;
-    if (more) fetch(k0 + CT_K);
-    mma_lowp(u.st[buf].a, u.st[buf].b, acc, wm, wn, lane);
-    buf ^= 1;
-    if (more) {
-      commit(buf);
-      __syncthreads();
+  for (int k0 = 0; k0 < dm; k0 += 2 * CT_K) {
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int k = k0 + h * CT_K;
+      if (k >= dm) break;
+      if (k + 2 * CT_K < dm) fetch(pa[h], pb[h], k + 2 * CT_K);
+      mma_lowp(u.st[h].a, u.st[h].b, acc, wm, wn, lane);
+      if (k + CT_K < dm) {
+        commit(pa[h ^ 1], pb[h ^ 1], h ^ 1);
+        __syncthreads();
+      }
     }
   }
   __syncthreads();
