@@ -474,7 +474,7 @@ void chol_precondition(const double2* X, int ldx, int len, int n, double2* G, in
 // (K x N, ld ldb), D_z = D + z sd (M x N, ld ldd), overwritten.  kUpperA /
 // kUpperB: that operand is upper triangular, and the K range it leaves zero in
 // a tile is not gone through (half of the work).
-enum { kGeneral, kUpperA, kUpperB };
+enum { kUpperA, kUpperB };
 __global__ __launch_bounds__(GT_THREADS) void k_cgemm_cm(const double2* A, int lda, int64_t sa, const double2* B,
                                                         int ldb, int64_t sb, double2* D, int ldd, int64_t sd, int M,
                                                         int N, int K, double alpha, int upper) {
