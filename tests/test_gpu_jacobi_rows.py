@@ -48,3 +48,25 @@ def test_inner_sweeps(env, ln, cnt, inner):
         _check(rcs, torch, ln, cnt)
     finally:
         rcs.tuning_clear()
+
+
+@pytest.mark.parametrize("fixed,free", [(64, 64), (96, 33), (16, 80)])
+def test_blocks_that_never_rotate(env, fixed, free):
+    """Column blocks orthogonal to everything are skipped from the second
+    sweep on while the others go on: the Gram blocks carried between rounds
+    have to follow both.  The bars of _check; the fixed columns are the
+    largest, so they fill the first blocks."""
+    rcs, torch = env
+    ln = fixed + free + 9
+    M = np.zeros((ln, fixed + free), dtype=np.complex128)
+    M[np.arange(fixed), np.arange(fixed)] = np.linspace(3.0, 2.0, fixed)
+    M[fixed:, fixed:] = inputs.planted_matrix(free + 9, free, np.geomspace(1.0, 1e-3, free), seed=free)
+    x = torch.from_numpy(np.ascontiguousarray(M.T)).cuda()
+    s = torch.zeros(fixed + free, dtype=torch.float64, device="cuda")
+    u = torch.zeros(fixed + free, ln, dtype=torch.complex128, device="cuda")
+    rcs.svd_jacobi(x, s, u)
+    s, U = s.cpu().numpy(), u.cpu().numpy().T
+    ref = np.concatenate([np.linspace(3.0, 2.0, fixed), np.geomspace(1.0, 1e-3, free)])
+    assert np.abs(s - ref).max() <= 1e-13 * np.sqrt(ln) * ref[0]
+    tol = 4 * 16 * 1.11e-16 * np.sqrt(ln)
+    assert np.abs(U.conj().T @ U - np.eye(fixed + free)).max() <= tol
