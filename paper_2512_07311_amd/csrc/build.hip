@@ -271,7 +271,9 @@ __global__ void k_sum_sq(const double* v, int n, double* out) {
   if (threadIdx.x == 0) *out = red[0];
 }
 
-// Sort sigma descending (ties by index), apply the rank rule.
+// Sort sigma descending (ties by index), apply the rank rule (unless out is
+// null: its sums, in one thread for their order, take longer than the sort: 69
+// against 22 us in all at 1024 values).
 //  w = sum s^2; s^2 <= 1e-24 w counts as zero; tail(k) = sum_{r>=k} s_r^2
 //  from the smallest upward; k_eps = min{k>=1 : tail(k) <= eps w};
 //  k = min(k_eps, cap); eps_step = tail(k)/w; nrm = sqrt(sum_{r<k} s_r^2).
@@ -315,11 +317,12 @@ __global__ __launch_bounds__(1024) void k_sort_rank(const double* sigma, int cnt
     sorted[i] = key[i];
     order[i] = idx[i];
   }
-  if (threadIdx.x == 0) {
+  if (threadIdx.x == 0 && out) {
     // extra: discarded weight that lies outside the decomposed subspace
     const double extra = extra_tail ? fmax(*extra_tail, 0.0) : 0.0;
     double w = extra;
     int bad = 0;
+#pragma unroll 8
     for (int i = cnt - 1; i >= 0; --i) {
       double v = key[i];
       if (!(v == v) || v > 1e300) bad = 1;
@@ -327,6 +330,7 @@ __global__ __launch_bounds__(1024) void k_sort_rank(const double* sigma, int cnt
     }
     const double floor = 1e-24 * w;
     int nnz = 0;
+#pragma unroll 8
     for (int i = 0; i < cnt; ++i)
       if (key[i] * key[i] > floor) nnz = i + 1;
     // tail sums from the smallest upward; find the smallest k >= 1 with
@@ -355,12 +359,14 @@ __global__ __launch_bounds__(1024) void k_sort_rank(const double* sigma, int cnt
     if (k == k_eps) {
       tk = tail_k;
     } else {
+#pragma unroll 8
       for (int i = cnt - 1; i >= k; --i) {
         double v2 = key[i] * key[i];
         tk += (v2 <= floor) ? 0.0 : v2;
       }
     }
     double kept = 0.0;
+#pragma unroll 8
     for (int i = 0; i < k; ++i) kept += key[i] * key[i];
     out->k = k;
     out->nnz = nnz;
@@ -659,7 +665,7 @@ static SplitResult svd_split(rcs_state_s& st, BuildWork& ws, const JacobiPlan& p
   if (sort_columns_first()) {
     // order columns by norm (X0 keeps the original order for the projection)
     RCS_PROBED_LAUNCH(kKcFactor, k_sort_rank, dim3(1), dim3(1024), 0, s, ws.sigma.as<double>(), pl.cnt, pl.cnt, 0.0,
-                       ws.sorted.as<double>(), ws.order.as<int>(), ws.scal.as<RankOut>(), nullptr);
+                       ws.sorted.as<double>(), ws.order.as<int>(), nullptr, nullptr);
     HIP_LAUNCH_OK();
     RCS_PROBED_LAUNCH(kKcFactor, k_permute_cols, dim3(ceil_div(pl.len, 256), pl.cnt), dim3(256), 0, s, ws.X0.as<double2>(),
                        pl.ldx, pl.len, ws.order.as<int>(), X);
@@ -802,7 +808,7 @@ static bool svd_split_chol(rcs_state_s& st, BuildWork& ws, const JacobiPlan& pl,
   // columns in descending-norm order (the pivoting of the QR preconditioner)
   ws.order_x.ensure((size_t)n * sizeof(int));
   RCS_PROBED_LAUNCH(kKcFactor, k_sort_rank, dim3(1), dim3(1024), 0, s, ws.sigma.as<double>(), n, n, 0.0,
-                     ws.sorted.as<double>(), ws.order_x.as<int>(), ws.scal.as<RankOut>(), nullptr);
+                     ws.sorted.as<double>(), ws.order_x.as<int>(), nullptr, nullptr);
   HIP_LAUNCH_OK();
   RCS_PROBED_LAUNCH(kKcFactor, k_permute_cols, dim3(ceil_div(len, 256), n), dim3(256), 0, s, X0, pl.ldx, len,
                      ws.order_x.as<int>(), X);
@@ -1608,7 +1614,7 @@ rcs_status rcs_svd_jacobi(int32_t len, int32_t cnt, double* x_dev, double* s_dev
   HIP_LAUNCH_OK();
   // columns in descending-norm order
   hipLaunchKernelGGL(rcs::k_sort_rank, dim3(1), dim3(1024), 0, s, ws->sigma.as<double>(), cnt, cnt, 0.0,
-                     ws->sorted.as<double>(), ws->order.as<int>(), ws->scal.as<rcs::RankOut>(), nullptr);
+                     ws->sorted.as<double>(), ws->order.as<int>(), nullptr, nullptr);
   HIP_LAUNCH_OK();
   hipLaunchKernelGGL(rcs::k_permute_cols, dim3(rcs::ceil_div(len, 256), cnt), dim3(256), 0, s,
                      ws->X0.as<double2>(), pl.ldx, len, ws->order.as<int>(), X);
@@ -1625,7 +1631,7 @@ rcs_status rcs_svd_jacobi(int32_t len, int32_t cnt, double* x_dev, double* s_dev
   hipLaunchKernelGGL(rcs::k_colnorm, dim3(cnt), dim3(256), 0, s, X, pl.ldx, len, ws->sigma.as<double>());
   HIP_LAUNCH_OK();
   hipLaunchKernelGGL(rcs::k_sort_rank, dim3(1), dim3(1024), 0, s, ws->sigma.as<double>(), cnt, cnt, 0.0,
-                     ws->sorted.as<double>(), ws->order.as<int>(), ws->scal.as<rcs::RankOut>(), nullptr);
+                     ws->sorted.as<double>(), ws->order.as<int>(), nullptr, nullptr);
   HIP_LAUNCH_OK();
   hipLaunchKernelGGL(rcs::k_copy_out, dim3(rcs::ceil_div(len, 256), cnt), dim3(256), 0, s, X, pl.ldx, len, cnt,
                      ws->order.as<int>(), ws->sorted.as<double>(), s_dev, reinterpret_cast<double2*>(u_dev));
@@ -1654,7 +1660,7 @@ rcs_status rcs_svd_jacobi_f32(int32_t len, int32_t cnt, const double* x_dev, dou
   HIP_LAUNCH_OK();
   // columns in descending-norm order, then the fp32 copy
   hipLaunchKernelGGL(rcs::k_sort_rank, dim3(1), dim3(1024), 0, s, ws->sigma.as<double>(), cnt, cnt, 0.0,
-                     ws->sorted.as<double>(), ws->order.as<int>(), ws->scal.as<rcs::RankOut>(), nullptr);
+                     ws->sorted.as<double>(), ws->order.as<int>(), nullptr, nullptr);
   HIP_LAUNCH_OK();
   hipLaunchKernelGGL(rcs::k_permute_cols, dim3(rcs::ceil_div(len, 256), cnt), dim3(256), 0, s,
                      ws->X0.as<double2>(), pl.ldx, len, ws->order.as<int>(), X);
@@ -1674,7 +1680,7 @@ rcs_status rcs_svd_jacobi_f32(int32_t len, int32_t cnt, const double* x_dev, dou
   hipLaunchKernelGGL(rcs::k_colnorm_c64, dim3(cnt), dim3(256), 0, s, X32, pl.ldx, len, ws->sigma.as<double>());
   HIP_LAUNCH_OK();
   hipLaunchKernelGGL(rcs::k_sort_rank, dim3(1), dim3(1024), 0, s, ws->sigma.as<double>(), cnt, cnt, 0.0,
-                     ws->sorted.as<double>(), ws->order.as<int>(), ws->scal.as<rcs::RankOut>(), nullptr);
+                     ws->sorted.as<double>(), ws->order.as<int>(), nullptr, nullptr);
   HIP_LAUNCH_OK();
   hipLaunchKernelGGL(rcs::k_copy_out_c64, dim3(rcs::ceil_div(len, 256), cnt), dim3(256), 0, s, X32, pl.ldx, len,
                      cnt, ws->order.as<int>(), ws->sorted.as<double>(), s_dev, reinterpret_cast<double2*>(u_dev));
@@ -1757,7 +1763,7 @@ rcs_status rcs_rsvd(int32_t len, int32_t cnt, const double* x_dev, int32_t l, in
                      ws->sigma.as<double>());
   HIP_LAUNCH_OK();
   hipLaunchKernelGGL(rcs::k_sort_rank, dim3(1), dim3(1024), 0, s, ws->sigma.as<double>(), l, l, 0.0,
-                     ws->sorted.as<double>(), ws->order.as<int>(), ws->scal.as<rcs::RankOut>(), nullptr);
+                     ws->sorted.as<double>(), ws->order.as<int>(), nullptr, nullptr);
   HIP_LAUNCH_OK();
   HIP_OK(hipMemcpyAsync(s_dev, ws->sorted.p, l * sizeof(double), hipMemcpyDeviceToDevice, s));
   HIP_OK(hipStreamSynchronize(s));
