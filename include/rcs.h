@@ -391,7 +391,8 @@ rcs_status rcs_cholqr(int32_t len, int32_t cnt, const double* x_dev, double* q_d
 /* Two-site contraction: theta'[(s1,a),(s2,c)] = sum_{s1',s2'} G[(s1,s2),(s1',s2')]
  * sum_b A[a,s1',b] B[b,s2',c] with A (dl,2,dm), B (dm,2,dr) in export
  * layout, G 4x4 row-major complex; out_dev receives the (2dl) x (2dr)
- * matrix column-major.  precision = rcs_precision. */
+ * matrix column-major and may share memory with A or B (then read from a
+ * copy).  precision = rcs_precision. */
 rcs_status rcs_two_site(int32_t dl, int32_t dm, int32_t dr, const double* a_dev,
                         const double* b_dev, const double* gate_host, int32_t precision,
                         double* out_dev, void* stream);

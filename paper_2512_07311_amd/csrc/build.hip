@@ -1594,6 +1594,12 @@ rcs_status rcs_build_state_ex(rcs_circuit circuit, int32_t chi, double trunc_eps
   RCS_API_END
 }
 
+// Whether the na bytes at a and the nb bytes at b share any.
+static bool overlap(const void* a, size_t na, const void* b, size_t nb) {
+  const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
+  return x < y + nb && y < x + na;
+}
+
 rcs_status rcs_svd_jacobi(int32_t len, int32_t cnt, double* x_dev, double* s_dev, double* u_dev,
                           void* stream) {
   RCS_API_BEGIN
@@ -1698,11 +1704,7 @@ rcs_status rcs_cholqr(int32_t len, int32_t cnt, const double* x_dev, double* q_d
   // are allocated instead of an SVD's workspace with padded copies: 4.8 -> 3.1 ms
   // at 2048 x 1024 (2.8 with split products).  An output that overlaps x gets a copy of x.
   const size_t xbytes = (size_t)len * cnt * sizeof(double2), rbytes = (size_t)cnt * cnt * sizeof(double2);
-  auto overlaps = [&](const void* out, size_t n) {
-    const uintptr_t x = reinterpret_cast<uintptr_t>(x_dev), o = reinterpret_cast<uintptr_t>(out);
-    return o < x + xbytes && x < o + n;
-  };
-  const bool copy = overlaps(q_dev, xbytes) || overlaps(r_dev, rbytes);
+  const bool copy = overlap(x_dev, xbytes, q_dev, xbytes) || overlap(x_dev, xbytes, r_dev, rbytes);
   // One allocation: beyond 64 MB in all, each costs about 300 us.  The partial
   // tiles go where nothing is needed meanwhile, if they fit there.
   const size_t qrbytes = rcs::QrWork::bytes(cnt), nelem = (size_t)len * cnt;
@@ -1801,9 +1803,28 @@ rcs_status rcs_two_site(int32_t dl, int32_t dm, int32_t dr, const double* a_dev,
   hipStream_t s = rcs::as_stream(stream);
   rcs::Gate4 G;
   for (int e = 0; e < 16; ++e) G.g[e] = make_double2(gate_host[2 * e], gate_host[2 * e + 1]);
-  // the export layout (a, s, b), read in place
-  rcs::contract_mix(rcs::SiteView{reinterpret_cast<const double2*>(a_dev), dm, 2 * dm},
-                    rcs::SiteView{reinterpret_cast<const double2*>(b_dev), dr, 2 * dr}, G, dl, dm, dr, precision,
+  // The operands are read in place (export layout (a, s, b)) while other
+  // workgroups already write the output: one that shares memory with it is
+  // read from a copy.
+  const double2 *a = reinterpret_cast<const double2*>(a_dev), *b = reinterpret_cast<const double2*>(b_dev);
+  const size_t na = (size_t)2 * dl * dm, nb = (size_t)2 * dm * dr, nout = (size_t)4 * dl * dr;
+  const bool copy_a = overlap(a, na * sizeof(double2), out_dev, nout * sizeof(double2));
+  const bool copy_b = overlap(b, nb * sizeof(double2), out_dev, nout * sizeof(double2));
+  rcs::DevBuf buf;
+  if (copy_a || copy_b) {
+    buf.ensure(((copy_a ? na : 0) + (copy_b ? nb : 0)) * sizeof(double2));
+    double2* to = buf.as<double2>();
+    if (copy_a) {
+      HIP_OK(hipMemcpyAsync(to, a, na * sizeof(double2), hipMemcpyDeviceToDevice, s));
+      a = to;
+      to += na;
+    }
+    if (copy_b) {
+      HIP_OK(hipMemcpyAsync(to, b, nb * sizeof(double2), hipMemcpyDeviceToDevice, s));
+      b = to;
+    }
+  }
+  rcs::contract_mix(rcs::SiteView{a, dm, 2 * dm}, rcs::SiteView{b, dr, 2 * dr}, G, dl, dm, dr, precision,
                     rcs::MixOut{reinterpret_cast<double2*>(out_dev), nullptr, 2 * dl, 1}, s);
   HIP_OK(hipStreamSynchronize(s));
   RCS_API_END
