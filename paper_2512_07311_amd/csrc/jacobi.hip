@@ -966,44 +966,44 @@ static bool use_graphs() {
   return v;
 }
 
-// Cached executable graphs of one sweep (not the first), keyed by the plan
-// and the buffers they were captured with.
-namespace {
+// One sweep (not the first) as an executable graph.  It belongs to one run: the
+// launches it replays carry that matrix's addresses and thresholds.
 struct SweepGraph {
-  int len, cnt, jb, inner;
-  void *x, *work;
-  int* rc;
-  hipGraphExec_t exec;
-};
-std::vector<SweepGraph> g_graphs;
-std::mutex g_graph_mu;
-}  // namespace
-
-static hipGraphExec_t sweep_graph(const JacobiPlan& pl, const JacArgs<double>& a, void* work, hipStream_t stream) {
-  std::lock_guard<std::mutex> lk(g_graph_mu);
-  for (auto& g : g_graphs)
-    if (g.len == pl.len && g.cnt == pl.cnt && g.jb == pl.jb && g.inner == a.max_inner && g.x == a.x &&
-        g.work == work && g.rc == a.rot_count)
-      return g.exec;
-  hipStream_t cs;
-  HIP_OK(hipStreamCreateWithFlags(&cs, hipStreamNonBlocking));
-  hipGraph_t graph = nullptr;
   hipGraphExec_t exec = nullptr;
-  HIP_OK(hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal));
-  launch_sweep(pl, a, cs, false);
-  hipError_t e = hipStreamEndCapture(cs, &graph);
-  if (e == hipSuccess) e = hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0);
-  if (graph) (void)hipGraphDestroy(graph);
-  (void)hipStreamDestroy(cs);
-  HIP_OK(e);
-  if (g_graphs.size() > 64) {
-    for (auto& g : g_graphs) (void)hipGraphExecDestroy(g.exec);
-    g_graphs.clear();
+  SweepGraph() = default;
+  SweepGraph(const SweepGraph&) = delete;
+  SweepGraph& operator=(const SweepGraph&) = delete;
+  ~SweepGraph() {
+    if (exec) (void)hipGraphExecDestroy(exec);
   }
-  g_graphs.push_back({pl.len, pl.cnt, pl.jb, a.max_inner, a.x, work, a.rot_count, exec});
-  (void)stream;
-  return exec;
-}
+  void launch(const JacobiPlan& pl, const JacArgs<double>& a, hipStream_t stream) {
+    if (!exec) capture(pl, a);
+    HIP_OK(hipGraphLaunch(exec, stream));
+  }
+
+ private:
+  void capture(const JacobiPlan& pl, const JacArgs<double>& a) {
+    hipStream_t cs;
+    HIP_OK(hipStreamCreateWithFlags(&cs, hipStreamNonBlocking));
+    hipGraph_t graph = nullptr;
+    hipError_t e = hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal);
+    if (e == hipSuccess) {
+      try {
+        launch_sweep(pl, a, cs, false);
+      } catch (...) {
+        (void)hipStreamEndCapture(cs, &graph);
+        if (graph) (void)hipGraphDestroy(graph);
+        (void)hipStreamDestroy(cs);
+        throw;
+      }
+      e = hipStreamEndCapture(cs, &graph);
+    }
+    if (e == hipSuccess) e = hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0);
+    if (graph) (void)hipGraphDestroy(graph);
+    (void)hipStreamDestroy(cs);
+    HIP_OK(e);
+  }
+};
 
 template <typename R>
 static int jacobi_run_t(const JacobiPlan& pl, typename JT<R>::C* x, void* work, int* rot_count_dev,
@@ -1033,12 +1033,12 @@ static int jacobi_run_t(const JacobiPlan& pl, typename JT<R>::C* x, void* work, 
   a.neg2 = (R)(t.delta2 * std::max(fro2, 1e-300));
   a.qtol = (R)(jacobi_qstop() > 0.0 ? (double)a.tol / jacobi_qstop() : 0.0);
   a.max_inner = pl.inner;
-  bool graphs = false;
-  if constexpr (std::is_same<R, double>::value) graphs = use_graphs() && pl.nbp > 4;
+  [[maybe_unused]] const bool graphs = use_graphs() && pl.nbp > 4;
+  [[maybe_unused]] SweepGraph graph;
   for (int sweep = 1; sweep <= max_sweeps; ++sweep) {
     if constexpr (std::is_same<R, double>::value) {
       if (graphs && sweep > 1)
-        HIP_OK(hipGraphLaunch(sweep_graph(pl, a, work, stream), stream));
+        graph.launch(pl, a, stream);
       else
         launch_sweep(pl, a, stream, sweep == 1);
     } else {
