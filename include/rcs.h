@@ -361,6 +361,8 @@ rcs_status rcs_dense_gather(const double* psi_dev, int32_t n_qubits, const uint6
  * (column j at x_dev + 2*len*j) by one-sided block Jacobi in fp64:
  * s_dev[cnt] = singular values in descending order, u_dev (len x cnt,
  * column-major) = left singular vectors (zero columns where s = 0).
+ * ||X||_F^2 must be a normal fp64 number or 0; within that range scaling X by
+ * a power of two scales s and leaves u, bit for bit.
  * x_dev is overwritten.  Errors: NUMERIC if not converged. */
 rcs_status rcs_svd_jacobi(int32_t len, int32_t cnt, double* x_dev, double* s_dev, double* u_dev,
                           void* stream);

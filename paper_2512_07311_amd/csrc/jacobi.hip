@@ -28,6 +28,7 @@
 // pass raises a flag otherwise): at that point convergence is quadratic and
 // the next sweep would rotate nothing.
 #include <algorithm>
+#include <cmath>
 #include <cstdlib>
 #include <mutex>
 #include <type_traits>
@@ -1005,6 +1006,27 @@ struct SweepGraph {
   }
 };
 
+// x *= 2^e, exactly (up to underflow).
+__global__ void k_jac_scale(double2* x, int64_t n, int e) {
+  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x)
+    x[i] = make_double2(ldexp(x[i].x, e), ldexp(x[i].y, e));
+}
+static void jac_scale(const JacobiPlan& pl, double2* x, int e, hipStream_t s) {
+  const int64_t n = (int64_t)pl.ldx * pl.cnt_pad;
+  hipLaunchKernelGGL(k_jac_scale, dim3((unsigned)std::min<int64_t>((n + 255) / 256, 65535)), dim3(256), 0, s, x, n, e);
+  HIP_LAUNCH_OK();
+}
+// The exponent by which the fp64 iteration scales its columns: 0 where
+// ||x||_F^2 is within 2^(+-300).  The rotations form products of two Gram
+// entries next to an addend of 1e-300 (jac_rot_t): beyond 2^512 they overflow,
+// and the smallest ones that matter (cosines at the tolerance between columns
+// at the zero level, about 1e-88 fro2^2) stay clear of the addend down to
+// 2^-320.  A power of two leaves every rounding of the iteration alike.
+static int jac_scale_exponent(double fro2) {
+  if (!(fro2 > 0.0) || !std::isfinite(fro2) || (fro2 >= 0x1p-300 && fro2 <= 0x1p300)) return 0;
+  return -(int)std::floor(0.5 * std::ilogb(fro2));
+}
+
 template <typename R>
 static int jacobi_run_t(const JacobiPlan& pl, typename JT<R>::C* x, void* work, int* rot_count_dev,
                         int* rot_count_host, double fro2, hipStream_t stream, int max_sweeps, double tol) {
@@ -1060,7 +1082,12 @@ static int jacobi_run_t(const JacobiPlan& pl, typename JT<R>::C* x, void* work, 
 
 int jacobi_run(const JacobiPlan& pl, double2* x, void* work, int* rot_count_dev, int* rot_count_host, double fro2,
                hipStream_t stream, int max_sweeps, double tol) {
-  return jacobi_run_t<double>(pl, x, work, rot_count_dev, rot_count_host, fro2, stream, max_sweeps, tol);
+  const int e = jac_scale_exponent(fro2);
+  if (e) jac_scale(pl, x, e, stream);
+  const int sweeps = jacobi_run_t<double>(pl, x, work, rot_count_dev, rot_count_host, std::ldexp(fro2, 2 * e), stream,
+                                          max_sweeps, tol);
+  if (e) jac_scale(pl, x, -e, stream);
+  return sweeps;
 }
 
 int jacobi_run_f32(const JacobiPlan& pl, float2* x, void* work, int* rot_count_dev, int* rot_count_host, double fro2,

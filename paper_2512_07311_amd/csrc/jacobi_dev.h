@@ -308,6 +308,9 @@ __device__ __forceinline__ void apply_round(double2 (&y)[S::cols], const double2
 // a = c t with t = +-g / (|d| + sqrt(d^2 + |g|^2)), d = (gjj - gii) / 2 (the
 // smaller-angle root), and 1 / c.  t may be off by the hardware estimates'
 // ~1e-8 (see jac_rot); c is refined, so c^2 (1 + |t|^2) = 1 to rounding.
+// Range: d^2 and |g|^2 have to stay finite and, for pairs that rotate, well
+// above the guard of 1e-300: jacobi_run scales columns whose summed squares are
+// not within 2^(+-300), and the small split's matrices have unit norm.
 // The dependent chain is what a round waits
 // for: the guard against 0 sits in |g|^2's first product, an inactive pair's
 // infinity in the addend of the denominator, the sign on g, and the test is
