@@ -505,6 +505,12 @@ rcs_status rcs_dense_simulate(rcs_circuit c, double* psi_dev, int64_t n_amps, vo
   } catch (const rcs::Error& e) {
     rcs::set_last_error(e.what());
     return e.status;
+  } catch (const std::bad_alloc&) {
+    rcs::set_last_error("host allocation failed");
+    return RCS_ERR_OUT_OF_MEMORY;
+  } catch (const std::exception& e) {
+    rcs::set_last_error(e.what());
+    return RCS_ERR_DEVICE;
   }
   return RCS_OK;
 }
@@ -519,6 +525,12 @@ rcs_status rcs_dense_gather(const double* psi_dev, int32_t n_qubits, const uint6
   } catch (const rcs::Error& e) {
     rcs::set_last_error(e.what());
     return e.status;
+  } catch (const std::bad_alloc&) {
+    rcs::set_last_error("host allocation failed");
+    return RCS_ERR_OUT_OF_MEMORY;
+  } catch (const std::exception& e) {
+    rcs::set_last_error(e.what());
+    return RCS_ERR_DEVICE;
   }
   return RCS_OK;
 }

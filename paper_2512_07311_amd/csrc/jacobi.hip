@@ -1105,6 +1105,12 @@ rcs_status rcs_tuning_set(int32_t cnt_max, int32_t block, int32_t inner_sweeps) 
   } catch (const rcs::Error& e) {
     rcs::set_last_error(e.what());
     return e.status;
+  } catch (const std::bad_alloc&) {
+    rcs::set_last_error("host allocation failed");
+    return RCS_ERR_OUT_OF_MEMORY;
+  } catch (const std::exception& e) {
+    rcs::set_last_error(e.what());
+    return RCS_ERR_DEVICE;
   }
   return RCS_OK;
 }

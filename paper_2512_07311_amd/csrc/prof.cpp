@@ -110,6 +110,12 @@ rcs_status rcs_profile_enable(int32_t every) {
   } catch (const rcs::Error& e) {
     rcs::set_last_error(e.what());
     return e.status;
+  } catch (const std::bad_alloc&) {
+    rcs::set_last_error("host allocation failed");
+    return RCS_ERR_OUT_OF_MEMORY;
+  } catch (const std::exception& e) {
+    rcs::set_last_error(e.what());
+    return RCS_ERR_DEVICE;
   }
   return RCS_OK;
 }
@@ -129,6 +135,12 @@ rcs_status rcs_profile_read(int32_t kclass, int64_t* launches, int64_t* timed, d
   } catch (const rcs::Error& e) {
     rcs::set_last_error(e.what());
     return e.status;
+  } catch (const std::bad_alloc&) {
+    rcs::set_last_error("host allocation failed");
+    return RCS_ERR_OUT_OF_MEMORY;
+  } catch (const std::exception& e) {
+    rcs::set_last_error(e.what());
+    return RCS_ERR_DEVICE;
   }
   return RCS_OK;
 }
@@ -159,6 +171,12 @@ rcs_status rcs_profile_event_floor(double* seconds) {
   } catch (const rcs::Error& e) {
     rcs::set_last_error(e.what());
     return e.status;
+  } catch (const std::bad_alloc&) {
+    rcs::set_last_error("host allocation failed");
+    return RCS_ERR_OUT_OF_MEMORY;
+  } catch (const std::exception& e) {
+    rcs::set_last_error(e.what());
+    return RCS_ERR_DEVICE;
   }
   return RCS_OK;
 }
