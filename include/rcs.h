@@ -465,6 +465,8 @@ const char* rcs_profile_class_name(int32_t kclass);
  * Launch parameters of the Jacobi SVD (fp64 and fp32) per column-count bucket: the
  * first entry with cnt <= cnt_max applies (block = 16 or 32 columns per
  * block, inner_sweeps in [1, 8] two-sided sweeps per block-pair meeting).
+ * Inside state builds, full splits and centre moves of at most 128 rows and
+ * 32 columns run as one launch of a fixed form instead, which no entry changes.
  * Process-wide; written by the autotuner (paper_2512_07311_amd/autotune.py)
  * from device timings.  Without entries: block 16, one inner sweep. */
 rcs_status rcs_tuning_set(int32_t cnt_max, int32_t block, int32_t inner_sweeps);

@@ -751,6 +751,7 @@ static SplitResult svd_split_small(rcs_state_s& st, BuildWork& ws, const JacobiP
   split_small(a, s);
   HIP_OK(hipStreamSynchronize(s));
   const RankOut r = *ws.host_rank;
+  if (jacobi_debug()) std::fprintf(stderr, "jacobi %dx%d in one launch: %d sweeps\n", pl.len, pl.cnt, r.sweeps);
   if (r.sweeps < 0) fail(RCS_ERR_NUMERIC, "one-sided Jacobi SVD did not converge");
   st.jacobi_sweeps_max = std::max(st.jacobi_sweeps_max, r.sweeps);
   if (r.bad) fail(RCS_ERR_NUMERIC, "non-finite singular values");

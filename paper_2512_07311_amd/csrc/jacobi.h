@@ -35,6 +35,8 @@ JacobiTol jacobi_tol(int len, double tol = 0.0);
 // jacobi_run_f32 (its Gram chunks differ).
 JacobiPlan jacobi_plan(int len, int cnt, int jb = 0, bool f32 = false);
 size_t jacobi_work_bytes(const JacobiPlan& pl);
+// RCS_DEBUG_JACOBI=1: every SVD's sweeps on stderr.
+bool jacobi_debug();
 // Orthogonalises the columns of x in place; returns the number of sweeps
 // (the last one rotates nothing, or its largest entering cosine squared is
 // below tol / 100, after which the next would rotate nothing: quadratic

@@ -752,7 +752,7 @@ __global__ void k_jac_roll(int* rot_prev, int* rot_cur, int* rot_count, int* big
 }
 
 // ------------------------------------------------------------- driver
-static bool debug_jacobi() {
+bool jacobi_debug() {
   static const bool v = [] {
     const char* e = std::getenv("RCS_DEBUG_JACOBI");
     return e && e[0] == '1';
@@ -1069,7 +1069,7 @@ static int jacobi_run_t(const JacobiPlan& pl, typename JT<R>::C* x, void* work, 
     HIP_OK(hipMemcpyAsync(rot_count_host, rot_count_dev, 2 * sizeof(int), hipMemcpyDeviceToHost, stream));
     HIP_OK(hipStreamSynchronize(stream));
     const bool big = rot_count_host[1] != 0;
-    if (debug_jacobi())
+    if (jacobi_debug())
       std::fprintf(stderr, "jacobi %dx%d sweep %d: %d pair rotations%s\n", pl.len, pl.cnt, sweep, *rot_count_host,
                    big ? "" : ", all entering cosines below the quadratic-stop level");
     if (*rot_count_host == 0) return sweep;
