@@ -183,7 +183,7 @@ static Gate4 to_gate4(const double2* g16) {
 static SiteView site_view(const double2* p, int da, int db) { return SiteView{p, (int64_t)da * db, db}; }
 
 // Single-site orthogonalisation input.  right: X[b][(s,a)] = A[s][a][b];
-// left: X[a][(s,b)] = conj(A[s][a][b]).
+// left: X[a][(s,b)] = conj(A[s][a][b]).  X0: the same; X may be null.
 __global__ void k_load_site(const double2* A, int dl, int dr, int right, double2* X, double2* X0,
                             int ldx) {
   const int64_t tot = (int64_t)2 * dl * dr;
@@ -201,7 +201,7 @@ __global__ void k_load_site(const double2* A, int dl, int dr, int right, double2
       idx = (int64_t)a * ldx + s * dr + b;
       v.y = -v.y;
     }
-    X[idx] = v;
+    if (X) X[idx] = v;
     X0[idx] = v;
   }
 }
@@ -337,8 +337,6 @@ __global__ __launch_bounds__(1024) void k_sort_rank(const double* sigma, int cnt
     // tail(k) <= eps w by scanning k downward while the condition holds.
     double tail = extra;
     int k_eps = cnt;
-    double tail_at[1];
-    (void)tail_at;
     // walk down accumulating; tail(cnt) is the outside weight, so when even
     // that exceeds eps w the scan stops at once and k_eps = cnt discards it
     double tail_k = extra;
@@ -1076,13 +1074,13 @@ static void move_center(rcs_state_s& st, BuildWork& ws, bool right) {
   const bool small = split_small_fits(len, cnt), try_chol = cholqr_moves_enabled() && cnt >= 2 && cnt <= len;
   const bool in_place = small && try_chol && move_cholqr_small(st, ws, st.site[c], dl, dr, right);
   if (!in_place) {
-    // the one-launch split reads its input with bounds: no padding to clear
+    // the one-launch split reads its input, X0, with bounds: no padding to clear
     if (!small) {
       HIP_OK(hipMemsetAsync(ws.X.p, 0, (size_t)pl.ldx * pl.cnt_pad * sizeof(double2), s));
       HIP_OK(hipMemsetAsync(ws.X0.p, 0, (size_t)pl.ldx * pl.cnt_pad * sizeof(double2), s));
     }
     hipLaunchKernelGGL(k_load_site, dim3(grid1d((int64_t)2 * dl * dr)), dim3(256), 0, s, st.site[c], dl, dr,
-                       right ? 1 : 0, ws.X.as<double2>(), ws.X0.as<double2>(), pl.ldx);
+                       right ? 1 : 0, small ? nullptr : ws.X.as<double2>(), ws.X0.as<double2>(), pl.ldx);
     HIP_LAUNCH_OK();
   }
   int k;

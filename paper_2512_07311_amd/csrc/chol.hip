@@ -171,14 +171,6 @@ void project(const double2* Q, int ldq, const double2* X, int ldx, int len, int 
   ahb(Q, ldq, X, ldx, len, k, cnt, false, part, StoreP{P, k, cnt, pm, pn, scale}, s);
 }
 
-__device__ inline double2 cmul_c(double2 a, double2 b) {
-  return make_double2(a.x * b.x - a.y * b.y, a.x * b.y + a.y * b.x);
-}
-// conj(a) * b
-__device__ inline double2 cmul_hc(double2 a, double2 b) {
-  return make_double2(a.x * b.x + a.y * b.y, a.x * b.y - a.y * b.x);
-}
-
 // Panel jb: every workgroup factors the 64 x 64 diagonal block G_jj = R^H R in
 // LDS, in four 16-wide steps; workgroup t >= 1 carries its 64-column tile of
 // the block row along (R_jt = R^{-H} G_jt), workgroup 0 stores R_jj

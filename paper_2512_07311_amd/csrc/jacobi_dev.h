@@ -37,18 +37,6 @@ struct JT<float> {
   __host__ __device__ static C mk(float x, float y) { return make_float2(x, y); }
 };
 
-// 1/sqrt(x) for normal positive x: hardware estimate plus two Newton steps
-// (each doubles the correct bits; the estimate carries about 23), i.e.
-// within a couple of ulps.
-__device__ inline double rsqrt_nr(double x) {
-  double r = __builtin_amdgcn_rsq(x);
-  const double h = 0.5 * x;
-  double e = fma(-h * r, r, 0.5);
-  r = fma(r, e, r);
-  e = fma(-h * r, r, 0.5);
-  return fma(r, e, r);
-}
-
 // Plane rotation J = [[c, s e], [-s conj(e), c]] (rows: old columns i < j,
 // columns: new) that (nearly) zeroes G_ij of the Hermitian 2x2 [[gii, g],
 // [conj g, gjj]] in J^H G J; the identity when the pair is already
@@ -81,7 +69,7 @@ __device__ inline Rot<double> jac_rot(double gii, double gjj, double2 g, double 
   const float t32 = __builtin_amdgcn_rcpf(tf > 1e18f ? 2.0f * tf : root);
   const double t = tau < 0.0 ? -(double)t32 : (double)t32;
   const double ex = g.x * rh, ey = g.y * rh;
-  const double c = rsqrt_nr(fma(t * t, ex * ex + ey * ey, 1.0));
+  const double c = rsqrt_fast(fma(t * t, ex * ex + ey * ey, 1.0));
   Rot<double> r;
   r.c = act ? c : 1.0;
   r.s = act ? t * c : 0.0;
