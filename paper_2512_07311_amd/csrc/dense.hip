@@ -330,11 +330,13 @@ void dense_simulate(const rcs_circuit_s& c, double2* psi, hipStream_t s) {
       pl.last_left[q] = 1;
     }
   };
-  // Factors common to all amplitudes, collected until they are worth a multiply
-  // of a coupler's entry 00: amplitudes grow by at most a few hundred binary
-  // orders meanwhile (the couplers that can run before it are those within the
-  // light cones of the qubits).
-  xcplx common(1.0L);
+  // Factors common to all amplitudes, collected per qubit line until they are
+  // worth a multiply of a coupler's entry 00.  Whatever order the passes run
+  // the couplers in, amplitudes are then too large by no more than what is on
+  // its way along the lines, 2^16 for each of at most 36.  (Collected over the
+  // circuit instead, the factors can all land on couplers that do not touch
+  // some qubits, whose own couplers may run first, hundreds in a row.)
+  std::vector<xcplx> owed(n, xcplx(1.0L));
   for (int t = 0; t < c.n_cycles; ++t) {
     layer_1q(c.layers_1q[t]);
     for (auto& e : c.layers_2q[t]) {
@@ -348,10 +350,11 @@ void dense_simulate(const rcs_circuit_s& c, double2* psi, hipStream_t s) {
         const int row = kCouplerRow[e], col = kCouplerCol[e];
         B.f[e] = xcplx(c.fsim[4 * row + col]) * (col & 2 ? ea.d1 : xcplx(1.0L)) * (col & 1 ? eb.d1 : xcplx(1.0L));
       }
-      common *= ea.common * eb.common;
-      if (std::abs(common) < 0x1p-32L) {
-        for (xcplx& f : B.f) f *= common;
-        common = xcplx(1.0L);
+      owed[a] *= owed[b] * ea.common * eb.common;
+      owed[b] = xcplx(1.0L);
+      if (std::abs(owed[a]) < 0x1p-16L) {
+        for (xcplx& f : B.f) f *= owed[a];
+        owed[a] = xcplx(1.0L);
       }
       for (int q : {a, b}) {
         if (!pl.line[q].empty()) {
@@ -371,6 +374,8 @@ void dense_simulate(const rcs_circuit_s& c, double2* psi, hipStream_t s) {
   // The first coupler takes the rest, and the mean of what rounding to fp64 does
   // to the others: a gate that repeats repeats its error, which would otherwise
   // grow with the number of couplers instead of its root.
+  xcplx common(1.0L);
+  for (const xcplx& f : owed) common *= f;
   for (size_t i = 1; i < pl.blocks.size(); ++i) {
     xcplx num(0.0L);
     long double den = 0.0L;
