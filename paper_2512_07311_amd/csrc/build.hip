@@ -174,6 +174,28 @@ void contract_mix(const SiteView& A, const SiteView& B, const Gate4& G, int dl, 
   HIP_LAUNCH_OK();
 }
 
+// out = M (rows x cols, column-major) or M^H by out.orient.  A rejected randomized
+// split leaves M: 37 us at bond 1024 (a read and two writes of 64 MB, the bound),
+// where contracting again takes 581 us.
+__global__ __launch_bounds__(256) void k_from_matrix(const double2* M, int ldm, int rows, int cols, MixOut out) {
+  __shared__ double2 t[TS_T][TS_T + 1];
+  const int r0 = blockIdx.x * TS_T, c0 = blockIdx.y * TS_T;
+  for (int e = threadIdx.x; e < TS_T * TS_T; e += 256) {
+    const int i = e % TS_T, j = e / TS_T;
+    if (r0 + i < rows && c0 + j < cols) t[j][i] = M[(int64_t)(c0 + j) * ldm + r0 + i];
+  }
+  __syncthreads();
+  for (int e = threadIdx.x; e < TS_T * TS_T; e += 256) {
+    const int i = out.orient == 1 ? e % TS_T : e / TS_T, j = out.orient == 1 ? e / TS_T : e % TS_T;
+    if (r0 + i >= rows || c0 + j >= cols) continue;
+    double2 v = t[j][i];
+    if (out.orient != 1) v.y = -v.y;
+    const int64_t at = out.orient == 1 ? (int64_t)(c0 + j) * out.ld + r0 + i : (int64_t)(r0 + i) * out.ld + c0 + j;
+    out.x[at] = v;
+    if (out.x0) out.x0[at] = v;
+  }
+}
+
 static Gate4 to_gate4(const double2* g16) {
   Gate4 G;
   for (int e = 0; e < 16; ++e) G.g[e] = g16[e];
@@ -1137,6 +1159,7 @@ struct UpdateCtx {
   std::vector<double> prev_eps;     // discarded fraction of each bond's last truncation
   RsvdWork rw;
   DevBuf M;
+  int ldm = 0;                      // M holds this update's two-site matrix with this leading dimension; 0: it does not
   int chi_cap = 0;
   bool pred_capped = true;          // learned mode: the network predicted k_hat >= cap for this update
   double* dev_scalars() { return scal2.as<double>(); }
@@ -1218,6 +1241,7 @@ static bool randomized_split(rcs_state_s& st, BuildWork& ws, UpdateCtx& ctx, int
   double2* M = ctx.M.as<double2>();
   contract_mix(site_view(st.site[i], dl, dm), site_view(st.site[i + 1], dm, dr), to_gate4(gate16), dl, dm, dr,
                o.contraction, MixOut{M, nullptr, ldm, 1}, s);
+  ctx.ldm = ldm;
   range_finder(M, ldm, len, cnt, l, std::max(0, o.rsvd_q), o.rsvd_seed, (uint64_t)ctx.update_index, ctx.rw, s);
   JacobiPlan pl = jacobi_plan(cnt, l);
   ensure_work(ws, pl);
@@ -1313,6 +1337,7 @@ static void two_site_update(rcs_state_s& st, BuildWork& ws, UpdateCtx& ctx, int 
   ctx.update_index += 1;
   const size_t n_log = st.rsvd_log.size();
   ctx.pred_capped = true;
+  ctx.ldm = 0;
   if (ctx.o && ctx.o->rank_mode != RCS_RANK_FULL_SVD &&
       randomized_split(st, ws, ctx, i, gate16, cap_eff, eps, cycle, log_spectra))
     return;
@@ -1341,8 +1366,15 @@ static void two_site_update(rcs_state_s& st, BuildWork& ws, UpdateCtx& ctx, int 
     HIP_OK(hipMemsetAsync(ws.X.p, 0, (size_t)pl.ldx * pl.cnt_pad * sizeof(double2), s));
     HIP_OK(hipMemsetAsync(ws.X0.p, 0, (size_t)pl.ldx * pl.cnt_pad * sizeof(double2), s));
   }
-  contract_mix(site_view(st.site[i], dl, dm), site_view(st.site[i + 1], dm, dr), to_gate4(gate16), dl, dm, dr, precision,
-               MixOut{ws.X0.as<double2>(), small ? nullptr : ws.X.as<double2>(), pl.ldx, orient}, s);
+  const MixOut x{ws.X0.as<double2>(), small ? nullptr : ws.X.as<double2>(), pl.ldx, orient};
+  if (ctx.ldm) {
+    hipLaunchKernelGGL(k_from_matrix, dim3(ceil_div(2 * dl, TS_T), ceil_div(2 * dr, TS_T)), dim3(256), 0, s,
+                       ctx.M.as<double2>(), ctx.ldm, 2 * dl, 2 * dr, x);
+    HIP_LAUNCH_OK();
+  } else {
+    contract_mix(site_view(st.site[i], dl, dm), site_view(st.site[i + 1], dm, dr), to_gate4(gate16), dl, dm, dr,
+                 precision, x, s);
+  }
   std::vector<double> spec;
   SplitResult r{};
   int ldw = pl.ldx, p_row = pl.cnt, side = orient;
