@@ -44,7 +44,10 @@ constexpr int CB = 64;          // Cholesky block
 // us instead of 330 (whole tiles, both triangles 336); the 20-qubit build at
 // bond 512, whose Grams have 36 tiles and fewer, 234 -> 221 ms.
 constexpr int AHB_MIN_K = 128;     // rows of a unit, at least
-constexpr int AHB_UNITS = 576;     // units of a split product, at most (64 KB of partials each)
+// Units of a split product, at most (64 KB of partials each): the 136 tiles of
+// the 2048 x 1024 Gram get three ranges and their QR takes 2.62 ms; at most 256
+// units leave them whole and it takes 2.83, at most 1,024 change nothing.
+constexpr int AHB_UNITS = 576;
 
 // Tile t of a product: row-major over all tiles, or over the upper triangle.
 __device__ inline void ahb_tile(int t, int nbn, int upper, int& tm, int& tn) {
@@ -131,8 +134,12 @@ static int ahb_tiles(int M, int N, bool upper) {
   const int nbm = ceil_div(M, GT_M), nbn = ceil_div(N, GT_N);
   return upper ? nbn * (nbn + 1) / 2 : nbm * nbn;
 }
-// The number of K ranges that leaves the fewest rounds of the chip, a little
-// charged for each range's partials.
+// The number of K ranges that leaves the fewest rounds of the chip, and 0.02 of
+// one charged for each range's partials.  Whole QR calls: without the charge
+// 1500 x 700 takes 1.78 ms instead of 1.53 (ranges that only pay for
+// themselves), with 0.05 or 0.1 1024 x 300 takes 0.67 or 0.71 instead of 0.63
+// (unsplit 1.00).  Long narrow products would take more ranges than this gives
+// them (8192 x 256: 1.00 ms, without the charge 0.72).
 static int ahb_splits(int tiles, int K) {
   int best = 1;
   double cost = 1e30;

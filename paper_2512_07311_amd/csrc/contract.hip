@@ -140,7 +140,10 @@ __device__ inline void mma_lowp(const StageBf16& a, const StageBf16& b, AccLowp&
 // Tile of this workgroup.  Consecutive workgroups go to the eight dies in
 // turn, each with an L2 of its own, so die d takes the d-th eighth of an
 // order that walks strips of six tile columns row by row: its tiles form a
-// patch that shares operand rows and columns.
+// patch that shares operand rows and columns.  The width matters where the
+// operands are several times an L2: at bond 2048 in split bf16 four to eight
+// columns take 1.31 ms, one 1.41 and twelve 1.35; up to bond 1024 anything
+// from three on is within 3%.
 __device__ inline void xcd_tile(int& tx, int& ty) {
   const int gx = gridDim.x, gy = gridDim.y, n = gx * gy, id = blockIdx.y * gx + blockIdx.x;
   const int d = id & 7, q = n / 8, r = n % 8, t = d * q + min(d, r) + (id >> 3);
