@@ -648,7 +648,7 @@ __global__ __launch_bounds__(JSOLVE + ROWS) void k_jac_rotate_rows(JacArgs<doubl
 #pragma unroll
       for (int c = 0; c < 32; ++c) {
         double2* col = a.x + (int64_t)((c < 16 ? bi : bj) * 16 + (c & 15)) * a.ldx;
-        const double d = sm.scale[c];
+        const double d = column_scale(sm, c);
         col[row] = make_double2(y[c].x * d, y[c].y * d);
       }
     }
@@ -686,7 +686,10 @@ __global__ __launch_bounds__(JSOLVE + ROWS) void k_jac_rotate_rows(JacArgs<doubl
   }
   fill_schedule<S>(sm, tid, JSOLVE);
   const Moves<S> moves = block_moves<S>(tid);
-  if (tid < 32) sm.scale[tid] = 1.0;
+  if (tid < 32) {
+    sm.scale[tid] = 1.0;
+    sm.scale_err[tid] = 0.0;
+  }
   if (tid == 0) {
     sm.any_flag = 0;
     sm.big = 0;

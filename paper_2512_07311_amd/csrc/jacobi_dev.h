@@ -304,7 +304,7 @@ __device__ __forceinline__ void apply_round(double2 (&y)[S::cols], const double2
 // infinity in the addend of the denominator, the sign on g, and the test is
 // one comparison (a conjunction of four goes through the scalar unit).
 struct RotT {
-  double c, ax, ay, ci;
+  double c, ax, ay, ci, x;   // x: 1 + |t|^2
 };
 __device__ inline RotT jac_rot_t(double gii, double gjj, double2 g, double tol, double neg2) {
   const double h2 = fma(g.x, g.x, fma(g.y, g.y, 1e-300)), d = 0.5 * (gjj - gii);
@@ -319,6 +319,7 @@ __device__ inline RotT jac_rot_t(double gii, double gjj, double2 g, double tol, 
   RotT r;
   r.c = fma(q * e, fma(0.375, e, 0.5), q);
   r.ci = x * r.c;
+  r.x = x;
   const double ct = r.c * k;
   r.ax = (d < 0.0 ? -g.x : g.x) * ct;
   r.ay = (d < 0.0 ? -g.y : g.y) * ct;
@@ -329,10 +330,14 @@ struct SolveLds {
   double2 G[32 * 32];      // the Gram, all of it
   double2 B[2][4][192];    // the solve's copy: entry (side a, side b) of a thread's pair block
   double2 rot[2][2][16];   // u and w of a round's rotations, from the publishing wave
-  double scale[32];
+  double scale[32], scale_err[32];   // column scales are scale (1 + scale_err)
   unsigned short pair[31][16];   // the schedule: i | j << 8
   int any_flag, big;
 };
+
+__device__ __forceinline__ double column_scale(const SolveLds& sm, int c) {
+  return fma(sm.scale[c], sm.scale_err[c], sm.scale[c]);
+}
 
 // Round r's shears on the lane's row.
 template <class S, int R_>
@@ -442,25 +447,49 @@ __device__ inline Moves<S> block_moves(int tid) {
 // The publishing wave's side: it takes the same rotations from the blocks as
 // the solve does, one a lane, and turns them into shears with the column
 // scales, which the solve's chain does not wait for.
+// The rounding of c, 1 / c and the scales is the same for a whole column, so it
+// does not average out in the column's norm as that of its entries does: what
+// it was is added up per column, a round behind.  Singular values, relative to
+// 64-bit ones, geometric mean over 40 matrices of up to about 1,000 columns:
+// 0.06 of the error without it, 0.07 of that of a product with the unitary.  SVD
+// 203 x 131 and 2048 x 2048 take 2.17 and 80.6 ms without, 2.14 and 80.9 with
+// (two runs differ by 4% and 0.4%).
 template <class S>
 __device__ inline void publish_sweeps(SolveLds& sm, int lane, double tol_in, double neg2, int inner) {
   constexpr int P = S::pairs;
   const int q = lane & (P - 1);
-  int buf = 0;
+  int buf = 0, li = q, lj = P + q;   // the previous round's columns and
+  double pi = 0.0, pj = 0.0;         // errors of their scales
+  auto add_err = [&] {
+    if (lane < P) {
+      sm.scale_err[li] += pi;
+      sm.scale_err[lj] += pj;
+    }
+  };
   for (int left = inner * S::rounds, r = 0; left > 0; --left) {
     const double gii = sm.B[buf][0][q].x, gjj = sm.B[buf][3][q].x;
     const double2 gij = sm.B[buf][1][q];
     const int pair = sm.pair[r][q], i = pair & 31, j = pair >> 8;
+    add_err();
     const double di = sm.scale[i], dj = sm.scale[j];
-    const double qi = dj * rcp_fast(di), qj = di * rcp_fast(dj);
+    const double ri = rcp_fast(di), rj = rcp_fast(dj);
+    const double qi = dj * ri, qj = di * rj;
     const RotT t = jac_rot_t(gii, gjj, gij, tol_in, neg2);
+    const double ni = di * t.c, nj = dj * t.ci;
     if (lane < P) {
       const double fu = t.ci * qi, fw = t.c * qj;
       sm.rot[buf][0][q] = make_double2(t.ax * fu, t.ay * fu);
       sm.rot[buf][1][q] = make_double2(t.ax * fw, t.ay * fw);
-      sm.scale[i] = di * t.c;
-      sm.scale[j] = dj * t.ci;
+      sm.scale[i] = ni;
+      sm.scale[j] = nj;
     }
+    // x c = ci (1 + rc), x c^2 = 1 + 2 ec, di c = ni + ..., dj ci = nj + ...
+    const double rc = fma(t.x, t.c, -t.ci) * t.c, ec = 0.5 * (fma(t.ci, t.c, -1.0) + rc);
+    pi = fma(di, t.c, -ni) * ri - ec;
+    pj = fma(dj, t.ci, -nj) * rj + (rc - ec);
+    li = i;
+    lj = j;
+    if (left == 1) add_err();
     __syncthreads();
     buf ^= 1;
     r = r + 1 == S::rounds ? 0 : r + 1;

@@ -245,6 +245,7 @@ __global__ __launch_bounds__(SS_THREADS) void k_split_small(SplitSmallArgs a) {
     fill_schedule<S>(sm.sv, tid, JSOLVE);
     if (tid < 32) {
       sm.sv.scale[tid] = 1.0;
+      sm.sv.scale_err[tid] = 0.0;
       sm.order[tid] = tid;
     }
     if (tid == 0) sm.sv.any_flag = sm.sv.big = sm.bad = 0;
@@ -299,7 +300,7 @@ __global__ __launch_bounds__(SS_THREADS) void k_split_small(SplitSmallArgs a) {
       row_sweeps<S>(y, sm.sv, lane, 1);
 #pragma unroll
       for (int c = 0; c < N; ++c) {
-        const double d = sm.sv.scale[c];
+        const double d = column_scale(sm.sv, c);
         y[c] = make_double2(y[c].x * d, y[c].y * d);
         sm.Y[c * SS_LD + row] = y[c];
       }
@@ -307,7 +308,10 @@ __global__ __launch_bounds__(SS_THREADS) void k_split_small(SplitSmallArgs a) {
       solve_sweeps<S>(sm.sv, moves, tid, 0.5 * a.tol, neg2, 1);
     }
     __syncthreads();
-    if (tid < 32) sm.sv.scale[tid] = 1.0;
+    if (tid < 32) {
+      sm.sv.scale[tid] = 1.0;
+      sm.sv.scale_err[tid] = 0.0;
+    }
     if (tid == 0) sm.sv.any_flag = sm.sv.big = 0;
     small_gram(sm, a.len, tid);
     if (a.qtol > 0.0 && !big) break;
