@@ -193,7 +193,7 @@ void project(const double2* Q, int ldq, const double2* X, int ldx, int len, int 
 // Bound: the chain of 64 pivots (sqrt, division and a shuffle each).  Two
 // barriers per pivot and per substitution row, with every thread's terms read
 // from LDS, took 112 us per panel; this form with four rows of a column per
-// lane, handed around by shuffles, 39 us, and with whole columns 32 us.
+// lane, handed around by shuffles, 39 us, and with whole columns 31 us.
 constexpr int PANEL_THREADS = 512;
 constexpr int PW = 16;                     // inner block
 constexpr int PLD = CB + 1;

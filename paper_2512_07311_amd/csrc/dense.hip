@@ -20,7 +20,7 @@
 //    set grown from the first gate in line, each step adding the qubits that
 //    let most gates run per qubit added.
 // 28 qubits (4 x 7), 8 cycles: 10 passes instead of the 64 that one window
-// and one layer per pass took, 27.9 ms instead of 165 (2.7 ms per pass against
+// and one layer per pass took, 28.0 ms instead of 166 (2.7 ms per pass against
 // 2.6: a pass now carries about 9 couplers with their gates; the copy rate
 // alone would be 2.0).  With general 2x2 matrices and places worked out for
 // every amplitude: 34.8 ms.

@@ -614,7 +614,7 @@ __global__ __launch_bounds__(ROT_THREADS) void k_jac_rotate_cross(JacArgs<float>
 // that a skipped pair of the next first round leaves in place).  They drift
 // by rounding only and are taken afresh every sweep.  At 2048 x 2048 the Gram
 // pass of a cross round takes 13.5 instead of 22.8 us and the rotate pass, with
-// a quarter of the partials to read, 29 instead of 32.
+// a quarter of the partials to read, 28 instead of 32.
 template <int ROWS, class S>
 __global__ __launch_bounds__(JSOLVE + ROWS) void k_jac_rotate_rows(JacArgs<double> a) {
   __shared__ SolveLds sm;

@@ -158,7 +158,8 @@ __device__ inline void rot_left(const RotA<R>& r, C& xi, C& xj) {
 // wave per SIMD) and the read and write of the matrix (64 MB, 25 us on its
 // own).  Measured, per launch at 64 x 64 / 512 x 512: the LDS solve with a V
 // product on the matrix cores (still the 32-column and fp32 form) 21.5 / 22
-// us, this scheme 12.1 / 13.7 us; 2048 x 2048 43 -> 32 us inside an SVD.  Its
+// us, this scheme 12.1 / 13.7 us; 2048 x 2048 43 -> 32 us inside an SVD (28
+// since the Gram pass leaves it a quarter of the partials).  Its
 // first form, a full Gram of 256 blocks in four waves, places computed each
 // round and the shears from a row wave, took 15.2 / 16.7 us: index arithmetic
 // between barriers cost 310 cycles a round.  Tried and slower: the whole

@@ -400,7 +400,7 @@ __global__ __launch_bounds__(SS_THREADS) void k_split_small(SplitSmallArgs a) {
 }
 
 // CholeskyQR of a small matrix in one launch, for centre moves: the general
-// path's Gram, Cholesky panel (a 64-column one, 39 us), inverse, products,
+// path's Gram, Cholesky panel (a 64-column one, 31 us), inverse, products,
 // clears and copies are about sixteen launches.
 // Elimination on [G | I] by the whole workgroup, one barrier a pivot: the row
 // operations that turn G into R turn I into R^{-H}, both up to a row scale.
